@@ -707,6 +707,7 @@ citron_status citron_load_csr(int32_t n, int64_t nnz, const int32_t* row_ptr, co
     int64_t* acct = &g->device_bytes;
     if ((st = dalloc(&g->d_row_ptr, (size_t)n + 1, acct, "row_ptr")) ||
         (st = dalloc(&g->d_col, (size_t)nnz, acct, "col_idx")) ||
+        (st = dalloc(&g->d_outdeg, (size_t)n + 1, acct, "outdeg")) ||
         (st = dalloc(&g->d_small, 1, acct, "counters"))) {
         free_graph_memory(g);
         delete g;
@@ -720,39 +721,32 @@ citron_status citron_load_csr(int32_t n, int64_t nnz, const int32_t* row_ptr, co
     e = hipMemcpyAsync(g->d_row_ptr, row_ptr, sizeof(int32_t) * ((size_t)n + 1), kind, s);
     if (e == hipSuccess && nnz > 0)
         e = hipMemcpyAsync(g->d_col, col_idx, sizeof(int32_t) * (size_t)nnz, kind, s);
+    // device-side validation: offsets first, then, where those are in range,
+    // entries; one wait for both
+    SmallDev* sd = g->d_small;
+    if (e == hipSuccess) e = launch_fill_u64((unsigned long long*)sd, 0, sizeof(SmallDev) / 8, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(g->h_small->ends, g->d_row_ptr, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+        e = launch_validate(n, nnz, g->d_row_ptr, g->d_col, &sd->err, g->d_outdeg, &sd->max_outdeg, &sd->kept, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(g->h_small->ends + 1, g->d_row_ptr + n, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+        e = hipMemcpyAsync(&g->h_small->err, &sd->err, 2 * sizeof(int32_t) + sizeof(uint64_t),
+                           hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) { free_graph_memory(g); delete g; return hip_fail(e, "copying the CSR"); }
-    if (g->h_small->ends[0] != 0 || g->h_small->ends[1] != nnz) {
+    if (e != hipSuccess) { free_graph_memory(g); delete g; return hip_fail(e, "loading the CSR"); }
+    int32_t bits = g->h_small->err;
+    if (!bits && (int64_t)g->h_small->kept != nnz / 2) bits |= 16;
+    if (bits) {
         free_graph_memory(g);
         delete g;
-        return fail(CITRON_EINVAL, "row_ptr[0] must be 0 and row_ptr[n] must equal nnz");
+        if (bits & 32) return fail(CITRON_EINVAL, "row_ptr[0] must be 0 and row_ptr[n] must equal nnz");
+        std::string why;
+        if (bits & 1) why += " row_ptr not non-decreasing within [0, nnz];";
+        if (bits & 2) why += " column id out of range;";
+        if (bits & 4) why += " self-loop;";
+        if (bits & 8) why += " row not strictly ascending (unsorted or duplicate);";
+        if (bits & 16) why += " graph not symmetric;";
+        return fail(CITRON_EINVAL, "invalid CSR:" + why);
     }
-    // device-side validation: offsets first (so that rows are in range), then entries
-    for (int stage = 0; stage < 2; ++stage) {
-        int32_t* err = &g->d_small->err;
-        e = launch_fill_i32(err, 0, 1, s);
-        if (e == hipSuccess) e = launch_validate(n, nnz, g->d_row_ptr, g->d_col, err, stage, s);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(&g->h_small->err, err, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) { free_graph_memory(g); delete g; return hip_fail(e, "validation"); }
-        const int32_t bits = g->h_small->err;
-        if (bits) {
-            std::string why;
-            if (bits & 1) why += " row_ptr not non-decreasing within [0, nnz];";
-            if (bits & 2) why += " column id out of range;";
-            if (bits & 4) why += " self-loop;";
-            if (bits & 8) why += " row not strictly ascending (unsorted or duplicate);";
-            if (bits & 16) why += " graph not symmetric;";
-            free_graph_memory(g);
-            delete g;
-            return fail(CITRON_EINVAL, "invalid CSR:" + why);
-        }
-    }
+    g->max_outdeg = g->h_small->max_outdeg;   // under the degree ordering
     *out = g;
     return CITRON_OK;
 }
@@ -838,19 +832,25 @@ static citron_status order_impl(citron_graph* g, int kind)
     citron_status st;
     g->scan_ws_ints = scan_workspace_ints((int64_t)g->n + 1) + 64;
     // a call that failed part-way keeps what it allocated; a retry reuses it
-    if ((!g->d_outdeg && (st = dalloc(&g->d_outdeg, (size_t)g->n + 1, acct, "outdeg"))) ||
-        (!g->d_dag_ptr && (st = dalloc(&g->d_dag_ptr, (size_t)g->n + 1, acct, "dag_ptr"))) ||
+    if ((!g->d_dag_ptr && (st = dalloc(&g->d_dag_ptr, (size_t)g->n + 1, acct, "dag_ptr"))) ||
         (!g->d_dag_col && (st = dalloc(&g->d_dag_col, (size_t)g->m, acct, "dag_col"))) ||
         (!g->d_dag_src && (st = dalloc(&g->d_dag_src, (size_t)g->m, acct, "dag_src"))) ||
         (!g->d_scan_ws && (st = dalloc(&g->d_scan_ws, g->scan_ws_ints, acct, "scan workspace"))))
         return st;
     if (kind == 1 && g->n > 0 && (st = peel_key(g))) return st;
     hipStream_t s = g->stream;
+    // the degree ordering's out-degrees are the load's; the core ordering
+    // counts its own over the same buffer (and a degree ordering after a core
+    // ordering that failed part-way counts them again)
     int32_t* mx = &g->d_small->max_outdeg;
-    e = launch_fill_i32(mx, 0, 1, s);
+    const bool recount = kind == 1 || g->outdeg_replaced;
+    if (recount) {
+        g->outdeg_replaced = true;
+        e = launch_fill_i32(mx, 0, 1, s);
+    }
     if (e == hipSuccess)
         e = launch_orient(g->n, g->d_row_ptr, g->d_col, g->d_outdeg, g->d_dag_ptr, g->d_dag_col,
-                          g->d_dag_src, mx, g->d_scan_ws, s, kind == 1 ? g->d_key : nullptr);
+                          g->d_dag_src, mx, g->d_scan_ws, s, kind == 1 ? g->d_key : nullptr, recount);
     if (e == hipSuccess && g->n == 0) e = launch_fill_i32(g->d_dag_ptr, 0, 1, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(&g->h_small->max_outdeg, mx, sizeof(int32_t), hipMemcpyDeviceToHost, s);

@@ -18,6 +18,7 @@ struct SmallDev {
     int32_t item_ctr;
     int32_t err;
     int32_t max_outdeg;
+    unsigned long long kept;     // sum of the out-degrees (validation)
     unsigned long long tri_acc;
     int32_t tri_ovf;
     int32_t build_ctr;
@@ -30,8 +31,9 @@ struct SmallHost {
     uint64_t acc;
     int32_t overflow;
     int32_t item_ctr;
-    int32_t err;
+    int32_t err;                 // err, max_outdeg, kept: copied together
     int32_t max_outdeg;
+    unsigned long long kept;
     int32_t ends[2];
     PlanHeader plan;
     QueryDesc query;
@@ -61,6 +63,7 @@ struct citron_graph {
     int32_t* d_row_ptr = nullptr;
     int32_t* d_col = nullptr;
     int32_t* d_outdeg = nullptr;
+    bool outdeg_replaced = false;          // d_outdeg no longer holds the load's counts
     int32_t* d_dag_ptr = nullptr;
     int32_t* d_dag_col = nullptr;
     int32_t* d_dag_src = nullptr;

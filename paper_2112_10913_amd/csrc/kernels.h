@@ -8,12 +8,17 @@ namespace citron {
 // ---- ordering phase (kernels_order.hip)
 size_t scan_workspace_ints(int64_t n);
 hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* ws, hipStream_t s);
-hipError_t launch_validate(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col,
-                           int32_t* err, int stage, hipStream_t s);
-// key: nullptr for the degree ordering, else the per-vertex order key (ties by id)
+// *err, *max_outdeg, *kept: zeroed before the call.  Leaves the error bits and,
+// when there are none, the out-degrees under the degree ordering, the largest
+// of them and their sum, which is nnz / 2 iff the graph is symmetric.
+hipError_t launch_validate(int32_t n, int64_t nnz, const int32_t* row_ptr, const int32_t* col, int32_t* err,
+                           int32_t* outdeg, int32_t* max_outdeg, unsigned long long* kept, hipStream_t s);
+// key: nullptr for the degree ordering, else the per-vertex order key (ties by
+// id).  count: outdeg is counted here (*max_outdeg, zeroed before, too); else
+// it is launch_validate's, which is the degree ordering's
 hipError_t launch_orient(int32_t n, const int32_t* row_ptr, const int32_t* col, int32_t* outdeg,
                          int32_t* dag_ptr, int32_t* dag_col, int32_t* dag_src, int32_t* max_outdeg,
-                         int32_t* scan_ws, hipStream_t s, const int32_t* key = nullptr);
+                         int32_t* scan_ws, hipStream_t s, const int32_t* key, bool count);
 
 // ---- core ordering by level-synchronous peeling (kernels_core.hip)
 // deg[v] = degree, round[v] = -1; *min_deg = smallest degree (preset to INT_MAX)

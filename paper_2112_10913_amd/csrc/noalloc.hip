@@ -25,8 +25,8 @@ namespace {
 constexpr int32_t kNoAllocMaxN = 1 << 22;
 // scan workspace ints reserved (scan_workspace_ints(2^22 + 1) is 2,052)
 constexpr int64_t kNoAllocScanInts = 8192;
-// layout, in int32 words: [0] error bits, [1] largest out-degree, [2..63]
-// unused, [64 .. 64 + n] out-degrees, then the scan workspace
+// layout, in int32 words: [0] error bits, [1] largest out-degree, [2..3] sum
+// of the out-degrees (64-bit), [4..63] unused, [64 .. 64 + n] out-degrees, then the scan workspace
 constexpr int64_t kOutdegOff = 64;
 constexpr int64_t kScanOff = kOutdegOff + (int64_t)kNoAllocMaxN + 64;
 constexpr int64_t kScratchInts = kScanOff + kNoAllocScanInts;
@@ -80,34 +80,27 @@ extern "C" citron_status citron_order_noalloc(int32_t n, int64_t nnz, const int3
     if (st) return st;
     int32_t* err = base;
     int32_t* mx = base + 1;
+    int32_t* kept = base + 2;      // 64-bit
     int32_t* outdeg = base + kOutdegOff;
     int32_t* ws = base + kScanOff;
     hipStream_t s = (hipStream_t)stream;
 
-    // offsets first: row_ptr[0] = 0 and row_ptr[n] = nnz (host words on the
-    // caller's stack; a copy to pageable memory allocates nothing here)
-    int32_t ends[2] = {-1, -1};
-    e = hipMemcpyAsync(&ends[0], row_ptr, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipMemcpyAsync(&ends[1], row_ptr + n, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(e, "citron_order_noalloc: reading row_ptr");
-    if (ends[0] != 0 || (int64_t)ends[1] != nnz)
-        return fail(CITRON_EINVAL, "invalid CSR: row_ptr[0] must be 0 and row_ptr[n] must equal nnz");
-    // validation as in citron_load_csr: offsets, then entries
-    for (int stage = 0; stage < 2; ++stage) {
-        int32_t bits = 0;
-        e = launch_fill_i32(err, 0, 1, s);
-        if (e == hipSuccess) e = launch_validate(n, nnz, row_ptr, col_idx, err, stage, s);
-        if (e == hipSuccess) e = hipMemcpyAsync(&bits, err, sizeof(int32_t), hipMemcpyDeviceToHost, s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
-        if (e != hipSuccess) return hip_fail(e, "citron_order_noalloc: validation");
-        if (bits) return fail(CITRON_EINVAL, "invalid CSR (bits " + std::to_string(bits) +
-                                                 ": 1 offsets, 2 id range, 4 self-loop, 8 order, 16 symmetry)");
-    }
-    // Algorithm 3: out-degrees, scan, scatter
-    e = launch_fill_i32(mx, 0, 1, s);
+    // validation as in citron_load_csr: offsets, then entries (results in host
+    // words on the caller's stack; a copy to pageable memory allocates nothing)
+    struct { int32_t err, mx; unsigned long long kept; } chk = {0, 0, 0};
+    e = launch_fill_i32(err, 0, 4, s);
     if (e == hipSuccess)
-        e = launch_orient(n, row_ptr, col_idx, outdeg, dag_ptr, dag_col, nullptr, mx, ws, s);
+        e = launch_validate(n, nnz, row_ptr, col_idx, err, outdeg, mx, reinterpret_cast<unsigned long long*>(kept), s);
+    if (e == hipSuccess) e = hipMemcpyAsync(&chk, err, sizeof(chk), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e, "citron_order_noalloc: validation");
+    if (!chk.err && (int64_t)chk.kept != nnz / 2) chk.err |= 16;
+    if (chk.err & 32)
+        return fail(CITRON_EINVAL, "invalid CSR: row_ptr[0] must be 0 and row_ptr[n] must equal nnz");
+    if (chk.err) return fail(CITRON_EINVAL, "invalid CSR (bits " + std::to_string(chk.err) +
+                                                ": 1 offsets, 2 id range, 4 self-loop, 8 order, 16 symmetry)");
+    // Algorithm 3: scan of the out-degrees, scatter
+    e = launch_orient(n, row_ptr, col_idx, outdeg, dag_ptr, dag_col, nullptr, mx, ws, s, nullptr, false);
     if (e == hipSuccess && n == 0) e = launch_fill_i32(dag_ptr, 0, 1, s);
     int32_t res[2] = {0, -1};
     if (e == hipSuccess) e = hipMemcpyAsync(&res[0], mx, sizeof(int32_t), hipMemcpyDeviceToHost, s);

@@ -1,0 +1,70 @@
+"""Sizes at which a kernel's tiles, groups or tables end, against the oracle.
+All results are whole numbers: no tolerance."""
+import numpy as np
+import pytest
+
+import graphgen as gg
+
+pytestmark = pytest.mark.gpu
+
+
+def _hubs(degrees, seed=1):
+    """Hubs of the given degrees over shared leaves, some leaves joined."""
+    rng = np.random.default_rng(seed)
+    leaves = max(degrees) + 7
+    src, dst = [], []
+    for h, d in enumerate(degrees):
+        src += [h] * d
+        dst += list(len(degrees) + rng.choice(leaves, d, replace=False))
+    extra = len(degrees) + rng.integers(0, leaves, (2, 3 * leaves))
+    return gg.csr_from_edges(len(degrees) + leaves, np.concatenate([src, extra[0]]),
+                             np.concatenate([dst, extra[1]]), perm_seed=seed)
+
+
+@pytest.mark.parametrize("degrees", [[1, 15, 16, 17], [255, 256, 257], [63, 64, 65, 600, 2, 1023]])
+def test_row_walk_at_group_and_wave_sizes(citron_gpu, degrees):
+    """Rows walked by 16 lanes (up to 256 entries) or by a whole wave."""
+    import oracle
+    g = _hubs(degrees)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    ptr, col = h.dag()
+    want_ptr, want_col = oracle.orient(g.n, g.row_ptr, g.col)
+    assert np.array_equal(ptr, want_ptr) and np.array_equal(col, want_col)
+    assert h.info()["max_outdeg"] == int(np.diff(want_ptr).max())
+    h.free()
+
+
+@pytest.mark.parametrize("lower_row", [False, True])
+def test_a_missing_mirror_entry_is_refused(citron_gpu, lower_row):
+    """One entry dropped, from the row of the edge's lower endpoint (the
+    mirror is searched for there) or of the higher (the counts differ); a
+    second one-sided entry keeps the number of entries even."""
+    g = _hubs([300, 20, 20])
+    deg = np.diff(g.row_ptr)
+    src = np.repeat(np.arange(g.n), deg)
+    lower = (deg[src] < deg[g.col]) | ((deg[src] == deg[g.col]) & (src < g.col))
+    drop = np.nonzero(lower == lower_row)[0][[3, -5]]
+    assert (src[drop[0]], g.col[drop[0]]) != (g.col[drop[1]], src[drop[1]])
+    keep = np.ones(g.nnz, bool)
+    keep[drop] = False
+    row_ptr = np.concatenate([[0], np.cumsum(np.bincount(src[keep], minlength=g.n))]).astype(np.int32)
+    with pytest.raises(citron_gpu.CitronError) as e:
+        citron_gpu.Graph.from_csr(row_ptr, g.col[keep])
+    assert e.value.status == 1
+
+
+def test_degree_ordering_after_load_with_a_core_ordered_neighbour(citron_gpu):
+    """The load's out-degrees serve the degree ordering of their own graph,
+    whatever another handle of the same graph does in between."""
+    import oracle
+    g = gg.rmat(9, 12, seed=77)
+    a = citron_gpu.Graph.from_csr(g.row_ptr, g.col)
+    b = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order("core")
+    a.order()
+    want_ptr, want_col = oracle.orient(g.n, g.row_ptr, g.col)
+    ptr, col = a.dag()
+    assert np.array_equal(ptr, want_ptr) and np.array_equal(col, want_col)
+    for k in (3, 4, 5):
+        assert a.count(k) == b.count(k) == oracle.count(g, k)[0]
+    a.free()
+    b.free()

@@ -137,7 +137,7 @@ static void free_graph_memory(citron_graph* g)
     dfree(g->d_small);
     dfree(g->d_scan_ws);
     dfree(g->d_key);
-    dfree(g->d_query);
+    dfree(g->d_ctl);
     dfree(g->d_scratch);
     dfree(g->d_stats);
     dfree(g->d_rows_off);
@@ -592,19 +592,21 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
         st = dalloc(&g->d_stats, kNumStats, &g->device_bytes, "stats");
         if (st) return st;
     }
-    SmallDev* sd = g->d_small;
-    if ((e = launch_fill_u64(&sd->acc, seed, 1, s)) != hipSuccess ||
-        (e = launch_fill_i32(&sd->overflow, 0, 1, s)) != hipSuccess ||
-        (e = launch_fill_i32(&sd->item_ctr, 0, 1, s)) != hipSuccess)
-        return hip_fail(e, "fill");
+    if (!g->d_ctl) {
+        st = dalloc(&g->d_ctl, 1, &g->device_bytes, "query");
+        if (st) return st;
+    }
+    CountCtl& ctl = g->h_small->ctl;
+    memset(&ctl, 0, sizeof(ctl));
+    ctl.acc[0] = seed;
     if (stats && ((e = launch_fill_u64(g->d_stats, 0, kNumStats, s)) != hipSuccess ||
                   (e = launch_fill_u64(g->d_stats + kStatWaveFirst, ~0ull, 1, s)) != hipSuccess))
         return hip_fail(e, "fill");
     if (per_arc && (e = launch_fill_u64(per_arc, 0, arc_list ? n_list : g->m, s)) != hipSuccess)
         return hip_fail(e, "fill");
-    g->h_small->query = make_query(g, k, &sd->acc, &sd->overflow, per_arc, stats ? g->d_stats : nullptr, 0);
+    ctl.query = make_query(g, k, g->d_ctl->acc, &g->d_ctl->overflow, per_arc, stats ? g->d_stats : nullptr, 0);
     if (vertex_rooted) {
-        QueryDesc& q = g->h_small->query;
+        QueryDesc& q = ctl.query;
         q.buckets = g->d_vbuckets[k];
         q.n_buckets = g->n_vbuckets[k];
         q.n_work = g->n_vwork[k];
@@ -613,7 +615,7 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
     ListItems li;
     if (nparts > 1) {
         // items part, part + nparts, part + 2 nparts, ... of the schedule
-        QueryDesc& q = g->h_small->query;
+        QueryDesc& q = ctl.query;
         q.item_lo = part;
         q.item_stride = nparts;
         q.n_items = q.n_work > part ? (q.n_work - part + nparts - 1) / nparts : 0;
@@ -622,21 +624,17 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
         // items of the listed arcs: heavy ones split into parts like the full schedule
         st = li.build(g, arc_list, n_list, k, s);
         if (st) return st;
-        g->h_small->query.arc_list = arc_list;
-        g->h_small->query.arc_items = li.items;
-        g->h_small->query.n_items = li.total;
+        ctl.query.arc_list = arc_list;
+        ctl.query.arc_items = li.items;
+        ctl.query.n_items = li.total;
     }
-    if (!g->d_query) {
-        st = dalloc(&g->d_query, 1, &g->device_bytes, "query");
-        if (st) return st;
-    }
-    e = hipMemcpyAsync(g->d_query, &g->h_small->query, sizeof(QueryDesc), hipMemcpyHostToDevice, s);
+    e = hipMemcpyAsync(g->d_ctl, &ctl, sizeof(CountCtl), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(query)");
     CountLaunch cl;
-    cl.queries = g->d_query;
+    cl.queries = &g->d_ctl->query;
     cl.n_queries = 1;
-    cl.total_items = g->h_small->query.n_items;
-    cl.item_ctr = &sd->item_ctr;
+    cl.total_items = ctl.query.n_items;
+    cl.item_ctr = g->d_ctl->cursors;
     cl.scratch = g->d_scratch;
     cl.scratch_words = swords;
     cl.max_k = stack_k;
@@ -649,8 +647,7 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
     cl.per_arc = per_arc != nullptr;
     e = launch_count(cl, s);
     if (e != hipSuccess) return hip_fail(e, "count kernel launch");
-    e = hipMemcpyAsync(&g->h_small->acc, &sd->acc, sizeof(uint64_t) + sizeof(int32_t) * 2,
-                       hipMemcpyDeviceToHost, s);
+    e = hipMemcpyAsync(&ctl, g->d_ctl, sizeof(ctl.acc) + sizeof(ctl.overflow), hipMemcpyDeviceToHost, s);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(result)");
     if (stats) {
         e = hipMemcpyAsync(g->h_small->stats, g->d_stats, sizeof(uint64_t) * kNumStats,
@@ -659,7 +656,8 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
     }
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "count kernel");
-    *out_count = g->h_small->acc;
+    bool carry = ctl.overflow != 0;
+    *out_count = sum_acc_slots(ctl.acc, &carry);
     if (stats && stats_out) {
         // copied while the graph is still locked: another call may reuse
         // the pinned mirror as soon as the lock is released
@@ -669,7 +667,7 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
         stats_out[kStatEntries] = g->build_stats[kStatEntries];
         stats_out[kStatBytes] = g->build_stats[kStatBytes];
     }
-    if (g->h_small->overflow) return fail(CITRON_EOVERFLOW, "count is >= 2^64; value is mod 2^64");
+    if (carry) return fail(CITRON_EOVERFLOW, "count is >= 2^64; value is mod 2^64");
     return CITRON_OK;
 }
 

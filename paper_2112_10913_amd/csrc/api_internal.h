@@ -13,9 +13,8 @@ namespace citron {
 // Small device-side words of one graph (zeroed by fill kernels, never by
 // hipMemsetAsync, so that the sequences stay valid inside captured graphs).
 struct SmallDev {
-    unsigned long long acc;
-    int32_t overflow;
     int32_t item_ctr;
+    int32_t pad;
     int32_t err;
     int32_t max_outdeg;
     unsigned long long kept;     // sum of the out-degrees (validation)
@@ -26,17 +25,25 @@ struct SmallDev {
     unsigned long long build_stats[kNumStats];
 };
 
+// What one count launch reads and updates: uploaded as one copy before the
+// launch (partial sums, flag and cursors in their starting state); the sums
+// and the flag come back as one copy.
+struct CountCtl {
+    unsigned long long acc[kAccWords];
+    int32_t overflow;
+    int32_t pad;
+    QueryDesc query;
+    int32_t cursors[kClaimInts];
+};
+
 // Pinned host mirror for the copies back.
 struct SmallHost {
-    uint64_t acc;
-    int32_t overflow;
-    int32_t item_ctr;
+    CountCtl ctl;
     int32_t err;                 // err, max_outdeg, kept: copied together
     int32_t max_outdeg;
     unsigned long long kept;
     int32_t ends[2];
     PlanHeader plan;
-    QueryDesc query;
     uint64_t stats[kNumStats];
     uint64_t tri_acc;
     int32_t tri_ovf;
@@ -78,7 +85,7 @@ struct citron_graph {
     citron::PlanHeader plan = {};
     citron_tuning plan_tuning = {};
     bool plan_valid = false;
-    citron::QueryDesc* d_query = nullptr;
+    citron::CountCtl* d_ctl = nullptr;
     unsigned long long* d_scratch = nullptr;
     int64_t scratch_bytes = 0;
     unsigned long long* d_stats = nullptr;

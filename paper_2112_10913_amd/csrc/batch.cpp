@@ -35,14 +35,14 @@ struct BatchExec {
     int32_t nq = 0;                    // kernel queries
     int32_t total_items = 0;           // work items of the launch
     std::vector<int32_t> qmap;         // kernel query -> caller index
-    unsigned long long* d_acc = nullptr;  // nq
-    int32_t* d_ovf = nullptr;          // nq
-    int32_t* d_item_ctr = nullptr;
+    unsigned long long* d_acc = nullptr;  // nq * kAccWords, then nq flags and the cursors
+    int32_t* d_ovf = nullptr;          // nq, within d_acc's allocation
+    int32_t* d_item_ctr = nullptr;     // kClaimInts, likewise
     QueryDesc* d_q = nullptr;
     void* d_scratch = nullptr;
     QueryDesc* h_q = nullptr;          // pinned
-    unsigned long long* h_acc = nullptr;  // pinned
-    int32_t* h_ovf = nullptr;          // pinned
+    unsigned long long* h_acc = nullptr;  // pinned: sums and flags
+    int32_t* h_ovf = nullptr;          // within h_acc's allocation
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     std::vector<const citron_graph*> graphs;
@@ -52,13 +52,10 @@ struct BatchExec {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
         if (d_acc) (void)hipFree(d_acc);
-        if (d_ovf) (void)hipFree(d_ovf);
-        if (d_item_ctr) (void)hipFree(d_item_ctr);
         if (d_q) (void)hipFree(d_q);
         if (d_scratch) (void)hipFree(d_scratch);
         if (h_q) (void)hipHostFree(h_q);
         if (h_acc) (void)hipHostFree(h_acc);
-        if (h_ovf) (void)hipHostFree(h_ovf);
     }
 };
 
@@ -130,18 +127,22 @@ citron_status batch_build(const BatchKey& key, const citron_tuning& t, BatchExec
         e = hipMalloc((void**)&(p), (bytes) > 0 ? (bytes) : 8);                       \
         if (e != hipSuccess) return fail(CITRON_ENOMEM, "hipMalloc failed for batch"); \
     } while (0)
-    BALLOC(be->d_acc, sizeof(unsigned long long) * nq);
-    BALLOC(be->d_ovf, sizeof(int32_t) * nq);
-    BALLOC(be->d_item_ctr, sizeof(int32_t));
+    // one block: partial sums, flags (rounded to 8 bytes), claim cursors
+    const size_t ovf_words = ((size_t)nq + 1) / 2;
+    const size_t res_words = (size_t)nq * kAccWords + ovf_words;
+    const size_t ctl_words = res_words + kClaimInts / 2;
+    BALLOC(be->d_acc, sizeof(unsigned long long) * ctl_words);
+    be->d_ovf = reinterpret_cast<int32_t*>(be->d_acc + (size_t)nq * kAccWords);
+    be->d_item_ctr = reinterpret_cast<int32_t*>(be->d_acc + res_words);
     BALLOC(be->d_q, sizeof(QueryDesc) * nq);
     BALLOC(be->d_scratch, (size_t)(swords * 8 * blocks));
 #undef BALLOC
     if (hipHostMalloc((void**)&be->h_q, sizeof(QueryDesc) * nq, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&be->h_acc, sizeof(unsigned long long) * nq, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void**)&be->h_ovf, sizeof(int32_t) * nq, hipHostMallocDefault) != hipSuccess)
+        hipHostMalloc((void**)&be->h_acc, sizeof(unsigned long long) * res_words, hipHostMallocDefault) != hipSuccess)
         return fail(CITRON_ENOMEM, "hipHostMalloc failed for batch");
+    be->h_ovf = reinterpret_cast<int32_t*>(be->h_acc + (size_t)nq * kAccWords);
     for (int32_t i = 0; i < nq; ++i) {
-        be->h_q[i] = make_query(key.graphs[i], key.ks[i], be->d_acc + i, be->d_ovf + i, nullptr, nullptr,
+        be->h_q[i] = make_query(key.graphs[i], key.ks[i], be->d_acc + (size_t)i * kAccWords, be->d_ovf + i, nullptr, nullptr,
                                 total_items);
         total_items += be->h_q[i].n_items;
     }
@@ -168,16 +169,12 @@ citron_status batch_build(const BatchKey& key, const citron_tuning& t, BatchExec
     // capture: resets, descriptor upload, kernel, download
     e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-    hipError_t ce = launch_fill_u64(be->d_acc, 0, nq, s);
-    if (ce == hipSuccess) ce = launch_fill_i32(be->d_ovf, 0, nq, s);
-    if (ce == hipSuccess) ce = launch_fill_i32(be->d_item_ctr, 0, 1, s);
+    hipError_t ce = launch_fill_u64(be->d_acc, 0, (int64_t)ctl_words, s);
     if (ce == hipSuccess)
         ce = hipMemcpyAsync(be->d_q, be->h_q, sizeof(QueryDesc) * nq, hipMemcpyHostToDevice, s);
     if (ce == hipSuccess) ce = launch_count(cl, s);
     if (ce == hipSuccess)
-        ce = hipMemcpyAsync(be->h_acc, be->d_acc, sizeof(unsigned long long) * nq, hipMemcpyDeviceToHost, s);
-    if (ce == hipSuccess)
-        ce = hipMemcpyAsync(be->h_ovf, be->d_ovf, sizeof(int32_t) * nq, hipMemcpyDeviceToHost, s);
+        ce = hipMemcpyAsync(be->h_acc, be->d_acc, sizeof(unsigned long long) * res_words, hipMemcpyDeviceToHost, s);
     e = hipStreamEndCapture(s, &be->graph);
     if (ce != hipSuccess) return hip_fail(ce, "batch capture");
     if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
@@ -286,8 +283,9 @@ extern "C" citron_status citron_count_batch(citron_graph* const* gs, const int32
             if (e != hipSuccess) return hip_fail(e, "batch launch");
             for (int32_t j = 0; j < be->nq; ++j) {
                 const int32_t i = kmap[j];
-                counts[i] = be->h_acc[j];
-                if (be->h_ovf[j]) qst[i] = CITRON_EOVERFLOW;
+                bool carry = be->h_ovf[j] != 0;
+                counts[i] = sum_acc_slots(be->h_acc + (size_t)j * kAccWords, &carry);
+                if (carry) qst[i] = CITRON_EOVERFLOW;
             }
         }
     }

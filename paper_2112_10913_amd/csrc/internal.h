@@ -14,6 +14,30 @@ constexpr int kMaxDeg = kMaxWords * 64;
 constexpr int kKMax = 32;
 constexpr int kArcLdsMax = 256;      // largest candidate set an LDS subgraph copy holds
 
+// Shared words of a count launch.  Atomics on one word are serialised by the
+// device at about 12 ns each, so what every wave of a launch touches is
+// spread out: work items are claimed from kClaimShards cursors (128 bytes
+// apart), and a query's sum is kept in kAccSlots partial sums (64 bytes
+// apart), which the host adds up with the same carry check.
+constexpr int kClaimShards = 16;
+constexpr int kClaimStride = 32;                        // int32 words
+constexpr int kClaimInts = kClaimShards * kClaimStride;
+constexpr int kAccSlots = 8;
+constexpr int kAccStride = 8;                           // uint64 words
+constexpr int kAccWords = kAccSlots * kAccStride;
+
+// Sum of a query's partial sums (mod 2^64); *carry is set when one carries.
+inline unsigned long long sum_acc_slots(const unsigned long long* acc, bool* carry)
+{
+    unsigned long long s = 0;
+    for (int i = 0; i < kAccSlots; ++i) {
+        const unsigned long long v = acc[i * kAccStride];
+        if (s + v < s) *carry = true;
+        s += v;
+    }
+    return s;
+}
+
 // Count-kernel statistics slots (citron_work_stats).
 enum StatSlot {
     kStatVertices = 0,     // subgraphs built
@@ -82,7 +106,7 @@ struct QueryDesc {
     const int32_t* dag_src;      // source vertex of every arc
     const int32_t* order;        // vertices by out-degree descending
     RowsDev rows;
-    unsigned long long* acc;     // count accumulator
+    unsigned long long* acc;     // kAccSlots partial sums, kAccStride words apart
     int32_t* overflow;           // set to 1 when an addition carried
     unsigned long long* per_arc; // optional per-arc counts (nullptr: off)
     unsigned long long* stats;   // optional work counters (nullptr: off)

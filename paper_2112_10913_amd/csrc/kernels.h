@@ -94,7 +94,7 @@ struct CountLaunch {
     const QueryDesc* queries;   // device table
     int32_t n_queries;
     int32_t total_items;
-    int32_t* item_ctr;          // device, zeroed by the launch sequence
+    int32_t* item_ctr;          // device: kClaimInts cursors, zeroed by the launch sequence
     unsigned long long* scratch;   // stacks of k > 12, scratch_words per block
     int64_t scratch_words;
     int32_t max_k;

@@ -10,9 +10,10 @@
 // last level summing popcounts only (degrees-only heuristic) and masks too
 // small for the rest of the clique pruned (size heuristic).
 //
-// Scheduling.  Every wave works on its own and pulls items from one global
-// cursor: first the arcs of heavy vertices (out-degree > 64) in order of
-// |C_uv|, largest first, then the light vertices (out-degree <= 64).
+// Scheduling.  Every wave works on its own and claims runs of items from a
+// few global cursors, in order of cost: the arcs of heavy vertices
+// (out-degree > 64) by |C_uv| and the light vertices (out-degree <= 64),
+// largest first.  The items of a run are decoded side by side, a lane each.
 //
 // Engines.  Light work -- subgraphs with at most 64 vertices, one 64-bit
 // word per row -- is searched by the light engine: one depth-first search
@@ -39,12 +40,13 @@ constexpr int kMaxBlock = 512;          // threads per count workgroup (8 waves)
 constexpr int kWaveBufRows = 128;       // one-word rows queued per wave
 constexpr int kLdsStackLevels = 8;      // deeper stacks (k > 12) live in device memory
 constexpr int kArcMaxC = kArcLdsMax;    // LDS subgraph copies hold at most this many rows
-constexpr int kLaneMaxWords = 4;        // multi-word masks a lane holds in registers
 constexpr int kDonateMinIdle = 8;       // idle lanes that trigger work donation
 constexpr int kBurstIters = 32;         // last-level steps of one leaf burst at most
 constexpr int kBurstMinLanes = 32;      // lanes at a last-level node to keep a burst going
 constexpr int kN3Burst = 8;             // two-level steps between refills of idle lanes
 constexpr int kMaxClaim = 16;           // items a wave claims at once, at most
+// decoded items of a claimed run, one int32 per field and item
+enum ItemField { kItQuery, kItKind, kItRowsOff, kItTag, kItArc0, kItDegree, kItRow, kItPart, kItFields };
 // donation mailbox per lane: M, R, (need, base), and the arc tag of per-arc launches
 __host__ __device__ constexpr int mbox_words(bool per_arc) { return per_arc ? 4 : 3; }
 constexpr int kPosList = 3 * kWave * 2; // candidate positions the smaller mailbox area holds (1.5 KB)
@@ -193,8 +195,8 @@ __host__ __device__ inline int arc_copy_words(int arc_max)
 
 // Per-wave LDS, in this order: queued rows (u64), their meta (i32), their
 // arc tags (i32, per-arc launches only), the subgraph copy (u64), the
-// donation mailbox (u64 per lane), the unit list (i32), the stacks kept in
-// LDS.  Every part starts 8-byte aligned; the size is rounded to 16 bytes.
+// donation mailbox (u64 per lane), the unit list (i32), the claimed items
+// (i32 fields), the stacks kept in LDS.  Every part starts 8-byte aligned; the size is rounded to 16 bytes.
 // The LDS per wave bounds the waves per CU (160 KB per CU), and the count
 // kernel is latency-bound, so the layout is sized by what a launch uses.
 __host__ __device__ inline int wave_lds_bytes(int max_k, int arc_max, bool per_arc)
@@ -203,26 +205,9 @@ __host__ __device__ inline int wave_lds_bytes(int max_k, int arc_max, bool per_a
     b += 8 * arc_copy_words(arc_max);
     b += 8 * mbox_words(per_arc) * kWave;
     b += 4 * kWaveBufRows;
+    b += 4 * kItFields * kMaxClaim;
     if (stack_mode(max_k) == kStackLds) b += 8 * (int)wave_stack_words(max_k);
     return (b + 15) & ~15;
-}
-
-int32_t count_lds_bytes(int32_t arc_max, int32_t max_k, int32_t wg_waves, bool per_arc)
-{
-    return wg_waves * wave_lds_bytes(max_k, arc_max, per_arc);
-}
-
-int64_t count_deep_scratch_words(int32_t max_k, int32_t wg_waves)
-{
-    if (stack_mode(max_k) != kStackGlobal) return 0;
-    return ((int64_t)wg_waves * wave_stack_words(max_k) + 31) & ~31ll;
-}
-
-int64_t count_scratch_words(int32_t, int32_t max_k, int32_t wg_waves)
-{
-    const int64_t w = wave_global_stack_words(max_k);
-    if (w == 0) return 0;
-    return ((int64_t)wg_waves * w + 31) & ~31ll;
 }
 
 // ------------------------------------------------------------ light engine
@@ -914,15 +899,133 @@ struct KParams {
     const QueryDesc* queries;
     int32_t n_queries;
     int32_t total_items;
-    int32_t* item_ctr;
+    int32_t* item_ctr;      // kClaimShards cursors
     u64* scratch;
     int64_t scratch_words;
     int32_t max_k;
     int32_t flush_rows;     // a wave runs its queue once it holds this many rows
     int32_t arc_lds_max;    // representation switch of heavy nodes (64..kArcMaxC)
     int32_t* progress;      // host-mapped word: items claimed, updated every 512 (nullable)
-    int32_t chunk;          // consecutive items a wave claims with one atomic
+    int32_t chunk;          // consecutive items a wave claims at once
 };
+
+// The wave's next run of items.  Runs of P.chunk consecutive items are dealt
+// to kClaimShards cursors in turn (run j to cursor j mod kClaimShards), so
+// that the items still start in order of cost.  A wave's first run is fixed
+// by its number and costs no atomic; later ones come from the cursor of its
+// home shard, and once that is dry from any that is not, found by one load of
+// all cursors.  Returns the run's first item, or -1 when none is left.
+//
+// One cursor for all waves served 85 M claims a second: G(50001, 37) at
+// k = 4, one light vertex per item, took 590 us of claims alone, and every
+// launch of 4,096 waves about 50 us for their last, empty-handed claims.
+__device__ __forceinline__ int claim_run(const KParams& P, int wave, int waves, int& shard, bool& fresh)
+{
+    const int lane = lane_of();
+    int c;
+    if (fresh) {
+        fresh = false;
+        c = wave / kClaimShards;
+    } else {
+        int v = 0;
+        if (lane == 0) v = atomicAdd(P.item_ctr + shard * kClaimStride, 1);
+        c = __builtin_amdgcn_readfirstlane(v) + (waves - shard + kClaimShards - 1) / kClaimShards;
+    }
+    for (;;) {
+        const int64_t g = ((int64_t)c * kClaimShards + shard) * P.chunk;
+        if (g < P.total_items) return (int)g;
+        bool has = false;
+        if (lane < kClaimShards) {
+            const int64_t next = (int64_t)__hip_atomic_load(P.item_ctr + lane * kClaimStride, __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT) +
+                                 (waves - lane + kClaimShards - 1) / kClaimShards;
+            has = (next * kClaimShards + lane) * P.chunk < P.total_items;
+        }
+        const unsigned left = (unsigned)__ballot(has);
+        if (left == 0u) return -1;
+        // the next shard with work after the present one, cyclically
+        const unsigned after = left & ~((2u << shard) - 1u);
+        shard = __builtin_ctz(after ? after : left);
+        int v = 0;
+        if (lane == 0) v = atomicAdd(P.item_ctr + shard * kClaimStride, 1);
+        c = __builtin_amdgcn_readfirstlane(v) + (waves - shard + kClaimShards - 1) / kClaimShards;
+    }
+}
+static_assert(kClaimShards <= 31, "shard masks are 32-bit words");
+
+// Lane j < n decodes item g0 + j of the launch into the wave's LDS fields:
+// its query, then one part of a heavy arc or (a part of) a light vertex.  The
+// chain of dependent loads (query, bucket, arc or vertex, DAG offsets, row
+// offset: about 14 on a graph with a few hundred buckets) is paid once per
+// run instead of once per item.
+__device__ __forceinline__ void decode_run(const KParams& P, int g0, int n, int32_t* item)
+{
+    const int j = lane_of();
+    if (j >= n) return;
+    const int g = g0 + j;
+    int qi;
+    {
+        int lo = 0, hi = P.n_queries - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (P.queries[mid].item_begin <= g) lo = mid;
+            else hi = mid - 1;
+        }
+        qi = lo;
+    }
+    const QueryDesc& q = P.queries[qi];
+    const int i = q.item_lo + (g - q.item_begin) * q.item_stride;
+    int u, r = -1, part, nparts, tag, kind = kItemHeavyArc;
+    if (q.arc_list) {
+        // list mode: one part of one listed arc; counts go to its list slot
+        tag = q.arc_items[2 * i];
+        const int pw = q.arc_items[2 * i + 1];
+        const int e = q.arc_list[tag];
+        u = q.dag_src[e];
+        r = e - q.dag_ptr[u];
+        part = pw & 0xffff;
+        nparts = pw >> 16;
+        kind = q.dag_ptr[u + 1] - q.dag_ptr[u] > kLightMaxDeg ? kItemHeavyArc : kItemLightVertex;
+    } else {
+        // bucket holding item i, then the arc or vertex and the part (part-major)
+        int lo = 0, hi = q.n_buckets - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (q.buckets[4 * mid] <= i) lo = mid;
+            else hi = mid - 1;
+        }
+        const int key = q.buckets[4 * lo + 3] >> 2;
+        kind = q.buckets[4 * lo + 3] & 3;
+        const int cnt = q.buckets[4 * lo + 2];
+        const int local = i - q.buckets[4 * lo];
+        part = local / cnt;
+        const int which = q.buckets[4 * lo + 1] + (local - part * cnt);
+        if (kind == kItemHeavyArc) {
+            const int e = q.rows.harcs[which];
+            u = q.dag_src[e];
+            r = e - q.dag_ptr[u];
+            nparts = arc_parts(key, q.k, q.split_pct);
+            tag = e;
+        } else if (kind == kItemHeavyVertex) {
+            u = q.order[which];
+            nparts = 1;
+            tag = -1;
+        } else {
+            u = q.order[q.light_first + which];
+            nparts = kind == kItemLightVertex ? light_parts(key + 1, q.k, q.split_pct) : 1;
+            tag = -1;
+        }
+    }
+    const int a0 = q.dag_ptr[u];
+    item[kItQuery * kMaxClaim + j] = qi;
+    item[kItKind * kMaxClaim + j] = kind;
+    item[kItRowsOff * kMaxClaim + j] = q.rows.rows_off[u];
+    item[kItTag * kMaxClaim + j] = tag;
+    item[kItArc0 * kMaxClaim + j] = a0;
+    item[kItDegree * kMaxClaim + j] = q.dag_ptr[u + 1] - a0;
+    item[kItRow * kMaxClaim + j] = r;
+    item[kItPart * kMaxClaim + j] = part | (nparts << 16);
+}
 
 template <int kMode, bool kStats, bool kPerArc>
 __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(kMode == kStackReg ? 4 : 2))) count_kernel(KParams P)
@@ -930,7 +1033,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     constexpr int kRegL = kMode == kStackReg ? kRegLevels : 0;
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = lane_of();
-    const int wid = threadIdx.x / kWave;
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int nwaves = blockDim.x / kWave;
     const int levels = stack_levels(P.max_k);
     unsigned char* wbase = smem + wid * wave_lds_bytes(P.max_k, P.arc_lds_max, kPerArc);
@@ -948,12 +1051,13 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     off += 8 * mbox_words(kPerArc) * kWave;
     wb.units = reinterpret_cast<int32_t*>(wbase + off);
     off += 4 * kWaveBufRows;
+    int32_t* item = reinterpret_cast<int32_t*>(wbase + off);
+    off += 4 * kItFields * kMaxClaim;
     u64* stacks;
     if (kMode == kStackLds)
         stacks = reinterpret_cast<u64*>(wbase + off);
     else
         stacks = P.scratch + (int64_t)blockIdx.x * P.scratch_words + (int64_t)wid * wave_global_stack_words(P.max_k);
-    (void)nwaves;
     if (kMode == kStackReg) {
         wb.sM = nullptr;
         wb.sR = nullptr;
@@ -984,36 +1088,35 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     }
     u64 item_max = 0ull;
 
-    int g_next = 0, g_end = 0;         // the wave's claimed run of items
+    const int wave = blockIdx.x * nwaves + wid;
+    const int waves = gridDim.x * nwaves;
+    const int acc_slot = (wave & (kAccSlots - 1)) * kAccStride;
+    int shard = wave % kClaimShards;
+    bool fresh = true;
+    int g0 = 0, j = 0, nj = 0;         // the wave's run of items, decoded
     for (;;) {
-        if (g_next >= g_end) {
-            int g0 = 0;
-            if (lane == 0) g0 = atomicAdd(P.item_ctr, P.chunk);
-            g0 = __shfl(g0, 0, kWave);
-            g_next = g0;
-            g_end = g0 + P.chunk;
+        if (j >= nj) {
+            g0 = claim_run(P, wave, waves, shard, fresh);
+            if (g0 < 0) break;
+            nj = min(P.chunk, P.total_items - g0);
+            j = 0;
+            __builtin_amdgcn_wave_barrier();
+            decode_run(P, g0, nj, item);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            // progress for the host, read without any HIP call while the launch runs
+            if (P.progress && lane == 0 && (((g0 + nj - 1) ^ (g0 - 1)) & ~511))
+                __hip_atomic_store(P.progress, g0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
-        const int g = g_next++;
-        if (g >= P.total_items) break;
-        // progress for the host, read without any HIP call while the launch runs
-        if (P.progress && lane == 0 && (g & 511) == 0)
-            __hip_atomic_store(P.progress, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        int qi = 0;
-        {
-            int lo = 0, hi = P.n_queries - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (P.queries[mid].item_begin <= g) lo = mid;
-                else hi = mid - 1;
-            }
-            qi = lo;
-        }
+        const int g = g0 + j;
+        auto field = [&](int f) { return __builtin_amdgcn_readfirstlane(item[f * kMaxClaim + j]); };
+        const int qi = field(kItQuery);
         const QueryDesc& q = P.queries[qi];
         if (qi != cur) {
             if (cur >= 0) {
                 const QueryDesc& oq = P.queries[cur];
                 flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
-                wave_flush(A.acc, A.ovf, oq.acc, oq.overflow);
+                wave_flush(A.acc, A.ovf, oq.acc + acc_slot, oq.overflow);
                 if (kStats) wave_flush_stats(A.st, oq.stats);
                 A.acc = 0ull;
                 A.ovf = 0;
@@ -1023,59 +1126,15 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
             cur = qi;
             per_arc = q.per_arc;
         }
-        const int i = q.item_lo + (g - q.item_begin) * q.item_stride;
         const int k = q.k;
         const u64 t_item = kStats ? wall_clock64() : 0ull;
-        // the item: one part of a heavy arc, or (a part of) a light vertex
-        int u, r = -1, part, nparts, tag;
-        int kind = kItemHeavyArc;
-        bool heavy;
-        if (q.arc_list) {
-            // list mode: one part of one listed arc; counts go to its list slot
-            tag = q.arc_items[2 * i];
-            const int pw = q.arc_items[2 * i + 1];
-            const int e = q.arc_list[tag];
-            u = q.dag_src[e];
-            r = e - q.dag_ptr[u];
-            part = pw & 0xffff;
-            nparts = pw >> 16;
-            heavy = q.dag_ptr[u + 1] - q.dag_ptr[u] > kLightMaxDeg;
-        } else {
-            // bucket holding item i, then the arc or vertex and the part (part-major)
-            int lo = 0, hi = q.n_buckets - 1;
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (q.buckets[4 * mid] <= i) lo = mid;
-                else hi = mid - 1;
-            }
-            const int key = q.buckets[4 * lo + 3] >> 2;
-            kind = q.buckets[4 * lo + 3] & 3;
-            heavy = kind == kItemHeavyArc || kind == kItemHeavyVertex;
-            const int cnt = q.buckets[4 * lo + 2];
-            const int local = i - q.buckets[4 * lo];
-            part = local / cnt;
-            const int which = q.buckets[4 * lo + 1] + (local - part * cnt);
-            if (kind == kItemHeavyArc) {
-                const int e = q.rows.harcs[which];
-                u = q.dag_src[e];
-                r = e - q.dag_ptr[u];
-                nparts = arc_parts(key, k, q.split_pct);
-                tag = e;
-            } else if (kind == kItemHeavyVertex) {
-                u = q.order[which];
-                nparts = 1;
-                tag = -1;
-            } else {
-                u = q.order[q.light_first + which];
-                nparts = kind == kItemLightVertex ? light_parts(key + 1, k, q.split_pct) : 1;
-                tag = -1;
-            }
-        }
-        const int a0 = q.dag_ptr[u];
-        const int d = q.dag_ptr[u + 1] - a0;
-        if (heavy) {
-            const HeavyCtx<true> H{RowRef<true>{(glb_u64*)(q.rows.rows + q.rows.rows_off[u])},
-                                   (d + 63) >> 6, k - 1, tag};
+        const int kind = field(kItKind), r = field(kItRow), tag = field(kItTag), a0 = field(kItArc0);
+        const int d = field(kItDegree), pw = field(kItPart);
+        const int part = pw & 0xffff, nparts = pw >> 16;
+        const u64* rows = q.rows.rows + field(kItRowsOff);
+        ++j;
+        if (kind == kItemHeavyArc || kind == kItemHeavyVertex) {
+            const HeavyCtx<true> H{RowRef<true>{(glb_u64*)rows}, (d + 63) >> 6, k - 1, tag};
             if (kind == kItemHeavyVertex) heavy_vertex<kStats, kPerArc, kRegL>(H, d, wb, A, per_arc);
             else heavy_arc<kStats, kPerArc, kRegL>(H, r, part, nparts, wb, A, per_arc);
         } else if (kind == kItemLightRoot) {
@@ -1083,7 +1142,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
             // the vertex itself (mask of all d positions, k - 1 to choose)
             if (wb.n + d + 1 > kWaveBufRows) flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
             if (lane < d) {
-                wb.rows[wb.n + lane] = q.rows.rows[q.rows.rows_off[u] + lane];
+                wb.rows[wb.n + lane] = rows[lane];
                 wb.meta[wb.n + lane] = (wb.n << 8) | (k - 2);
             }
             if (lane == 0) {
@@ -1098,7 +1157,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
             // (every nparts-th one, or the one listed) become units
             if (wb.n + d > kWaveBufRows) flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
             if (lane < d) {
-                wb.rows[wb.n + lane] = q.rows.rows[q.rows.rows_off[u] + lane];
+                wb.rows[wb.n + lane] = rows[lane];
                 wb.meta[wb.n + lane] = (wb.n << 8) | (k - 2);
                 if (kPerArc) wb.tags[wb.n + lane] = tag < 0 ? a0 + lane : tag;
             }
@@ -1117,7 +1176,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     if (cur >= 0) {
         const QueryDesc& oq = P.queries[cur];
         flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
-        wave_flush(A.acc, A.ovf, oq.acc, oq.overflow);
+        wave_flush(A.acc, A.ovf, oq.acc + acc_slot, oq.overflow);
         if (kStats) wave_flush_stats(A.st, oq.stats);
     }
     if (kStats && lane == 0) {
@@ -1148,7 +1207,7 @@ static hipError_t launch_variant(const KParams& P, const CountLaunch& cl, hipStr
 }
 
 template <int kMode>
-static hipError_t launch_mode(const KParams& P, const CountLaunch& cl, hipStream_t s)
+hipError_t launch_mode(const KParams& P, const CountLaunch& cl, hipStream_t s)
 {
     const int v = (cl.stats ? 2 : 0) | (cl.per_arc ? 1 : 0);
     switch (v) {
@@ -1157,6 +1216,35 @@ static hipError_t launch_mode(const KParams& P, const CountLaunch& cl, hipStream
     case 2: return launch_variant<kMode, true, false>(P, cl, s);
     default: return launch_variant<kMode, true, true>(P, cl, s);
     }
+}
+
+// One translation unit per stack mode, so that they compile side by side:
+// this file by itself holds the host functions and the variants of k <= 8,
+// and is included with CITRON_COUNT_UNIT set to another mode by
+// kernels_count_lds.hip and kernels_count_deep.hip.
+#ifdef CITRON_COUNT_UNIT
+template hipError_t launch_mode<CITRON_COUNT_UNIT>(const KParams&, const CountLaunch&, hipStream_t);
+#else
+template hipError_t launch_mode<kStackReg>(const KParams&, const CountLaunch&, hipStream_t);
+extern template hipError_t launch_mode<kStackLds>(const KParams&, const CountLaunch&, hipStream_t);
+extern template hipError_t launch_mode<kStackGlobal>(const KParams&, const CountLaunch&, hipStream_t);
+
+int64_t count_scratch_words(int32_t, int32_t max_k, int32_t wg_waves)
+{
+    const int64_t w = wave_global_stack_words(max_k);
+    if (w == 0) return 0;
+    return ((int64_t)wg_waves * w + 31) & ~31ll;
+}
+
+int64_t count_deep_scratch_words(int32_t max_k, int32_t wg_waves)
+{
+    if (stack_mode(max_k) != kStackGlobal) return 0;
+    return ((int64_t)wg_waves * wave_stack_words(max_k) + 31) & ~31ll;
+}
+
+int32_t count_lds_bytes(int32_t arc_max, int32_t max_k, int32_t wg_waves, bool per_arc)
+{
+    return wg_waves * wave_lds_bytes(max_k, arc_max, per_arc);
 }
 
 hipError_t launch_count(const CountLaunch& cl, hipStream_t s)
@@ -1175,24 +1263,21 @@ hipError_t launch_count(const CountLaunch& cl, hipStream_t s)
     P.flush_rows = cl.flush_rows > kWaveBufRows ? kWaveBufRows : cl.flush_rows;
     P.arc_lds_max = clamp_arc_max(cl.arc_lds_max);
     P.progress = cl.progress;
-    // Items claimed per atomic.  All waves claim from one device-wide
-    // counter, whose atomics are serialised (about 12 ns each on MI355X, so
-    // one item per claim caps a launch near 85 M items/s); a wave claims a
-    // run of consecutive items instead, short enough that every wave still
-    // makes about eight claims.  Items are in descending cost order, so the
-    // items of a run cost about the same.
+    // A launch is no wider than its items.  Items per claim: a run short
+    // enough that every wave still makes about eight claims; items are in
+    // descending cost order, so those of a run cost about the same.
+    CountLaunch c2 = cl;
     {
-        const int64_t waves = (int64_t)cl.blocks * cl.wg_waves;
+        const int64_t need = ((int64_t)cl.total_items + cl.wg_waves - 1) / cl.wg_waves;
+        if (need < c2.blocks) c2.blocks = (int32_t)need;
+        const int64_t waves = (int64_t)c2.blocks * cl.wg_waves;
         int64_t c = (int64_t)cl.total_items / (waves * 8);
-        c = c < 1 ? 1 : (c > kMaxClaim ? kMaxClaim : c);
-        // the counter ends at most waves * chunk past total_items
-        if ((int64_t)cl.total_items + waves * c >= (1ll << 31)) c = 1;
-        P.chunk = (int32_t)c;
+        P.chunk = (int32_t)(c < 1 ? 1 : (c > kMaxClaim ? kMaxClaim : c));
     }
     switch (stack_mode(cl.max_k)) {
-    case kStackReg: return launch_mode<kStackReg>(P, cl, s);
-    case kStackLds: return launch_mode<kStackLds>(P, cl, s);
-    default: return launch_mode<kStackGlobal>(P, cl, s);
+    case kStackReg: return launch_mode<kStackReg>(P, c2, s);
+    case kStackLds: return launch_mode<kStackLds>(P, c2, s);
+    default: return launch_mode<kStackGlobal>(P, c2, s);
     }
 }
 
@@ -1293,5 +1378,6 @@ hipError_t launch_fill_u64(u64* p, u64 v, int64_t n, hipStream_t s)
     fill_u64_kernel<<<(unsigned)blocks, 256, 0, s>>>(p, v, n);
     return hipGetLastError();
 }
+#endif  // CITRON_COUNT_UNIT
 
 }  // namespace citron

@@ -202,7 +202,7 @@ bool issue_step(citron_server* s, Step& st, bool fast, int wg, int32_t blocks)
         }
     }
     hipError_t e = hipEventRecord(st.start, st.stream);
-    if (e == hipSuccess) e = launch_fill_i32(st.d_item_ctr, 0, 1, st.stream);
+    if (e == hipSuccess) e = launch_fill_i32(st.d_item_ctr, 0, kClaimInts, st.stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(st.d_q, st.h_q, sizeof(QueryDesc) * (size_t)nq, hipMemcpyHostToDevice, st.stream);
     if (e == hipSuccess) {
@@ -313,7 +313,7 @@ void worker_main(citron_server* s)
                 s->used += r.footprint;
                 r.t_admit = now_ns();
                 r.id = s->next_id++;
-                r.q = make_query(g, r.k, s->d_acc + r.slot, s->d_ovf + r.slot, nullptr, nullptr, 0);
+                r.q = make_query(g, r.k, s->d_acc + (size_t)r.slot * kAccWords, s->d_ovf + r.slot, nullptr, nullptr, 0);
                 r.n_items = r.q.n_items;
                 r.fast = r.n_items <= kFastItems;
                 r.issued = 0;
@@ -330,7 +330,7 @@ void worker_main(citron_server* s)
             // zero the new slots before any step can touch them
             hipError_t e = hipSuccess;
             for (int32_t slot : fresh_slots) {
-                if (e == hipSuccess) e = launch_fill_u64(s->d_acc + slot, 0, 1, s->ctl);
+                if (e == hipSuccess) e = launch_fill_u64(s->d_acc + (size_t)slot * kAccWords, 0, kAccWords, s->ctl);
                 if (e == hipSuccess) e = launch_fill_i32(s->d_ovf + slot, 0, 1, s->ctl);
             }
             if (e == hipSuccess) e = hipStreamSynchronize(s->ctl);
@@ -380,8 +380,8 @@ void worker_main(citron_server* s)
         for (const Req& r : fin) {
             if (r.failed) continue;
             if (e == hipSuccess)
-                e = hipMemcpyAsync(s->h_acc + r.slot, s->d_acc + r.slot, sizeof(unsigned long long),
-                                   hipMemcpyDeviceToHost, s->ctl);
+                e = hipMemcpyAsync(s->h_acc + (size_t)r.slot * kAccWords, s->d_acc + (size_t)r.slot * kAccWords,
+                                   sizeof(unsigned long long) * kAccWords, hipMemcpyDeviceToHost, s->ctl);
             if (e == hipSuccess)
                 e = hipMemcpyAsync(s->h_ovf + r.slot, s->d_ovf + r.slot, sizeof(int32_t), hipMemcpyDeviceToHost,
                                    s->ctl);
@@ -390,8 +390,10 @@ void worker_main(citron_server* s)
         if (e != hipSuccess) s->worker_error = hipGetErrorString(e);
         std::lock_guard<std::mutex> lock(s->mu);
         for (Req& r : fin) {
+            bool carry = s->h_ovf[r.slot] != 0;
+            const uint64_t c = sum_acc_slots(s->h_acc + (size_t)r.slot * kAccWords, &carry);
             if (r.failed || e != hipSuccess) complete(s, r, 0, CITRON_EDEVICE);
-            else complete(s, r, s->h_acc[r.slot], s->h_ovf[r.slot] ? CITRON_EOVERFLOW : CITRON_OK);
+            else complete(s, r, c, carry ? CITRON_EOVERFLOW : CITRON_OK);
             s->free_slots.push_back(r.slot);
             s->used -= r.footprint;
         }
@@ -441,10 +443,10 @@ citron_server* citron_server_create(int64_t hbm_budget_bytes, int32_t max_slots,
     // deepest supported k sizes the stack scratch of each step
     const int32_t blocks = device_cus(s->device) * s->tuning.blocks_per_cu;
     s->scratch_words = count_scratch_words(0, CITRON_KMAX, s->tuning.wg_waves);
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_acc, sizeof(unsigned long long) * (size_t)max_slots);
+    if (e == hipSuccess) e = hipMalloc((void**)&s->d_acc, sizeof(unsigned long long) * kAccWords * (size_t)max_slots);
     if (e == hipSuccess) e = hipMalloc((void**)&s->d_ovf, sizeof(int32_t) * (size_t)max_slots);
     if (e == hipSuccess)
-        e = hipHostMalloc((void**)&s->h_acc, sizeof(unsigned long long) * (size_t)max_slots, hipHostMallocDefault);
+        e = hipHostMalloc((void**)&s->h_acc, sizeof(unsigned long long) * kAccWords * (size_t)max_slots, hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_ovf, sizeof(int32_t) * (size_t)max_slots, hipHostMallocDefault);
     for (Step& st : s->steps) {
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&st.stream, hipStreamNonBlocking);
@@ -453,7 +455,7 @@ citron_server* citron_server_create(int64_t hbm_budget_bytes, int32_t max_slots,
         if (e == hipSuccess) e = hipMalloc((void**)&st.d_q, sizeof(QueryDesc) * (size_t)max_slots);
         if (e == hipSuccess)
             e = hipHostMalloc((void**)&st.h_q, sizeof(QueryDesc) * (size_t)max_slots, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipMalloc((void**)&st.d_item_ctr, sizeof(int32_t));
+        if (e == hipSuccess) e = hipMalloc((void**)&st.d_item_ctr, sizeof(int32_t) * kClaimInts);
         if (e == hipSuccess) e = hipMalloc((void**)&st.d_scratch, (size_t)(s->scratch_words * 8 * blocks));
     }
     if (e != hipSuccess) {

@@ -68,3 +68,28 @@ def test_degree_ordering_after_load_with_a_core_ordered_neighbour(citron_gpu):
         assert a.count(k) == b.count(k) == oracle.count(g, k)[0]
     a.free()
     b.free()
+
+
+@pytest.mark.parametrize("n_arcs", [1, 2, 15, 16, 17, 31, 33, 4095, 4097, 70001])
+@pytest.mark.parametrize("k", [4, 5])
+def test_claims_at_run_shard_and_grid_sizes(citron_gpu, n_arcs, k):
+    """Work items in numbers around a run, a round of the cursors, the waves
+    of the grid and several runs per wave: every listed arc counted once."""
+    import oracle
+    g = gg.rmat(9, 20, seed=5)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    total, every = h.count_per_arc(k)
+    assert total == oracle.count(g, k)[0] == int(every.sum())
+    arcs = np.random.default_rng(n_arcs).integers(0, g.m, n_arcs).astype(np.int32)
+    assert np.array_equal(h.count_arcs(k, arcs), every[arcs])
+    h.free()
+
+
+def test_runs_that_span_queries(citron_gpu):
+    """A batch whose queries are smaller than a claimed run of items."""
+    import oracle
+    gs = [gg.rmat(6, 6, seed=900 + i) for i in range(40)] + [gg.rmat(11, 16, seed=950)]
+    hs = [citron_gpu.Graph.from_csr(g.row_ptr, g.col).order() for g in gs]
+    q = [(i, k) for k in (4, 5, 6) for i in range(len(gs))]
+    got = citron_gpu.count_batch([hs[i] for i, _ in q], [k for _, k in q])
+    assert got == [oracle.count(gs[i], k)[0] for i, k in q]

@@ -143,6 +143,9 @@ static void free_graph_memory(citron_graph* g)
     dfree(g->d_rows_off);
     dfree(g->d_rows);
     dfree(g->d_arc_c);
+    dfree(g->d_hoff);
+    dfree(g->d_hrows);
+    dfree(g->d_hpos);
     dfree(g->d_harcs);
     dfree(g->d_hscan);
     for (int32_t* p : g->retired_buckets) dfree(p);
@@ -254,16 +257,30 @@ citron_status ensure_rows(citron_graph* g)
         if (total >= (1LL << 31)) return fail(CITRON_EINVAL, "subgraph rows exceed 2^31 words");
     }
     // row offsets: exclusive scan of d(u) * W(u) (outdeg buffer as scratch)
-    e = launch_rows_len(g->n, g->d_dag_ptr, g->d_outdeg, s);
+    e = launch_rows_len(g->n, g->d_dag_ptr, false, g->d_outdeg, s);
     if (e == hipSuccess) e = scan_exclusive(g->d_outdeg, g->d_rows_off, g->n, g->d_scan_ws, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(&g->h_small->rows_total, g->d_rows_off + g->n, sizeof(int32_t),
                            hipMemcpyDeviceToHost, s);
+    const bool heavy = g->plan.n_heavy > 0;
+    if (heavy) {
+        if ((!g->d_hoff && (st = dalloc(&g->d_hoff, (size_t)g->n + 1, acct, "sorted rows"))) ||
+            (!g->d_hpos && (st = dalloc(&g->d_hpos, (size_t)g->m, acct, "sorted rows"))))
+            return st;
+        if (e == hipSuccess) e = launch_rows_len(g->n, g->d_dag_ptr, true, g->d_outdeg, s);
+        if (e == hipSuccess) e = scan_exclusive(g->d_outdeg, g->d_hoff, g->n, g->d_scan_ws, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(&g->h_small->hrows_total, g->d_hoff + g->n, sizeof(int32_t),
+                               hipMemcpyDeviceToHost, s);
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "row offsets");
     const int64_t words = g->h_small->rows_total;
     if (words < 0) return fail(CITRON_EINVAL, "subgraph rows exceed 2^31 words");
     if (!g->d_rows && (st = dalloc(&g->d_rows, (size_t)std::max<int64_t>(words, 1), acct, "subgraph rows")))
+        return st;
+    if (heavy && !g->d_hrows &&
+        (st = dalloc(&g->d_hrows, (size_t)g->h_small->hrows_total, acct, "sorted rows")))
         return st;
     SmallDev* sd = g->d_small;
     // vertices of out-degree < 2 are not built (their arcs close no
@@ -291,6 +308,22 @@ citron_status ensure_rows(citron_graph* g)
     P.build_stats = sd->build_stats;
     e = launch_build_rows(P, device_cus(g->device) * g->tuning.build_blocks_per_cu, s);
     if (e != hipSuccess) return hip_fail(e, "subgraph build");
+    if (heavy) {
+        SortedRowsParams sp;
+        sp.n_heavy = g->plan.n_heavy;
+        sp.order = g->pb.order;
+        sp.dag_ptr = g->d_dag_ptr;
+        sp.dag_col = g->d_dag_col;
+        sp.row_ptr = g->d_row_ptr;
+        sp.key = g->order_kind == 1 ? g->d_key : nullptr;
+        sp.rows_off = g->d_rows_off;
+        sp.rows = g->d_rows;
+        sp.hoff = g->d_hoff;
+        sp.hrows = g->d_hrows;
+        sp.hpos = g->d_hpos;
+        e = launch_sorted_rows(sp, s);
+        if (e != hipSuccess) return hip_fail(e, "sorted rows");
+    }
     SortBuffers sb = {};
     {
         const size_t tb = sched_sort_temp_bytes(g->m);
@@ -345,11 +378,13 @@ citron_status ensure_scratch(citron_graph* g, int64_t bytes)
     return CITRON_OK;
 }
 
-// Work items of a k-clique count (k >= 4): heavy arcs with |C_uv| >= k-2 in
-// buckets of equal |C_uv|, light vertices with out-degree >= k-1 in buckets of
-// equal out-degree, merged into one table by cost key (|C_uv|, or out-degree
-// - 1 for a light vertex), largest first, so that the costliest work starts
-// first.  Arcs and vertices are split into parts (arc_parts, light_parts).
+// Work items of a k-clique count (k >= 4): the dense kernel's arcs
+// (dense_arc) in buckets of equal |C_uv|, largest first; then the other heavy
+// arcs with |C_uv| >= k-2 in buckets of equal |C_uv| and light vertices with
+// out-degree >= k-1 in buckets of equal out-degree, merged by cost key
+// (|C_uv|, or out-degree - 1 for a light vertex), largest first, so that the
+// costliest work starts first.  Arcs and vertices are split into parts
+// (dense_parts, arc_parts, light_parts).
 citron_status ensure_buckets(citron_graph* g, int32_t k)
 {
     const int32_t pct = g->tuning.split_pct;
@@ -367,34 +402,48 @@ citron_status ensure_buckets(citron_graph* g, int32_t k)
         return g->h_vscan[(size_t)(D - x + 1)];
     };
     const int64_t n_heavy = v_at_least(kLightMaxDeg + 1);
-    struct B { int32_t key, first, cnt, light; };
-    std::vector<B> hb, lb;
+    struct B { int32_t key, first, cnt, kind; };
+    std::vector<B> db, hb, lb;
     // heavy-arc buckets: bucket j of the arc order holds |C_uv| = D-1-j
     for (int32_t j = 0; j < D; ++j) {
         const int32_t c = D - 1 - j;
         if (c < k - 2) break;
         const int32_t cnt = g->h_hscan[(size_t)j + 1] - g->h_hscan[(size_t)j];
-        if (cnt > 0) hb.push_back({c, g->h_hscan[(size_t)j], cnt, 0});
+        if (cnt <= 0) continue;
+        if (dense_arc(c, k)) db.push_back({c, g->h_hscan[(size_t)j], cnt, kItemDenseArc});
+        else hb.push_back({c, g->h_hscan[(size_t)j], cnt, kItemHeavyArc});
     }
     // light-vertex buckets: out-degree d = 64 down to max(k-1, 2)
     for (int32_t d = kLightMaxDeg; d >= std::max(k - 1, 2); --d) {
         const int64_t cnt = v_at_least(d) - v_at_least(d + 1);
-        if (cnt > 0) lb.push_back({d - 1, (int32_t)(v_at_least(d + 1) - n_heavy), (int32_t)cnt, 1});
+        if (cnt > 0) lb.push_back({d - 1, (int32_t)(v_at_least(d + 1) - n_heavy), (int32_t)cnt, kItemLightVertex});
     }
     std::vector<int32_t> tab;
     int64_t items = 0;
-    size_t ih = 0, il = 0;
-    while (ih < hb.size() || il < lb.size()) {
-        const bool take_h = il >= lb.size() || (ih < hb.size() && hb[ih].key >= lb[il].key);
-        const B b = take_h ? hb[ih++] : lb[il++];
-        const int32_t parts = b.light ? light_parts(b.key + 1, k, pct) : arc_parts(b.key, k, pct);
+    auto add = [&](const B& b) {
+        const int32_t parts = b.kind == kItemLightVertex ? light_parts(b.key + 1, k, pct)
+                              : b.kind == kItemDenseArc  ? dense_parts(b.key, k, pct)
+                                                         : arc_parts(b.key, k, pct);
         tab.push_back((int32_t)items);
         tab.push_back(b.first);
         tab.push_back(b.cnt);
-        tab.push_back((b.key << 2) | (b.light ? kItemLightVertex : kItemHeavyArc));
+        tab.push_back((b.key << kItemKindBits) | b.kind);
         items += (int64_t)b.cnt * parts;
-        if (items > 0x7fffffffLL) return fail(CITRON_EINVAL, "too many work items for one count");
+        return items <= 0x7fffffffLL;
+    };
+    bool fits = true;
+    int32_t ends[kDenseClasses];
+    size_t id = 0;
+    for (int32_t s = 0; s < kDenseClasses; ++s) {
+        while (fits && id < db.size() && dense_space(db[id].key) == s) fits = add(db[id++]);
+        ends[s] = (int32_t)std::min<int64_t>(items, 0x7fffffff);
     }
+    size_t ih = 0, il = 0;
+    while (fits && (ih < hb.size() || il < lb.size())) {
+        const bool take_h = il >= lb.size() || (ih < hb.size() && hb[ih].key >= lb[il].key);
+        fits = add(take_h ? hb[ih++] : lb[il++]);
+    }
+    if (!fits) return fail(CITRON_EINVAL, "too many work items for one count");
     const int32_t nb = (int32_t)(tab.size() / 4);
     tab.push_back((int32_t)items);
     tab.push_back(0);
@@ -407,6 +456,7 @@ citron_status ensure_buckets(citron_graph* g, int32_t k)
     if (e != hipSuccess) return hip_fail(e, "item buckets");
     g->n_buckets[k] = nb;
     g->n_work[k] = (int32_t)items;
+    memcpy(g->sched_end[k], ends, sizeof(ends));
     g->bucket_split[k] = pct;
     return CITRON_OK;
 }
@@ -434,7 +484,7 @@ citron_status ensure_vbuckets(citron_graph* g, int32_t k)
         tab.push_back((int32_t)items);
         tab.push_back((int32_t)(heavy ? v_at_least(d + 1) : v_at_least(d + 1) - n_heavy));
         tab.push_back((int32_t)cnt);
-        tab.push_back((d << 2) | (heavy ? kItemHeavyVertex : kItemLightRoot));
+        tab.push_back((d << kItemKindBits) | (heavy ? kItemHeavyVertex : kItemLightRoot));
         items += cnt;
     }
     const int32_t nb = (int32_t)(tab.size() / 4);
@@ -453,7 +503,7 @@ citron_status ensure_vbuckets(citron_graph* g, int32_t k)
 }
 
 QueryDesc make_query(const citron_graph* g, int32_t k, unsigned long long* acc, int32_t* ovf,
-                     unsigned long long* per_arc, unsigned long long* stats, int32_t item_begin)
+                     unsigned long long* per_arc, unsigned long long* stats)
 {
     QueryDesc q;
     memset(&q, 0, sizeof(q));
@@ -464,6 +514,9 @@ QueryDesc make_query(const citron_graph* g, int32_t k, unsigned long long* acc, 
     q.rows.rows = g->d_rows;
     q.rows.arc_c = g->d_arc_c;
     q.rows.harcs = g->d_harcs;
+    q.rows.hoff = g->d_hoff;
+    q.rows.hrows = g->d_hrows;
+    q.rows.hpos = g->d_hpos;
     q.acc = acc;
     q.overflow = ovf;
     q.per_arc = per_arc;
@@ -473,7 +526,7 @@ QueryDesc make_query(const citron_graph* g, int32_t k, unsigned long long* acc, 
     q.n_buckets = g->n_buckets[k];
     q.light_first = g->plan.n_heavy;
     q.n_work = g->n_work[k];
-    q.item_begin = item_begin;
+    memcpy(q.sched_end, g->sched_end[k], sizeof(q.sched_end));
     q.n_items = q.n_work;
     q.item_stride = 1;
     q.split_pct = g->bucket_split[k];
@@ -604,13 +657,14 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
         return hip_fail(e, "fill");
     if (per_arc && (e = launch_fill_u64(per_arc, 0, arc_list ? n_list : g->m, s)) != hipSuccess)
         return hip_fail(e, "fill");
-    ctl.query = make_query(g, k, g->d_ctl->acc, &g->d_ctl->overflow, per_arc, stats ? g->d_stats : nullptr, 0);
+    ctl.query = make_query(g, k, g->d_ctl->acc, &g->d_ctl->overflow, per_arc, stats ? g->d_stats : nullptr);
     if (vertex_rooted) {
         QueryDesc& q = ctl.query;
         q.buckets = g->d_vbuckets[k];
         q.n_buckets = g->n_vbuckets[k];
         q.n_work = g->n_vwork[k];
         q.n_items = q.n_work;
+        memset(q.sched_end, 0, sizeof(q.sched_end));
     }
     ListItems li;
     if (nparts > 1) {
@@ -628,12 +682,13 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
         ctl.query.arc_items = li.items;
         ctl.query.n_items = li.total;
     }
+    // instrumented launches keep to the count kernel, which counts its work
+    CountLaunch cl;
+    place_query(ctl.query, !stats, cl.space_items);
     e = hipMemcpyAsync(g->d_ctl, &ctl, sizeof(CountCtl), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(query)");
-    CountLaunch cl;
     cl.queries = &g->d_ctl->query;
     cl.n_queries = 1;
-    cl.total_items = ctl.query.n_items;
     cl.item_ctr = g->d_ctl->cursors;
     cl.scratch = g->d_scratch;
     cl.scratch_words = swords;

@@ -28,12 +28,13 @@ struct SmallDev {
 // What one count launch reads and updates: uploaded as one copy before the
 // launch (partial sums, flag and cursors in their starting state); the sums
 // and the flag come back as one copy.
+// What is only read, what waves add to and what they claim from lie in lines
+// of their own.
 struct CountCtl {
-    unsigned long long acc[kAccWords];
+    alignas(256) unsigned long long acc[kAccWords];
     int32_t overflow;
-    int32_t pad;
-    QueryDesc query;
-    int32_t cursors[kClaimInts];
+    alignas(256) QueryDesc query;
+    alignas(256) int32_t cursors[kLaunchInts];
 };
 
 // Pinned host mirror for the copies back.
@@ -48,6 +49,7 @@ struct SmallHost {
     uint64_t tri_acc;
     int32_t tri_ovf;
     int32_t rows_total;
+    int32_t hrows_total;
     int32_t peel[4];
     uint64_t build_stats[kNumStats];
 };
@@ -98,6 +100,9 @@ struct citron_graph {
     int32_t* d_rows_off = nullptr;          // n + 1
     unsigned long long* d_rows = nullptr;
     int32_t* d_arc_c = nullptr;             // m
+    int32_t* d_hoff = nullptr;              // n + 1: the heavy vertices' rows in sorted positions
+    unsigned long long* d_hrows = nullptr;
+    uint16_t* d_hpos = nullptr;             // m
     int32_t* d_harcs = nullptr;             // m
     int32_t* d_hscan = nullptr;             // D + 1
     std::vector<int32_t> h_hscan;           // heavy arcs by |C_uv|, scanned
@@ -113,6 +118,7 @@ struct citron_graph {
     int64_t bucket_bytes[CITRON_KMAX + 1] = {};   // device bytes of each table
     int32_t n_buckets[CITRON_KMAX + 1] = {};
     int32_t n_work[CITRON_KMAX + 1] = {};
+    int32_t sched_end[CITRON_KMAX + 1][citron::kDenseClasses] = {};   // ends of the dense spaces
     // per k: the vertex-rooted schedule (whole vertices, no split)
     int32_t* d_vbuckets[CITRON_KMAX + 1] = {};
     int64_t vbucket_bytes[CITRON_KMAX + 1] = {};
@@ -136,7 +142,7 @@ citron_status ensure_buckets(citron_graph* g, int32_t k);
 citron_status ensure_vbuckets(citron_graph* g, int32_t k);
 citron_status check_count_args(const citron_graph* g, int32_t k, bool* trivial, uint64_t* value);
 QueryDesc make_query(const citron_graph* g, int32_t k, unsigned long long* acc, int32_t* ovf,
-                     unsigned long long* per_arc, unsigned long long* stats, int32_t item_begin);
+                     unsigned long long* per_arc, unsigned long long* stats);
 void batch_forget_graph(const citron_graph* g);
 
 }  // namespace citron

@@ -37,7 +37,7 @@ struct BatchExec {
     std::vector<int32_t> qmap;         // kernel query -> caller index
     unsigned long long* d_acc = nullptr;  // nq * kAccWords, then nq flags and the cursors
     int32_t* d_ovf = nullptr;          // nq, within d_acc's allocation
-    int32_t* d_item_ctr = nullptr;     // kClaimInts, likewise
+    int32_t* d_item_ctr = nullptr;     // kLaunchInts, likewise
     QueryDesc* d_q = nullptr;
     void* d_scratch = nullptr;
     QueryDesc* h_q = nullptr;          // pinned
@@ -116,7 +116,8 @@ void batch_forget_graph(const citron_graph* g)
 citron_status batch_build(const BatchKey& key, const citron_tuning& t, BatchExec* be, hipStream_t s)
 {
     const int32_t nq = (int32_t)key.ks.size();
-    int32_t total_items = 0, max_k = 4;
+    int32_t max_k = 4;
+    CountLaunch cl;
     for (int32_t i = 0; i < nq; ++i) max_k = std::max(max_k, key.ks[i]);
     hipError_t e;
     const int wg = t.wg_waves;
@@ -127,10 +128,10 @@ citron_status batch_build(const BatchKey& key, const citron_tuning& t, BatchExec
         e = hipMalloc((void**)&(p), (bytes) > 0 ? (bytes) : 8);                       \
         if (e != hipSuccess) return fail(CITRON_ENOMEM, "hipMalloc failed for batch"); \
     } while (0)
-    // one block: partial sums, flags (rounded to 8 bytes), claim cursors
-    const size_t ovf_words = ((size_t)nq + 1) / 2;
+    // one block: partial sums, flags, and from a line of their own the cursors
+    const size_t ovf_words = (((size_t)nq + 1) / 2 + 31) & ~(size_t)31;
     const size_t res_words = (size_t)nq * kAccWords + ovf_words;
-    const size_t ctl_words = res_words + kClaimInts / 2;
+    const size_t ctl_words = res_words + kLaunchInts / 2;
     BALLOC(be->d_acc, sizeof(unsigned long long) * ctl_words);
     be->d_ovf = reinterpret_cast<int32_t*>(be->d_acc + (size_t)nq * kAccWords);
     be->d_item_ctr = reinterpret_cast<int32_t*>(be->d_acc + res_words);
@@ -142,17 +143,14 @@ citron_status batch_build(const BatchKey& key, const citron_tuning& t, BatchExec
         return fail(CITRON_ENOMEM, "hipHostMalloc failed for batch");
     be->h_ovf = reinterpret_cast<int32_t*>(be->h_acc + (size_t)nq * kAccWords);
     for (int32_t i = 0; i < nq; ++i) {
-        be->h_q[i] = make_query(key.graphs[i], key.ks[i], be->d_acc + (size_t)i * kAccWords, be->d_ovf + i, nullptr, nullptr,
-                                total_items);
-        total_items += be->h_q[i].n_items;
+        be->h_q[i] = make_query(key.graphs[i], key.ks[i], be->d_acc + (size_t)i * kAccWords, be->d_ovf + i, nullptr, nullptr);
+        place_query(be->h_q[i], true, cl.space_items);
     }
     be->nq = nq;
-    be->total_items = total_items;
+    be->total_items = (int32_t)launch_items(cl);
 
-    CountLaunch cl;
     cl.queries = be->d_q;
     cl.n_queries = nq;
-    cl.total_items = total_items;
     cl.item_ctr = be->d_item_ctr;
     cl.scratch = reinterpret_cast<unsigned long long*>(be->d_scratch);
     cl.scratch_words = swords;

@@ -98,7 +98,25 @@ struct RowsDev {
     const unsigned long long* rows; // all rows
     const int32_t* arc_c;           // m: popcount of arc e's row = |C_uv|
     const int32_t* harcs;           // arcs of heavy vertices by |C_uv| descending
+    // Rows of the heavy vertices again, in the order of the DAG: positions
+    // sorted by the ordering (key, id), so that a vertex's neighbours come
+    // after it and every matrix of rows is strictly upper triangular.  The
+    // dense kernel works on these; the count kernel, whose lanes take a row
+    // each, keeps to the id order, which spreads the long rows (with sorted
+    // rows its k = 4 launch on a 2^20-vertex power-law graph took twice as
+    // long).
+    const int32_t* hoff;            // n: first word of u's rows in hrows (heavy u)
+    const unsigned long long* hrows;
+    const uint16_t* hpos;           // m: sorted position of arc e among its source's (heavy sources)
 };
+
+// Item spaces of a launch: dense arcs by row words, kDenseClasses of them
+// down to 1, then everything else.
+constexpr int kDenseClasses = 6;
+constexpr int kSpaces = kDenseClasses + 1;
+constexpr int kRestSpace = kDenseClasses;
+constexpr int kLaunchInts = kSpaces * kClaimInts;
+__host__ __device__ inline int dense_space(int c) { return kDenseClasses - (c + 63) / 64; }
 
 // One query of the count kernel (a (graph, k) pair).
 struct QueryDesc {
@@ -114,7 +132,7 @@ struct QueryDesc {
     // buckets (key |C_uv|) and light-vertex buckets (key out-degree - 1),
     // merged.  Bucket b: buckets[4b] = first item, [4b+1] = first arc (index
     // into harcs) or first light vertex (index into the light part of order),
-    // [4b+2] = arcs or vertices in the bucket, [4b+3] = key << 2 | kind
+    // [4b+2] = arcs or vertices in the bucket, [4b+3] = key << 3 | kind
     // (BucketKind).  An arc or vertex is split into parts (arc_parts /
     // light_parts); items of a bucket are part-major.  buckets[4 n_buckets]
     // = item count.  The vertex-rooted schedule has only the two vertex
@@ -124,12 +142,18 @@ struct QueryDesc {
     int32_t light_first;         // index in order of the first light vertex
     int32_t k;
     int32_t n_work;              // items of the query (all buckets)
-    int32_t item_begin;          // first global item of this query
     int32_t n_items;             // items of this query in the launch
-    int32_t item_lo;             // local index of the query's first item in the launch
-    int32_t item_stride;         // local item of launch item g: item_lo + (g - item_begin) * item_stride
+    int32_t item_lo;             // schedule item of the query's j-th launch item: item_lo + j * item_stride
+    int32_t item_stride;
+    // The kernels of a launch each take a space of items: the dense kernel's
+    // instances by row words, largest first, then the count kernel.  In the
+    // schedule the spaces follow one another (sched_end); place_query sets
+    // where the query's launch items of space s start among all of s's items
+    // (space_begin), and how many launch items come before them (space_off).
+    int32_t sched_end[kDenseClasses];
+    int32_t space_begin[kSpaces];
+    int32_t space_off[kSpaces];
     int32_t split_pct;           // split scale the buckets were built with (arc_parts, light_parts)
-    int32_t pad;
     // list mode (arc_list != nullptr): item j is (slot, part) = (arc_items[2j],
     // arc_items[2j+1] & 0xffff) of arc arc_list[slot], split into
     // arc_items[2j+1] >> 16 parts; its counts go to per-arc slot `slot`
@@ -137,12 +161,14 @@ struct QueryDesc {
     const int32_t* arc_items;
 };
 
-// Kinds of work item (low two bits of a bucket's key word).
+// Kinds of work item (low bits of a bucket's key word).
+constexpr int kItemKindBits = 3;
 enum BucketKind {
     kItemHeavyArc = 0,     // one part of an arc of a heavy vertex (edge-rooted)
     kItemLightVertex = 1,  // (a part of) a light vertex, its arcs the units (edge-rooted)
     kItemHeavyVertex = 2,  // a whole heavy vertex, searched from its own root (vertex-rooted)
-    kItemLightRoot = 3     // a whole light vertex, one unit rooted at the vertex (vertex-rooted)
+    kItemLightRoot = 3,    // a whole light vertex, one unit rooted at the vertex (vertex-rooted)
+    kItemDenseArc = 4      // one part of a heavy vertex's arc for the dense kernel (edge-rooted)
 };
 
 // Parts a heavy arc with |C_uv| = c is split into for a k-clique count; each
@@ -163,6 +189,22 @@ __host__ __device__ inline int arc_parts(int c, int k, int pct)
     return scale_parts(c < 16 ? 1 : (c / 8 < 32 ? c / 8 : 32), pct);
 }
 
+// Arcs of heavy vertices the dense kernel takes in a k-clique count: at least
+// two levels above the triangle level (k >= 6), so that an arc's subgraph,
+// once laid out, serves many triangle counts, and sizes whose tiles fit LDS.
+constexpr int kDenseMin = 17;
+constexpr int kDenseMax = 64 * kDenseClasses;
+__host__ __device__ inline bool dense_arc(int c, int k) { return k >= 6 && c >= kDenseMin && c <= kDenseMax; }
+
+// Parts of such an arc (every P-th first-level branch): the workgroup shares
+// the arc's first level already, so parts only shorten the tail of deep counts.
+__host__ __device__ inline int dense_parts(int c, int k, int pct)
+{
+    if (k <= 6) return 1;
+    if (k == 7) return scale_parts(c / 64, pct);
+    return scale_parts(c / 8 < 32 ? c / 8 : 32, pct);
+}
+
 // Parts a light vertex (out-degree d <= 64, its subgraph one word per row)
 // is split into; each part takes every P-th arc of the vertex (speed only).
 __host__ __device__ inline int light_parts(int d, int k, int pct)
@@ -170,6 +212,27 @@ __host__ __device__ inline int light_parts(int d, int k, int pct)
     if (k <= 5) return 1;
     if (k == 6) return scale_parts(d >= 32 ? d / 8 : 1, pct);
     return scale_parts(d >= 12 ? d / 2 : 1, pct);
+}
+
+// Place a query's launch items (n_items, item_lo, item_stride set) in the
+// item spaces, after those placed before.  Without `dense` the count kernel
+// takes them all.
+inline void place_query(QueryDesc& q, bool dense, int32_t* space_items)
+{
+    int64_t before = 0;
+    for (int s = 0; s < kSpaces; ++s) {
+        int64_t upto = q.n_items;
+        if (s < kRestSpace) {
+            // launch items j with item_lo + j * item_stride < sched_end[s]
+            const int64_t end = dense && !q.arc_list ? q.sched_end[s] : 0;
+            upto = end > q.item_lo ? (end - q.item_lo + q.item_stride - 1) / q.item_stride : 0;
+            if (upto > q.n_items) upto = q.n_items;
+        }
+        q.space_off[s] = (int32_t)before;
+        q.space_begin[s] = space_items[s];
+        space_items[s] += (int32_t)(upto - before);
+        before = upto;
+    }
 }
 
 }  // namespace citron

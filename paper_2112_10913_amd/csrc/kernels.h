@@ -85,7 +85,23 @@ struct BuildParams {
     unsigned long long* build_stats;   // kNumStats slots
 };
 int32_t build_lds_bytes(int32_t light_rows, int32_t max_deg);
-hipError_t launch_rows_len(int32_t n, const int32_t* dag_ptr, int32_t* len, hipStream_t s);
+// len[u] = row words of u, or of the heavy u only
+hipError_t launch_rows_len(int32_t n, const int32_t* dag_ptr, bool heavy_only, int32_t* len, hipStream_t s);
+// rows of the heavy vertices (order[0 .. n_heavy)) in sorted positions
+struct SortedRowsParams {
+    int32_t n_heavy;
+    const int32_t* order;
+    const int32_t* dag_ptr;
+    const int32_t* dag_col;
+    const int32_t* row_ptr;
+    const int32_t* key;          // order key, or nullptr for the degree ordering
+    const int32_t* rows_off;
+    const unsigned long long* rows;
+    const int32_t* hoff;
+    unsigned long long* hrows;
+    uint16_t* hpos;
+};
+hipError_t launch_sorted_rows(const SortedRowsParams& P, hipStream_t s);
 hipError_t launch_build_rows(const BuildParams& P, int32_t blocks, hipStream_t s);
 hipError_t launch_arc_c_to_u64(int64_t m, const int32_t* arc_c, unsigned long long* out, hipStream_t s);
 
@@ -93,8 +109,8 @@ hipError_t launch_arc_c_to_u64(int64_t m, const int32_t* arc_c, unsigned long lo
 struct CountLaunch {
     const QueryDesc* queries;   // device table
     int32_t n_queries;
-    int32_t total_items;
-    int32_t* item_ctr;          // device: kClaimInts cursors, zeroed by the launch sequence
+    int32_t space_items[kSpaces] = {};   // items of each space (place_query)
+    int32_t* item_ctr;          // device: kLaunchInts cursors, zeroed by the launch sequence
     unsigned long long* scratch;   // stacks of k > 12, scratch_words per block
     int64_t scratch_words;
     int32_t max_k;
@@ -114,6 +130,14 @@ int64_t count_deep_scratch_words(int32_t max_k, int32_t wg_waves);
 // dynamic LDS of a count launch: arc_max is its arc_lds_max tuning value
 int32_t count_lds_bytes(int32_t arc_max, int32_t max_k, int32_t wg_waves, bool per_arc);
 hipError_t launch_count(const CountLaunch& cl, hipStream_t s);
+// its dense spaces (kernels_dense.hip)
+hipError_t launch_dense(const CountLaunch& cl, hipStream_t s);
+inline int64_t launch_items(const CountLaunch& cl)
+{
+    int64_t n = 0;
+    for (int s = 0; s < kSpaces; ++s) n += cl.space_items[s];
+    return n;
+}
 hipError_t launch_check_arcs(const int32_t* arcs, int32_t n, int64_t m, int32_t* err, hipStream_t s);
 hipError_t launch_list_parts(const int32_t* arcs, int32_t n, const int32_t* dag_src, const int32_t* dag_ptr,
                              const int32_t* arc_c, int32_t k, int32_t pct, int32_t* parts, hipStream_t s);

@@ -30,11 +30,10 @@
 // step and cannot run 2^58 steps, so these never wrap; 32-bit partial sums
 // are bounded where they are used); wave sums and the global accumulator
 // are carry-checked, and a carry sets the query's overflow flag.
-#include "kernels.h"
+#include "items.h"
+#include "wave.h"
 
 namespace citron {
-
-typedef unsigned long long u64;
 
 constexpr int kMaxBlock = 512;          // threads per count workgroup (8 waves)
 constexpr int kWaveBufRows = 128;       // one-word rows queued per wave
@@ -44,117 +43,10 @@ constexpr int kDonateMinIdle = 8;       // idle lanes that trigger work donation
 constexpr int kBurstIters = 32;         // last-level steps of one leaf burst at most
 constexpr int kBurstMinLanes = 32;      // lanes at a last-level node to keep a burst going
 constexpr int kN3Burst = 8;             // two-level steps between refills of idle lanes
-constexpr int kMaxClaim = 16;           // items a wave claims at once, at most
-// decoded items of a claimed run, one int32 per field and item
-enum ItemField { kItQuery, kItKind, kItRowsOff, kItTag, kItArc0, kItDegree, kItRow, kItPart, kItFields };
 // donation mailbox per lane: M, R, (need, base), and the arc tag of per-arc launches
 __host__ __device__ constexpr int mbox_words(bool per_arc) { return per_arc ? 4 : 3; }
 constexpr int kPosList = 3 * kWave * 2; // candidate positions the smaller mailbox area holds (1.5 KB)
 static_assert(kArcMaxC <= kPosList, "candidate positions of an LDS node fit the mailbox area");
-
-// ------------------------------------------------------------------ helpers
-
-__device__ __forceinline__ int lane_of() { return threadIdx.x & (kWave - 1); }
-
-__device__ __forceinline__ u64 shfl64(u64 v, int src)
-{
-    unsigned lo = __shfl((unsigned)v, src, kWave);
-    unsigned hi = __shfl((unsigned)(v >> 32), src, kWave);
-    return ((u64)hi << 32) | lo;
-}
-
-__device__ __forceinline__ u64 readlane64(u64 v, int lane)
-{
-    unsigned lo = __builtin_amdgcn_readlane((unsigned)v, lane);
-    unsigned hi = __builtin_amdgcn_readlane((unsigned)(v >> 32), lane);
-    return ((u64)hi << 32) | lo;
-}
-
-// Sum over the wave of per-lane values in 0..127, from seven ballots (no
-// LDS traffic, no cross-lane shuffles).
-__device__ __forceinline__ int wave_sum_small(int v)
-{
-    int s = 0;
-#pragma unroll
-    for (int b = 0; b < 7; ++b) s += __popcll(__ballot((v >> b) & 1)) << b;
-    return s;
-}
-
-__device__ __forceinline__ u64 wave_sum_u64(u64 v)
-{
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += shfl64(v, lane_of() ^ o);
-    return v;
-}
-
-// Wave-wide carry-checked reduction; lane 0 adds the total to *dst.
-__device__ void wave_flush(u64 acc, int ovf, u64* dst, int32_t* ovf_dst)
-{
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        const u64 other = shfl64(acc, lane_of() ^ o);
-        ovf |= __shfl_xor(ovf, o, kWave);
-        const u64 s = acc + other;
-        ovf |= (s < acc) ? 1 : 0;
-        acc = s;
-    }
-    if (lane_of() == 0) {
-        if (acc) {
-            const u64 old = atomicAdd(dst, acc);
-            if (old + acc < old) ovf = 1;
-        }
-        if (ovf) atomicOr(ovf_dst, 1);
-    }
-}
-
-__device__ __forceinline__ void wave_flush_stats(const u64* vals, u64* dst)
-{
-#pragma unroll
-    for (int i = 0; i < kNumStats; ++i) {
-        // written once per wave at its end
-        if ((i >= kStatWaveBusy && i <= kStatWaves) || (i >= kStatWaveBusyMax && i <= kStatCycTotal)) continue;
-        const u64 v = wave_sum_u64(vals[i]);
-        if (lane_of() == 0 && v) atomicAdd(dst + i, v);
-    }
-}
-
-// Position of the r-th (0-based) set bit of v; always in 0..63.
-__device__ __forceinline__ int select64(u64 v, int r)
-{
-    int pos = 0;
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) {
-        const u64 low = v & ((1ull << s) - 1);
-        const int c = __popcll(low);
-        if (r >= c) {
-            r -= c;
-            v >>= s;
-            pos += s;
-        } else {
-            v = low;
-        }
-    }
-    return pos;
-}
-
-// A W-word mask held one word per lane (lane w holds word w, lanes >= W
-// hold 0).  Returns, in lane j, the position of the j-th set bit (for j
-// below the popcount).  Uniform control flow: the whole wave calls it.
-__device__ __forceinline__ int wave_select(u64 m, int j, int W)
-{
-    int before = 0, my_w = 0, my_r = 0;
-    u64 my_word = 0;
-    for (int w = 0; w < W; ++w) {
-        const u64 mw = readlane64(m, w);
-        const int pc = __popcll(mw);
-        const bool here = j >= before && j < before + pc;
-        my_w = here ? w : my_w;
-        my_r = here ? j - before : my_r;
-        my_word = here ? mw : my_word;
-        before += pc;
-    }
-    return my_w * 64 + select64(my_word, my_r);
-}
 
 // ------------------------------------------------------------------ layout
 
@@ -508,59 +400,6 @@ struct HeavyCtx {
     int tag;   // the arc (per-arc output)
 };
 
-// Parallel bit extract with a wave-uniform mask (Hacker's Delight, section
-// 7-4, "compress"): the masks are prepared once per mask word (scalar
-// work), then each lane packs its own word in six shift-and-merge steps.
-struct Pext {
-    u64 m, v0, v1, v2, v3, v4, v5;
-};
-
-__device__ __forceinline__ u64 prefix_xor64(u64 x)
-{
-    x ^= x << 1;
-    x ^= x << 2;
-    x ^= x << 4;
-    x ^= x << 8;
-    x ^= x << 16;
-    x ^= x << 32;
-    return x;
-}
-
-__device__ __forceinline__ Pext pext_prep(u64 m)
-{
-    Pext p;
-    p.m = m;
-    u64 mk = ~m << 1;
-    u64 v[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        const u64 mp = prefix_xor64(mk);
-        v[i] = mp & m;
-        m = (m ^ v[i]) | (v[i] >> (1 << i));
-        mk &= ~mp;
-    }
-    p.v0 = v[0];
-    p.v1 = v[1];
-    p.v2 = v[2];
-    p.v3 = v[3];
-    p.v4 = v[4];
-    p.v5 = v[5];
-    return p;
-}
-
-__device__ __forceinline__ u64 pext_apply(u64 x, const Pext& p)
-{
-    u64 t;
-    x &= p.m;
-    t = x & p.v0; x = (x ^ t) | (t >> 1);
-    t = x & p.v1; x = (x ^ t) | (t >> 2);
-    t = x & p.v2; x = (x ^ t) | (t >> 4);
-    t = x & p.v3; x = (x ^ t) | (t >> 8);
-    t = x & p.v4; x = (x ^ t) | (t >> 16);
-    t = x & p.v5; x = (x ^ t) | (t >> 32);
-    return x;
-}
-
 // Row x of H restricted to the candidates of M (lane q holds word q of M)
 // and packed: bit i of the result is candidate i.  At most 256 candidates
 // (four words o0..o3).  Uniform control flow: the whole wave calls it.
@@ -698,8 +537,8 @@ __device__ __forceinline__ unsigned need3_lanes(const HeavyCtx<false>& H, const 
 }
 
 template <bool kStats, bool kPerArc, bool kGlobal, int kRegL>
-__device__ __forceinline__ void heavy_dfs(const HeavyCtx<kGlobal>& H, u64 M, int need0, int lvl0, int part, int P,
-                                          WaveBuf& wb, Acc& A, u64& uacc, u64* per_arc);
+__device__ __forceinline__ void heavy_search(const HeavyCtx<kGlobal>& H, u64 ch, int need0, int lvl0, int part, int P,
+                                             WaveBuf& wb, Acc& A, u64& uacc, u64* per_arc);
 
 // Handle a node with mask m (c candidates, `need` more vertices to choose;
 // rows in device memory when kGlobal, else in the wave's LDS copy).  Returns
@@ -751,8 +590,7 @@ __device__ __forceinline__ bool heavy_node(const HeavyCtx<kGlobal>& H, u64 m, in
         const int rem = c - 64 * lane;
         const u64 all = lane < W2 ? (rem >= 64 ? ~0ull : ((1ull << rem) - 1)) : 0ull;
         if (kStats && lane == 0) A.st[kStatArcLds] += 1;
-        if (heavy_node<kStats, kPerArc, false, kRegL>(HL, all, c, need, lvl, part, P, wb, A, uacc, per_arc))
-            heavy_dfs<kStats, kPerArc, false, kRegL>(HL, all, need, lvl, part, P, wb, A, uacc, per_arc);
+        heavy_search<kStats, kPerArc, false, kRegL>(HL, all, need, lvl, part, P, wb, A, uacc, per_arc);
         __builtin_amdgcn_wave_barrier();
         return false;
     }
@@ -821,211 +659,71 @@ __device__ __forceinline__ bool heavy_node(const HeavyCtx<kGlobal>& H, u64 m, in
     return true;
 }
 
-// Depth-first search, all lanes in step, below a node with mask M (more
-// than 64 candidates, need0 more vertices), rows in H; stack levels from lvl0.
+// Depth-first search, all lanes in step, of a node with mask ch (need0 more
+// vertices to choose), rows in H; stack levels from lvl0.  One call site for
+// every node, the root among them: the engines below a node are inlined
+// there, and each further copy costs instruction cache and registers.
 template <bool kStats, bool kPerArc, bool kGlobal, int kRegL>
-__device__ __forceinline__ void heavy_dfs(const HeavyCtx<kGlobal>& H, u64 M, int need0, int lvl0, int part, int P,
-                                          WaveBuf& wb, Acc& A, u64& uacc, u64* per_arc)
+__device__ __forceinline__ void heavy_search(const HeavyCtx<kGlobal>& H, u64 ch, int need0, int lvl0, int part, int P,
+                                             WaveBuf& wb, Acc& A, u64& uacc, u64* per_arc)
 {
     const int q = lane_of();
-    u64 R = M;
-    int t = 1;
+    u64 M = 0ull, R = 0ull;
+    int t = 0;                 // open levels: M, R is level t's, the others' are on the stack
     int jroot = 0;
     for (;;) {
-        const u64 b = __ballot(R != 0ull);
-        if (b == 0ull) {
-            if (t == 1) break;
-            --t;
-            M = wb.hM[(lvl0 + t - 1) * kWave + q];
-            R = wb.hR[(lvl0 + t - 1) * kWave + q];
-            continue;
-        }
-        const int f = __builtin_ctzll(b);
-        const u64 Rf = readlane64(R, f);
-        const int x = f * 64 + __builtin_ctzll(Rf);
-        if (q == f) R &= R - 1;
-        if (t == 1) {
-            const int jr = jroot++;
-            if (P > 1 && jr % P != part) continue;
-        }
-        const u64 ch = M & (q < H.W ? H.rows((unsigned)(x * H.W + q)) : 0ull);
         const int cc = wave_sum_small(__popcll(ch));
-        if (kStats && q == 0) A.st[kStatHeavySteps] += 1;
-        if (heavy_node<kStats, kPerArc, kGlobal, kRegL>(H, ch, cc, need0 - t, lvl0 + t, 0, 1, wb, A, uacc, per_arc)) {
-            wb.hM[(lvl0 + t - 1) * kWave + q] = M;
-            wb.hR[(lvl0 + t - 1) * kWave + q] = R;
+        const bool root = t == 0;
+        if (heavy_node<kStats, kPerArc, kGlobal, kRegL>(H, ch, cc, need0 - t, lvl0 + t, root ? part : 0, root ? P : 1,
+                                                        wb, A, uacc, per_arc)) {
+            if (t > 0) {
+                wb.hM[(lvl0 + t - 1) * kWave + q] = M;
+                wb.hR[(lvl0 + t - 1) * kWave + q] = R;
+                if (kStats && q == 0) A.st[kStatPushes] += 1;
+            }
             M = ch;
             R = ch;
             ++t;
-            if (kStats && q == 0) A.st[kStatPushes] += 1;
         }
+        // the next node: a child of the deepest open level with candidates left
+        int x = -1;
+        while (t > 0) {
+            const u64 b = __ballot(R != 0ull);
+            if (b == 0ull) {
+                if (--t > 0) {
+                    M = wb.hM[(lvl0 + t - 1) * kWave + q];
+                    R = wb.hR[(lvl0 + t - 1) * kWave + q];
+                }
+                continue;
+            }
+            const int f = __builtin_ctzll(b);
+            const u64 Rf = readlane64(R, f);
+            if (q == f) R &= R - 1;
+            if (t == 1) {
+                const int jr = jroot++;
+                if (P > 1 && jr % P != part) continue;
+            }
+            x = f * 64 + __builtin_ctzll(Rf);
+            break;
+        }
+        if (x < 0) break;
+        ch = M & (q < H.W ? H.rows((unsigned)(x * H.W + q)) : 0ull);
+        if (kStats && q == 0) A.st[kStatHeavySteps] += 1;
     }
-}
-
-template <bool kStats, bool kPerArc, int kRegL>
-__device__ __forceinline__ void heavy_arc(const HeavyCtx<true>& H, int r, int part, int P, WaveBuf& wb, Acc& A,
-                                          u64* per_arc)
-{
-    const int q = lane_of();
-    u64 uacc = 0;
-    const u64 M = q < H.W ? H.rows((unsigned)(r * H.W + q)) : 0ull;
-    const int c = wave_sum_small(__popcll(M));
-    const int need = H.L - 1;
-    if (heavy_node<kStats, kPerArc, true, kRegL>(H, M, c, need, 0, part, P, wb, A, uacc, per_arc))
-        heavy_dfs<kStats, kPerArc, true, kRegL>(H, M, need, 0, part, P, wb, A, uacc, per_arc);
-    if (kPerArc) {
-        const u64 s = wave_sum_u64(uacc);
-        if (q == 0 && s) atomicAdd(per_arc + H.tag, s);
-    }
-}
-
-// Vertex-rooted unit (Algorithm 2 per vertex): the whole subgraph of u, all
-// d positions as candidates and k - 1 vertices still to choose; its first
-// level walks the arcs of u in turn within this one work item.
-template <bool kStats, bool kPerArc, int kRegL>
-__device__ __forceinline__ void heavy_vertex(const HeavyCtx<true>& H, int d, WaveBuf& wb, Acc& A, u64* per_arc)
-{
-    const int q = lane_of();
-    u64 uacc = 0;
-    const int rem = d - 64 * q;
-    const u64 M = q < H.W ? (rem >= 64 ? ~0ull : ((1ull << rem) - 1ull)) : 0ull;
-    if (heavy_node<kStats, kPerArc, true, kRegL>(H, M, d, H.L, 0, 0, 1, wb, A, uacc, per_arc))
-        heavy_dfs<kStats, kPerArc, true, kRegL>(H, M, H.L, 0, 0, 1, wb, A, uacc, per_arc);
 }
 
 // --------------------------------------------------------------- the kernel
 
 struct KParams {
-    const QueryDesc* queries;
-    int32_t n_queries;
-    int32_t total_items;
-    int32_t* item_ctr;      // kClaimShards cursors
+    ItemSpace items;        // the items the dense kernel does not take
     u64* scratch;
     int64_t scratch_words;
     int32_t max_k;
     int32_t flush_rows;     // a wave runs its queue once it holds this many rows
     int32_t arc_lds_max;    // representation switch of heavy nodes (64..kArcMaxC)
     int32_t* progress;      // host-mapped word: items claimed, updated every 512 (nullable)
-    int32_t chunk;          // consecutive items a wave claims at once
+    int32_t progress_base;  // items the launch claimed before this kernel
 };
-
-// The wave's next run of items.  Runs of P.chunk consecutive items are dealt
-// to kClaimShards cursors in turn (run j to cursor j mod kClaimShards), so
-// that the items still start in order of cost.  A wave's first run is fixed
-// by its number and costs no atomic; later ones come from the cursor of its
-// home shard, and once that is dry from any that is not, found by one load of
-// all cursors.  Returns the run's first item, or -1 when none is left.
-//
-// One cursor for all waves served 85 M claims a second: G(50001, 37) at
-// k = 4, one light vertex per item, took 590 us of claims alone, and every
-// launch of 4,096 waves about 50 us for their last, empty-handed claims.
-__device__ __forceinline__ int claim_run(const KParams& P, int wave, int waves, int& shard, bool& fresh)
-{
-    const int lane = lane_of();
-    int c;
-    if (fresh) {
-        fresh = false;
-        c = wave / kClaimShards;
-    } else {
-        int v = 0;
-        if (lane == 0) v = atomicAdd(P.item_ctr + shard * kClaimStride, 1);
-        c = __builtin_amdgcn_readfirstlane(v) + (waves - shard + kClaimShards - 1) / kClaimShards;
-    }
-    for (;;) {
-        const int64_t g = ((int64_t)c * kClaimShards + shard) * P.chunk;
-        if (g < P.total_items) return (int)g;
-        bool has = false;
-        if (lane < kClaimShards) {
-            const int64_t next = (int64_t)__hip_atomic_load(P.item_ctr + lane * kClaimStride, __ATOMIC_RELAXED,
-                                                            __HIP_MEMORY_SCOPE_AGENT) +
-                                 (waves - lane + kClaimShards - 1) / kClaimShards;
-            has = (next * kClaimShards + lane) * P.chunk < P.total_items;
-        }
-        const unsigned left = (unsigned)__ballot(has);
-        if (left == 0u) return -1;
-        // the next shard with work after the present one, cyclically
-        const unsigned after = left & ~((2u << shard) - 1u);
-        shard = __builtin_ctz(after ? after : left);
-        int v = 0;
-        if (lane == 0) v = atomicAdd(P.item_ctr + shard * kClaimStride, 1);
-        c = __builtin_amdgcn_readfirstlane(v) + (waves - shard + kClaimShards - 1) / kClaimShards;
-    }
-}
-static_assert(kClaimShards <= 31, "shard masks are 32-bit words");
-
-// Lane j < n decodes item g0 + j of the launch into the wave's LDS fields:
-// its query, then one part of a heavy arc or (a part of) a light vertex.  The
-// chain of dependent loads (query, bucket, arc or vertex, DAG offsets, row
-// offset: about 14 on a graph with a few hundred buckets) is paid once per
-// run instead of once per item.
-__device__ __forceinline__ void decode_run(const KParams& P, int g0, int n, int32_t* item)
-{
-    const int j = lane_of();
-    if (j >= n) return;
-    const int g = g0 + j;
-    int qi;
-    {
-        int lo = 0, hi = P.n_queries - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (P.queries[mid].item_begin <= g) lo = mid;
-            else hi = mid - 1;
-        }
-        qi = lo;
-    }
-    const QueryDesc& q = P.queries[qi];
-    const int i = q.item_lo + (g - q.item_begin) * q.item_stride;
-    int u, r = -1, part, nparts, tag, kind = kItemHeavyArc;
-    if (q.arc_list) {
-        // list mode: one part of one listed arc; counts go to its list slot
-        tag = q.arc_items[2 * i];
-        const int pw = q.arc_items[2 * i + 1];
-        const int e = q.arc_list[tag];
-        u = q.dag_src[e];
-        r = e - q.dag_ptr[u];
-        part = pw & 0xffff;
-        nparts = pw >> 16;
-        kind = q.dag_ptr[u + 1] - q.dag_ptr[u] > kLightMaxDeg ? kItemHeavyArc : kItemLightVertex;
-    } else {
-        // bucket holding item i, then the arc or vertex and the part (part-major)
-        int lo = 0, hi = q.n_buckets - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (q.buckets[4 * mid] <= i) lo = mid;
-            else hi = mid - 1;
-        }
-        const int key = q.buckets[4 * lo + 3] >> 2;
-        kind = q.buckets[4 * lo + 3] & 3;
-        const int cnt = q.buckets[4 * lo + 2];
-        const int local = i - q.buckets[4 * lo];
-        part = local / cnt;
-        const int which = q.buckets[4 * lo + 1] + (local - part * cnt);
-        if (kind == kItemHeavyArc) {
-            const int e = q.rows.harcs[which];
-            u = q.dag_src[e];
-            r = e - q.dag_ptr[u];
-            nparts = arc_parts(key, q.k, q.split_pct);
-            tag = e;
-        } else if (kind == kItemHeavyVertex) {
-            u = q.order[which];
-            nparts = 1;
-            tag = -1;
-        } else {
-            u = q.order[q.light_first + which];
-            nparts = kind == kItemLightVertex ? light_parts(key + 1, q.k, q.split_pct) : 1;
-            tag = -1;
-        }
-    }
-    const int a0 = q.dag_ptr[u];
-    item[kItQuery * kMaxClaim + j] = qi;
-    item[kItKind * kMaxClaim + j] = kind;
-    item[kItRowsOff * kMaxClaim + j] = q.rows.rows_off[u];
-    item[kItTag * kMaxClaim + j] = tag;
-    item[kItArc0 * kMaxClaim + j] = a0;
-    item[kItDegree * kMaxClaim + j] = q.dag_ptr[u + 1] - a0;
-    item[kItRow * kMaxClaim + j] = r;
-    item[kItPart * kMaxClaim + j] = part | (nparts << 16);
-}
 
 template <int kMode, bool kStats, bool kPerArc>
 __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(kMode == kStackReg ? 4 : 2))) count_kernel(KParams P)
@@ -1083,8 +781,8 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     const u64 t_start = kStats ? wall_clock64() : 0ull;
     const u64 cyc_start = kStats ? __builtin_readcyclecounter() : 0ull;
     if (kStats && lane == 0) {
-        const u64 now = atomicAdd(P.queries[0].stats + kStatResidentNow, 1ull) + 1;
-        atomicMax(P.queries[0].stats + kStatResidentMax, now);
+        const u64 now = atomicAdd(P.items.queries[0].stats + kStatResidentNow, 1ull) + 1;
+        atomicMax(P.items.queries[0].stats + kStatResidentMax, now);
     }
     u64 item_max = 0ull;
 
@@ -1095,94 +793,103 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     bool fresh = true;
     int g0 = 0, j = 0, nj = 0;         // the wave's run of items, decoded
     for (;;) {
+        bool end = false;
         if (j >= nj) {
-            g0 = claim_run(P, wave, waves, shard, fresh);
-            if (g0 < 0) break;
-            nj = min(P.chunk, P.total_items - g0);
+            g0 = claim_run(P.items, wave, waves, shard, fresh);
+            end = g0 < 0;
+            nj = end ? 0 : min(P.items.chunk, P.items.total - g0);
             j = 0;
             __builtin_amdgcn_wave_barrier();
-            decode_run(P, g0, nj, item);
+            decode_run<kRestSpace>(P.items, g0, nj, item);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             // progress for the host, read without any HIP call while the launch runs
-            if (P.progress && lane == 0 && (((g0 + nj - 1) ^ (g0 - 1)) & ~511))
-                __hip_atomic_store(P.progress, g0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (P.progress && !end && lane == 0 && (((g0 + nj - 1) ^ (g0 - 1)) & ~511))
+                __hip_atomic_store(P.progress, P.progress_base + g0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
-        const int g = g0 + j;
         auto field = [&](int f) { return __builtin_amdgcn_readfirstlane(item[f * kMaxClaim + j]); };
-        const int qi = field(kItQuery);
-        const QueryDesc& q = P.queries[qi];
-        if (qi != cur) {
-            if (cur >= 0) {
-                const QueryDesc& oq = P.queries[cur];
-                flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
-                wave_flush(A.acc, A.ovf, oq.acc + acc_slot, oq.overflow);
-                if (kStats) wave_flush_stats(A.st, oq.stats);
-                A.acc = 0ull;
-                A.ovf = 0;
+        const int qi = end ? -1 : field(kItQuery);
+        const int kind = end ? kItemHeavyArc : field(kItKind);
+        const int d = end ? 0 : field(kItDegree);
+        const bool heavy = kind != kItemLightVertex && kind != kItemLightRoot;
+        // run the queue before an item whose rows it cannot take, once it is
+        // full enough, and before the query changes
+        if (wb.n + (heavy ? 0 : d + 1) > kWaveBufRows || wb.n >= P.flush_rows || qi != cur) {
+            flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
+            if (qi != cur) {
+                if (cur >= 0) {
+                    const QueryDesc& oq = P.items.queries[cur];
+                    wave_flush(A.acc, A.ovf, oq.acc + acc_slot, oq.overflow);
+                    if (kStats) wave_flush_stats(A.st, oq.stats);
+                    A.acc = 0ull;
+                    A.ovf = 0;
 #pragma unroll
-                for (int i = 0; i < kNumStats; ++i) A.st[i] = 0ull;
+                    for (int i = 0; i < kNumStats; ++i) A.st[i] = 0ull;
+                }
+                if (end) break;
+                cur = qi;
+                per_arc = P.items.queries[qi].per_arc;
             }
-            cur = qi;
-            per_arc = q.per_arc;
         }
+        if (end) break;
+        const QueryDesc& q = P.items.queries[qi];
         const int k = q.k;
         const u64 t_item = kStats ? wall_clock64() : 0ull;
-        const int kind = field(kItKind), r = field(kItRow), tag = field(kItTag), a0 = field(kItArc0);
-        const int d = field(kItDegree), pw = field(kItPart);
+        const int r = field(kItRow), tag = field(kItTag), pw = field(kItPart);
         const int part = pw & 0xffff, nparts = pw >> 16;
         const u64* rows = q.rows.rows + field(kItRowsOff);
-        ++j;
-        if (kind == kItemHeavyArc || kind == kItemHeavyVertex) {
+        const int g = g0 + j;
+        if (heavy) {
+            // a part of an arc, searched below its row, or (vertex-rooted
+            // unit, Algorithm 2 per vertex) a whole vertex: all d positions
+            // are candidates and its first level walks its arcs in turn
             const HeavyCtx<true> H{RowRef<true>{(glb_u64*)rows}, (d + 63) >> 6, k - 1, tag};
-            if (kind == kItemHeavyVertex) heavy_vertex<kStats, kPerArc, kRegL>(H, d, wb, A, per_arc);
-            else heavy_arc<kStats, kPerArc, kRegL>(H, r, part, nparts, wb, A, per_arc);
-        } else if (kind == kItemLightRoot) {
-            // vertex-rooted light vertex: its rows, then one unit rooted at
-            // the vertex itself (mask of all d positions, k - 1 to choose)
-            if (wb.n + d + 1 > kWaveBufRows) flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
+            const int rem = d - 64 * lane;
+            u64 M = 0ull;
+            if (lane < H.W) {
+                if (kind == kItemHeavyVertex) M = rem >= 64 ? ~0ull : ((1ull << rem) - 1ull);
+                else M = H.rows((unsigned)(r * H.W + lane));
+            }
+            u64 uacc = 0;
+            heavy_search<kStats, kPerArc, true, kRegL>(H, M, kind == kItemHeavyVertex ? H.L : H.L - 1, 0, part, nparts,
+                                                       wb, A, uacc, per_arc);
+            if (kPerArc) {
+                const u64 s = wave_sum_u64(uacc);
+                if (lane == 0 && s && tag >= 0) atomicAdd(per_arc + tag, s);
+            }
+        } else {
+            // rows of the vertex into the wave's buffer; the searched arcs
+            // (every nparts-th one, or the one listed) become units, or, for
+            // a vertex-rooted light vertex, one unit rooted at the vertex
+            // itself (mask of all d positions, k - 1 to choose)
+            const bool from_root = kind == kItemLightRoot;
             if (lane < d) {
                 wb.rows[wb.n + lane] = rows[lane];
                 wb.meta[wb.n + lane] = (wb.n << 8) | (k - 2);
+                if (kPerArc) wb.tags[wb.n + lane] = tag < 0 ? field(kItArc0) + lane : tag;
             }
-            if (lane == 0) {
+            if (from_root && lane == 0) {
                 wb.rows[wb.n + d] = d >= 64 ? ~0ull : ((1ull << d) - 1ull);
                 wb.meta[wb.n + d] = (wb.n << 8) | (k - 1);
                 wb.units[wb.nu] = wb.n + d;
             }
-            wb.nu += 1;
-            wb.n += d + 1;
-        } else {
-            // rows of the vertex into the wave's buffer; the searched arcs
-            // (every nparts-th one, or the one listed) become units
-            if (wb.n + d > kWaveBufRows) flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
-            if (lane < d) {
-                wb.rows[wb.n + lane] = rows[lane];
-                wb.meta[wb.n + lane] = (wb.n << 8) | (k - 2);
-                if (kPerArc) wb.tags[wb.n + lane] = tag < 0 ? a0 + lane : tag;
-            }
-            const bool unit = lane < d && (r >= 0 ? lane == r : (nparts == 1 || lane % nparts == part));
+            const bool unit = !from_root && lane < d &&
+                              (r >= 0 ? lane == r : (nparts == 1 || lane % nparts == part));
             const u64 um = __ballot(unit);
             if (unit) wb.units[wb.nu + __popcll(um & (lane == 0 ? 0ull : (~0ull >> (kWave - lane))))] = wb.n + lane;
-            wb.nu += __popcll(um);
-            wb.n += d;
+            wb.nu += __popcll(um) + (from_root ? 1 : 0);
+            wb.n += d + (from_root ? 1 : 0);
         }
-        if (wb.n >= P.flush_rows) flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
+        ++j;
         if (kStats && lane == 0) {
             const u64 dt = wall_clock64() - t_item;
             if (dt > (item_max >> 32)) item_max = (dt << 32) | (u64)(unsigned)g;
         }
     }
-    if (cur >= 0) {
-        const QueryDesc& oq = P.queries[cur];
-        flush_tasks<kStats, kPerArc, kRegL>(wb, A, per_arc);
-        wave_flush(A.acc, A.ovf, oq.acc + acc_slot, oq.overflow);
-        if (kStats) wave_flush_stats(A.st, oq.stats);
-    }
     if (kStats && lane == 0) {
         // wave timing (instrumented single-query launches)
         const u64 t_end = wall_clock64();
-        u64* st = P.queries[0].stats;
+        u64* st = P.items.queries[0].stats;
         atomicAdd(st + kStatWaveBusy, t_end - t_start);
         atomicMin(st + kStatWaveFirst, t_start);
         atomicMax(st + kStatWaveLast, t_end);
@@ -1249,13 +956,18 @@ int32_t count_lds_bytes(int32_t arc_max, int32_t max_k, int32_t wg_waves, bool p
 
 hipError_t launch_count(const CountLaunch& cl, hipStream_t s)
 {
-    if (cl.total_items <= 0) return hipSuccess;
+    if (launch_items(cl) <= 0) return hipSuccess;
     if (cl.wg_waves < 1 || cl.wg_waves * kWave > kMaxBlock) return hipErrorInvalidValue;
+    // the dense arcs first (the costliest items of a launch), then the rest
+    hipError_t e = launch_dense(cl, s);
+    if (e != hipSuccess) return e;
+    const int32_t rest = cl.space_items[kRestSpace];
+    if (rest <= 0) return hipSuccess;
     KParams P;
-    P.queries = cl.queries;
-    P.n_queries = cl.n_queries;
-    P.total_items = cl.total_items;
-    P.item_ctr = cl.item_ctr;
+    P.items.queries = cl.queries;
+    P.items.n_queries = cl.n_queries;
+    P.items.total = rest;
+    P.items.cursors = cl.item_ctr + kRestSpace * kClaimInts;
     P.scratch = cl.scratch;
     P.scratch_words = cl.scratch_words;
     P.max_k = cl.max_k;
@@ -1263,16 +975,17 @@ hipError_t launch_count(const CountLaunch& cl, hipStream_t s)
     P.flush_rows = cl.flush_rows > kWaveBufRows ? kWaveBufRows : cl.flush_rows;
     P.arc_lds_max = clamp_arc_max(cl.arc_lds_max);
     P.progress = cl.progress;
+    P.progress_base = (int32_t)(launch_items(cl) - rest);
     // A launch is no wider than its items.  Items per claim: a run short
     // enough that every wave still makes about eight claims; items are in
     // descending cost order, so those of a run cost about the same.
     CountLaunch c2 = cl;
     {
-        const int64_t need = ((int64_t)cl.total_items + cl.wg_waves - 1) / cl.wg_waves;
+        const int64_t need = ((int64_t)rest + cl.wg_waves - 1) / cl.wg_waves;
         if (need < c2.blocks) c2.blocks = (int32_t)need;
         const int64_t waves = (int64_t)c2.blocks * cl.wg_waves;
-        int64_t c = (int64_t)cl.total_items / (waves * 8);
-        P.chunk = (int32_t)(c < 1 ? 1 : (c > kMaxClaim ? kMaxClaim : c));
+        const int64_t c = (int64_t)rest / (waves * 8);
+        P.items.chunk = (int32_t)(c < 1 ? 1 : (c > kMaxClaim ? kMaxClaim : c));
     }
     switch (stack_mode(cl.max_k)) {
     case kStackReg: return launch_mode<kStackReg>(P, c2, s);

@@ -245,12 +245,70 @@ __global__ void __launch_bounds__(256) build_rows_kernel(BuildParams P)
 }
 
 // rows_len[u] = d(u) * W(u), the words of u's rows
-__global__ void rows_len_kernel(int32_t n, const int32_t* __restrict__ dag_ptr, int32_t* __restrict__ len)
+__global__ void rows_len_kernel(int32_t n, const int32_t* __restrict__ dag_ptr, int32_t min_deg,
+                                int32_t* __restrict__ len)
 {
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= n) return;
     const int d = dag_ptr[u + 1] - dag_ptr[u];
-    len[u] = d * ((d + 63) >> 6);
+    len[u] = d >= min_deg ? d * ((d + 63) >> 6) : 0;
+}
+
+// The rows of a heavy vertex once more, with rows and bits in the order of
+// the DAG instead of ascending id: row and bit i stand for the i-th
+// out-neighbour by (key, id).  An out-neighbour's own out-neighbours all come
+// later, so the matrix is strictly upper triangular: the tile kernel skips
+// the lower half, and the row walks meet zero words.  One workgroup per
+// vertex sorts by counting smaller keys (d^2 compares); then a wave per row
+// gathers the bits of 64 sorted positions, one per lane, and a ballot is the
+// word.
+__global__ void __launch_bounds__(256) sorted_rows_kernel(SortedRowsParams P)
+{
+    __shared__ int32_t key[kMaxDeg];
+    __shared__ uint16_t pos[kMaxDeg];     // sorted index -> position
+    const int tid = threadIdx.x, lane = lane_of(), wid = tid / kWave_;
+    for (int b = blockIdx.x; b < P.n_heavy; b += gridDim.x) {
+        const int u = P.order[b];
+        const int a0 = P.dag_ptr[u];
+        const int d = P.dag_ptr[u + 1] - a0;
+        const int W = (d + 63) >> 6;
+        for (int i = tid; i < d; i += blockDim.x) {
+            const int v = P.dag_col[a0 + i];
+            key[i] = P.key ? P.key[v] : P.row_ptr[v + 1] - P.row_ptr[v];
+        }
+        __syncthreads();
+        for (int i = tid; i < d; i += blockDim.x) {
+            const int ki = key[i];
+            int rank = 0;
+            // positions ascend with the id, so ties keep their order
+            for (int j = 0; j < d; ++j) rank += (key[j] < ki || (key[j] == ki && j < i)) ? 1 : 0;
+            pos[rank] = (uint16_t)i;
+            P.hpos[a0 + i] = (uint16_t)rank;
+        }
+        __syncthreads();
+        const u64* __restrict__ src = P.rows + P.rows_off[u];
+        u64* __restrict__ dst = P.hrows + P.hoff[u];
+        for (int a = wid; a < d; a += blockDim.x / kWave_) {
+            const u64* __restrict__ row = src + (int64_t)pos[a] * W;
+            u64 mine = 0;
+            for (int w = a >> 6; w < W; ++w) {
+                const int i = w * 64 + lane;
+                const int s = i < d ? pos[i] : 0;
+                const u64 bits = __ballot(i < d && ((row[s >> 6] >> (s & 63)) & 1));
+                if (lane == w) mine = bits;
+            }
+            if (lane < W) dst[(int64_t)a * W + lane] = mine;
+        }
+        __syncthreads();
+    }
+}
+
+hipError_t launch_sorted_rows(const SortedRowsParams& P, hipStream_t s)
+{
+    if (P.n_heavy <= 0) return hipSuccess;
+    const int blocks = P.n_heavy < 2048 ? P.n_heavy : 2048;
+    sorted_rows_kernel<<<blocks, 256, 0, s>>>(P);
+    return hipGetLastError();
 }
 
 // per_arc[e] = |C_uv| (the k = 3 per-arc counts)
@@ -260,10 +318,10 @@ __global__ void arc_c_to_u64_kernel(int64_t m, const int32_t* __restrict__ arc_c
     if (e < m) out[e] = (u64)arc_c[e];
 }
 
-hipError_t launch_rows_len(int32_t n, const int32_t* dag_ptr, int32_t* len, hipStream_t s)
+hipError_t launch_rows_len(int32_t n, const int32_t* dag_ptr, bool heavy_only, int32_t* len, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    rows_len_kernel<<<(n + 255) / 256, 256, 0, s>>>(n, dag_ptr, len);
+    rows_len_kernel<<<(n + 255) / 256, 256, 0, s>>>(n, dag_ptr, heavy_only ? kLightMaxDeg + 1 : 0, len);
     return hipGetLastError();
 }
 

@@ -161,6 +161,7 @@ bool issue_step(citron_server* s, Step& st, bool fast, int wg, int32_t blocks)
     if (with_work == 0) return false;
     const int32_t cap = fast ? kFastStepItems : kHeavyMaxSlice;
     int32_t total = 0, maxk = 4, nq = 0;
+    CountLaunch cl;
     st.parts.clear();
     // fast lane: admission order; heavy lane: round robin over the heavy
     // requests with items left, from the one after the last served, so that
@@ -188,9 +189,9 @@ bool issue_step(citron_server* s, Step& st, bool fast, int wg, int32_t blocks)
             take = std::min(take, r.slice);
         }
         QueryDesc q = r.q;
-        q.item_begin = total;
         q.item_lo = r.issued;
         q.n_items = take;
+        place_query(q, true, cl.space_items);
         st.h_q[nq++] = q;
         st.parts.emplace_back(r.id, take);
         r.issued += take;
@@ -202,14 +203,12 @@ bool issue_step(citron_server* s, Step& st, bool fast, int wg, int32_t blocks)
         }
     }
     hipError_t e = hipEventRecord(st.start, st.stream);
-    if (e == hipSuccess) e = launch_fill_i32(st.d_item_ctr, 0, kClaimInts, st.stream);
+    if (e == hipSuccess) e = launch_fill_i32(st.d_item_ctr, 0, kLaunchInts, st.stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(st.d_q, st.h_q, sizeof(QueryDesc) * (size_t)nq, hipMemcpyHostToDevice, st.stream);
     if (e == hipSuccess) {
-        CountLaunch cl;
         cl.queries = st.d_q;
         cl.n_queries = nq;
-        cl.total_items = total;
         cl.item_ctr = st.d_item_ctr;
         cl.scratch = st.d_scratch;
         cl.scratch_words = s->scratch_words;
@@ -313,7 +312,7 @@ void worker_main(citron_server* s)
                 s->used += r.footprint;
                 r.t_admit = now_ns();
                 r.id = s->next_id++;
-                r.q = make_query(g, r.k, s->d_acc + (size_t)r.slot * kAccWords, s->d_ovf + r.slot, nullptr, nullptr, 0);
+                r.q = make_query(g, r.k, s->d_acc + (size_t)r.slot * kAccWords, s->d_ovf + r.slot, nullptr, nullptr);
                 r.n_items = r.q.n_items;
                 r.fast = r.n_items <= kFastItems;
                 r.issued = 0;
@@ -455,7 +454,7 @@ citron_server* citron_server_create(int64_t hbm_budget_bytes, int32_t max_slots,
         if (e == hipSuccess) e = hipMalloc((void**)&st.d_q, sizeof(QueryDesc) * (size_t)max_slots);
         if (e == hipSuccess)
             e = hipHostMalloc((void**)&st.h_q, sizeof(QueryDesc) * (size_t)max_slots, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipMalloc((void**)&st.d_item_ctr, sizeof(int32_t) * kClaimInts);
+        if (e == hipSuccess) e = hipMalloc((void**)&st.d_item_ctr, sizeof(int32_t) * kLaunchInts);
         if (e == hipSuccess) e = hipMalloc((void**)&st.d_scratch, (size_t)(s->scratch_words * 8 * blocks));
     }
     if (e != hipSuccess) {

@@ -93,3 +93,46 @@ def test_runs_that_span_queries(citron_gpu):
     q = [(i, k) for k in (4, 5, 6) for i in range(len(gs))]
     got = citron_gpu.count_batch([hs[i] for i, _ in q], [k for _, k in q])
     assert got == [oracle.count(gs[i], k)[0] for i, k in q]
+
+
+@pytest.mark.parametrize("n,ks", [(67, (6, 7, 8)), (98, (6, 7)), (131, (6, 7)), (195, (6,)), (259, (6,)),
+                                  (323, (6,)), (388, (6,))])
+def test_dense_arcs_of_complete_graphs(citron_gpu, n, ks):
+    """K_n holds an arc with |C_uv| = c for every c up to n - 2, so every row
+    word and tile count of the dense kernel up to that size, and every mask
+    product at its largest; beyond 384 candidates the count kernel goes on."""
+    from math import comb
+    g = gg.complete(n)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    for k in ks:
+        assert h.count(k) == comb(n, k)
+    h.free()
+
+
+@pytest.mark.parametrize("n,p,k", [(90, 0.9, 6), (90, 0.9, 7), (100, 0.75, 8), (110, 0.6, 9), (90, 0.6, 13),
+                                   (150, 0.8, 6), (150, 0.5, 7), (230, 0.7, 6), (300, 0.5, 6), (420, 0.4, 6)])
+def test_dense_arcs_against_the_count_kernel(citron_gpu, n, p, k):
+    """Whole, per-arc, strided and batched counts of dense random graphs
+    against the vertex-rooted unit and the listed arcs, which stay on the
+    count kernel."""
+    g = gg.erdos_renyi(n, p * (n - 1), seed=n + k)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    want = h.count_vertex_rooted(k)
+    assert h.count(k) == want
+    total, every = h.count_per_arc(k)
+    assert total == want
+    assert np.array_equal(every, h.count_arcs(k, np.arange(g.m)))
+    parts = [h.count_part(k, i, 5) for i in range(5)]
+    assert sum(c for c, _ in parts) == want and not any(o for _, o in parts)
+    assert citron_gpu.count_batch([h, h, h], [6, k, 5]) == [h.count_vertex_rooted(6), want, h.count_vertex_rooted(5)]
+    h.free()
+
+
+@pytest.mark.parametrize("ordering", ["degree", "core"])
+def test_dense_arcs_under_both_orderings(citron_gpu, ordering):
+    import oracle
+    g = gg.rmat(10, 32, seed=31)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order(ordering)
+    for k in (6, 7):
+        assert h.count(k) == oracle.count(g, k)[0]
+    h.free()

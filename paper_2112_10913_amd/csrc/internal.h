@@ -206,13 +206,24 @@ __host__ __device__ inline int dense_parts(int c, int k, int pct)
 }
 
 // Parts a light vertex (out-degree d <= 64, its subgraph one word per row)
-// is split into; each part takes every P-th arc of the vertex (speed only).
-__host__ __device__ inline int light_parts(int d, int k, int pct)
+// is split into: light_arcs of them take every light_arcs-th arc of the
+// vertex, and for deep counts each of these is split again into light_subs
+// (a power of two) that take the first-level branches of the same arcs at
+// positions of one residue (speed only).  One wave searching two arcs of a
+// planted 40-clique at k = 9 ran 24 of a launch's 28 ms while 88 % of the
+// wave time was idle (Chung-Lu 2^14; with 4 sub-parts and short runs 15.2 ms,
+// with 16 of them 12.3 ms, with complete nodes counted as binomials 6.4 ms).
+__host__ __device__ inline int light_arcs(int d, int k, int pct)
 {
     if (k <= 5) return 1;
     if (k == 6) return scale_parts(d >= 32 ? d / 8 : 1, pct);
     return scale_parts(d >= 12 ? d / 2 : 1, pct);
 }
+__host__ __device__ inline int light_subs(int d, int k)
+{
+    return k >= 9 && d >= 24 ? 16 : 1;
+}
+__host__ __device__ inline int light_parts(int d, int k, int pct) { return light_arcs(d, k, pct) * light_subs(d, k); }
 
 // Place a query's launch items (n_items, item_lo, item_stride set) in the
 // item spaces, after those placed before.  Without `dense` the count kernel

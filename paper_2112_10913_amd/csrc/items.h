@@ -16,11 +16,34 @@ struct ItemSpace {
     int32_t n_queries;
     int32_t total;
     int32_t* cursors;       // kClaimInts words, zeroed before the launch
-    int32_t chunk;          // consecutive items claimed at once
+    int32_t singles;        // the first, costliest items are claimed one at a time,
+    int32_t chunk;          // the others in runs of this many consecutive items
 };
 
-// The wave's next run of items.  Runs of P.chunk consecutive items are dealt
-// to kClaimShards cursors in turn (run j to cursor j mod kClaimShards), so
+// First item of run j, and the items of the run that starts at g.
+__device__ __forceinline__ int64_t run_begin(const ItemSpace& P, int64_t j)
+{
+    return j < P.singles ? j : P.singles + (j - P.singles) * P.chunk;
+}
+__device__ __forceinline__ int run_length(const ItemSpace& P, int g)
+{
+    return g < P.singles ? 1 : min(P.chunk, P.total - g);
+}
+
+// Runs for `claimers` waves or workgroups: about eight claims each, after two
+// single ones.  Items are in descending cost order, so a run's cost about the
+// same; a first run of 16 of a deep count's costliest items held one wave for
+// 21 ms of a launch whose waves were busy 4.6 ms on average (Chung-Lu 2^14,
+// k = 9).
+inline void set_runs(ItemSpace& P, int64_t claimers, int max_chunk)
+{
+    P.singles = (int32_t)(2 * claimers < P.total ? 2 * claimers : P.total);
+    const int64_t c = (P.total - P.singles) / (claimers * 8);
+    P.chunk = (int32_t)(c < 1 ? 1 : (c > max_chunk ? max_chunk : c));
+}
+
+// The claimer's next run of items.  Runs of consecutive items are dealt to
+// kClaimShards cursors in turn (run j to cursor j mod kClaimShards), so
 // that the items still start in order of cost.  A claimer's (a
 // wave's, or a block's) first run is fixed by its number and costs no atomic; later ones come from the cursor of its
 // home shard, and once that is dry from any that is not, found by one load of
@@ -42,14 +65,14 @@ __device__ __forceinline__ int claim_run(const ItemSpace& P, int wave, int waves
         c = __builtin_amdgcn_readfirstlane(v) + (waves - shard + kClaimShards - 1) / kClaimShards;
     }
     for (;;) {
-        const int64_t g = ((int64_t)c * kClaimShards + shard) * P.chunk;
+        const int64_t g = run_begin(P, (int64_t)c * kClaimShards + shard);
         if (g < P.total) return (int)g;
         bool has = false;
         if (lane < kClaimShards) {
             const int64_t next = (int64_t)__hip_atomic_load(P.cursors + lane * kClaimStride, __ATOMIC_RELAXED,
                                                             __HIP_MEMORY_SCOPE_AGENT) +
                                  (waves - lane + kClaimShards - 1) / kClaimShards;
-            has = (next * kClaimShards + lane) * P.chunk < P.total;
+            has = run_begin(P, next * kClaimShards + lane) < P.total;
         }
         const unsigned left = (unsigned)__ballot(has);
         if (left == 0u) return -1;

@@ -17,8 +17,9 @@
 //
 // Engines.  Light work -- subgraphs with at most 64 vertices, one 64-bit
 // word per row -- is searched by the light engine: one depth-first search
-// per lane over one first-level branch at a time, rows in the wave's LDS
-// buffer, stacks in registers (k <= 8), LDS (k <= 12) or device memory.
+// per lane (a whole arc, or one branch below an arc in deep counts), rows in
+// the wave's LDS
+// buffer, stacks in registers (k <= 9), LDS (k <= 12) or device memory.
 // A heavy arc is walked by the whole wave in step (lane q holding word q of
 // each mask).  A node with at most 256 candidates is copied to the wave's
 // LDS, compacted to ceil(c/64) words per row; a node with at most 64
@@ -27,9 +28,10 @@
 // finished lane-per-child from the LDS copy (need3_lanes).
 //
 // Exact arithmetic: per-lane uint64 accumulators (a lane adds at most 64 per
-// step and cannot run 2^58 steps, so these never wrap; 32-bit partial sums
-// are bounded where they are used); wave sums and the global accumulator
-// are carry-checked, and a carry sets the query's overflow flag.
+// step and cannot run 2^58 steps; the binomials of complete nodes, which can
+// be large, are carry-checked; 32-bit partial sums are bounded where they are
+// used); wave sums and the global accumulator are carry-checked, and a carry
+// sets the query's overflow flag.
 #include "items.h"
 #include "wave.h"
 
@@ -37,9 +39,21 @@ namespace citron {
 
 constexpr int kMaxBlock = 512;          // threads per count workgroup (8 waves)
 constexpr int kWaveBufRows = 128;       // one-word rows queued per wave
-constexpr int kLdsStackLevels = 8;      // deeper stacks (k > 12) live in device memory
+constexpr int kLdsStackLevels = 7;      // deeper stacks (k > 12) live in device memory
 constexpr int kArcMaxC = kArcLdsMax;    // LDS subgraph copies hold at most this many rows
 constexpr int kDonateMinIdle = 8;       // idle lanes that trigger work donation
+// A unit with at least this many vertices to choose is dealt branch by branch:
+// a wave's queue holds few units of a deep count (two arcs per part of a split
+// vertex), which kept lanes idle or trading work.
+constexpr int kBranchNeed = 4;
+// A node with at least this many vertices to choose has its edges counted
+// before it is searched: when every pair is adjacent its count is a binomial.
+// The probe costs one word operation per candidate, against a subtree of
+// about c^3 / 24 in a dense subgraph; in graphs with planted cliques most
+// such nodes are complete (Chung-Lu 2^14, k = 9: 12.0 -> 6.4 ms; R-MAT 16,
+// k = 7, where they hardly ever are: no change).
+constexpr int kProbeNeed = 4;
+constexpr int kDeepClaim = 2;           // items a wave claims at once, at most, for k >= 8
 constexpr int kBurstIters = 32;         // last-level steps of one leaf burst at most
 constexpr int kBurstMinLanes = 32;      // lanes at a last-level node to keep a burst going
 constexpr int kN3Burst = 8;             // two-level steps between refills of idle lanes
@@ -50,27 +64,28 @@ static_assert(kArcMaxC <= kPosList, "candidate positions of an LDS node fit the 
 
 // ------------------------------------------------------------------ layout
 
-__host__ __device__ inline int stack_levels(int max_k) { return max_k > 4 ? max_k - 4 : 1; }
+// Open levels of a heavy search (nodes with 3 .. k - 2 vertices to choose) and
+// of a light one, which starts a branch below its unit.
+__host__ __device__ inline int heavy_levels(int max_k) { return max_k > 4 ? max_k - 4 : 1; }
+__host__ __device__ inline int light_levels(int max_k) { return max_k > 6 ? max_k - 5 : 1; }
 
-// Where the search stacks live, by the largest k of a launch: light stacks
-// in registers and heavy stacks in device memory (k <= 8: the heavy stacks
-// are touched only when a heavy node is pushed or popped, and keeping them
-// out of LDS lets more waves share a CU), all in LDS (k <= 12), or all in
-// device memory.
+// Where the light stacks live, by the largest k of a launch: registers (one
+// level for k <= 6, four for k <= 9: each access selects among them), LDS
+// (k <= 12) or device memory.  The heavy stacks are always in
+// device memory: they are touched only when a heavy node is pushed or popped,
+// and keeping them out of LDS lets more waves share a CU.
 constexpr int kRegLevels = 4;
-enum StackMode { kStackReg = 0, kStackLds = 1, kStackGlobal = 2 };
+enum StackMode { kStackOne, kStackReg, kStackLds, kStackGlobal };
 __host__ __device__ inline int stack_mode(int max_k)
 {
-    const int l = stack_levels(max_k);
-    return l <= kRegLevels ? kStackReg : (l <= kLdsStackLevels ? kStackLds : kStackGlobal);
+    const int l = light_levels(max_k);
+    return l <= 1 ? kStackOne : l <= kRegLevels ? kStackReg : (l <= kLdsStackLevels ? kStackLds : kStackGlobal);
 }
-// per wave: four stacks (light M/R, heavy M/R) of levels x 64 words
-__host__ __device__ inline int64_t wave_stack_words(int max_k) { return 4ll * stack_levels(max_k) * kWave; }
-// the part of them kept in device memory, per wave
+// device-memory stack words per wave: heavy M and R, and for the deepest
+// counts light M and R in as many levels
 __host__ __device__ inline int64_t wave_global_stack_words(int max_k)
 {
-    const int mode = stack_mode(max_k);
-    return mode == kStackGlobal ? wave_stack_words(max_k) : (mode == kStackReg ? wave_stack_words(max_k) / 2 : 0);
+    return (stack_mode(max_k) == kStackGlobal ? 4ll : 2ll) * heavy_levels(max_k) * kWave;
 }
 
 // Largest LDS subgraph copy of a launch: nodes with 64 < c <= arc_max
@@ -98,7 +113,7 @@ __host__ __device__ inline int wave_lds_bytes(int max_k, int arc_max, bool per_a
     b += 8 * mbox_words(per_arc) * kWave;
     b += 4 * kWaveBufRows;
     b += 4 * kItFields * kMaxClaim;
-    if (stack_mode(max_k) == kStackLds) b += 8 * (int)wave_stack_words(max_k);
+    if (stack_mode(max_k) == kStackLds) b += 8 * 2 * light_levels(max_k) * kWave;
     return (b + 15) & ~15;
 }
 
@@ -125,7 +140,7 @@ struct WaveBuf {
     u64* sR;
     u64* hM;         // heavy stacks
     u64* hR;
-    int32_t* units;  // rows that are search roots (a part of a split arc uses some rows only)
+    int32_t* units;  // search roots: row | sub-part << 8 | log2 of the sub-parts << 16
     int n;           // rows in use (wave-uniform)
     int nu;          // units in use (wave-uniform)
     int arc_max;     // nodes with 64 < c <= arc_max are copied to LDS
@@ -165,6 +180,20 @@ struct LightStack<4> {
 static_assert(kRegLevels == 4, "LightStack<4> holds the register levels");
 
 template <>
+struct LightStack<1> {
+    u64 m = 0, r = 0;
+    __device__ __forceinline__ LightStack(const WaveBuf&) {}
+    __device__ __forceinline__ void put(int, u64 M, u64 R)
+    {
+        m = M;
+        r = R;
+    }
+    __device__ __forceinline__ void set_r(int, u64 R) { r = R; }
+    __device__ __forceinline__ u64 get_m(int) const { return m; }
+    __device__ __forceinline__ u64 get_r(int) const { return r; }
+};
+
+template <>
 struct LightStack<0> {
     u64* __restrict__ sM;
     u64* __restrict__ sR;
@@ -179,6 +208,21 @@ struct LightStack<0> {
     __device__ __forceinline__ u64 get_m(int s) const { return sM[s * kWave + lane]; }
     __device__ __forceinline__ u64 get_r(int s) const { return sR[s * kWave + lane]; }
 };
+
+// C(n, r) for n <= 64 and r <= 30 (k <= 32, two vertices chosen by the arc):
+// below 2^61.
+struct Binomials {
+    u64 c[kWave + 1][kKMax - 1];
+};
+constexpr Binomials make_binomials()
+{
+    Binomials b = {};
+    for (int n = 0; n <= kWave; ++n)
+        for (int r = 0; r < kKMax - 1; ++r)
+            b.c[n][r] = r == 0 ? 1 : (n == 0 ? 0 : b.c[n - 1][r - 1] + b.c[n - 1][r]);
+    return b;
+}
+__device__ const Binomials binomials = make_binomials();
 
 // One degrees-only step on a last-level node: the next two candidates x of
 // R (R != 0) leave R, and the result is the sum of popcount(M AND row_x).
@@ -203,43 +247,100 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
     const u64 lt_mask = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
     const u64* __restrict__ rows = wb.rows;
     LightStack<kRegL> stk(wb);
+    constexpr bool kProbe = kRegL != 1;   // k <= 6 has no node that is probed
     const int nunits = wb.nu;
     int next = 0;                      // wave-uniform unit counter
+    u64 branches = 0ull;               // first-level branches left of the unit before it (wave-uniform)
+    int urow = 0, uneed = 0, ubase = 0;
     bool active = false;
+    bool probe = false;                // counting the node's edges before searching it
+    unsigned edges = 0;
     u64 M = 0, R = 0, uacc = 0;
     int t = 0, need = 0, base = 0, tag = 0;
     for (;;) {
-        const u64 want = __ballot(!active);
-        if (want && next < nunits) {
-            const int u = next + __popcll(want & lt_mask);
-            next += __popcll(want);
-            if (!active && u < nunits) {
-                const int row = wb.units[u];
-                const int mt = wb.meta[row];
-                const u64 m1 = rows[row];
-                base = mt >> 8;
-                need = mt & 255;
-                const int c = __popcll(m1);
-                if (kStats) A.st[kStatLightUnits] += 1;
-                if (kPerArc) tag = wb.tags[row];
-                if (need == 1) {
-                    A.acc += (u64)c;
-                    if (kPerArc && c) atomicAdd(per_arc + tag, (u64)c);
-                } else if (c >= need) {
-                    M = m1;
-                    R = m1;
-                    t = 1;
-                    uacc = 0;
-                    active = true;
+        u64 want = __ballot(!active);
+        while (want && (branches || next < nunits)) {
+            if (branches == 0ull) {
+                // the next units: with at least kBranchNeed vertices to choose
+                // one unit is dealt branch by branch, smaller ones whole, a
+                // lane each
+                const int uw = __builtin_amdgcn_readfirstlane(wb.units[next]);
+                const int row = uw & 0xff;
+                const int mt = __builtin_amdgcn_readfirstlane(wb.meta[row]);
+                if ((mt & 255) >= kBranchNeed) {
+                    const u64 m1 = readlane64(rows[row], 0);
+                    urow = row;
+                    uneed = mt & 255;
+                    ubase = mt >> 8;
+                    // a sub-part takes the branches at positions q mod 2^s
+                    const int s = uw >> 16;
+                    branches = m1 & ((s == 4 ? 0x0001000100010001ull : s == 2 ? 0x1111111111111111ull : ~0ull)
+                                     << ((uw >> 8) & 0xff));
+                    if (__popcll(m1) < uneed) branches = 0ull;
+                    ++next;
+                    continue;
+                }
+                const int u = next + __popcll(want & lt_mask);
+                const int row_u = u < nunits ? wb.units[u] & 0xff : row;
+                const int mt_u = wb.meta[row_u];
+                // units of one kind lead the list; the rest waits for its turn
+                const u64 small = __ballot(u < nunits && (mt_u & 255) < kBranchNeed) & want;
+                const u64 stop = want & ~small;
+                const u64 take = stop ? small & ((1ull << __builtin_ctzll(stop)) - 1ull) : small;
+                next += __popcll(take);
+                if ((take >> lane) & 1) {
+                    const u64 m1 = rows[row_u];
+                    base = mt_u >> 8;
+                    need = mt_u & 255;
+                    const int c = __popcll(m1);
+                    if (kStats) A.st[kStatLightUnits] += 1;
+                    if (kPerArc) tag = wb.tags[row_u];
+                    if (need == 1) {
+                        A.acc += (u64)c;
+                        if (kPerArc && c) atomicAdd(per_arc + tag, (u64)c);
+                    } else if (c >= need) {
+                        M = m1;
+                        R = m1;
+                        t = 1;
+                        uacc = 0;
+                        active = true;
+                    }
+                }
+            } else {
+                const int r = __popcll(want & lt_mask);
+                const int left = __popcll(branches);
+                const u64 m1 = readlane64(rows[urow], 0);
+                if (!active && r < left) {
+                    const u64 nm = m1 & rows[ubase + select64(branches, r)];
+                    if (kStats) A.st[kStatLightUnits] += 1;
+                    if (__popcll(nm) >= uneed - 1) {
+                        M = nm;
+                        R = nm;
+                        t = 1;
+                        need = uneed - 1;
+                        base = ubase;
+                        probe = kProbe && need >= kProbeNeed;
+                        edges = 0;
+                        if (kPerArc) tag = wb.tags[urow];
+                        uacc = 0;
+                        active = true;
+                    }
+                }
+                const int taken = __popcll(want);
+                if (taken >= left) {
+                    branches = 0ull;
+                } else {
+                    const int last = __builtin_amdgcn_readfirstlane(select64(branches, taken - 1));
+                    branches &= ~0ull << last << 1;
                 }
             }
+            want = __ballot(!active);
         }
         const u64 act = __ballot(active);
         if (act == 0ull) {
-            if (next >= nunits) break;
-            continue;
+            break;               // no lane holds work and no unit is left
         }
-        if (next >= nunits && __popcll(~act) >= kDonateMinIdle) {
+        if (next >= nunits && branches == 0ull && __popcll(~act) >= kDonateMinIdle) {
             // work donation: no unit is left and lanes are idle, so every busy
             // lane offers the upper half of the remaining candidates of its
             // shallowest level that still holds real work; idle lanes take
@@ -247,7 +348,7 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
             int lvl = 0;
             u64 Ml = 0ull, Rl = 0ull;
             if (active) {
-                for (int l = 1; l <= t; ++l) {
+                for (int l = 1; l <= t - (probe ? 1 : 0); ++l) {
                     const u64 r = (l == t) ? R : stk.get_r(l - 1);
                     const int pc = __popcll(r);
                     if (pc >= 2 && (need + (t - l) >= 3 || pc >= 8)) {
@@ -289,6 +390,7 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
                     t = 1;
                     uacc = 0;
                     active = true;
+                    probe = false;
                     if (kStats) A.st[kStatDonations] += 1;
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -300,11 +402,13 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
         }
         if (active) {
             if (R != 0ull) {
-                if (need == 2) {
-                    // degrees-only last level, two candidates per step
+                if (need == 2 || probe) {
+                    // degrees-only last level (or the probe's edge count), two
+                    // candidates per step
                     const unsigned c = leaf_step(rows, base, M, R);
-                    A.acc += (u64)c;
-                    if (kPerArc) uacc += (u64)c;
+                    if (probe) edges += c;
+                    else A.acc += (u64)c;
+                    if (kPerArc && !probe) uacc += (u64)c;
                     if (kStats) A.st[kStatWordOps] += 2;
                 } else {
                     const int x = __builtin_ctzll(R);
@@ -316,11 +420,13 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
                         R = nm;
                         ++t;
                         --need;
+                        probe = kProbe && need >= kProbeNeed;
+                        edges = 0;
                         if (kStats) A.st[kStatPushes] += 1;
                     }
                 }
             }
-            if (need == 2 && R != 0ull) {
+            if ((need == 2 || probe) && R != 0ull) {
                 // leaf burst: while most lanes sit at a last-level node, run
                 // only last-level steps, two candidates at a time
                 unsigned bacc = 0;             // <= 2 * 64 * kBurstIters
@@ -332,8 +438,23 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
                         if (kStats) A.st[kStatWordOps] += 2;
                     }
                 }
-                A.acc += (u64)bacc;
-                if (kPerArc) uacc += (u64)bacc;
+                if (probe) edges += bacc;
+                else A.acc += (u64)bacc;
+                if (kPerArc && !probe) uacc += (u64)bacc;
+            }
+            if (kProbe && probe && R == 0ull) {
+                // every pair adjacent: the node's cliques are its subsets of
+                // `need`; otherwise it is searched
+                const int c = __popcll(M);
+                probe = false;
+                if (2 * edges == (unsigned)(c * (c - 1))) {
+                    const u64 b = binomials.c[c][need];
+                    A.acc += b;
+                    if (A.acc < b) A.ovf = 1;
+                    if (kPerArc) uacc += b;
+                } else {
+                    R = M;
+                }
             }
             if (R == 0ull) {
                 if (t == 1) {
@@ -726,14 +847,14 @@ struct KParams {
 };
 
 template <int kMode, bool kStats, bool kPerArc>
-__global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(kMode == kStackReg ? 4 : 2))) count_kernel(KParams P)
+__global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(kMode <= kStackReg ? 4 : kMode == kStackLds ? 3 : 2))) count_kernel(KParams P)
 {
-    constexpr int kRegL = kMode == kStackReg ? kRegLevels : 0;
+    constexpr int kRegL = kMode == kStackOne ? 1 : kMode == kStackReg ? kRegLevels : 0;
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = lane_of();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int nwaves = blockDim.x / kWave;
-    const int levels = stack_levels(P.max_k);
+    const int levels = heavy_levels(P.max_k);
     unsigned char* wbase = smem + wid * wave_lds_bytes(P.max_k, P.arc_lds_max, kPerArc);
     WaveBuf wb;
     int off = 0;
@@ -751,21 +872,17 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     off += 4 * kWaveBufRows;
     int32_t* item = reinterpret_cast<int32_t*>(wbase + off);
     off += 4 * kItFields * kMaxClaim;
-    u64* stacks;
-    if (kMode == kStackLds)
-        stacks = reinterpret_cast<u64*>(wbase + off);
-    else
-        stacks = P.scratch + (int64_t)blockIdx.x * P.scratch_words + (int64_t)wid * wave_global_stack_words(P.max_k);
-    if (kMode == kStackReg) {
-        wb.sM = nullptr;
-        wb.sR = nullptr;
-        wb.hM = stacks;
-        wb.hR = stacks + (int64_t)levels * kWave;
-    } else {
-        wb.sM = stacks;
-        wb.sR = stacks + (int64_t)levels * kWave;
-        wb.hM = stacks + 2ll * levels * kWave;
-        wb.hR = stacks + 3ll * levels * kWave;
+    u64* stacks = P.scratch + (int64_t)blockIdx.x * P.scratch_words + (int64_t)wid * wave_global_stack_words(P.max_k);
+    wb.hM = stacks;
+    wb.hR = stacks + (int64_t)levels * kWave;
+    wb.sM = nullptr;
+    wb.sR = nullptr;
+    if (kMode == kStackLds) {
+        wb.sM = reinterpret_cast<u64*>(wbase + off);
+        wb.sR = wb.sM + light_levels(P.max_k) * kWave;
+    } else if (kMode == kStackGlobal) {
+        wb.sM = stacks + 2ll * levels * kWave;
+        wb.sR = stacks + 3ll * levels * kWave;
     }
     wb.n = 0;
     wb.nu = 0;
@@ -797,7 +914,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
         if (j >= nj) {
             g0 = claim_run(P.items, wave, waves, shard, fresh);
             end = g0 < 0;
-            nj = end ? 0 : min(P.items.chunk, P.items.total - g0);
+            nj = end ? 0 : run_length(P.items, g0);
             j = 0;
             __builtin_amdgcn_wave_barrier();
             decode_run<kRestSpace>(P.items, g0, nj, item);
@@ -873,10 +990,14 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
                 wb.meta[wb.n + d] = (wb.n << 8) | (k - 1);
                 wb.units[wb.nu] = wb.n + d;
             }
-            const bool unit = !from_root && lane < d &&
-                              (r >= 0 ? lane == r : (nparts == 1 || lane % nparts == part));
+            // part = arc residue + light_arcs * sub-part
+            const int subs = nparts > 1 ? light_subs(d, k) : 1;
+            const int every = nparts / subs, sub = part / every;
+            const bool unit = !from_root && lane < d && (r >= 0 ? lane == r : lane % every == part - sub * every);
             const u64 um = __ballot(unit);
-            if (unit) wb.units[wb.nu + __popcll(um & (lane == 0 ? 0ull : (~0ull >> (kWave - lane))))] = wb.n + lane;
+            if (unit)
+                wb.units[wb.nu + __popcll(um & (lane == 0 ? 0ull : (~0ull >> (kWave - lane))))] =
+                    (wb.n + lane) | (sub << 8) | (subs == 16 ? 4 << 16 : subs == 4 ? 2 << 16 : 0);
             wb.nu += __popcll(um) + (from_root ? 1 : 0);
             wb.n += d + (from_root ? 1 : 0);
         }
@@ -926,13 +1047,14 @@ hipError_t launch_mode(const KParams& P, const CountLaunch& cl, hipStream_t s)
 }
 
 // One translation unit per stack mode, so that they compile side by side:
-// this file by itself holds the host functions and the variants of k <= 8,
+// this file by itself holds the host functions and the variants of k <= 6,
 // and is included with CITRON_COUNT_UNIT set to another mode by
-// kernels_count_lds.hip and kernels_count_deep.hip.
+// kernels_count_reg.hip, kernels_count_lds.hip and kernels_count_deep.hip.
 #ifdef CITRON_COUNT_UNIT
 template hipError_t launch_mode<CITRON_COUNT_UNIT>(const KParams&, const CountLaunch&, hipStream_t);
 #else
-template hipError_t launch_mode<kStackReg>(const KParams&, const CountLaunch&, hipStream_t);
+template hipError_t launch_mode<kStackOne>(const KParams&, const CountLaunch&, hipStream_t);
+extern template hipError_t launch_mode<kStackReg>(const KParams&, const CountLaunch&, hipStream_t);
 extern template hipError_t launch_mode<kStackLds>(const KParams&, const CountLaunch&, hipStream_t);
 extern template hipError_t launch_mode<kStackGlobal>(const KParams&, const CountLaunch&, hipStream_t);
 
@@ -946,7 +1068,7 @@ int64_t count_scratch_words(int32_t, int32_t max_k, int32_t wg_waves)
 int64_t count_deep_scratch_words(int32_t max_k, int32_t wg_waves)
 {
     if (stack_mode(max_k) != kStackGlobal) return 0;
-    return ((int64_t)wg_waves * wave_stack_words(max_k) + 31) & ~31ll;
+    return ((int64_t)wg_waves * wave_global_stack_words(max_k) + 31) & ~31ll;
 }
 
 int32_t count_lds_bytes(int32_t arc_max, int32_t max_k, int32_t wg_waves, bool per_arc)
@@ -976,18 +1098,16 @@ hipError_t launch_count(const CountLaunch& cl, hipStream_t s)
     P.arc_lds_max = clamp_arc_max(cl.arc_lds_max);
     P.progress = cl.progress;
     P.progress_base = (int32_t)(launch_items(cl) - rest);
-    // A launch is no wider than its items.  Items per claim: a run short
-    // enough that every wave still makes about eight claims; items are in
-    // descending cost order, so those of a run cost about the same.
+    // a launch is no wider than its items
     CountLaunch c2 = cl;
-    {
-        const int64_t need = ((int64_t)rest + cl.wg_waves - 1) / cl.wg_waves;
-        if (need < c2.blocks) c2.blocks = (int32_t)need;
-        const int64_t waves = (int64_t)c2.blocks * cl.wg_waves;
-        const int64_t c = (int64_t)rest / (waves * 8);
-        P.items.chunk = (int32_t)(c < 1 ? 1 : (c > kMaxClaim ? kMaxClaim : c));
-    }
+    const int64_t need = ((int64_t)rest + cl.wg_waves - 1) / cl.wg_waves;
+    if (need < c2.blocks) c2.blocks = (int32_t)need;
+    // deep counts: an item's cost is far from what its key says, so runs stay
+    // short (16 light items of a planted clique's vertices in one run took as
+    // long as the rest of a k = 9 launch)
+    set_runs(P.items, (int64_t)c2.blocks * cl.wg_waves, cl.max_k <= 6 ? kMaxClaim : (cl.max_k == 7 ? 8 : kDeepClaim));
     switch (stack_mode(cl.max_k)) {
+    case kStackOne: return launch_mode<kStackOne>(P, c2, s);
     case kStackReg: return launch_mode<kStackReg>(P, c2, s);
     case kStackLds: return launch_mode<kStackLds>(P, c2, s);
     default: return launch_mode<kStackGlobal>(P, c2, s);

@@ -423,7 +423,7 @@ __global__ void __launch_bounds__(dense_waves(K) * kWave)
     for (;;) {
         if (threadIdx.x < kWave) {
             const int g = claim_run(P.items, blockIdx.x, gridDim.x, shard, fresh);
-            const int n = g < 0 ? 0 : min(P.items.chunk, P.items.total - g);
+            const int n = g < 0 ? 0 : run_length(P.items, g);
             decode_run<kDenseClasses - K>(P.items, g, n, item);
             if (lane == 0) {
                 shared[1] = g;
@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(dense_waves(K) * kWave)
         __syncthreads();
         const int g0 = __builtin_amdgcn_readfirstlane(shared[1]);
         if (g0 < 0) break;
-        const int n = min(P.items.chunk, P.items.total - g0);
+        const int n = run_length(P.items, g0);
         for (int j = 0; j < n; ++j) {
             auto field = [&](int f) { return __builtin_amdgcn_readfirstlane(item[f * kMaxClaim + j]); };
             const int qi = field(kItQuery);
@@ -478,8 +478,7 @@ static hipError_t launch_class(const CountLaunch& cl, int cus, int32_t base, hip
     const int by_lds = 160 * 1024 / lds, by_regs = dense_cu_waves(K) / dense_waves(K);
     int64_t blocks = (int64_t)cus * (by_lds < by_regs ? by_lds : by_regs);
     if (blocks > n) blocks = n;
-    const int64_t c = n / (blocks * 8);
-    P.items.chunk = (int32_t)(c < 1 ? 1 : (c > kDenseClaim ? kDenseClaim : c));
+    set_runs(P.items, blocks, kDenseClaim);
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)dense_kernel<K>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;

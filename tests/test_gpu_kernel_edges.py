@@ -136,3 +136,53 @@ def test_dense_arcs_under_both_orderings(citron_gpu, ordering):
     for k in (6, 7):
         assert h.count(k) == oracle.count(g, k)[0]
     h.free()
+
+
+@pytest.mark.parametrize("k", [7, 8, 9, 10, 12, 13, 20, 32])
+def test_complete_nodes_of_light_vertices(citron_gpu, k):
+    """Disjoint cliques up to K_65, whose vertices are all light (out-degree
+    at most 64): every probed node is complete and counted by a binomial."""
+    from math import comb
+    sizes = list(range(5, 66, 4)) + [64]
+    g = gg.disjoint_cliques(sizes)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    want = sum(comb(s, k) for s in sizes)
+    assert want < 2 ** 64
+    assert h.count(k) == want
+    assert h.count_vertex_rooted(k) == want
+    total, every = h.count_per_arc(k)
+    assert total == want == sum(int(x) for x in every)
+    h.free()
+
+
+def test_binomials_that_carry(citron_gpu):
+    from math import comb
+    g = gg.disjoint_cliques([65] * 6)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    want = 6 * comb(65, 32)
+    assert want > 2 ** 64
+    assert h.count_checked(32) == (want % 2 ** 64, True)
+    h.free()
+
+
+@pytest.mark.parametrize("n,missing,k", [(24, 1, 7), (30, 12, 7), (30, 12, 8), (28, 3, 9), (26, 40, 9), (24, 9, 10),
+                                         (22, 5, 13)])
+def test_nearly_complete_nodes(citron_gpu, n, missing, k):
+    """A clique with a few edges taken out, beside a sparse graph: probes that
+    fail at the root and hold below it."""
+    import oracle
+    rng = np.random.default_rng(n * 100 + k)
+    i, j = np.triu_indices(n, 1)
+    keep = np.ones(i.size, bool)
+    keep[rng.choice(i.size, missing, replace=False)] = False
+    extra = rng.integers(0, 200, (2, 900))
+    g = gg.csr_from_edges(200, np.concatenate([i[keep], extra[0]]), np.concatenate([j[keep], extra[1]]), perm_seed=k)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    want, ovf = oracle.count(g, k)
+    assert not ovf and want > 0
+    assert h.count(k) == want
+    assert h.count_vertex_rooted(k) == want
+    total, every = h.count_per_arc(k)
+    assert total == want == int(every.sum())
+    assert sum(h.count_part(k, p, 7)[0] for p in range(7)) == want
+    h.free()

@@ -27,6 +27,9 @@ citron_status hip_fail(hipError_t e, const char* what)
     return fail(CITRON_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
 
+// Phases of the peeling queued before the host looks whether it has ended.
+constexpr int32_t kPeelBatch = 48;
+
 citron_tuning default_tuning()
 {
     citron_tuning t;
@@ -805,67 +808,44 @@ citron_status citron_load_csr(int32_t n, int64_t nnz, const int32_t* row_ptr, co
 }
 
 // Level-synchronous peeling (kernels_core.hip): g->d_key[v] = the round in
-// which v leaves.  Frontier buffers are temporary.
+// which v leaves.  The lists are temporary.
 static citron_status peel_key(citron_graph* g)
 {
     hipStream_t s = g->stream;
     int64_t* acct = &g->device_bytes;
     citron_status st;
     if (!g->d_key && (st = dalloc(&g->d_key, (size_t)g->n + 1, acct, "order key"))) return st;
-    int32_t *deg = nullptr, *fa = nullptr, *fb = nullptr;
-    if ((st = dalloc(&deg, (size_t)g->n + 1, nullptr, "peeling")) ||
-        (st = dalloc(&fa, (size_t)g->n + 1, nullptr, "peeling")) ||
-        (st = dalloc(&fb, (size_t)g->n + 1, nullptr, "peeling"))) {
-        dfree(deg); dfree(fa); dfree(fb);
-        return st;
-    }
-    int32_t* cnt = g->d_small->peel;          // [0], [1]: frontier sizes, [2]: smallest degree
-    int32_t* hp = g->h_small->peel;
-    auto sync_read = [&](int32_t* dst, const int32_t* src, int count) -> hipError_t {
-        hipError_t e = hipMemcpyAsync(dst, src, sizeof(int32_t) * (size_t)count, hipMemcpyDeviceToHost, s);
-        return e == hipSuccess ? hipStreamSynchronize(s) : e;
-    };
-    hipError_t e = launch_fill_i32(cnt, 0, 2, s);
-    if (e == hipSuccess) e = launch_fill_i32(cnt + 2, 0x7fffffff, 1, s);
-    if (e == hipSuccess) e = launch_peel_init(g->n, g->d_row_ptr, deg, g->d_key, cnt + 2, s);
-    if (e == hipSuccess) e = sync_read(hp, cnt, 3);
-    int32_t t = hp[2], r = 0, remaining = g->n, nf = 0;
-    int32_t* cur = fa;
-    int32_t* nxt = fb;
-    int cur_slot = 0;
-    while (e == hipSuccess && remaining > 0) {
-        if (nf == 0) {
-            // no vertex left at degree <= t: raise t to the smallest degree present
-            if (r > 0) {
-                e = launch_fill_i32(cnt + 2, 0x7fffffff, 1, s);
-                if (e == hipSuccess) e = launch_peel_min(g->n, deg, g->d_key, cnt + 2, s);
-                if (e == hipSuccess) e = sync_read(hp + 2, cnt + 2, 1);
-                if (e != hipSuccess) break;
-                t = hp[2];
-            }
-            e = launch_fill_i32(cnt + cur_slot, 0, 1, s);
-            if (e == hipSuccess) e = launch_peel_collect(g->n, deg, g->d_key, t, cur, cnt + cur_slot, s);
-            if (e == hipSuccess) e = sync_read(hp + cur_slot, cnt + cur_slot, 1);
-            if (e != hipSuccess) break;
-            nf = hp[cur_slot];
-            if (nf <= 0) { e = hipErrorUnknown; break; }     // cannot happen while vertices remain
-        }
-        e = launch_fill_i32(cnt + (1 - cur_slot), 0, 1, s);
+    int32_t* lists = nullptr;                 // degrees, two frontiers, two lists of the vertices left
+    const size_t len = (size_t)g->n + 1;
+    if ((st = dalloc(&lists, 5 * len, nullptr, "peeling"))) return st;
+    PeelParams P;
+    P.row_ptr = g->d_row_ptr;
+    P.col = g->d_col;
+    P.deg = lists;
+    P.round = g->d_key;
+    P.frontier[0] = lists + len;
+    P.frontier[1] = lists + 2 * len;
+    P.alive[0] = lists + 3 * len;
+    P.alive[1] = lists + 4 * len;
+    P.ctl = &g->d_small->peel;
+    const PeelCtl& c = g->h_small->peel;
+    hipError_t e = launch_peel_init(g->n, P, s);
+    // each launch is one phase; the host looks after every batch of them.  A
+    // vertex leaves in one round, and a round is at most four phases.
+    int64_t left = 4ll * g->n + 4;
+    bool done = false;
+    while (e == hipSuccess && !done && left > 0) {
+        e = launch_peel_steps(P, kPeelBatch, s);
+        left -= kPeelBatch;
         if (e == hipSuccess)
-            e = launch_peel_round(nf, cur, g->d_row_ptr, g->d_col, deg, g->d_key, t, r, nxt, cnt + (1 - cur_slot), s);
-        if (e == hipSuccess) e = sync_read(hp + (1 - cur_slot), cnt + (1 - cur_slot), 1);
-        if (e != hipSuccess) break;
-        remaining -= nf;
-        ++r;
-        nf = hp[1 - cur_slot];
-        std::swap(cur, nxt);
-        cur_slot = 1 - cur_slot;
+            e = hipMemcpyAsync(&g->h_small->peel, P.ctl, sizeof(PeelCtl), hipMemcpyDeviceToHost, s);
+        if (e == hipSuccess) e = hipStreamSynchronize(s);
+        done = e == hipSuccess && c.phase == kPeelDone;
     }
-    dfree(deg);
-    dfree(fa);
-    dfree(fb);
+    dfree(lists);
+    if (e == hipSuccess && !done) e = hipErrorUnknown;   // cannot happen: every round removes a vertex
     if (e != hipSuccess) return hip_fail(e, "peeling kernels");
-    g->peel_rounds = r;
+    g->peel_rounds = c.r;
     return CITRON_OK;
 }
 

@@ -21,9 +21,10 @@ struct SmallDev {
     unsigned long long tri_acc;
     int32_t tri_ovf;
     int32_t build_ctr;
-    int32_t peel[4];             // peeling: frontier counts (2), smallest degree, spare
+    PeelCtl peel;
     unsigned long long build_stats[kNumStats];
 };
+static_assert(sizeof(SmallDev) % 8 == 0, "cleared in 8-byte words");
 
 // What one count launch reads and updates: uploaded as one copy before the
 // launch (partial sums, flag and cursors in their starting state); the sums
@@ -50,7 +51,7 @@ struct SmallHost {
     int32_t tri_ovf;
     int32_t rows_total;
     int32_t hrows_total;
-    int32_t peel[4];
+    PeelCtl peel;
     uint64_t build_stats[kNumStats];
 };
 

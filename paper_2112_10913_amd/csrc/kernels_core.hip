@@ -10,131 +10,239 @@
 // round numbers are the order key (ties by id): every out-degree of the
 // resulting DAG is at most the t of its vertex's round, which never exceeds
 // the degeneracy.
+//
+// The device drives itself: each launch of peel_step_kernel does one phase
+// that the control block names, and the workgroup that finishes last sets up
+// the next one, so the host only queues launches and looks at the control
+// block once per batch.  No workgroup ever waits for another.  Small steps
+// (marking a short frontier, raising t over a short list of the vertices
+// left) are done by that last workgroup at once.  Bound by latency: a round
+// is one launch of about 11 us, most of it a chain of dependent loads and
+// atomics (128, 256 and 1,024 workgroups are alike).  (With the host reading each round's
+// frontier size and launching four kernels for it, a round took 38 us:
+// R-MAT 16, 314 rounds: 12.5 ms for load, ordering and DAG, now 5.8 ms.)
 #include "kernels.h"
 
 namespace citron {
 
 namespace {
 
+constexpr int kPeelBlock = 512;
+constexpr int kPeelWaves = kPeelBlock / kWave;
+constexpr int kPeelBlocks = 128;
+constexpr int kPerThread = 8;                  // list entries a thread takes before another workgroup starts
+constexpr int kInlineMark = 16 * kPeelBlock;   // lists the last workgroup handles itself
+constexpr int kInlineRaise = 16 * kPeelBlock;
+
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 
-// Block-wide minimum, then one atomic per block.
-__device__ void block_min_to(int v, int32_t* out)
+// Smallest v over the workgroup, in every thread.
+__device__ int block_min(int v)
 {
-    __shared__ int wmin[1024 / kWave];
+    __shared__ int wmin[kPeelWaves];
     const int lane = lane_id(), wid = threadIdx.x / kWave;
 #pragma unroll
     for (int o = kWave / 2; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, kWave));
+    __syncthreads();
     if (lane == 0) wmin[wid] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int m = wmin[0];
-        for (int w = 1; w < (int)(blockDim.x / kWave); ++w) m = min(m, wmin[w]);
-        if (m != 0x7fffffff) atomicMin(out, m);
+    int m = wmin[0];
+#pragma unroll
+    for (int w = 1; w < kPeelWaves; ++w) m = min(m, wmin[w]);
+    return m;
+}
+
+// Appends the lanes' v with `take` to list at *cnt: one atomic per wave.
+__device__ __forceinline__ void wave_append(bool take, int32_t v, int32_t* list, int32_t* cnt)
+{
+    const unsigned long long mask = __ballot(take);
+    if (!mask) return;
+    const int lane = lane_id();
+    int base = 0;
+    if (lane == 0) base = atomicAdd(cnt, __popcll(mask));
+    base = __shfl(base, 0, kWave);
+    const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
+    if (take) list[base + __popcll(mask & below)] = v;
+}
+
+// Vertices of `alive` still present: those of degree <= t become the round's
+// frontier (marked), the others the next list of vertices left.
+__device__ void peel_collect(const PeelParams& P, PeelCtl* c, const int32_t* alive, int n_alive, int t, int r,
+                             int32_t* frontier, int32_t* left, int first, int step)
+{
+    for (int i0 = first; i0 < n_alive; i0 += step) {       // uniform over a wave
+        const int i = i0 + lane_id();
+        const int32_t v = i < n_alive ? alive[i] : -1;
+        const bool here = v >= 0 && P.round[v] < 0;
+        const bool now = here && P.deg[v] <= t;
+        if (now) P.round[v] = r;
+        wave_append(now, v, frontier, &c->n_frontier);
+        wave_append(here && !now, v, left, &c->n_left);
     }
 }
 
 }  // namespace
 
-__global__ void peel_init_kernel(int32_t n, const int32_t* __restrict__ row_ptr, int32_t* __restrict__ deg,
-                                 int32_t* __restrict__ round, int32_t* __restrict__ min_deg)
+__global__ void peel_init_kernel(int32_t n, PeelParams P)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int d = 0x7fffffff;
     if (v < n) {
-        d = row_ptr[v + 1] - row_ptr[v];
-        deg[v] = d;
-        round[v] = -1;
+        P.deg[v] = P.row_ptr[v + 1] - P.row_ptr[v];
+        P.round[v] = -1;
+        P.alive[0][v] = (int32_t)v;
     }
-    block_min_to(d, min_deg);
-}
-
-__global__ void peel_min_kernel(int32_t n, const int32_t* __restrict__ deg, const int32_t* __restrict__ round,
-                                int32_t* __restrict__ min_deg)
-{
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int d = (v < n && round[v] < 0) ? deg[v] : 0x7fffffff;
-    block_min_to(d, min_deg);
-}
-
-// Ballot compaction per wave, one atomic per wave.
-__global__ void peel_collect_kernel(int32_t n, const int32_t* __restrict__ deg, const int32_t* __restrict__ round,
-                                    int32_t t, int32_t* __restrict__ frontier, int32_t* __restrict__ cnt)
-{
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int lane = lane_id();
-    const bool take = v < n && round[v] < 0 && deg[v] <= t;
-    const unsigned long long mask = __ballot(take);
-    if (!mask) return;
-    int base = 0;
-    if (lane == 0) base = atomicAdd(cnt, __popcll(mask));
-    base = __shfl(base, 0, kWave);
-    if (take) {
-        const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
-        frontier[base + __popcll(mask & below)] = (int32_t)v;
+    if (v == 0) {
+        PeelCtl c = {};
+        c.phase = kPeelMin;
+        c.remaining = n;
+        c.n_alive = n;
+        c.min_deg = 0x7fffffff;
+        *P.ctl = c;
     }
 }
 
-__global__ void peel_mark_kernel(int32_t nf, const int32_t* __restrict__ frontier, int32_t* __restrict__ round,
-                                 int32_t r)
+__global__ void __launch_bounds__(kPeelBlock) peel_step_kernel(PeelParams P)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < nf) round[frontier[i]] = r;
-}
-
-// One wave per frontier vertex, lanes over its neighbours.
-__global__ void peel_relax_kernel(int32_t nf, const int32_t* __restrict__ frontier,
-                                  const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
-                                  int32_t* __restrict__ deg, const int32_t* __restrict__ round, int32_t t,
-                                  int32_t* __restrict__ next, int32_t* __restrict__ next_cnt)
-{
-    const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave;
-    if (i >= nf) return;
-    const int lane = lane_id();
-    const int32_t v = frontier[i];
-    const int32_t a = row_ptr[v], b = row_ptr[v + 1];
-    for (int32_t e = a + lane; e < b; e += kWave) {
-        const int32_t w = col[e];
-        if (round[w] >= 0) continue;            // gone, or leaving in this round
-        const int32_t old = atomicSub(&deg[w], 1);
-        if (old == t + 1) next[atomicAdd(next_cnt, 1)] = w;
+    __shared__ int last;
+    PeelCtl* const c = P.ctl;
+    const int phase = c->phase;
+    if (phase == kPeelDone) return;
+    const int cur = c->cur, side = c->side, t = c->t, r = c->r;
+    const int nf = c->n_cur, n_alive = c->n_alive;
+    int32_t* const frontier = P.frontier[cur];
+    int32_t* const next = P.frontier[1 - cur];
+    const int32_t* const alive = P.alive[side];
+    // workgroups the phase needs; the others leave at once
+    const int items = phase == kPeelRelax ? nf : phase == kPeelMark ? nf : n_alive;
+    const int per_block = phase == kPeelRelax ? kPeelWaves : kPeelBlock * kPerThread;
+    const int groups = min((int)gridDim.x, max(1, (items + per_block - 1) / per_block));
+    if ((int)blockIdx.x >= groups) return;
+    const int wid = threadIdx.x / kWave, lane = lane_id();
+    const int wave = blockIdx.x * kPeelWaves + wid, waves = groups * kPeelWaves;
+    if (phase == kPeelRelax) {
+        // one wave per frontier vertex, lanes over its neighbours
+        for (int i = wave; i < nf; i += waves) {
+            const int32_t v = frontier[i];
+            const int32_t a = P.row_ptr[v], b = P.row_ptr[v + 1];
+            for (int32_t e0 = a; e0 < b; e0 += kWave) {
+                const int32_t e = e0 + lane;
+                const int32_t w = e < b ? P.col[e] : -1;
+                // gone, or leaving in this round, when its round is set
+                const bool join = w >= 0 && P.round[w] < 0 && atomicSub(&P.deg[w], 1) == t + 1;
+                wave_append(join, w, next, &c->n_frontier);
+            }
+        }
+    } else if (phase == kPeelMark) {
+        for (int i = blockIdx.x * kPeelBlock + threadIdx.x; i < nf; i += groups * kPeelBlock) P.round[frontier[i]] = r;
+    } else if (phase == kPeelMin) {
+        int m = 0x7fffffff;
+        for (int i = blockIdx.x * kPeelBlock + threadIdx.x; i < n_alive; i += groups * kPeelBlock) {
+            const int32_t v = alive[i];
+            if (P.round[v] < 0) m = min(m, P.deg[v]);
+        }
+        m = block_min(m);
+        if (threadIdx.x == 0 && m != 0x7fffffff) atomicMin(&c->min_deg, m);
+    } else {
+        peel_collect(P, c, alive, n_alive, t, r, frontier, P.alive[1 - side], wave * kWave, waves * kWave);
+    }
+    // the workgroup that finishes last sets up the next phase
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        last = atomicAdd(&c->done, 1) == groups - 1;
+        __threadfence();
+    }
+    __syncthreads();
+    if (!last) return;
+    auto read = [](const int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    if (phase == kPeelMin) {
+        if (threadIdx.x == 0) {
+            c->t = read(&c->min_deg);
+            c->min_deg = 0x7fffffff;
+            c->phase = kPeelCollect;
+            c->done = 0;
+        }
+        return;
+    }
+    if (phase == kPeelMark) {
+        if (threadIdx.x == 0) {
+            c->phase = kPeelRelax;
+            c->done = 0;
+        }
+        return;
+    }
+    if (phase == kPeelCollect) {
+        if (threadIdx.x == 0) {
+            c->n_cur = read(&c->n_frontier);
+            c->n_alive = read(&c->n_left);
+            c->n_frontier = 0;
+            c->n_left = 0;
+            c->side = 1 - side;
+            c->phase = kPeelRelax;
+            c->done = 0;
+        }
+        return;
+    }
+    // a round is over
+    const int joined = read(&c->n_frontier);
+    const int remaining = c->remaining - nf;
+    __syncthreads();                    // every thread has read what thread 0 writes below
+    if (threadIdx.x == 0) {
+        c->remaining = remaining;
+        c->r = r + 1;
+        c->n_frontier = 0;
+        c->done = 0;
+    }
+    if (remaining == 0) {
+        if (threadIdx.x == 0) c->phase = kPeelDone;
+        return;
+    }
+    if (joined > 0) {
+        if (threadIdx.x == 0) {
+            c->cur = 1 - cur;
+            c->n_cur = joined;
+            c->phase = joined <= kInlineMark ? kPeelRelax : kPeelMark;
+        }
+        if (joined <= kInlineMark)
+            for (int i = threadIdx.x; i < joined; i += kPeelBlock) P.round[read(&next[i])] = r + 1;
+        return;
+    }
+    // no vertex at or below t is left: t rises to the smallest degree present
+    if (n_alive > kInlineRaise) {
+        if (threadIdx.x == 0) c->phase = kPeelMin;
+        return;
+    }
+    int m = 0x7fffffff;
+    for (int i = threadIdx.x; i < n_alive; i += kPeelBlock) {
+        const int32_t v = alive[i];
+        if (read(&P.round[v]) < 0) m = min(m, read(&P.deg[v]));
+    }
+    m = block_min(m);
+    __syncthreads();
+    // (n_frontier was just cleared by thread 0, before the barriers)
+    peel_collect(P, c, alive, n_alive, m, r + 1, frontier, P.alive[1 - side], wid * kWave, kPeelWaves * kWave);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        c->t = m;
+        c->n_cur = read(&c->n_frontier);
+        c->n_alive = read(&c->n_left);
+        c->n_frontier = 0;
+        c->n_left = 0;
+        c->side = 1 - side;
+        c->phase = kPeelRelax;
     }
 }
 
-hipError_t launch_peel_init(int32_t n, const int32_t* row_ptr, int32_t* deg, int32_t* round, int32_t* min_deg,
-                            hipStream_t s)
+hipError_t launch_peel_init(int32_t n, const PeelParams& P, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    peel_init_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, row_ptr, deg, round, min_deg);
+    peel_init_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, P);
     return hipGetLastError();
 }
 
-hipError_t launch_peel_min(int32_t n, const int32_t* deg, const int32_t* round, int32_t* min_deg, hipStream_t s)
+hipError_t launch_peel_steps(const PeelParams& P, int32_t steps, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    peel_min_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, deg, round, min_deg);
-    return hipGetLastError();
-}
-
-hipError_t launch_peel_collect(int32_t n, const int32_t* deg, const int32_t* round, int32_t t, int32_t* frontier,
-                               int32_t* cnt, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    peel_collect_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, deg, round, t, frontier, cnt);
-    return hipGetLastError();
-}
-
-hipError_t launch_peel_round(int32_t nf, const int32_t* frontier, const int32_t* row_ptr, const int32_t* col,
-                             int32_t* deg, int32_t* round, int32_t t, int32_t r, int32_t* next, int32_t* next_cnt,
-                             hipStream_t s)
-{
-    if (nf <= 0) return hipSuccess;
-    peel_mark_kernel<<<(unsigned)((nf + 255) / 256), 256, 0, s>>>(nf, frontier, round, r);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int64_t threads = (int64_t)nf * kWave;
-    peel_relax_kernel<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(nf, frontier, row_ptr, col, deg, round, t,
-                                                                       next, next_cnt);
+    for (int32_t i = 0; i < steps; ++i) peel_step_kernel<<<kPeelBlocks, kPeelBlock, 0, s>>>(P);
     return hipGetLastError();
 }
 

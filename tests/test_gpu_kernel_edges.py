@@ -186,3 +186,26 @@ def test_nearly_complete_nodes(citron_gpu, n, missing, k):
     assert total == want == int(every.sum())
     assert sum(h.count_part(k, p, 7)[0] for p in range(7)) == want
     h.free()
+
+
+@pytest.mark.parametrize("chains", [1, 63, 4095, 4096, 4097, 9000])
+def test_peeling_at_the_sizes_where_phases_change(citron_gpu, chains):
+    """Frontiers and lists of the vertices left around the sizes that one
+    workgroup handles by itself (8192): chains that peel from both ends, and
+    cliques whose rise of the threshold comes after them."""
+    import oracle
+    chain = np.arange(chains)[:, None] * 7 + np.arange(6)[None, :]
+    n = chains * 7
+    src, dst = [chain.ravel()], [chain.ravel() + 1]
+    for size in (4, 5, 9):
+        for _ in range(1 + chains // 4):
+            i, j = np.triu_indices(size, 1)
+            src.append(n + i)
+            dst.append(n + j)
+            n += size
+    g = gg.csr_from_edges(n, np.concatenate(src), np.concatenate(dst), perm_seed=chains)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order("core")
+    key, rounds = h.order_key()
+    want = oracle.peel_rounds(g.n, g.row_ptr, g.col)
+    assert np.array_equal(key, want) and rounds == int(want.max()) + 1
+    h.free()

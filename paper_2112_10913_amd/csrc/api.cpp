@@ -290,9 +290,7 @@ citron_status ensure_rows(citron_graph* g)
     // triangle): their rows and sizes must read as zero
     if ((e = launch_fill_u64(g->d_rows, 0, std::max<int64_t>(words, 1), s)) != hipSuccess ||
         (e = launch_fill_i32(g->d_arc_c, 0, g->m, s)) != hipSuccess ||
-        (e = launch_fill_u64(&sd->tri_acc, 0, 1, s)) != hipSuccess ||
-        (e = launch_fill_i32(&sd->tri_ovf, 0, 2, s)) != hipSuccess ||
-        (e = launch_fill_u64(sd->build_stats, 0, kNumStats, s)) != hipSuccess)
+        (e = launch_fill_u64((unsigned long long*)sd->build, 0, sizeof(sd->build) / 8, s)) != hipSuccess)
         return hip_fail(e, "fill");
     BuildParams P;
     P.dag_ptr = g->d_dag_ptr;
@@ -305,10 +303,7 @@ citron_status ensure_rows(citron_graph* g)
     P.rows_off = g->d_rows_off;
     P.rows = g->d_rows;
     P.arc_c = g->d_arc_c;
-    P.tri_acc = &sd->tri_acc;
-    P.tri_ovf = &sd->tri_ovf;
-    P.item_ctr = &sd->build_ctr;
-    P.build_stats = sd->build_stats;
+    P.sums = sd->build;
     e = launch_build_rows(P, device_cus(g->device) * g->tuning.build_blocks_per_cu, s);
     if (e != hipSuccess) return hip_fail(e, "subgraph build");
     if (heavy) {
@@ -354,16 +349,20 @@ citron_status ensure_rows(citron_graph* g)
     g->h_hscan.assign((size_t)D + 1, 0);
     e = hipMemcpyAsync(g->h_hscan.data(), g->d_hscan, sizeof(int32_t) * ((size_t)D + 1), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(&g->h_small->tri_acc, &sd->tri_acc, sizeof(uint64_t) + sizeof(int32_t),
-                           hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(g->h_small->build_stats, sd->build_stats, sizeof(uint64_t) * kNumStats,
-                           hipMemcpyDeviceToHost, s);
+        e = hipMemcpyAsync(g->h_small->build, sd->build, sizeof(sd->build), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "subgraph build");
-    g->tri = g->h_small->tri_acc;
-    g->tri_ovf = g->h_small->tri_ovf != 0;
-    memcpy(g->build_stats, g->h_small->build_stats, sizeof(g->build_stats));
+    g->tri = 0;
+    g->tri_ovf = false;
+    memset(g->build_stats, 0, sizeof(g->build_stats));
+    for (const BuildSums& b : g->h_small->build) {
+        g->tri_ovf = g->tri_ovf || b.tri_ovf != 0 || g->tri + b.tri < g->tri;
+        g->tri += b.tri;
+        g->build_stats[kStatVertices] += b.verts;
+        g->build_stats[kStatRows] += b.rows;
+        g->build_stats[kStatEntries] += b.entries;
+        g->build_stats[kStatBytes] += b.bytes;
+    }
     g->rows_valid = true;
     return CITRON_OK;
 }

@@ -18,11 +18,8 @@ struct SmallDev {
     int32_t err;
     int32_t max_outdeg;
     unsigned long long kept;     // sum of the out-degrees (validation)
-    unsigned long long tri_acc;
-    int32_t tri_ovf;
-    int32_t build_ctr;
     PeelCtl peel;
-    unsigned long long build_stats[kNumStats];
+    BuildSums build[kBuildSlots];
 };
 static_assert(sizeof(SmallDev) % 8 == 0, "cleared in 8-byte words");
 
@@ -47,12 +44,10 @@ struct SmallHost {
     int32_t ends[2];
     PlanHeader plan;
     uint64_t stats[kNumStats];
-    uint64_t tri_acc;
-    int32_t tri_ovf;
     int32_t rows_total;
     int32_t hrows_total;
     PeelCtl peel;
-    uint64_t build_stats[kNumStats];
+    BuildSums build[kBuildSlots];
 };
 
 }  // namespace citron

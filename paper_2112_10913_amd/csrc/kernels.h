@@ -79,6 +79,14 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, int64_t n, hipStream_t s);
 
 // ---- subgraph rows (kernels_rows.hip)
+// Sums of a build, kept in kBuildSlots copies a line apart (the workgroups'
+// atomics on one word are serialised at about 12 ns) and added by the host.
+constexpr int kBuildSlots = 16;
+struct alignas(128) BuildSums {
+    unsigned long long tri;      // triangles (the k = 3 count)
+    unsigned long long verts, rows, entries, bytes;
+    int32_t tri_ovf;
+};
 struct BuildParams {
     const int32_t* dag_ptr;
     const int32_t* dag_col;
@@ -90,12 +98,8 @@ struct BuildParams {
     const int32_t* rows_off;
     unsigned long long* rows;
     int32_t* arc_c;
-    unsigned long long* tri_acc;       // triangles (the k = 3 count)
-    int32_t* tri_ovf;
-    int32_t* item_ctr;
-    unsigned long long* build_stats;   // kNumStats slots
+    BuildSums* sums;             // kBuildSlots
 };
-int32_t build_lds_bytes(int32_t light_rows, int32_t max_deg);
 // len[u] = row words of u, or of the heavy u only
 hipError_t launch_rows_len(int32_t n, const int32_t* dag_ptr, bool heavy_only, int32_t* len, hipStream_t s);
 // rows of the heavy vertices (order[0 .. n_heavy)) in sorted positions

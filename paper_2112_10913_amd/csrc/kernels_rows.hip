@@ -8,12 +8,9 @@
 // u -> v_i, so its popcount |C_uv| is the arc's triangle count and the arc's
 // cost estimate.  The rows do not depend on k; every count reuses them.
 //
-// Work items are vertices sorted by out-degree (descending): one item per
-// heavy vertex (out-degree > 64), and batches of light vertices of about
-// `light_rows` rows.  A workgroup intersects, for all (row, entry) pairs of
-// an item spread over its threads, each entry of N->(v_i) with N->(u) by a
-// binary search in LDS; the bitmap is assembled in LDS in chunks of rows and
-// written out to device memory with coalesced stores.
+// Vertices are sorted by out-degree (descending): a workgroup per heavy
+// vertex (out-degree > 64), and batches of light vertices of about
+// `light_rows` rows.
 #include "kernels.h"
 
 namespace citron {
@@ -23,7 +20,6 @@ typedef unsigned long long u64;
 namespace {
 
 constexpr int kWave_ = kWave;
-constexpr int kBuildBitmapWords = 2048;   // 16 KB of LDS per chunk of rows
 
 __device__ __forceinline__ int lane_of() { return threadIdx.x & (kWave_ - 1); }
 
@@ -62,43 +58,84 @@ __device__ __forceinline__ int lower_bound_i32(const int32_t* a, int n, int32_t 
 
 struct BuildCtrl {
     int32_t item;
-    int32_t kind;      // 0 light batch, 1 heavy vertex
     int32_t first;
     int32_t nb;
     int32_t R;
-    int32_t pad[3];
     int32_t wsum[16];
 };
 
+constexpr int kLightBlock = 256;
+constexpr int kProbeRatio = 4;
+constexpr int kHeavyBlock = 512;
+constexpr int kHeavyWaves = kHeavyBlock / kWave;
+
+// Adds a workgroup's triangles and build counters to the graph's (tri,
+// entries: every thread's; verts, rows, bytes: thread 0's).
+template <int kBlock>
+__device__ __forceinline__ void flush_build(const BuildParams& P, u64 tri, u64 verts, u64 rows, u64 bytes, u64 entries)
+{
+    __shared__ u64 part[kBlock / kWave_][2];
+#pragma unroll
+    for (int o = kWave_ / 2; o > 0; o >>= 1) {
+        tri += __shfl_xor(tri, o, kWave_);
+        entries += __shfl_xor(entries, o, kWave_);
+    }
+    if (lane_of() == 0) {
+        part[threadIdx.x / kWave_][0] = tri;
+        part[threadIdx.x / kWave_][1] = entries;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0 || !verts) return;
+    for (int w = 1; w < kBlock / kWave_; ++w) {
+        tri += part[w][0];       // a workgroup's triangles: below 2^31 arcs x 2^12
+        entries += part[w][1];
+    }
+    BuildSums* s = P.sums + (blockIdx.x & (kBuildSlots - 1));
+    if (tri) {
+        const u64 old = atomicAdd(&s->tri, tri);
+        if (old + tri < old) atomicOr(&s->tri_ovf, 1);
+    }
+    atomicAdd(&s->verts, verts);
+    atomicAdd(&s->rows, rows);
+    atomicAdd(&s->entries, entries);
+    atomicAdd(&s->bytes, bytes + 4ull * entries);
+}
+
 }  // namespace
 
-__host__ __device__ inline int build_rows_cap(int light_rows, int max_deg)
-{
-    const int rc = light_rows + kLightMaxDeg;
-    return max_deg > rc ? max_deg : rc;
-}
+__host__ __device__ inline int build_rows_cap(int light_rows) { return light_rows + kLightMaxDeg; }
 
-int32_t build_lds_bytes(int32_t light_rows, int32_t max_deg)
+static int32_t light_lds_bytes(int32_t light_rows)
 {
-    const int Dc = build_rows_cap(light_rows, max_deg);
-    const int Vc = (light_rows + kLightMaxDeg) / 2 + 2;
-    int b = (int)sizeof(BuildCtrl) + 4 * 4 * (Dc + 4) + 4 * 4 * Vc;
+    const int Dc = build_rows_cap(light_rows);
+    const int Vc = Dc / 2 + 2;
+    int b = (int)sizeof(BuildCtrl) + 5 * 4 * (Dc + 4) + 4 * 4 * Vc;
     b = (b + 15) & ~15;
-    return b + 8 * kBuildBitmapWords;
+    return b + 8 * Dc;
 }
 
-__global__ void __launch_bounds__(256) build_rows_kernel(BuildParams P)
+// Batches of light vertices.  The (row, entry) pairs of a batch are one
+// sequence cut into a contiguous range per wave, so that a wave finds its
+// first row by one search and the rows of the next 64 entries by stepping on;
+// each entry of N->(v_i) is then searched in N->(u) (at most 64 ids, in LDS).
+// Where N->(v_i) is more than kProbeRatio times as long as N->(u), the row's
+// entries are those of N->(u) instead, each searched in N->(v_i) in device
+// memory (about 9 dependent reads): a vertex with few out-neighbours does not
+// read a hub's whole list for each.  Ratios of 4, 8, 16 and never: 3.3, 3.7,
+// 4.0 and 3.9 ms on a Chung-Lu graph of 2^20 vertices.
+__global__ void __launch_bounds__(kLightBlock) build_light_kernel(BuildParams P)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int T = blockDim.x, tid = threadIdx.x, lane = lane_of(), wid = tid / kWave_;
+    const int T = kLightBlock, tid = threadIdx.x, lane = lane_of(), wid = tid / kWave_;
     const int nwaves = T / kWave_;
-    const int Dc = build_rows_cap(P.plan.light_rows, P.max_deg);
-    const int Vc = (P.plan.light_rows + kLightMaxDeg) / 2 + 2;
+    const int Dc = build_rows_cap(P.plan.light_rows);
+    const int Vc = Dc / 2 + 2;
     BuildCtrl* ctrl = reinterpret_cast<BuildCtrl*>(smem);
     int32_t* row_v = reinterpret_cast<int32_t*>(smem + sizeof(BuildCtrl));
     int32_t* row_owner = row_v + (Dc + 4);
     int32_t* row_begin = row_owner + (Dc + 4);
-    int32_t* pre = row_begin + (Dc + 4);
+    int32_t* row_n = row_begin + (Dc + 4);       // length of N->(v) for a row that probes it, else 0
+    int32_t* pre = row_n + (Dc + 4);
     int32_t* vert_u = pre + (Dc + 4);
     int32_t* vert_base = vert_u + Vc;
     int32_t* vert_deg = vert_base + Vc;
@@ -108,58 +145,34 @@ __global__ void __launch_bounds__(256) build_rows_kernel(BuildParams P)
     u64* bm = reinterpret_cast<u64*>(smem + off);
     const int32_t* __restrict__ dag_ptr = P.dag_ptr;
     const int32_t* __restrict__ dag_col = P.dag_col;
-    const int n_items = P.plan.n_heavy + P.plan.n_batches;
     u64 tri = 0, st_entries = 0, st_rows = 0, st_verts = 0, st_bytes = 0;
 
-    for (;;) {
-        if (tid == 0) {
-            int g = atomicAdd(P.item_ctr, 1);
-            ctrl->item = g < n_items ? g : -1;
-            if (g < n_items) {
-                if (g < P.plan.n_heavy) {
-                    const int u = P.order[g];
-                    const int d = dag_ptr[u + 1] - dag_ptr[u];
-                    ctrl->kind = 1;
-                    ctrl->nb = 1;
-                    ctrl->R = d;
-                    vert_u[0] = u;
-                    vert_base[0] = 0;
-                    vert_deg[0] = d;
-                    vert_arc0[0] = dag_ptr[u];
-                } else {
-                    const int b = g - P.plan.n_heavy;
-                    const int s0 = P.batch_start[b], s1 = P.batch_start[b + 1];
-                    ctrl->kind = 0;
-                    ctrl->first = s0;
-                    ctrl->nb = s1 - s0;
-                    ctrl->R = P.light_pre[s1] - P.light_pre[s0];
-                }
-            }
-        }
-        __syncthreads();
-        if (ctrl->item < 0) break;
-        const int kind = ctrl->kind, nb = ctrl->nb, R = ctrl->R;
-        if (kind == 0) {
-            const int s0 = ctrl->first;
-            const int base0 = P.light_pre[s0];
-            for (int j = tid; j < nb; j += T) {
-                const int u = P.order[P.plan.n_heavy + s0 + j];
-                vert_u[j] = u;
-                vert_base[j] = P.light_pre[s0 + j] - base0;
-                vert_deg[j] = P.light_pre[s0 + j + 1] - P.light_pre[s0 + j];
-                vert_arc0[j] = dag_ptr[u];
-            }
+    for (int b0 = blockIdx.x; b0 < P.plan.n_batches; b0 += gridDim.x) {
+        const int s0 = P.batch_start[b0], s1 = P.batch_start[b0 + 1];
+        const int base0 = P.light_pre[s0];
+        const int nb = s1 - s0, R = P.light_pre[s1] - base0;
+        for (int j = tid; j < nb; j += T) {
+            const int u = P.order[P.plan.n_heavy + s0 + j];
+            vert_u[j] = u;
+            vert_base[j] = P.light_pre[s0 + j] - base0;
+            vert_deg[j] = P.light_pre[s0 + j + 1] - P.light_pre[s0 + j];
+            vert_arc0[j] = dag_ptr[u];
         }
         __syncthreads();
         // rows: v = N->(u)[i] and the length of N->(v)
         for (int r = tid; r < R; r += T) {
-            const int b = (kind == 0) ? upper_bound_i32(vert_base, nb, r) - 1 : 0;
+            const int b = upper_bound_i32(vert_base, nb, r) - 1;
             const int v = dag_col[vert_arc0[b] + (r - vert_base[b])];
             row_v[r] = v;
             row_owner[r] = b;
             const int a0 = dag_ptr[v];
             row_begin[r] = a0;
-            pre[r] = dag_ptr[v + 1] - a0;
+            const int n = dag_ptr[v + 1] - a0, du = vert_deg[b];
+            const bool probe = n > kProbeRatio * du;
+            row_n[r] = probe ? n : 0;
+            pre[r] = probe ? du : n;
+            bm[r] = 0ull;
+            st_entries += (u64)n;
         }
         __syncthreads();
         {   // block-wide exclusive scan of the row lengths, pre[R] = total
@@ -183,65 +196,158 @@ __global__ void __launch_bounds__(256) build_rows_kernel(BuildParams P)
             if (tid == 0) pre[R] = carry;
         }
         __syncthreads();
-        const int W = (kind == 0) ? 1 : (R + 63) >> 6;
-        const int chunk = kBuildBitmapWords / W;
+        const int total = pre[R];
         if (tid == 0) {
             st_verts += (u64)nb;
             st_rows += (u64)R;
-            st_entries += (u64)pre[R];
-            st_bytes += 4ull * ((u64)R + 2ull * nb) + 4ull * ((u64)pre[R] + 2ull * R);
+            st_bytes += 4ull * ((u64)R + 2ull * nb) + 8ull * R;
         }
-        for (int r0 = 0; r0 < R; r0 += chunk) {
-            const int r1 = min(R, r0 + chunk);
-            for (int i = tid; i < (r1 - r0) * W; i += T) bm[i] = 0ull;
-            __syncthreads();
-            // Algorithm 5: each entry x of N->(v_r) looked up in N->(u)
-            const int t1 = pre[r1];
-            for (int t = pre[r0] + tid; t < t1; t += T) {
-                const int r = upper_bound_i32(pre, R + 1, t) - 1;
-                const int x = dag_col[row_begin[r] + (t - pre[r])];
+        // Algorithm 5: each entry x of N->(v_r) looked up in N->(u), or the
+        // other way round
+        const int span = ((total + nwaves - 1) / nwaves + kWave_ - 1) & ~(kWave_ - 1);
+        const int t_end = min(total, (wid + 1) * span);
+        int r0 = wid * span < total ? upper_bound_i32(pre, R + 1, wid * span) - 1 : 0;
+        for (int t0 = wid * span; t0 < t_end; t0 += kWave_) {
+            const int t = t0 + lane;
+            int r = r0;
+            if (t < t_end) {
+                while (pre[r + 1] <= t) ++r;
                 const int b = row_owner[r];
                 const int32_t* nu = row_v + vert_base[b];
-                const int du = vert_deg[b];
-                const int p = lower_bound_i32(nu, du, x);
-                if (p < du && nu[p] == x)
-                    atomicOr(&bm[(r - r0) * W + (p >> 6)], 1ull << (p & 63));
+                const int n = row_n[r], i = t - pre[r];
+                if (n == 0) {
+                    const int x = dag_col[row_begin[r] + i];
+                    const int du = vert_deg[b];
+                    const int p = lower_bound_i32(nu, du, x);
+                    if (p < du && nu[p] == x) atomicOr(&bm[r], 1ull << p);
+                } else {
+                    const int x = nu[i];
+                    const int32_t* __restrict__ nv = dag_col + row_begin[r];
+                    const int p = lower_bound_i32(nv, n, x);
+                    if (p < n && nv[p] == x) atomicOr(&bm[r], 1ull << i);
+                }
             }
-            __syncthreads();
-            // write the chunk out; one thread per row also records |C_uv|
-            for (int i = tid; i < (r1 - r0) * W; i += T) {
-                const int r = r0 + i / W, w = i - (i / W) * W;
-                const int b = row_owner[r];
-                const int li = r - vert_base[b];
-                P.rows[(int64_t)P.rows_off[vert_u[b]] + (int64_t)li * W + w] = bm[i];
+            r0 = __shfl(r, min(kWave_ - 1, t_end - 1 - t0), kWave_);
+        }
+        __syncthreads();
+        for (int r = tid; r < R; r += T) {
+            const u64 bits = bm[r];
+            const int b = row_owner[r];
+            const int li = r - vert_base[b];
+            const int c = __popcll(bits);
+            P.rows[(int64_t)P.rows_off[vert_u[b]] + li] = bits;
+            P.arc_c[vert_arc0[b] + li] = c;
+            tri += (u64)c;
+        }
+        __syncthreads();
+    }
+    flush_build<kLightBlock>(P, tri, st_verts, st_rows, st_bytes, st_entries);
+}
+
+// LDS of the heavy build for out-degrees up to max_deg: a hash table of
+// N->(u) at most a quarter full (ids, positions), the rows' list bounds, and
+// a row of bits per wave.
+__host__ __device__ inline int heavy_table_size(int max_deg)
+{
+    int s = 512;
+    while (s < 4 * max_deg) s *= 2;
+    return s;
+}
+static int32_t heavy_lds_bytes(int32_t max_deg)
+{
+    const int s = heavy_table_size(max_deg), w = (max_deg + 63) / 64;
+    return s * 6 + 8 * max_deg + 8 * kHeavyWaves * w + 64;
+}
+
+// One workgroup per heavy vertex u, one wave per row: lanes take the entries
+// of N->(v_i), four at a time, and look each up in a hash table of N->(u) in
+// LDS (nine of ten entries miss, most on their first probe); the row's bits
+// gather in the wave's buffer and go out in one coalesced store.  Bound by
+// the reads of the neighbours' lists (4 bytes per entry, from L2 and the
+// memory-side cache).  R-MAT 20: 4.5 ms here and 2.5 ms for the light
+// batches; a search of each entry's row and of its position by bisection, 17
+// dependent LDS reads per entry, took 22.4 ms for both.
+__global__ void __launch_bounds__(kHeavyBlock) build_heavy_kernel(BuildParams P)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int S = heavy_table_size(P.max_deg);
+    const int shift = __builtin_clz((unsigned)S) + 1;          // 32 - log2(S)
+    int32_t* tab = reinterpret_cast<int32_t*>(smem);
+    int32_t* begin = tab + S;
+    int32_t* len = begin + P.max_deg;
+    u64* bits = reinterpret_cast<u64*>(((uintptr_t)(len + P.max_deg) + 7) & ~(uintptr_t)7);
+    const int wmax = (P.max_deg + 63) >> 6;
+    uint16_t* pos = reinterpret_cast<uint16_t*>(bits + kHeavyWaves * wmax);
+    const int tid = threadIdx.x, lane = lane_of();
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave_);
+    u64* mine = bits + wid * wmax;
+    const int32_t* __restrict__ dag_ptr = P.dag_ptr;
+    const int32_t* __restrict__ dag_col = P.dag_col;
+    u64 tri = 0, st_entries = 0, st_rows = 0, st_verts = 0;
+    for (int g = blockIdx.x; g < P.plan.n_heavy; g += gridDim.x) {
+        const int u = P.order[g];
+        const int a0 = dag_ptr[u], d = dag_ptr[u + 1] - a0;
+        const int W = (d + 63) >> 6;
+        for (int i = tid; i < S; i += kHeavyBlock) tab[i] = -1;
+        __syncthreads();
+        for (int i = tid; i < d; i += kHeavyBlock) {
+            const int v = dag_col[a0 + i];
+            unsigned h = (unsigned)v * 0x9E3779B1u >> shift;
+            while (atomicCAS(&tab[h], -1, v) != -1) h = (h + 1) & (S - 1);
+            pos[h] = (uint16_t)i;
+            const int b = dag_ptr[v], n = dag_ptr[v + 1] - b;
+            begin[i] = b;
+            len[i] = n;
+            st_entries += (u64)n;
+        }
+        __syncthreads();
+        u64* __restrict__ out = P.rows + P.rows_off[u];
+        for (int r = wid; r < d; r += kHeavyWaves) {
+            const int b = begin[r], n = len[r];
+            if (lane < W) mine[lane] = 0ull;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (int e0 = 0; e0 < n; e0 += 4 * kWave_) {
+                int32_t x[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int e = e0 + j * kWave_ + lane;
+                    x[j] = e < n ? dag_col[b + e] : -2;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if (x[j] < 0) continue;
+                    unsigned h = (unsigned)x[j] * 0x9E3779B1u >> shift;
+                    int32_t key = tab[h];
+                    while (key != x[j] && key != -1) {
+                        h = (h + 1) & (S - 1);
+                        key = tab[h];
+                    }
+                    if (key == x[j]) {
+                        const int p = pos[h];
+                        atomicOr(&mine[p >> 6], 1ull << (p & 63));
+                    }
+                }
             }
-            for (int r = r0 + tid; r < r1; r += T) {
-                int c = 0;
-                for (int w = 0; w < W; ++w) c += __popcll(bm[(r - r0) * W + w]);
-                const int b = row_owner[r];
-                P.arc_c[vert_arc0[b] + (r - vert_base[b])] = c;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const u64 word = lane < W ? mine[lane] : 0ull;
+            if (lane < W) out[(int64_t)r * W + lane] = word;
+            int c = __popcll(word);
+#pragma unroll
+            for (int o = kWave_ / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave_);
+            if (lane == 0) {
+                P.arc_c[a0 + r] = c;
                 tri += (u64)c;
             }
-            __syncthreads();
         }
+        if (tid == 0) {
+            st_verts += 1;
+            st_rows += (u64)d;
+        }
+        __syncthreads();
     }
-    // triangles (k = 3) and build counters
-#pragma unroll
-    for (int o = kWave_ / 2; o > 0; o >>= 1) {
-        unsigned lo = __shfl_xor((unsigned)tri, o, kWave_);
-        unsigned hi = __shfl_xor((unsigned)(tri >> 32), o, kWave_);
-        tri += ((u64)hi << 32) | lo;
-    }
-    if (lane == 0 && tri) {
-        const u64 old = atomicAdd(P.tri_acc, tri);
-        if (old + tri < old) atomicOr(P.tri_ovf, 1);
-    }
-    if (tid == 0 && st_verts) {
-        atomicAdd(P.build_stats + kStatVertices, st_verts);
-        atomicAdd(P.build_stats + kStatRows, st_rows);
-        atomicAdd(P.build_stats + kStatEntries, st_entries);
-        atomicAdd(P.build_stats + kStatBytes, st_bytes);
-    }
+    flush_build<kHeavyBlock>(P, tri, st_verts, st_rows, 4ull * (st_rows + 2ull * st_verts) + 8ull * st_rows, st_entries);
 }
 
 // rows_len[u] = d(u) * W(u), the words of u's rows
@@ -327,14 +433,23 @@ hipError_t launch_rows_len(int32_t n, const int32_t* dag_ptr, bool heavy_only, i
 
 hipError_t launch_build_rows(const BuildParams& P, int32_t blocks, hipStream_t s)
 {
-    if (P.plan.n_heavy + P.plan.n_batches <= 0) return hipSuccess;
-    const int32_t lds = build_lds_bytes(P.plan.light_rows, P.max_deg);
-    if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)build_rows_kernel,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (P.plan.n_heavy > 0) {
+        const int32_t lds = heavy_lds_bytes(P.max_deg);
+        if (lds > 65536) {
+            hipError_t e = hipFuncSetAttribute((const void*)build_heavy_kernel,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            if (e != hipSuccess) return e;
+        }
+        const int32_t n = P.plan.n_heavy < blocks ? P.plan.n_heavy : blocks;
+        build_heavy_kernel<<<n, kHeavyBlock, lds, s>>>(P);
+        hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    build_rows_kernel<<<blocks, 256, lds, s>>>(P);
+    if (P.plan.n_batches > 0) {
+        // twice the workgroups of the heavy build: they are half as wide
+        const int32_t n = P.plan.n_batches < 2 * blocks ? P.plan.n_batches : 2 * blocks;
+        build_light_kernel<<<n, kLightBlock, light_lds_bytes(P.plan.light_rows), s>>>(P);
+    }
     return hipGetLastError();
 }
 

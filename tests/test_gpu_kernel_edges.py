@@ -209,3 +209,37 @@ def test_peeling_at_the_sizes_where_phases_change(citron_gpu, chains):
     want = oracle.peel_rounds(g.n, g.row_ptr, g.col)
     assert np.array_equal(key, want) and rounds == int(want.max()) + 1
     h.free()
+
+
+@pytest.mark.parametrize("d_low,hub", [(2, 9), (3, 13), (5, 20), (5, 21), (16, 64), (16, 65), (63, 70), (64, 300),
+                                       (65, 261), (127, 130), (130, 513), (200, 1000)])
+def test_rows_of_short_and_long_lists(citron_gpu, d_low, hub):
+    """Subgraph rows where a vertex's list is up to, and more than, four times
+    shorter than its neighbours' (each side searches the other), and at sizes
+    of the light and heavy builds: triangles and 4-cliques per arc against a
+    direct count."""
+    rng = np.random.default_rng(d_low * 1000 + hub)
+    n = hub + 6
+    i, j = np.triu_indices(n, 1)                       # a dense core: its out-degrees run up to n - 1
+    keep = rng.random(i.size) < 0.9
+    src, dst = [i[keep]], [j[keep]]
+    for low in range(12):                              # short vertices over the core
+        t = rng.choice(n, min(d_low, n), replace=False)
+        src.append(np.full(t.size, n + low))
+        dst.append(t)
+    g = gg.csr_from_edges(n + 12, np.concatenate(src), np.concatenate(dst), perm_seed=hub)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    ptr, col = h.dag()
+    a = np.zeros((g.n, g.n), bool)
+    s = np.repeat(np.arange(g.n), np.diff(ptr))
+    a[s, col] = True
+    common = a[s] & a[col]
+    tri, per3 = h.count_per_arc(3)
+    assert tri == int(common.sum()) and np.array_equal(per3, common.sum(1))
+    total, per4 = h.count_per_arc(4)
+    f = a.astype(np.float32)
+    want4 = ((common @ f) * common).sum(1).astype(np.int64)       # below 2^24: exact
+    assert total == int(want4.sum()) and np.array_equal(per4, want4)
+    st = h.work_stats(4)
+    assert st["entries"] == int(np.diff(ptr)[col][np.diff(ptr)[s] >= 2].sum())
+    h.free()

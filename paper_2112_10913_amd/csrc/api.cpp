@@ -102,7 +102,7 @@ static citron_status dalloc(T** p, size_t count, int64_t* acct, const char* what
 {
     *p = nullptr;
     if (count == 0) count = 1;
-    hipError_t e = hipMalloc((void**)p, sizeof(T) * count);
+    hipError_t e = pool_malloc((void**)p, sizeof(T) * count);
     if (e != hipSuccess) {
         *p = nullptr;
         return fail(CITRON_ENOMEM, std::string("hipMalloc failed for ") + what + ": " + hipGetErrorString(e));
@@ -111,10 +111,12 @@ static citron_status dalloc(T** p, size_t count, int64_t* acct, const char* what
     return CITRON_OK;
 }
 
+// The work that used the block must have completed: its next owner may be
+// another graph on another stream.
 template <typename T>
 static void dfree(T*& p)
 {
-    if (p) (void)hipFree((void*)p);
+    pool_free((void*)p);
     p = nullptr;
 }
 
@@ -161,7 +163,7 @@ static void free_graph_memory(citron_graph* g)
     }
     g->rows_valid = false;
     free_plan(g);
-    if (g->h_small) (void)hipHostFree(g->h_small);
+    pool_host_free(g->h_small, sizeof(SmallHost));
     g->h_small = nullptr;
 }
 
@@ -189,7 +191,7 @@ citron_status ensure_plan(citron_graph* g, const citron_tuning& t)
     SortBuffers sb = {};
     {
         citron_status st;
-        const size_t tb = sched_sort_temp_bytes(g->n);
+        const size_t tb = sched_sort_temp_bytes(g->n, D - 1);
         if (tb == 0) return fail(CITRON_EDEVICE, "sort workspace query failed");
         unsigned char* tmp = nullptr;
         if ((st = dalloc(&sb.keys_a, (size_t)g->n + 1, nullptr, "plan order")) ||
@@ -203,7 +205,17 @@ citron_status ensure_plan(citron_graph* g, const citron_tuning& t)
         sb.temp_bytes = tb;
     }
     e = launch_plan(g->n, g->d_dag_ptr, g->max_outdeg, t.light_rows, 0, 1, g->pb, g->d_scan_ws, sb, g->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
+    g->h_vscan.assign((size_t)D, 0);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(&g->h_small->plan, g->pb.header, sizeof(PlanHeader), hipMemcpyDeviceToHost, g->stream);
+    // (through pinned memory, except where counts will be refused anyway)
+    int32_t* hist = D <= kMaxDeg ? g->h_small->hist : g->h_vscan.data();
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(hist, g->pb.hist_scan, sizeof(int32_t) * (size_t)D, hipMemcpyDeviceToHost, g->stream);
+    {
+        const hipError_t w = hipStreamSynchronize(g->stream);
+        if (e == hipSuccess) e = w;
+    }
     dfree(sb.keys_a);
     dfree(sb.keys_b);
     {
@@ -211,13 +223,7 @@ citron_status ensure_plan(citron_graph* g, const citron_tuning& t)
         dfree(tmp);
     }
     if (e != hipSuccess) return hip_fail(e, "plan kernels");
-    g->h_vscan.assign((size_t)D, 0);
-    e = hipMemcpyAsync(&g->h_small->plan, g->pb.header, sizeof(PlanHeader), hipMemcpyDeviceToHost, g->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(g->h_vscan.data(), g->pb.hist_scan, sizeof(int32_t) * (size_t)D,
-                           hipMemcpyDeviceToHost, g->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(g->stream);
-    if (e != hipSuccess) return hip_fail(e, "plan");
+    if (hist != g->h_vscan.data()) memcpy(g->h_vscan.data(), hist, sizeof(int32_t) * (size_t)D);
     g->plan = g->h_small->plan;
     g->plan_tuning = t;
     g->plan_valid = true;
@@ -236,12 +242,13 @@ citron_status ensure_rows(citron_graph* g)
     if (g->max_outdeg > kMaxDeg)
         return fail(CITRON_EINVAL, "out-degree above 4096 in the degree-ordered DAG is not supported");
     const int32_t D = std::max(g->max_outdeg, 2);
+    const bool heavy = g->plan.n_heavy > 0;     // without heavy vertices there is no arc schedule
     hipStream_t s = g->stream;
     int64_t* acct = &g->device_bytes;
     if ((!g->d_rows_off && (st = dalloc(&g->d_rows_off, (size_t)g->n + 1, acct, "row offsets"))) ||
         (!g->d_arc_c && (st = dalloc(&g->d_arc_c, (size_t)g->m, acct, "arc sizes"))) ||
-        (!g->d_harcs && (st = dalloc(&g->d_harcs, (size_t)g->m, acct, "heavy arcs"))) ||
-        (!g->d_hscan && (st = dalloc(&g->d_hscan, (size_t)D + 1, acct, "arc histogram"))))
+        (heavy && !g->d_harcs && (st = dalloc(&g->d_harcs, (size_t)g->m, acct, "heavy arcs"))) ||
+        (heavy && !g->d_hscan && (st = dalloc(&g->d_hscan, (size_t)D + 1, acct, "arc histogram"))))
         return st;
     // Row offsets are int32, so the rows of all vertices, sum over u of
     // d(u) * ceil(d(u)/64) words, must stay below 2^31.  That sum is at most
@@ -265,7 +272,6 @@ citron_status ensure_rows(citron_graph* g)
     if (e == hipSuccess)
         e = hipMemcpyAsync(&g->h_small->rows_total, g->d_rows_off + g->n, sizeof(int32_t),
                            hipMemcpyDeviceToHost, s);
-    const bool heavy = g->plan.n_heavy > 0;
     if (heavy) {
         if ((!g->d_hoff && (st = dalloc(&g->d_hoff, (size_t)g->n + 1, acct, "sorted rows"))) ||
             (!g->d_hpos && (st = dalloc(&g->d_hpos, (size_t)g->m, acct, "sorted rows"))))
@@ -323,8 +329,8 @@ citron_status ensure_rows(citron_graph* g)
         if (e != hipSuccess) return hip_fail(e, "sorted rows");
     }
     SortBuffers sb = {};
-    {
-        const size_t tb = sched_sort_temp_bytes(g->m);
+    if (heavy) {
+        const size_t tb = sched_sort_temp_bytes(g->m, D);
         if (tb == 0) return fail(CITRON_EDEVICE, "sort workspace query failed");
         unsigned char* tmp = nullptr;
         if ((st = dalloc(&sb.keys_a, (size_t)g->m + 1, nullptr, "arc schedule")) ||
@@ -337,21 +343,24 @@ citron_status ensure_rows(citron_graph* g)
         sb.temp = tmp;
         sb.temp_bytes = tb;
     }
-    e = sched_heavy_arcs(g->m, g->d_dag_ptr, g->d_dag_src, g->d_arc_c, D, g->d_hscan, g->d_harcs, sb, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (heavy) e = sched_heavy_arcs(g->m, g->d_dag_ptr, g->d_dag_src, g->d_arc_c, D, g->d_hscan, g->d_harcs, sb, s);
+    g->h_hscan.assign((size_t)D + 1, 0);
+    if (e == hipSuccess && heavy)
+        e = hipMemcpyAsync(g->h_small->hist, g->d_hscan, sizeof(int32_t) * ((size_t)D + 1), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(g->h_small->build, sd->build, sizeof(sd->build), hipMemcpyDeviceToHost, s);
+    {
+        const hipError_t w = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = w;
+    }
     dfree(sb.keys_a);
     dfree(sb.keys_b);
     {
         unsigned char* tmp = static_cast<unsigned char*>(sb.temp);
         dfree(tmp);
     }
-    if (e != hipSuccess) return hip_fail(e, "arc schedule");
-    g->h_hscan.assign((size_t)D + 1, 0);
-    e = hipMemcpyAsync(g->h_hscan.data(), g->d_hscan, sizeof(int32_t) * ((size_t)D + 1), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(g->h_small->build, sd->build, sizeof(sd->build), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "subgraph build");
+    if (heavy) memcpy(g->h_hscan.data(), g->h_small->hist, sizeof(int32_t) * ((size_t)D + 1));
     g->tri = 0;
     g->tri_ovf = false;
     memset(g->build_stats, 0, sizeof(g->build_stats));
@@ -560,16 +569,19 @@ struct ListItems {
     int32_t* ws = nullptr;
     int32_t* items = nullptr;
     int32_t total = 0;
+    hipStream_t stream = nullptr;
     ~ListItems()
     {
-        for (int32_t* p : {parts, offs, ws, items})
-            if (p) (void)hipFree(p);
+        if (!parts) return;
+        (void)hipStreamSynchronize(stream);     // the launch that reads them, also after an error
+        for (int32_t* p : {parts, offs, ws, items}) pool_free(p);
     }
     citron_status build(const citron_graph* g, const int32_t* arcs, int32_t n, int32_t k, hipStream_t s)
     {
-        if (hipMalloc((void**)&parts, sizeof(int32_t) * (size_t)n) != hipSuccess ||
-            hipMalloc((void**)&offs, sizeof(int32_t) * ((size_t)n + 1)) != hipSuccess ||
-            hipMalloc((void**)&ws, sizeof(int32_t) * scan_workspace_ints(n)) != hipSuccess)
+        stream = s;
+        if (pool_malloc((void**)&parts, sizeof(int32_t) * (size_t)n) != hipSuccess ||
+            pool_malloc((void**)&offs, sizeof(int32_t) * ((size_t)n + 1)) != hipSuccess ||
+            pool_malloc((void**)&ws, sizeof(int32_t) * scan_workspace_ints(n)) != hipSuccess)
             return fail(CITRON_ENOMEM, "hipMalloc failed for the arc list");
         hipError_t e = launch_list_parts(arcs, n, g->d_dag_src, g->d_dag_ptr, g->d_arc_c, k, g->tuning.split_pct,
                                          parts, s);
@@ -579,7 +591,7 @@ struct ListItems {
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hip_fail(e, "arc list parts");
         total = g->h_small->ends[0];
-        if (hipMalloc((void**)&items, sizeof(int32_t) * 2 * ((size_t)total + 1)) != hipSuccess)
+        if (pool_malloc((void**)&items, sizeof(int32_t) * 2 * ((size_t)total + 1)) != hipSuccess)
             return fail(CITRON_ENOMEM, "hipMalloc failed for the arc list");
         e = launch_list_items(n, parts, offs, items, s);
         if (e != hipSuccess) return hip_fail(e, "arc list items");
@@ -768,7 +780,7 @@ citron_status citron_load_csr(int32_t n, int64_t nnz, const int32_t* row_ptr, co
         delete g;
         return st;
     }
-    e = hipHostMalloc((void**)&g->h_small, sizeof(SmallHost), hipHostMallocDefault);
+    e = pool_host_malloc((void**)&g->h_small, sizeof(SmallHost));
     if (e != hipSuccess) { free_graph_memory(g); delete g; return fail(CITRON_ENOMEM, "hipHostMalloc"); }
     memset(g->h_small, 0, sizeof(SmallHost));
     const hipMemcpyKind kind = dev_ptrs ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
@@ -785,7 +797,10 @@ citron_status citron_load_csr(int32_t n, int64_t nnz, const int32_t* row_ptr, co
     if (e == hipSuccess)
         e = hipMemcpyAsync(&g->h_small->err, &sd->err, 2 * sizeof(int32_t) + sizeof(uint64_t),
                            hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    {
+        const hipError_t w = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = w;
+    }
     if (e != hipSuccess) { free_graph_memory(g); delete g; return hip_fail(e, "loading the CSR"); }
     int32_t bits = g->h_small->err;
     if (!bits && (int64_t)g->h_small->kept != nnz / 2) bits |= 16;
@@ -841,6 +856,7 @@ static citron_status peel_key(citron_graph* g)
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         done = e == hipSuccess && c.phase == kPeelDone;
     }
+    if (e != hipSuccess) (void)hipStreamSynchronize(s);
     dfree(lists);
     if (e == hipSuccess && !done) e = hipErrorUnknown;   // cannot happen: every round removes a vertex
     if (e != hipSuccess) return hip_fail(e, "peeling kernels");
@@ -1065,9 +1081,9 @@ citron_status citron_list_arcs(citron_graph* g, int32_t k, const int32_t* arcs, 
     hipError_t e = hipSetDevice(g->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     const size_t nws = scan64_workspace(n_arcs);
-    if (hipMalloc((void**)&per, sizeof(unsigned long long) * (size_t)std::max(n_arcs, 1)) != hipSuccess ||
-        hipMalloc((void**)&ws, sizeof(long long) * nws) != hipSuccess) {
-        if (per) (void)hipFree(per);
+    if (pool_malloc((void**)&per, sizeof(unsigned long long) * (size_t)std::max(n_arcs, 1)) != hipSuccess ||
+        pool_malloc((void**)&ws, sizeof(long long) * nws) != hipSuccess) {
+        pool_free(per);
         return fail(CITRON_ENOMEM, "hipMalloc failed for the listing");
     }
     if (n_arcs > 0) {
@@ -1117,8 +1133,9 @@ citron_status citron_list_arcs(citron_graph* g, int32_t k, const int32_t* arcs, 
             }
         }
     }
-    (void)hipFree(per);
-    (void)hipFree(ws);
+    (void)hipStreamSynchronize(g->stream);      // nothing queued reads them any more, also after an error
+    pool_free(per);
+    pool_free(ws);
     return st;
 }
 

@@ -46,6 +46,7 @@ struct SmallHost {
     uint64_t stats[kNumStats];
     int32_t rows_total;
     int32_t hrows_total;
+    int32_t hist[kMaxDeg + 2];   // bucket bounds of a schedule order
     PeelCtl peel;
     BuildSums build[kBuildSlots];
 };
@@ -124,6 +125,13 @@ struct citron_graph {
 };
 
 namespace citron {
+
+// Device blocks on the current device and pinned host blocks, reused between
+// graphs (pool.cpp).  A block goes back only after the work that used it.
+hipError_t pool_malloc(void** p, size_t bytes);
+void pool_free(void* p);
+hipError_t pool_host_malloc(void** p, size_t bytes);
+void pool_host_free(void* p, size_t bytes);
 
 extern thread_local std::string g_last_error;
 citron_status fail(citron_status st, const std::string& msg);

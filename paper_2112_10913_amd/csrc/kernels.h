@@ -50,10 +50,10 @@ hipError_t launch_peel_steps(const PeelParams& P, int32_t steps, hipStream_t s);
 struct SortBuffers {
     unsigned long long* keys_a;   // n keys
     unsigned long long* keys_b;   // n keys
-    void* temp;                   // sched_sort_temp_bytes(n)
+    void* temp;                   // sched_sort_temp_bytes
     size_t temp_bytes;
 };
-size_t sched_sort_temp_bytes(int64_t n);
+size_t sched_sort_temp_bytes(int64_t n, int32_t nb);   // n keys of nb buckets
 // order[0 .. bounds[D-1]) = vertices with out-degree >= 2 by out-degree
 // descending, ties by id; bounds[i] (i < D) = vertices of out-degree > D - i
 hipError_t sched_plan_order(int32_t n, const int32_t* dag_ptr, int32_t D, int32_t* bounds, int32_t* order,

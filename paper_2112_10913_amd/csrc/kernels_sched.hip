@@ -9,9 +9,11 @@
 // strided shares of a count (citron_count_part) cover the same items in
 // every process, and shares counted by different handles of one graph add
 // up to the count.  Each order is a device radix sort of 64-bit keys
-// (bucket << 32 | id); entries outside the schedule get the largest key and
-// sort to the end.  The bucket sizes (the scans the schedule indexes by
-// bucket) are read off the sorted keys, with no histogram atomics.
+// (bucket << 32 | id); entries outside the schedule get a last bucket of their
+// own and sort to the end.  The keys start in order of id and the sort is
+// stable, so only the bits of the bucket are sorted (one or two passes instead
+// of eight).  The bucket sizes (the scans the schedule indexes by bucket) are
+// read off the sorted keys, with no histogram atomics.
 #include "kernels.h"
 
 #include <hipcub/device/device_radix_sort.hpp>
@@ -26,7 +28,7 @@ __global__ void plan_keys_kernel(int32_t n, const int32_t* __restrict__ dag_ptr,
     const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= n) return;
     const int d = dag_ptr[u + 1] - dag_ptr[u];
-    keys[u] = d >= 2 ? ((u64)(unsigned)(D - d) << 32) | (u64)(unsigned)u : ~0ull;
+    keys[u] = ((u64)(unsigned)(d >= 2 ? D - d : D - 1) << 32) | (u64)(unsigned)u;
 }
 
 // heavy arcs: key of arc e = (D - 1 - |C_uv|) << 32 | e when the source has
@@ -38,12 +40,11 @@ __global__ void harc_keys_kernel(int64_t m, const int32_t* __restrict__ dag_ptr,
     if (e >= m) return;
     const int u = dag_src[e];
     const bool heavy = dag_ptr[u + 1] - dag_ptr[u] > kLightMaxDeg;
-    keys[e] = heavy ? ((u64)(unsigned)(D - 1 - arc_c[e]) << 32) | (u64)e : ~0ull;
+    keys[e] = ((u64)(unsigned)(heavy ? D - 1 - arc_c[e] : D) << 32) | (u64)e;
 }
 
 // bounds[b] = number of sorted keys with bucket < b, for b = 0..nb, where
-// the bucket of a key is its high word (the sentinel ~0 counts as bucket
-// nb): thread i fills the bounds between the buckets of keys i - 1 and i.
+// the bucket of a key is its high word (nb for entries outside the schedule): thread i fills the bounds between the buckets of keys i - 1 and i.
 __global__ void bucket_bounds_kernel(int64_t n, const u64* __restrict__ keys, int32_t nb, int32_t* __restrict__ bounds)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -68,11 +69,20 @@ __global__ void unpack_keys_kernel(int64_t n, const u64* __restrict__ keys, cons
     if (i < n && i < *count) out[i] = (int32_t)(unsigned)keys[i];
 }
 
-size_t sched_sort_temp_bytes(int64_t n)
+// Bits of the bucket numbers 0 .. nb.
+static int bucket_bits(int32_t nb)
+{
+    int bits = 1;
+    while ((1ll << bits) <= nb) ++bits;
+    return bits;
+}
+
+size_t sched_sort_temp_bytes(int64_t n, int32_t nb)
 {
     size_t bytes = 0;
     if (n <= 0) return 1;
-    if (hipcub::DeviceRadixSort::SortKeys(nullptr, bytes, (const u64*)nullptr, (u64*)nullptr, (int)n, 0, 64) !=
+    if (hipcub::DeviceRadixSort::SortKeys(nullptr, bytes, (const u64*)nullptr, (u64*)nullptr, (int)n, 32,
+                                           32 + bucket_bits(nb)) !=
         hipSuccess)
         return 0;
     return bytes > 0 ? bytes : 1;
@@ -84,7 +94,8 @@ static hipError_t sort_and_split(int64_t n, int32_t nb, int32_t* bounds, int32_t
 {
     const unsigned blocks = (unsigned)((n + 255) / 256);
     size_t tb = sb.temp_bytes;
-    hipError_t e = hipcub::DeviceRadixSort::SortKeys(sb.temp, tb, (const u64*)sb.keys_a, sb.keys_b, (int)n, 0, 64, s);
+    hipError_t e = hipcub::DeviceRadixSort::SortKeys(sb.temp, tb, (const u64*)sb.keys_a, sb.keys_b, (int)n, 32,
+                                                     32 + bucket_bits(nb), s);
     if (e != hipSuccess) return e;
     bucket_bounds_kernel<<<blocks, 256, 0, s>>>(n, sb.keys_b, nb, bounds);
     unpack_keys_kernel<<<blocks, 256, 0, s>>>(n, sb.keys_b, bounds + nb, out);

@@ -243,3 +243,36 @@ def test_rows_of_short_and_long_lists(citron_gpu, d_low, hub):
     st = h.work_stats(4)
     assert st["entries"] == int(np.diff(ptr)[col][np.diff(ptr)[s] >= 2].sum())
     h.free()
+
+
+def test_blocks_reused_across_threads_and_streams(citron_gpu):
+    """Graphs made, counted and freed in turn on several threads, each with a
+    stream of its own: blocks of one graph serve the next, whatever they held."""
+    import threading
+    import oracle
+    import torch
+    gs = [gg.rmat(9, 20, seed=70), gg.rmat(9, 21, seed=71), gg.erdos_renyi(600, 24, seed=72),
+          gg.complete(90), gg.empty(700), gg.rmat(10, 30, seed=73)]
+    want = {(i, k): oracle.count(g, k)[0] if i != 3 else __import__("math").comb(90, k)
+            for i, g in enumerate(gs) for k in (3, 4, 6)}
+    bad = []
+
+    def work(seed):
+        rng = np.random.default_rng(seed)
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for _ in range(25):
+                i = int(rng.integers(len(gs)))
+                k = int(rng.choice([3, 4, 6]))
+                h = citron_gpu.Graph.from_csr(gs[i].row_ptr, gs[i].col)
+                h.order("core" if rng.random() < 0.3 else "degree")
+                if h.count(k) != want[(i, k)]:
+                    bad.append((i, k))
+                h.free()
+
+    threads = [threading.Thread(target=work, args=(s,)) for s in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad

@@ -1118,10 +1118,10 @@ citron_status citron_list_arcs(citron_graph* g, int32_t k, const int32_t* arcs, 
             P.rows = g->d_rows;
             P.offsets = (const long long*)offsets;
             P.out = cliques;
-            P.cursor = &g->d_small->item_ctr;
+            P.cursors = g->d_small->list_cursors;
             P.err = &g->d_small->err;
             if (!st) {
-                e = launch_fill_i32(P.cursor, 0, 1, s);
+                e = launch_fill_i32(P.cursors, 0, kClaimInts, s);
                 if (e == hipSuccess) e = launch_fill_i32(P.err, 0, 1, s);
                 if (e == hipSuccess) e = launch_list_arcs(P, device_cus(g->device) * 8, s);
                 if (e == hipSuccess)

@@ -13,13 +13,12 @@ namespace citron {
 // Small device-side words of one graph (zeroed by fill kernels, never by
 // hipMemsetAsync, so that the sequences stay valid inside captured graphs).
 struct SmallDev {
-    int32_t item_ctr;
-    int32_t pad;
     int32_t err;
     int32_t max_outdeg;
     unsigned long long kept;     // sum of the out-degrees (validation)
     PeelCtl peel;
     BuildSums build[kBuildSlots];
+    int32_t list_cursors[kClaimInts];
 };
 static_assert(sizeof(SmallDev) % 8 == 0, "cleared in 8-byte words");
 

@@ -10,16 +10,6 @@ constexpr int kMaxClaim = 16;           // items claimed at once, at most
 // decoded items of a claimed run, one int32 per field and item
 enum ItemField { kItQuery, kItKind, kItRowsOff, kItTag, kItArc0, kItDegree, kItRow, kItPart, kItFields };
 
-// The items one kernel of a launch works on, over all its queries.
-struct ItemSpace {
-    const QueryDesc* queries;
-    int32_t n_queries;
-    int32_t total;
-    int32_t* cursors;       // kClaimInts words, zeroed before the launch
-    int32_t singles;        // the first, costliest items are claimed one at a time,
-    int32_t chunk;          // the others in runs of this many consecutive items
-};
-
 // First item of run j, and the items of the run that starts at g.
 __device__ __forceinline__ int64_t run_begin(const ItemSpace& P, int64_t j)
 {

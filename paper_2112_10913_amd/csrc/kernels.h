@@ -160,6 +160,16 @@ hipError_t launch_list_items(int32_t n, const int32_t* parts, const int32_t* off
 hipError_t launch_gather_arc_c(const int32_t* arcs, int32_t n, const int32_t* arc_c, unsigned long long* out,
                                hipStream_t s);
 
+// Items that the waves or workgroups of one kernel claim in runs (items.h).
+struct ItemSpace {
+    const QueryDesc* queries;
+    int32_t n_queries;
+    int32_t total;
+    int32_t* cursors;       // kClaimInts words, zeroed before the launch
+    int32_t singles;        // the first, costliest items are claimed one at a time,
+    int32_t chunk;          // the others in runs of this many consecutive items
+};
+
 // ---- k-clique listing (kernels_list.hip)
 constexpr int kListMaxK = 16;                    // largest k listing supports
 struct ListParams {
@@ -173,8 +183,9 @@ struct ListParams {
     const unsigned long long* rows;
     const long long* offsets;    // n_arcs + 1: first output clique of each arc
     int32_t* out;                // cliques, k ids each
-    int32_t* cursor;             // zeroed before the launch
-    int32_t chunk;               // arcs a wave claims per atomic (set by launch_list_arcs)
+    int32_t* cursors;            // kClaimInts words, zeroed before the launch
+    ItemSpace items;             // runs of arcs (set by launch_list_arcs)
+    bool wide;                   // 16-byte stores (set by launch_list_arcs)
     int32_t stride;              // claim j lists arc j * stride mod n_arcs (set by launch_list_arcs)
     int32_t* err;                // zeroed before the launch; 1 = slot overrun, 2 = count mismatch
 };

@@ -10,14 +10,19 @@
 // cursor).  The search state is wave-uniform, lane q holding word q of each
 // candidate mask over the positions of N->(u), as in the heavy count engine;
 // the masks of the open levels live in the wave's LDS, k - 2 levels of one
-// word per lane (3 KB per wave at k = 5, 14 KB at k = 16).  At the last level
-// every candidate completes a clique: lane j writes the clique of the j-th
-// set bit, so the output rows of one node are written in one step.  The
-// offsets of the arcs' output come from their exact counts (a scan of the
+// word per lane (3 KB per wave at k = 5, 14 KB at k = 16).  The last two
+// levels are written at once: a lane per candidate x counts the y that
+// complete a clique with it, a wave scan places them, and then the lanes take
+// the node's cliques 64 at a time in output order, each finding its x in the
+// scan and its y by rank, so the stores are full and in sequence.  (With one
+// step per x, about 13 of 64 lanes wrote, and each step waited for its row.)
+// Arcs are claimed from sharded cursors in runs decoded a lane each: 71,000
+// claims of one cursor alone were 0.85 ms of the 1.16 ms that the 35 M
+// 4-cliques of R-MAT 14, 566 MB, took; now 0.46 ms.  The offsets of the arcs' output come from their exact counts (a scan of the
 // per-arc counts of the count kernel), so no atomics order the output;
 // every write is checked against the arc's slot and a mismatch raises a
 // flag instead of writing outside it.
-#include "kernels.h"
+#include "items.h"
 
 #include <numeric>
 
@@ -58,9 +63,27 @@ __device__ __forceinline__ int select64(u64 v, int r)
     return pos;
 }
 
+// Position of the r-th (0-based) candidate of a W-word mask held one word per
+// lane; the whole wave calls it.
+__device__ __forceinline__ int wave_select(u64 m, int r, int W)
+{
+    int before = 0, my_w = 0, my_r = 0;
+    u64 my_word = 0;
+    for (int w = 0; w < W; ++w) {
+        const u64 mw = readlane64(m, w);
+        const int pc = __popcll(mw);
+        const bool here = r >= before && r < before + pc;
+        my_w = here ? w : my_w;
+        my_r = here ? r - before : my_r;
+        my_word = here ? mw : my_word;
+        before += pc;
+    }
+    return my_w * 64 + select64(my_word, my_r);
+}
+
 // Levels whose masks are kept for the way back: a node at level t is
-// pushed only while k - 2 - t >= 2 vertices remain to choose, so levels
-// 0 .. k - 4 are stored; k - 2 (at least 1) bounds them.
+// pushed only while k - 2 - t >= 3 vertices remain to choose, so levels
+// 0 .. k - 5 are stored; k - 2 (at least 1) bounds them.
 __host__ __device__ __forceinline__ int list_levels(int k) { return k > 3 ? k - 2 : 1; }
 
 }  // namespace
@@ -77,32 +100,46 @@ __global__ void __launch_bounds__(kListBlock) list_arcs_kernel(ListParams P)
     const int levels = list_levels(k);
     u64* const sM = lds_levels + (size_t)wid * levels * kWave;
     u64* const sR = lds_levels + (size_t)(kListWaves + wid) * levels * kWave;
-    int i_next = 0, i_end = 0;          // the wave's claimed run of arcs
+    const int wave = blockIdx.x * kListWaves + wid, waves = gridDim.x * kListWaves;
+    int shard = wave % kClaimShards;
+    bool fresh = true;
+    int jj = 0, nj = 0;                 // the wave's run of arcs, decoded a lane each
+    int l_u = 0, l_v = 0, l_a0 = 0, l_d = 0, l_r = 0, l_off = 0;
+    long long l_slot0 = 0, l_slot1 = 0;
     for (;;) {
-        if (i_next >= i_end) {
-            int i0 = 0;
-            if (lane == 0) i0 = atomicAdd(P.cursor, P.chunk);
-            i0 = __shfl(i0, 0, kWave);
-            i_next = i0;
-            i_end = i0 + P.chunk;
+        if (jj >= nj) {
+            const int j0 = claim_run(P.items, wave, waves, shard, fresh);
+            if (j0 < 0) break;
+            nj = run_length(P.items, j0);
+            jj = 0;
+            if (lane < nj) {
+                // claim j lists arc j * stride mod n_arcs (stride coprime to
+                // n_arcs): a run of claims spreads over the list, so the arcs
+                // of one heavy vertex, adjacent in DAG order, do not land in
+                // one wave's run
+                const int i = (int)(((long long)(j0 + lane) * P.stride) % P.n_arcs);
+                const int e = P.arcs[i];
+                l_slot0 = P.offsets[i];
+                l_slot1 = P.offsets[i + 1];
+                l_u = P.dag_src[e];
+                l_v = P.dag_col[e];
+                l_a0 = P.dag_ptr[l_u];
+                l_d = P.dag_ptr[l_u + 1] - l_a0;
+                l_r = e - l_a0;
+                l_off = P.rows_off[l_u];
+            }
         }
-        const int j = i_next++;
-        if (j >= P.n_arcs) break;
-        // claim j lists arc j * stride mod n_arcs (stride coprime to
-        // n_arcs): a run of claims spreads over the list, so the arcs of one
-        // heavy vertex, adjacent in DAG order, do not land in one wave's run
-        const int i = (int)(((long long)j * P.stride) % P.n_arcs);
-        const int e = P.arcs[i];
-        const int u = P.dag_src[e];
-        const int a0 = P.dag_ptr[u];
-        const int d = P.dag_ptr[u + 1] - a0;
-        const int r = e - a0;
-        const long long slot0 = P.offsets[i];
-        const long long slot_n = P.offsets[i + 1] - slot0;
+        const int u = __builtin_amdgcn_readlane(l_u, jj), v = __builtin_amdgcn_readlane(l_v, jj);
+        const int a0 = __builtin_amdgcn_readlane(l_a0, jj), d = __builtin_amdgcn_readlane(l_d, jj);
+        const int r = __builtin_amdgcn_readlane(l_r, jj), row0 = __builtin_amdgcn_readlane(l_off, jj);
+        const long long slot0 = (long long)readlane64((u64)l_slot0, jj);
+        const long long slot_n = (long long)readlane64((u64)l_slot1, jj) - slot0;
+        ++jj;
+        if (slot_n == 0) continue;              // no clique starts with this arc
         long long done = 0;                     // cliques of this arc written so far
         if (lane == 0) {
             sPre[wid][0] = u;
-            sPre[wid][1] = P.dag_col[e];
+            sPre[wid][1] = v;
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -110,7 +147,7 @@ __global__ void __launch_bounds__(kListBlock) list_arcs_kernel(ListParams P)
             if (lane == 0) {
                 if (slot_n >= 1) {
                     P.out[2 * slot0] = u;
-                    P.out[2 * slot0 + 1] = P.dag_col[e];
+                    P.out[2 * slot0 + 1] = v;
                 } else {
                     atomicOr(P.err, 1);
                 }
@@ -118,7 +155,7 @@ __global__ void __launch_bounds__(kListBlock) list_arcs_kernel(ListParams P)
             done = 1;
         } else {
             const int W = (d + 63) >> 6;
-            const u64* __restrict__ rows = P.rows + P.rows_off[u];
+            const u64* __restrict__ rows = P.rows + row0;
             // level 0: the arc's candidate set C_uv, k - 2 vertices to choose
             u64 M = lane < W ? rows[(long long)r * W + lane] : 0ull;
             u64 R = M;
@@ -148,6 +185,70 @@ __global__ void __launch_bounds__(kListBlock) list_arcs_kernel(ListParams P)
                         before += pc;
                     }
                     done += before;
+                    R = 0ull;                   // node finished
+                }
+                if (need == 2) {
+                    int c = __popcll(M);
+#pragma unroll
+                    for (int o = kWave / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, kWave);
+                    for (int j0 = 0; j0 < c; j0 += kWave) {
+                        // the j-th candidate x, its id, and the cliques it leads to
+                        const int j = j0 + lane;
+                        const int sel = wave_select(M, j, W);       // any position past the last
+                        const int x = j < c ? sel : 0;
+                        const int xid = j < c ? P.dag_col[a0 + x] : 0;
+                        int cnt = 0;
+                        for (int w = 0; w < W; ++w) {
+                            const u64 mw = readlane64(M, w);
+                            if (j < c && mw) cnt += __popcll(mw & rows[(long long)x * W + w]);
+                        }
+                        int inc = cnt;
+#pragma unroll
+                        for (int o = 1; o < kWave; o <<= 1) {
+                            const int v = __shfl_up(inc, o, kWave);
+                            if (lane >= o) inc += v;
+                        }
+                        const int tot = __shfl(inc, kWave - 1, kWave);
+                        for (int o0 = 0; o0 < tot; o0 += kWave) {
+                            const int o = o0 + lane;
+                            // the first lane whose inclusive sum passes o
+                            int s = 0;
+#pragma unroll
+                            for (int h = kWave / 2; h > 0; h >>= 1)
+                                if (__shfl(inc, s + h - 1, kWave) <= o) s += h;
+                            s = min(s, kWave - 1);
+                            const int xs = __shfl(x, s, kWave), xsid = __shfl(xid, s, kWave);
+                            int r2 = o - __shfl(inc - cnt, s, kWave);
+                            int y = -1;
+                            for (int w = 0; w < W; ++w) {
+                                const u64 mw = readlane64(M, w);
+                                if (mw == 0ull) continue;
+                                if (o < tot && y < 0) {
+                                    const u64 word = mw & rows[(long long)xs * W + w];
+                                    const int pc = __popcll(word);
+                                    if (r2 < pc) y = w * 64 + select64(word, r2);
+                                    r2 -= pc;
+                                }
+                            }
+                            if (o < tot) {
+                                const long long idx = done + o;
+                                if (idx < slot_n && y >= 0) {
+                                    const int yid = P.dag_col[a0 + y];
+                                    int32_t* out = P.out + (slot0 + idx) * k;
+                                    if (P.wide) {           // k = 4, output aligned to 16 bytes
+                                        *reinterpret_cast<int4*>(out) = make_int4(sPre[wid][0], sPre[wid][1], xsid, yid);
+                                    } else {
+                                        for (int c2 = 0; c2 < k - 2; ++c2) out[c2] = sPre[wid][c2];
+                                        out[k - 2] = xsid;
+                                        out[k - 1] = yid;
+                                    }
+                                } else {
+                                    atomicOr(P.err, 1);
+                                }
+                            }
+                        }
+                        done += tot;
+                    }
                     R = 0ull;                   // node finished
                 }
                 // next candidate of this level, or back up
@@ -190,18 +291,18 @@ hipError_t launch_list_arcs(const ListParams& P, int32_t blocks, hipStream_t s)
     if (P.n_arcs <= 0) return hipSuccess;
     if (P.k < 2 || P.k > kListMaxK) return hipErrorInvalidValue;
     const size_t lds = 2 * (size_t)kListWaves * list_levels(P.k) * kWave * sizeof(u64);
-    // arcs claimed per atomic on the shared cursor (its atomics are
-    // serialised): runs of up to 16 arcs, about eight claims per wave
     ListParams Q = P;
-    const int64_t waves = (int64_t)blocks * kListWaves;
-    int64_t c = (int64_t)P.n_arcs / (waves * 8);
-    c = c < 1 ? 1 : (c > 16 ? 16 : c);
-    if ((int64_t)P.n_arcs + waves * c >= (1ll << 31)) c = 1;
-    Q.chunk = (int32_t)c;
+    Q.wide = P.k == 4 && (reinterpret_cast<uintptr_t>(P.out) & 15) == 0;
+    const int64_t need = (P.n_arcs + kListWaves - 1) / kListWaves;
+    if (need < blocks) blocks = (int32_t)need;
+    Q.items = {};
+    Q.items.total = P.n_arcs;
+    Q.items.cursors = P.cursors;
+    set_runs(Q.items, (int64_t)blocks * kListWaves, kMaxClaim);
     // a stride near 0.618 n_arcs (consecutive claims then land far apart,
     // as in Fibonacci hashing) that shares no factor with n_arcs
     int64_t st = 1;
-    if (c > 1) {
+    if (Q.items.chunk > 1) {
         for (int64_t t = (int64_t)(0.6180339887 * P.n_arcs); t < P.n_arcs; ++t)
             if (std::gcd(t, (int64_t)P.n_arcs) == 1) {
                 st = t;

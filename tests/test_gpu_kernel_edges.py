@@ -276,3 +276,31 @@ def test_blocks_reused_across_threads_and_streams(citron_gpu):
     for t in threads:
         t.join()
     assert not bad
+
+
+@pytest.mark.parametrize("n,p,k", [(66, 1.0, 4), (70, 0.6, 4), (70, 0.6, 5), (135, 0.5, 4), (200, 0.35, 5), (90, 0.3, 6)])
+def test_listing_of_dense_graphs(citron_gpu, n, p, k):
+    """Last levels of more than 64 candidates and of several row words, and an
+    output that is not aligned to 16 bytes: against the oracle's listing."""
+    import ctypes
+    import oracle
+    import torch
+    g = gg.erdos_renyi(n, p * (n - 1), seed=n * 10 + k)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    got, offsets = h.list_arcs(k)
+    ptr, col = h.dag()
+    want, per_arc = oracle.list_arcs(g.n, ptr, col, k, np.repeat(np.arange(g.n), np.diff(ptr)).astype(np.int32), col)
+    assert np.array_equal(np.diff(offsets.cpu().numpy()), per_arc.astype(np.int64))
+    assert np.array_equal(got.cpu().numpy(), want)
+    buf = torch.full((got.numel() + 4,), -9, dtype=torch.int32, device="cuda")
+    arcs = torch.arange(g.m, dtype=torch.int32, device="cuda")
+    off2 = torch.zeros(g.m + 1, dtype=torch.int64, device="cuda")
+    total = ctypes.c_int64(0)
+    torch.cuda.synchronize()
+    st = citron_gpu.load_library().citron_list_arcs(h._handle(), k, arcs.data_ptr(), g.m, off2.data_ptr(),
+                                                    buf.data_ptr() + 4, got.shape[0], ctypes.byref(total))
+    assert st == 0 and total.value == got.shape[0]
+    flat = buf.cpu().numpy()
+    assert np.array_equal(flat[1:1 + got.numel()], got.cpu().numpy().ravel())
+    assert flat[0] == -9 and (flat[1 + got.numel():] == -9).all()
+    h.free()

@@ -151,6 +151,7 @@ static void free_graph_memory(citron_graph* g)
     dfree(g->d_hoff);
     dfree(g->d_hrows);
     dfree(g->d_hpos);
+    dfree(g->d_hinv);
     dfree(g->d_harcs);
     dfree(g->d_hscan);
     for (int32_t* p : g->retired_buckets) dfree(p);
@@ -248,7 +249,7 @@ citron_status ensure_rows(citron_graph* g)
     if ((!g->d_rows_off && (st = dalloc(&g->d_rows_off, (size_t)g->n + 1, acct, "row offsets"))) ||
         (!g->d_arc_c && (st = dalloc(&g->d_arc_c, (size_t)g->m, acct, "arc sizes"))) ||
         (heavy && !g->d_harcs && (st = dalloc(&g->d_harcs, (size_t)g->m, acct, "heavy arcs"))) ||
-        (heavy && !g->d_hscan && (st = dalloc(&g->d_hscan, (size_t)D + 1, acct, "arc histogram"))))
+        (heavy && !g->d_hscan && (st = dalloc(&g->d_hscan, 2 * (size_t)D + 1, acct, "arc histogram"))))
         return st;
     // Row offsets are int32, so the rows of all vertices, sum over u of
     // d(u) * ceil(d(u)/64) words, must stay below 2^31.  That sum is at most
@@ -274,7 +275,8 @@ citron_status ensure_rows(citron_graph* g)
                            hipMemcpyDeviceToHost, s);
     if (heavy) {
         if ((!g->d_hoff && (st = dalloc(&g->d_hoff, (size_t)g->n + 1, acct, "sorted rows"))) ||
-            (!g->d_hpos && (st = dalloc(&g->d_hpos, (size_t)g->m, acct, "sorted rows"))))
+            (!g->d_hpos && (st = dalloc(&g->d_hpos, (size_t)g->m, acct, "sorted rows"))) ||
+            (!g->d_hinv && (st = dalloc(&g->d_hinv, (size_t)g->m, acct, "sorted rows"))))
             return st;
         if (e == hipSuccess) e = launch_rows_len(g->n, g->d_dag_ptr, true, g->d_outdeg, s);
         if (e == hipSuccess) e = scan_exclusive(g->d_outdeg, g->d_hoff, g->n, g->d_scan_ws, s);
@@ -325,12 +327,13 @@ citron_status ensure_rows(citron_graph* g)
         sp.hoff = g->d_hoff;
         sp.hrows = g->d_hrows;
         sp.hpos = g->d_hpos;
+        sp.hinv = g->d_hinv;
         e = launch_sorted_rows(sp, s);
         if (e != hipSuccess) return hip_fail(e, "sorted rows");
     }
     SortBuffers sb = {};
     if (heavy) {
-        const size_t tb = sched_sort_temp_bytes(g->m, D);
+        const size_t tb = sched_sort_temp_bytes(g->m, 2 * D);
         if (tb == 0) return fail(CITRON_EDEVICE, "sort workspace query failed");
         unsigned char* tmp = nullptr;
         if ((st = dalloc(&sb.keys_a, (size_t)g->m + 1, nullptr, "arc schedule")) ||
@@ -344,9 +347,10 @@ citron_status ensure_rows(citron_graph* g)
         sb.temp_bytes = tb;
     }
     if (heavy) e = sched_heavy_arcs(g->m, g->d_dag_ptr, g->d_dag_src, g->d_arc_c, D, g->d_hscan, g->d_harcs, sb, s);
-    g->h_hscan.assign((size_t)D + 1, 0);
+    g->h_hscan.assign(2 * (size_t)D + 1, 0);
     if (e == hipSuccess && heavy)
-        e = hipMemcpyAsync(g->h_small->hist, g->d_hscan, sizeof(int32_t) * ((size_t)D + 1), hipMemcpyDeviceToHost, s);
+        e = hipMemcpyAsync(g->h_small->hist, g->d_hscan, sizeof(int32_t) * (2 * (size_t)D + 1),
+                           hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(g->h_small->build, sd->build, sizeof(sd->build), hipMemcpyDeviceToHost, s);
     {
@@ -360,7 +364,7 @@ citron_status ensure_rows(citron_graph* g)
         dfree(tmp);
     }
     if (e != hipSuccess) return hip_fail(e, "subgraph build");
-    if (heavy) memcpy(g->h_hscan.data(), g->h_small->hist, sizeof(int32_t) * ((size_t)D + 1));
+    if (heavy) memcpy(g->h_hscan.data(), g->h_small->hist, sizeof(int32_t) * (2 * (size_t)D + 1));
     g->tri = 0;
     g->tri_ovf = false;
     memset(g->build_stats, 0, sizeof(g->build_stats));
@@ -389,8 +393,9 @@ citron_status ensure_scratch(citron_graph* g, int64_t bytes)
     return CITRON_OK;
 }
 
-// Work items of a k-clique count (k >= 4): the dense kernel's arcs
-// (dense_arc) in buckets of equal |C_uv|, largest first; then the other heavy
+// Work items of a k-clique count (k >= 4): the dense kernel's vertices
+// (dense_vertex) in buckets of equal out-degree, or its arcs (dense_arc) in
+// buckets of equal |C_uv|, largest first; then the other heavy
 // arcs with |C_uv| >= k-2 in buckets of equal |C_uv| and light vertices with
 // out-degree >= k-1 in buckets of equal out-degree, merged by cost key
 // (|C_uv|, or out-degree - 1 for a light vertex), largest first, so that the
@@ -415,15 +420,22 @@ citron_status ensure_buckets(citron_graph* g, int32_t k)
     const int64_t n_heavy = v_at_least(kLightMaxDeg + 1);
     struct B { int32_t key, first, cnt, kind; };
     std::vector<B> db, hb, lb;
-    // heavy-arc buckets: bucket j of the arc order holds |C_uv| = D-1-j
-    for (int32_t j = 0; j < D; ++j) {
-        const int32_t c = D - 1 - j;
-        if (c < k - 2) break;
-        const int32_t cnt = g->h_hscan[(size_t)j + 1] - g->h_hscan[(size_t)j];
-        if (cnt <= 0) continue;
-        if (dense_arc(c, k)) db.push_back({c, g->h_hscan[(size_t)j], cnt, kItemDenseArc});
-        else hb.push_back({c, g->h_hscan[(size_t)j], cnt, kItemHeavyArc});
+    // vertices the dense kernel takes whole (k = 4, 5), by out-degree
+    for (int32_t d = kDenseMax; d > kLightMaxDeg; --d) {
+        const int64_t cnt = v_at_least(d) - v_at_least(d + 1);
+        if (cnt > 0 && dense_vertex(d, k)) db.push_back({d, (int32_t)v_at_least(d + 1), (int32_t)cnt, kItemDenseVertex});
     }
+    // heavy-arc buckets by |C_uv|, of vertices above kDenseMax (group 0) and
+    // of the others, whose arcs are not scheduled where the vertices are
+    for (int32_t c = D - 1; c >= k - 2; --c)
+        for (int32_t grp = 0; grp < 2; ++grp) {
+            if (grp == 1 && dense_vertex(kDenseMax, k)) continue;
+            const size_t j = (size_t)(grp * D + D - 1 - c);
+            const int32_t cnt = g->h_hscan[j + 1] - g->h_hscan[j];
+            if (cnt <= 0) continue;
+            if (dense_arc(c, k)) db.push_back({c, g->h_hscan[j], cnt, kItemDenseArc});
+            else hb.push_back({c, g->h_hscan[j], cnt, kItemHeavyArc});
+        }
     // light-vertex buckets: out-degree d = 64 down to max(k-1, 2)
     for (int32_t d = kLightMaxDeg; d >= std::max(k - 1, 2); --d) {
         const int64_t cnt = v_at_least(d) - v_at_least(d + 1);
@@ -434,6 +446,7 @@ citron_status ensure_buckets(citron_graph* g, int32_t k)
     auto add = [&](const B& b) {
         const int32_t parts = b.kind == kItemLightVertex ? light_parts(b.key + 1, k, pct)
                               : b.kind == kItemDenseArc  ? dense_parts(b.key, k, pct)
+                              : b.kind == kItemDenseVertex ? 1
                                                          : arc_parts(b.key, k, pct);
         tab.push_back((int32_t)items);
         tab.push_back(b.first);
@@ -528,6 +541,7 @@ QueryDesc make_query(const citron_graph* g, int32_t k, unsigned long long* acc, 
     q.rows.hoff = g->d_hoff;
     q.rows.hrows = g->d_hrows;
     q.rows.hpos = g->d_hpos;
+    q.rows.hinv = g->d_hinv;
     q.acc = acc;
     q.overflow = ovf;
     q.per_arc = per_arc;
@@ -650,8 +664,9 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
     const int wg = t.wg_waves;
     const int32_t blocks = device_cus(g->device) * t.blocks_per_cu;
     // a unit rooted at a vertex has one more level to choose than one rooted
-    // at an arc: its stacks are sized as for k + 1
-    const int32_t stack_k = vertex_rooted ? k + 1 : k;
+    // at an arc: its stacks are sized as for k + 1 (the dense kernel's
+    // vertices are such units where an instrumented count kernel takes them)
+    const int32_t stack_k = vertex_rooted || (stats && k <= 5) ? k + 1 : k;
     const int64_t swords = count_scratch_words(g->max_outdeg, stack_k, wg);
     st = ensure_scratch(g, std::max<int64_t>(swords * 8 * blocks, 8));
     if (st) return st;

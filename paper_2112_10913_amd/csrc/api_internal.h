@@ -45,7 +45,7 @@ struct SmallHost {
     uint64_t stats[kNumStats];
     int32_t rows_total;
     int32_t hrows_total;
-    int32_t hist[kMaxDeg + 2];   // bucket bounds of a schedule order
+    int32_t hist[2 * kMaxDeg + 2];   // bucket bounds of a schedule order
     PeelCtl peel;
     BuildSums build[kBuildSlots];
 };
@@ -99,9 +99,10 @@ struct citron_graph {
     int32_t* d_hoff = nullptr;              // n + 1: the heavy vertices' rows in sorted positions
     unsigned long long* d_hrows = nullptr;
     uint16_t* d_hpos = nullptr;             // m
+    uint16_t* d_hinv = nullptr;             // m
     int32_t* d_harcs = nullptr;             // m
-    int32_t* d_hscan = nullptr;             // D + 1
-    std::vector<int32_t> h_hscan;           // heavy arcs by |C_uv|, scanned
+    int32_t* d_hscan = nullptr;             // 2 D + 1
+    std::vector<int32_t> h_hscan;           // heavy arcs by group and |C_uv|, scanned
     std::vector<int32_t> h_vscan;           // vertices by out-degree, scanned
     uint64_t tri = 0;
     bool tri_ovf = false;

@@ -97,7 +97,7 @@ struct RowsDev {
     const int32_t* rows_off;        // n + 1: first word of u's rows (< 2^31 words)
     const unsigned long long* rows; // all rows
     const int32_t* arc_c;           // m: popcount of arc e's row = |C_uv|
-    const int32_t* harcs;           // arcs of heavy vertices by |C_uv| descending
+    const int32_t* harcs;           // arcs of heavy vertices: of those above kDenseMax, then of the others, each by |C_uv| descending
     // Rows of the heavy vertices again, in the order of the DAG: positions
     // sorted by the ordering (key, id), so that a vertex's neighbours come
     // after it and every matrix of rows is strictly upper triangular.  The
@@ -108,6 +108,7 @@ struct RowsDev {
     const int32_t* hoff;            // n: first word of u's rows in hrows (heavy u)
     const unsigned long long* hrows;
     const uint16_t* hpos;           // m: sorted position of arc e among its source's (heavy sources)
+    const uint16_t* hinv;           // m: the way back, per sorted position
 };
 
 // Item spaces of a launch: dense arcs by row words, kDenseClasses of them
@@ -168,7 +169,8 @@ enum BucketKind {
     kItemLightVertex = 1,  // (a part of) a light vertex, its arcs the units (edge-rooted)
     kItemHeavyVertex = 2,  // a whole heavy vertex, searched from its own root (vertex-rooted)
     kItemLightRoot = 3,    // a whole light vertex, one unit rooted at the vertex (vertex-rooted)
-    kItemDenseArc = 4      // one part of a heavy vertex's arc for the dense kernel (edge-rooted)
+    kItemDenseArc = 4,     // one part of a heavy vertex's arc for the dense kernel (edge-rooted)
+    kItemDenseVertex = 5   // one part of a heavy vertex for the dense kernel: its arcs in turn
 };
 
 // Parts a heavy arc with |C_uv| = c is split into for a k-clique count; each
@@ -196,7 +198,16 @@ constexpr int kDenseMin = 17;
 constexpr int kDenseMax = 64 * kDenseClasses;
 __host__ __device__ inline bool dense_arc(int c, int k) { return k >= 6 && c >= kDenseMin && c <= kDenseMax; }
 
-// Parts of such an arc (every P-th first-level branch): the workgroup shares
+// Heavy vertices the dense kernel takes whole in counts of k = 4 and 5, where
+// an arc's subgraph would serve one triangle count at most: the vertex's own
+// subgraph serves one per arc (k = 5), or all its 4-cliques are its triangles
+// (k = 4), and its sorted rows need no packing.
+__host__ __device__ inline bool dense_vertex(int d, int k)
+{
+    return (k == 4 || k == 5) && d > kLightMaxDeg && d <= kDenseMax;
+}
+
+// Parts of a dense arc (every P-th first-level branch): the workgroup shares
 // the arc's first level already, so parts only shorten the tail of deep counts.
 __host__ __device__ inline int dense_parts(int c, int k, int pct)
 {

@@ -131,7 +131,7 @@ __device__ __forceinline__ void decode_run(const ItemSpace& P, int g0, int n, in
             r = sorted ? q.rows.hpos[e] : e - q.dag_ptr[u];
             nparts = kind == kItemDenseArc ? dense_parts(key, q.k, q.split_pct) : arc_parts(key, q.k, q.split_pct);
             tag = e;
-        } else if (kind == kItemHeavyVertex) {
+        } else if (kind == kItemHeavyVertex || kind == kItemDenseVertex) {
             u = q.order[which];
             nparts = 1;
             tag = -1;

@@ -58,8 +58,10 @@ size_t sched_sort_temp_bytes(int64_t n, int32_t nb);   // n keys of nb buckets
 // descending, ties by id; bounds[i] (i < D) = vertices of out-degree > D - i
 hipError_t sched_plan_order(int32_t n, const int32_t* dag_ptr, int32_t D, int32_t* bounds, int32_t* order,
                             const SortBuffers& sb, hipStream_t s);
-// harcs[0 .. bounds[D]) = arcs of vertices with out-degree > 64 by |C_uv|
-// descending, ties by arc index; bounds[i] (i <= D) = those with |C_uv| > D - 1 - i
+// harcs[0 .. bounds[2D]) = arcs of vertices with out-degree > 64: first those
+// of vertices above kDenseMax, then the others, each by |C_uv| descending,
+// ties by arc index; bucket (g, c) of group g = 0, 1 is g D + D - 1 - c, and
+// bounds[b] (b <= 2D) = arcs in the buckets before b
 hipError_t sched_heavy_arcs(int64_t m, const int32_t* dag_ptr, const int32_t* dag_src, const int32_t* arc_c,
                             int32_t D, int32_t* bounds, int32_t* harcs, const SortBuffers& sb, hipStream_t s);
 
@@ -115,6 +117,7 @@ struct SortedRowsParams {
     const int32_t* hoff;
     unsigned long long* hrows;
     uint16_t* hpos;
+    uint16_t* hinv;
 };
 hipError_t launch_sorted_rows(const SortedRowsParams& P, hipStream_t s);
 hipError_t launch_build_rows(const BuildParams& P, int32_t blocks, hipStream_t s);

@@ -961,14 +961,15 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
             // unit, Algorithm 2 per vertex) a whole vertex: all d positions
             // are candidates and its first level walks its arcs in turn
             const HeavyCtx<true> H{RowRef<true>{(glb_u64*)rows}, (d + 63) >> 6, k - 1, tag};
+            const bool whole = kind == kItemHeavyVertex || kind == kItemDenseVertex;
             const int rem = d - 64 * lane;
             u64 M = 0ull;
             if (lane < H.W) {
-                if (kind == kItemHeavyVertex) M = rem >= 64 ? ~0ull : ((1ull << rem) - 1ull);
+                if (whole) M = rem >= 64 ? ~0ull : ((1ull << rem) - 1ull);
                 else M = H.rows((unsigned)(r * H.W + lane));
             }
             u64 uacc = 0;
-            heavy_search<kStats, kPerArc, true, kRegL>(H, M, kind == kItemHeavyVertex ? H.L : H.L - 1, 0, part, nparts,
+            heavy_search<kStats, kPerArc, true, kRegL>(H, M, whole ? H.L : H.L - 1, 0, part, nparts,
                                                        wb, A, uacc, per_arc);
             if (kPerArc) {
                 const u64 s = wave_sum_u64(uacc);

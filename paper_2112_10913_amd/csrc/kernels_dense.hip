@@ -1,7 +1,9 @@
-// Dense kernel: k-clique counts of heavy arcs on the matrix cores.
+// Dense kernel: k-clique counts of heavy arcs and vertices on the matrix cores.
 //
 // A work item is an arc u -> v with kDenseMin <= c = |C_uv| <= kDenseMax of a
-// count with k >= 6 (dense_arc).  These subgraphs are dense (about 0.9 of all
+// count with k >= 6 (dense_arc), or a heavy vertex of up to kDenseMax
+// out-neighbours of a count with k = 4 or 5 (dense_vertex), whose subgraph
+// takes the place of the arc's below.  These subgraphs are dense (about 0.9 of all
 // pairs adjacent in the power-law families), and the search below an arc
 // ends, k - 5 levels down, in triangle counts of induced subgraphs
 //     T(M) = sum over x, y in M, A[x][y] = 1, of |row x & row y & M|,
@@ -41,7 +43,7 @@ namespace {
 // several workgroups of four waves on a CU; larger ones share a workgroup's
 // tiles among more waves.
 __host__ __device__ constexpr int dense_waves(int K) { return K <= 3 ? 4 : (K == 5 ? 12 : 8); }
-__host__ __device__ constexpr int dense_cu_waves(int K) { return K == 1 ? 32 : (K == 2 ? 20 : (K <= 4 ? 16 : dense_waves(K))); }
+__host__ __device__ constexpr int dense_cu_waves(int K) { return K == 1 ? 28 : (K == 2 ? 20 : (K <= 4 ? 16 : dense_waves(K))); }
 constexpr int kDenseClaim = 8;              // items a workgroup claims at once, at most
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -117,8 +119,9 @@ struct Dense {
     }
 
     // T(M), this lane's share.  pat: M's 4-bit patterns (per bit tile, the
-    // lane's half).
-    __device__ __forceinline__ unsigned triangles(const u64 (&M)[K], const v4i (&pat)[K]) const
+    // lane's half).  kSplit: the row tiles x = first mod kSplit only.
+    template <int kSplit>
+    __device__ __forceinline__ unsigned triangles(const u64 (&M)[K], const v4i (&pat)[K], int first) const
     {
         const int lane = lane_of();
         unsigned sum = 0, s[2 * K];      // per row tile y: its columns outside M are dropped at the end
@@ -127,7 +130,7 @@ struct Dense {
 #pragma unroll
         for (int x = 0; x < 2 * K; ++x) {
             const unsigned mx = (unsigned)(M[x >> 1] >> (32 * (x & 1)));
-            if (mx == 0u) continue;
+            if (mx == 0u || (kSplit > 1 && x % kSplit != first)) continue;
             const int in = lanes32(mx) ? -1 : 0;
             v4i a[K];
 #pragma unroll
@@ -211,7 +214,7 @@ struct Dense {
                     }
                     pat[z] = tiles[(tile_base(K, x >> 5) + z - w) * kWave + half * 32 + (x & 31)] & pp[z];
                 }
-                sum += triangles(M, pat);
+                sum += triangles<1>(M, pat, 0);
             }
         }
         return (u64)sum;
@@ -350,30 +353,40 @@ __device__ void build_tiles(const u64* __restrict__ rows, v4i* __restrict__ tile
         }
 }
 
-// One arc: lay its subgraph out, then share its first level among the waves.
-// Returns this lane's share of the count.
+// One item: an arc's subgraph (mask row r of its source's rows, packed) or a
+// whole vertex's (its rows as they are), laid out once; then its first level
+// is shared among the waves.  need: vertices to choose from the subgraph, 3
+// (one triangle count, k = 4) or more.  per_arc (vertices only): counts per
+// first vertex x go to per_arc[inv[x]].  Returns this lane's
+// share of the count.
 template <int K>
-__device__ __forceinline__ u64 dense_arc_item(const u64* __restrict__ src, int W, int r, int k, int part, int P,
-                                              unsigned char* smem, u64* stacks, int* branch)
+__device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, int d, int r, int need, int part, int P,
+                                          int max_k, unsigned char* smem, u64* stacks, int* branch, u64* per_arc,
+                                          const uint16_t* inv)
 {
     v4i* tiles = reinterpret_cast<v4i*>(smem);
     v4i* bytes = tiles + n_tiles(K) * kWave;
     u64* rows = reinterpret_cast<u64*>(bytes + n_pairs(K) * kWave);
     const int lane = lane_of();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const u64 M = lane < W ? src[(int64_t)r * W + lane] : 0ull;
-    const int c = wave_sum_small(__popcll(M));
-    const int nt = (c + 31) >> 5;
-    // rows past the last candidate, and words past a row's last, read as zero
-    for (int i = threadIdx.x; i < 64 * K * K; i += dense_waves(K) * kWave) rows[i] = 0ull;
+    int c = d;
     if (threadIdx.x == 0) *branch = 0;
-    __syncthreads();
-    pack_rows<K>(src, W, M, c, rows);
+    if (r < 0) {
+        // W = K: the vertex's class is that of its out-degree
+        for (int i = threadIdx.x; i < 64 * K * K; i += dense_waves(K) * kWave) rows[i] = i < d * K ? src[i] : 0ull;
+    } else {
+        const u64 M = lane < W ? src[(int64_t)r * W + lane] : 0ull;
+        c = wave_sum_small(__popcll(M));
+        // rows past the last candidate, and words past a row's last, read as zero
+        for (int i = threadIdx.x; i < 64 * K * K; i += dense_waves(K) * kWave) rows[i] = 0ull;
+        __syncthreads();
+        pack_rows<K>(src, W, M, c, rows);
+    }
+    const int nt = (c + 31) >> 5;
     __syncthreads();
     build_tiles<K>(rows, tiles, bytes, nt);
     __syncthreads();
     const Dense<K> D{tiles, bytes, rows, nt};
-    const int need = k - 2;
     u64 all[K];
 #pragma unroll
     for (int w = 0; w < K; ++w) {
@@ -381,23 +394,45 @@ __device__ __forceinline__ u64 dense_arc_item(const u64* __restrict__ src, int W
         all[w] = rem >= 64 ? ~0ull : (rem > 0 ? (1ull << rem) - 1ull : 0ull);
     }
     u64 sum = 0;
+    if (need == 3 && !per_arc) {
+        v4i pat[K];
+#pragma unroll
+        for (int z = 0; z < K; ++z) pat[z] = v4i{0x22222222, 0x22222222, 0x22222222, 0x22222222};
+        sum = D.template triangles<dense_waves(K)>(all, pat, wid);
+        __syncthreads();
+        return sum;
+    }
     for (;;) {
         int j = 0;
         if (lane == 0) j = atomicAdd(branch, 1);
         const int x = part + P * __builtin_amdgcn_readfirstlane(j);
         if (x >= c) break;
-        if (need == 4) {
+        u64 s = 0;
+        if (need == 3) {
+            // per-arc counts of k = 4 want row x's own sum: lanes over its y
+            u64 rx[K];
+            D.row(x, rx);
+            for (int y = lane; y < c; y += kWave)
+                if ((rows[x * K + (y >> 6)] >> (y & 63)) & 1)
+#pragma unroll
+                    for (int w = 0; w < K; ++w) s += (u64)__popcll(rx[w] & rows[y * K + w]);
+        } else if (need == 4) {
             u64 R[K];
 #pragma unroll
             for (int w = 0; w < K; ++w) R[w] = (x >> 6) == w ? 1ull << (x & 63) : 0ull;
-            sum += D.last_levels(all, R, true);
+            s = D.last_levels(all, R, true);
         } else {
             u64 ch[K];
             D.row(x, ch);
             int cc = 0;
 #pragma unroll
             for (int w = 0; w < K; ++w) cc += __popcll(ch[w]);
-            if (cc >= need - 1) sum += D.search(ch, need - 1, stacks + wid * dense_stack_words(K, k));
+            if (cc >= need - 1) s = D.search(ch, need - 1, stacks + wid * dense_stack_words(K, max_k));
+        }
+        sum += s;
+        if (per_arc) {
+            const u64 t = wave_sum_u64(s);
+            if (lane == 0 && t) atomicAdd(per_arc + inv[x], t);
         }
     }
     __syncthreads();
@@ -447,9 +482,13 @@ __global__ void __launch_bounds__(dense_waves(K) * kWave)
             const int tag = field(kItTag), r = field(kItRow), pw = field(kItPart);
             const int W = (field(kItDegree) + 63) >> 6;
             const u64* src = q.rows.hrows + field(kItRowsOff);
-            const u64 s = dense_arc_item<K>(src, W, r, q.k, pw & 0xffff, pw >> 16, smem, stacks, shared);
+            const bool vertex = field(kItKind) == kItemDenseVertex;
+            const int a0 = field(kItArc0);
+            const u64 s = dense_item<K>(src, W, field(kItDegree), r, vertex ? q.k - 1 : q.k - 2, pw & 0xffff, pw >> 16,
+                                        P.max_k, smem, stacks, shared, vertex && q.per_arc ? q.per_arc + a0 : nullptr,
+                                        q.rows.hinv + a0);
             acc += s;            // a lane adds at most 2^28 per mask's children: 2^36 of them before it could wrap
-            if (q.per_arc) {
+            if (q.per_arc && !vertex) {
                 const u64 t = wave_sum_u64(s);
                 if (lane == 0 && t) atomicAdd(q.per_arc + tag, t);
             }

@@ -390,6 +390,7 @@ __global__ void __launch_bounds__(256) sorted_rows_kernel(SortedRowsParams P)
             for (int j = 0; j < d; ++j) rank += (key[j] < ki || (key[j] == ki && j < i)) ? 1 : 0;
             pos[rank] = (uint16_t)i;
             P.hpos[a0 + i] = (uint16_t)rank;
+            P.hinv[a0 + rank] = (uint16_t)i;
         }
         __syncthreads();
         const u64* __restrict__ src = P.rows + P.rows_off[u];

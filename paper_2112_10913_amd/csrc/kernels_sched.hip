@@ -3,7 +3,8 @@
 // The plan: vertices of out-degree >= 2 by out-degree (descending), the
 // heavy ones (out-degree > 64) as items of their own, the light ones packed
 // into batches of about light_rows rows, and a header with the item counts.
-// The heavy arcs: arcs of heavy vertices by |C_uv| (descending).
+// The heavy arcs: arcs of heavy vertices, those above kDenseMax first, each
+// group by |C_uv| (descending).
 //
 // Both orders break ties by id, so they are fixed by the graph alone: the
 // strided shares of a count (citron_count_part) cover the same items in
@@ -31,16 +32,17 @@ __global__ void plan_keys_kernel(int32_t n, const int32_t* __restrict__ dag_ptr,
     keys[u] = ((u64)(unsigned)(d >= 2 ? D - d : D - 1) << 32) | (u64)(unsigned)u;
 }
 
-// heavy arcs: key of arc e = (D - 1 - |C_uv|) << 32 | e when the source has
-// out-degree > 64
+// heavy arcs: key of arc e = (group D + D - 1 - |C_uv|) << 32 | e when the
+// source has out-degree > 64, group 0 above kDenseMax, else 1
 __global__ void harc_keys_kernel(int64_t m, const int32_t* __restrict__ dag_ptr, const int32_t* __restrict__ dag_src,
                                  const int32_t* __restrict__ arc_c, int32_t D, u64* __restrict__ keys)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= m) return;
     const int u = dag_src[e];
-    const bool heavy = dag_ptr[u + 1] - dag_ptr[u] > kLightMaxDeg;
-    keys[e] = ((u64)(unsigned)(heavy ? D - 1 - arc_c[e] : D) << 32) | (u64)e;
+    const int d = dag_ptr[u + 1] - dag_ptr[u];
+    const int bucket = d <= kLightMaxDeg ? 2 * D : (d > kDenseMax ? 0 : D) + D - 1 - arc_c[e];
+    keys[e] = ((u64)(unsigned)bucket << 32) | (u64)e;
 }
 
 // bounds[b] = number of sorted keys with bucket < b, for b = 0..nb, where
@@ -116,12 +118,11 @@ hipError_t sched_plan_order(int32_t n, const int32_t* dag_ptr, int32_t D, int32_
 hipError_t sched_heavy_arcs(int64_t m, const int32_t* dag_ptr, const int32_t* dag_src, const int32_t* arc_c,
                             int32_t D, int32_t* bounds, int32_t* harcs, const SortBuffers& sb, hipStream_t s)
 {
-    if (m <= 0) return launch_fill_i32(bounds, 0, D + 1, s);
+    if (m <= 0) return launch_fill_i32(bounds, 0, 2 * D + 1, s);
     harc_keys_kernel<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(m, dag_ptr, dag_src, arc_c, D, sb.keys_a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // buckets D - 1 - c for c = D - 1 .. 0: D of them
-    return sort_and_split(m, D, bounds, harcs, sb, s);
+    return sort_and_split(m, 2 * D, bounds, harcs, sb, s);
 }
 
 // ---------------------------------------------------------------- plan

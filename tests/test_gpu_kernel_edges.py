@@ -304,3 +304,34 @@ def test_listing_of_dense_graphs(citron_gpu, n, p, k):
     assert np.array_equal(flat[1:1 + got.numel()], got.cpu().numpy().ravel())
     assert flat[0] == -9 and (flat[1 + got.numel():] == -9).all()
     h.free()
+
+
+@pytest.mark.parametrize("n", [66, 67, 98, 129, 130, 193, 258, 322, 385, 386, 400])
+def test_dense_vertices_of_complete_graphs(citron_gpu, n):
+    """K_n has a vertex of every out-degree up to n - 1: all the sizes of the
+    dense kernel's vertices at k = 4, 5, and those above and below them."""
+    from math import comb
+    g = gg.complete(n)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    assert h.count(4) == comb(n, 4)
+    assert h.count(5) == comb(n, 5)
+    h.free()
+
+
+@pytest.mark.parametrize("n,p,k", [(120, 0.8, 4), (120, 0.8, 5), (250, 0.5, 4), (250, 0.5, 5), (400, 0.6, 4), (400, 0.4, 5),
+                                   (520, 0.9, 4), (520, 0.6, 5)])
+def test_dense_vertices_against_the_count_kernel(citron_gpu, n, p, k):
+    """Counts, per-arc counts, strided shares and batches of k = 4, 5 against
+    the vertex-rooted unit and the listed arcs (the count kernel)."""
+    g = gg.erdos_renyi(n, p * (n - 1), seed=n + k)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    want = h.count_vertex_rooted(k)
+    assert h.count(k) == want
+    total, every = h.count_per_arc(k)
+    assert total == want
+    assert np.array_equal(every, h.count_arcs(k, np.arange(g.m)))
+    parts = [h.count_part(k, i, 6) for i in range(6)]
+    assert sum(c for c, _ in parts) == want
+    assert citron_gpu.count_batch([h, h], [k, 6 - k + 3]) == [want, h.count_vertex_rooted(6 - k + 3)]
+    assert h.work_stats(k)["word_ops"] > 0
+    h.free()

@@ -39,11 +39,18 @@ namespace citron {
 namespace {
 
 // Waves of a workgroup, and on a CU at most by registers (64 to 185 of the 512
-// a SIMD lane has).  The tiles of up to three row words are small enough for
-// several workgroups of four waves on a CU; larger ones share a workgroup's
-// tiles among more waves.
-__host__ __device__ constexpr int dense_waves(int K) { return K <= 3 ? 4 : (K == 5 ? 12 : 8); }
-__host__ __device__ constexpr int dense_cu_waves(int K) { return K == 1 ? 28 : (K == 2 ? 20 : (K <= 4 ? 16 : dense_waves(K))); }
+// a SIMD lane has).  Two and three row words leave LDS for several workgroups
+// of four waves on a CU (two waves for two words: 41 -> 43 ms); larger
+// subgraphs share a workgroup's tiles among more waves.  One-word subgraphs
+// are packed by one wave, and at k <= 6 searched in microseconds, so there
+// each wave has its own (R-MAT 20, k = 6: their 24 ms fell to 18 against four
+// waves and their barriers); deeper searches are worth sharing (R-MAT 16,
+// k = 7: 33.3 ms against 32.7).
+__host__ __device__ constexpr int dense_waves(int K, int max_k)
+{
+    return K == 1 ? (max_k <= 6 ? 1 : 4) : (K <= 3 ? 4 : (K == 5 ? 12 : 8));
+}
+__host__ __device__ constexpr int dense_cu_waves(int K) { return K == 1 ? 28 : (K == 2 ? 20 : (K <= 4 ? 16 : (K == 5 ? 12 : 8))); }
 constexpr int kDenseClaim = 8;              // items a workgroup claims at once, at most
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -68,7 +75,7 @@ __host__ __device__ constexpr int n_tiles(int K) { return tile_base(K, 2 * K); }
 __host__ __device__ constexpr int pair_base(int K, int x) { return x * 2 * K - x * (x - 1) / 2; }
 __host__ __device__ constexpr int n_pairs(int K) { return K * (2 * K + 1); }
 static_assert(tile_base(4, 8) == 20 && n_pairs(4) == 36, "upper triangles of 8 x 4 and 8 x 8 tiles");
-static_assert(1024 * (n_tiles(6) + n_pairs(6)) + 8 * 64 * 36 + 8 * dense_waves(6) * 26 * 12 + 2048 <= 160 * 1024,
+static_assert(1024 * (n_tiles(6) + n_pairs(6)) + 8 * 64 * 36 + 8 * dense_waves(6, 32) * 26 * 12 + 2048 <= 160 * 1024,
               "the largest instance fits LDS at k = 32");
 
 // LDS of a workgroup: [operand tiles 1 KB each][byte tiles 1 KB each][bit
@@ -80,7 +87,7 @@ __host__ __device__ constexpr int dense_stack_words(int K, int max_k)
 __host__ __device__ constexpr int dense_lds_bytes(int K, int max_k)
 {
     return 1024 * (n_tiles(K) + n_pairs(K)) + 8 * 64 * K * K +
-           8 * dense_waves(K) * dense_stack_words(K, max_k) + 4 * kItFields * kMaxClaim + 16;
+           8 * dense_waves(K, max_k) * dense_stack_words(K, max_k) + 4 * kItFields * kMaxClaim + 16;
 }
 
 __device__ __forceinline__ u64 uniform64(u64 v)
@@ -285,12 +292,12 @@ struct Dense {
 // Bit rows of the subgraph of mask M (lane q holds word q, W words) over the
 // sorted rows `src`, packed to K words each: the waves take 64 rows at a
 // time.  Rows c .. 64 K - 1 are zero.
-template <int K>
+template <int K, int kWaves>
 __device__ void pack_rows(const u64* __restrict__ src, int W, u64 M, int c, u64* __restrict__ dst)
 {
     const int lane = lane_of();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    for (int a0 = wid * kWave; a0 < 64 * K; a0 += dense_waves(K) * kWave) {
+    for (int a0 = wid * kWave; a0 < 64 * K; a0 += kWaves * kWave) {
         const int a = a0 + lane;
         const bool valid = a < c;
         const int xa = a0 < c ? wave_select(M, a, W) : 0;
@@ -316,7 +323,7 @@ __device__ void pack_rows(const u64* __restrict__ src, int W, u64 M, int c, u64*
 }
 
 // Operand and byte tiles of the bit rows.
-template <int K>
+template <int K, int kWaves>
 __device__ void build_tiles(const u64* __restrict__ rows, v4i* __restrict__ tiles, v4i* __restrict__ bytes, int nt)
 {
     const int lane = lane_of();
@@ -326,7 +333,7 @@ __device__ void build_tiles(const u64* __restrict__ rows, v4i* __restrict__ tile
     int f = 0;
     for (int x = 0; x < 2 * K; ++x)
         for (int z = x >> 1; z < K; ++z, ++f) {
-            if (f % dense_waves(K) != wid) continue;
+            if (f % kWaves != wid) continue;
             const unsigned b = rows32[((32 * x + l) * K + z) * 2 + half];
             v4i v;
 #pragma unroll
@@ -336,7 +343,7 @@ __device__ void build_tiles(const u64* __restrict__ rows, v4i* __restrict__ tile
     for (int x = 0; x < nt; ++x)
         for (int y = x; y < nt; ++y) {
             const int p = pair_base(K, x) + y - x;
-            if (p % dense_waves(K) != wid) continue;
+            if (p % kWaves != wid) continue;
             // accumulator 4 q + j of this lane: row 8 q + 4 half + j of tile x, column l of tile y
             v4i v;
 #pragma unroll
@@ -359,7 +366,7 @@ __device__ void build_tiles(const u64* __restrict__ rows, v4i* __restrict__ tile
 // (one triangle count, k = 4) or more.  per_arc (vertices only): counts per
 // first vertex x go to per_arc[inv[x]].  Returns this lane's
 // share of the count.
-template <int K>
+template <int K, int kWaves>
 __device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, int d, int r, int need, int part, int P,
                                           int max_k, unsigned char* smem, u64* stacks, int* branch, u64* per_arc,
                                           const uint16_t* inv)
@@ -373,18 +380,18 @@ __device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, in
     if (threadIdx.x == 0) *branch = 0;
     if (r < 0) {
         // W = K: the vertex's class is that of its out-degree
-        for (int i = threadIdx.x; i < 64 * K * K; i += dense_waves(K) * kWave) rows[i] = i < d * K ? src[i] : 0ull;
+        for (int i = threadIdx.x; i < 64 * K * K; i += kWaves * kWave) rows[i] = i < d * K ? src[i] : 0ull;
     } else {
         const u64 M = lane < W ? src[(int64_t)r * W + lane] : 0ull;
         c = wave_sum_small(__popcll(M));
         // rows past the last candidate, and words past a row's last, read as zero
-        for (int i = threadIdx.x; i < 64 * K * K; i += dense_waves(K) * kWave) rows[i] = 0ull;
+        for (int i = threadIdx.x; i < 64 * K * K; i += kWaves * kWave) rows[i] = 0ull;
         __syncthreads();
-        pack_rows<K>(src, W, M, c, rows);
+        pack_rows<K, kWaves>(src, W, M, c, rows);
     }
     const int nt = (c + 31) >> 5;
     __syncthreads();
-    build_tiles<K>(rows, tiles, bytes, nt);
+    build_tiles<K, kWaves>(rows, tiles, bytes, nt);
     __syncthreads();
     const Dense<K> D{tiles, bytes, rows, nt};
     u64 all[K];
@@ -398,7 +405,7 @@ __device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, in
         v4i pat[K];
 #pragma unroll
         for (int z = 0; z < K; ++z) pat[z] = v4i{0x22222222, 0x22222222, 0x22222222, 0x22222222};
-        sum = D.template triangles<dense_waves(K)>(all, pat, wid);
+        sum = D.template triangles<kWaves>(all, pat, wid);
         __syncthreads();
         return sum;
     }
@@ -441,20 +448,20 @@ __device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, in
 
 }  // namespace
 
-template <int K>
-__global__ void __launch_bounds__(dense_waves(K) * kWave)
+template <int K, int kWaves>
+__global__ void __launch_bounds__(kWaves * kWave)
     __attribute__((amdgpu_waves_per_eu(dense_cu_waves(K) / 4))) dense_kernel(DenseParams P)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = lane_of();
     u64* stacks = reinterpret_cast<u64*>(smem + 1024 * (n_tiles(K) + n_pairs(K)) + 8 * 64 * K * K);
-    int32_t* item = reinterpret_cast<int32_t*>(stacks + dense_waves(K) * dense_stack_words(K, P.max_k));
+    int32_t* item = reinterpret_cast<int32_t*>(stacks + kWaves * dense_stack_words(K, P.max_k));
     int* shared = item + kItFields * kMaxClaim;      // [0] branch counter, [1] first item of the run
     u64 acc = 0ull;
     int cur = -1;
     int shard = blockIdx.x % kClaimShards;
     bool fresh = true;
-    const int acc_slot = (int)((blockIdx.x * dense_waves(K) + threadIdx.x / kWave) & (kAccSlots - 1)) * kAccStride;
+    const int acc_slot = (int)((blockIdx.x * kWaves + threadIdx.x / kWave) & (kAccSlots - 1)) * kAccStride;
     for (;;) {
         if (threadIdx.x < kWave) {
             const int g = claim_run(P.items, blockIdx.x, gridDim.x, shard, fresh);
@@ -484,7 +491,7 @@ __global__ void __launch_bounds__(dense_waves(K) * kWave)
             const u64* src = q.rows.hrows + field(kItRowsOff);
             const bool vertex = field(kItKind) == kItemDenseVertex;
             const int a0 = field(kItArc0);
-            const u64 s = dense_item<K>(src, W, field(kItDegree), r, vertex ? q.k - 1 : q.k - 2, pw & 0xffff, pw >> 16,
+            const u64 s = dense_item<K, kWaves>(src, W, field(kItDegree), r, vertex ? q.k - 1 : q.k - 2, pw & 0xffff, pw >> 16,
                                         P.max_k, smem, stacks, shared, vertex && q.per_arc ? q.per_arc + a0 : nullptr,
                                         q.rows.hinv + a0);
             acc += s;            // a lane adds at most 2^28 per mask's children: 2^36 of them before it could wrap
@@ -498,7 +505,7 @@ __global__ void __launch_bounds__(dense_waves(K) * kWave)
     if (cur >= 0) wave_flush(acc, 0, P.items.queries[cur].acc + acc_slot, P.items.queries[cur].overflow);
 }
 
-template <int K>
+template <int K, int kWaves>
 static hipError_t launch_class(const CountLaunch& cl, int cus, int32_t base, hipStream_t s)
 {
     const int space = kDenseClasses - K;
@@ -514,15 +521,15 @@ static hipError_t launch_class(const CountLaunch& cl, int cus, int32_t base, hip
     P.progress = cl.progress;
     P.progress_base = base;
     // as many workgroups as LDS and registers hold, no more than items
-    const int by_lds = 160 * 1024 / lds, by_regs = dense_cu_waves(K) / dense_waves(K);
+    const int by_lds = 160 * 1024 / lds, by_regs = dense_cu_waves(K) / kWaves;
     int64_t blocks = (int64_t)cus * (by_lds < by_regs ? by_lds : by_regs);
     if (blocks > n) blocks = n;
     set_runs(P.items, blocks, kDenseClaim);
     if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)dense_kernel<K>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void*)dense_kernel<K, kWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
-    dense_kernel<K><<<(unsigned)blocks, dense_waves(K) * kWave, lds, s>>>(P);
+    dense_kernel<K, kWaves><<<(unsigned)blocks, kWaves * kWave, lds, s>>>(P);
     return hipGetLastError();
 }
 
@@ -533,17 +540,19 @@ hipError_t launch_dense(const CountLaunch& cl, hipStream_t s)
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     int32_t base = 0;
-    if (e == hipSuccess) e = launch_class<6>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<6, dense_waves(6, 6)>(cl, cus, base, s);
     base += cl.space_items[0];
-    if (e == hipSuccess) e = launch_class<5>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<5, dense_waves(5, 6)>(cl, cus, base, s);
     base += cl.space_items[1];
-    if (e == hipSuccess) e = launch_class<4>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<4, dense_waves(4, 6)>(cl, cus, base, s);
     base += cl.space_items[2];
-    if (e == hipSuccess) e = launch_class<3>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<3, dense_waves(3, 6)>(cl, cus, base, s);
     base += cl.space_items[3];
-    if (e == hipSuccess) e = launch_class<2>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<2, dense_waves(2, 6)>(cl, cus, base, s);
     base += cl.space_items[4];
-    if (e == hipSuccess) e = launch_class<1>(cl, cus, base, s);
+    if (e == hipSuccess)
+        e = cl.max_k <= 6 ? launch_class<1, dense_waves(1, 6)>(cl, cus, base, s)
+                          : launch_class<1, dense_waves(1, 7)>(cl, cus, base, s);
     return e;
 }
 

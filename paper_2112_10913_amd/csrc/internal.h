@@ -207,13 +207,16 @@ __host__ __device__ inline bool dense_vertex(int d, int k)
     return (k == 4 || k == 5) && d > kLightMaxDeg && d <= kDenseMax;
 }
 
-// Parts of a dense arc (every P-th first-level branch): the workgroup shares
-// the arc's first level already, so parts only shorten the tail of deep counts.
+// Parts of a dense arc (every P-th first-level branch).  One to four waves
+// share an arc, so counts of k >= 8 are cut finely for the launch's tail
+// (Chung-Lu 2^14, k = 9: c / 8 parts 7.3 ms, c / 4 6.5 ms); at k = 7 the
+// parts' repeated layout costs more than it saves (R-MAT 16: c / 64 21.6 ms,
+// c / 24 22.2 ms).
 __host__ __device__ inline int dense_parts(int c, int k, int pct)
 {
     if (k <= 6) return 1;
     if (k == 7) return scale_parts(c / 64, pct);
-    return scale_parts(c / 8 < 32 ? c / 8 : 32, pct);
+    return scale_parts(c / 4 < 64 ? c / 4 : 64, pct);
 }
 
 // Parts a light vertex (out-degree d <= 64, its subgraph one word per row)

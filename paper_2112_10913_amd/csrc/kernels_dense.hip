@@ -8,29 +8,30 @@
 // ends, k - 5 levels down, in triangle counts of induced subgraphs
 //     T(M) = sum over x, y in M, A[x][y] = 1, of |row x & row y & M|,
 // a matrix product: P = A_M A_M^T summed where A is 1, with A_M the rows of M
-// masked by M.  One workgroup lays an arc's subgraph out in LDS once, and its
-// waves count T(M) for every M the search reaches.
+// masked by M.  A is the same for every M of an item, so the products of all
+// its masks are added up in the accumulators, and summed where A is 1 once.
 //
 //  - Layout.  The c candidates in the order of the DAG (sorted rows, packed
 //    like everywhere by parallel bit extract), so A is strictly upper
-//    triangular; in three forms: bit rows (the search), 4-bit operand tiles
-//    (1.0 is 0b0010 in e2m1) of 32 rows x 64 bits in the operand order of
-//    v_mfma_f32_32x32x64_f8f6f4, and for every pair of 32-tiles the bytes
-//    A[x][y] in the order of the accumulators.
-//  - T(M).  For 32-row tiles x <= y from M's first tile on: the x operand is
-//    the tile AND M's 4-bit pattern, with the rows outside M cleared; the y
-//    operand is the plain tile; the products are small integers (at most
-//    254), exact in fp32.  Sixteen v_cvt_pk_u8_f32 pack the accumulators to
-//    bytes and four v_dot4_u32_u8 take them times A; columns outside M are
-//    dropped last.  Tiles before M's first and below the diagonal are never
-//    touched: a mask that starts at tile t of n costs (n - t)(n - t + 1) / 2
-//    tile pairs, whatever its size.
-//  - A mask's own pattern is its last vertex's tile row AND its parent's, so
-//    nothing is expanded from bits inside the search.
+//    triangular; in two forms in LDS: bit rows (the search), and 4-bit
+//    operand tiles (1.0 is 0b0010 in e2m1) of 32 rows x 64 bits in the
+//    operand order of v_mfma_f32_32x32x64_f8f6f4.
+//  - A mask.  For 32-row tiles x <= y from M's first tile on: both operands
+//    are the tile AND M's 4-bit pattern, with the rows outside M cleared (one
+//    v_bitop3 per register); a tile serves as x and as y.  A mask's own
+//    pattern is its last vertex's tile row AND its node's, so nothing is
+//    expanded from bits inside the search.  A mask that starts at tile t of n
+//    costs (n - t)(n - t + 1) / 2 tile pairs, whatever its size.
+//  - Accumulators hold small integers, exact in fp32: they are summed before
+//    any could reach 2^20.
 //
-// What bounds it: VALU issue, 20 instructions per tile pair (80 of its about
-// 150 cycles), then LDS reads (1 KB per operand tile and per byte tile); the
-// products themselves take 32 cycles per 32 x 32 x 64.
+// What bounds it: latency and VALU issue about evenly with the matrix cores
+// (R-MAT 20, k = 6, two row words: 300 cycles per mask and SIMD, of which 175
+// are products of 32 cycles per 32 x 32 x 64, with two waves of 255 registers
+// per SIMD), and for small subgraphs their layout (a third of the time for
+// two words).  With every mask's products packed to bytes and summed on their
+// own, 20 VALU instructions per tile pair, R-MAT 20, k = 6 took 165 ms and
+// R-MAT 16, k = 7 32.7 ms; now 96 and 21.6 ms.
 #include "items.h"
 #include "wave.h"
 
@@ -38,19 +39,14 @@ namespace citron {
 
 namespace {
 
-// Waves of a workgroup, and on a CU at most by registers (64 to 185 of the 512
-// a SIMD lane has).  Two and three row words leave LDS for several workgroups
-// of four waves on a CU (two waves for two words: 41 -> 43 ms); larger
-// subgraphs share a workgroup's tiles among more waves.  One-word subgraphs
-// are packed by one wave, and at k <= 6 searched in microseconds, so there
-// each wave has its own (R-MAT 20, k = 6: their 24 ms fell to 18 against four
-// waves and their barriers); deeper searches are worth sharing (R-MAT 16,
-// k = 7: 33.3 ms against 32.7).
-__host__ __device__ constexpr int dense_waves(int K, int max_k)
-{
-    return K == 1 ? (max_k <= 6 ? 1 : 4) : (K <= 3 ? 4 : (K == 5 ? 12 : 8));
-}
-__host__ __device__ constexpr int dense_cu_waves(int K) { return K == 1 ? 28 : (K == 2 ? 20 : (K <= 4 ? 16 : (K == 5 ? 12 : 8))); }
+// Waves of a workgroup, and on a CU at most by registers (100 for one row
+// word, else up to 256 of the 512 a SIMD lane has).  A workgroup of one wave
+// waits at no barrier, so up to three words, where LDS holds all eight waves'
+// subgraphs, each wave has an item of its own (two words with 1, 2 and 4
+// waves: 22.1, 26.6 and 34.2 ms of R-MAT 20, k = 6; three words with 2 and 4:
+// 28.9 and 31.5 ms; four with 4 and 8: 14.8 and 19.4 ms).
+__host__ __device__ constexpr int dense_waves(int K) { return K <= 3 ? 1 : (K == 4 ? 2 : 4); }
+__host__ __device__ constexpr int dense_cu_waves(int K) { return K == 1 ? 16 : 8; }
 constexpr int kDenseClaim = 8;              // items a workgroup claims at once, at most
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -71,23 +67,43 @@ __host__ __device__ constexpr int tile_base(int K, int t)
     return 2 * (t >> 1) * K - (t >> 1) * ((t >> 1) - 1) + (t & 1) * (K - (t >> 1));
 }
 __host__ __device__ constexpr int n_tiles(int K) { return tile_base(K, 2 * K); }
-// byte tiles of row-tile pairs x <= y
-__host__ __device__ constexpr int pair_base(int K, int x) { return x * 2 * K - x * (x - 1) / 2; }
-__host__ __device__ constexpr int n_pairs(int K) { return K * (2 * K + 1); }
-static_assert(tile_base(4, 8) == 20 && n_pairs(4) == 36, "upper triangles of 8 x 4 and 8 x 8 tiles");
-static_assert(1024 * (n_tiles(6) + n_pairs(6)) + 8 * 64 * 36 + 8 * dense_waves(6, 32) * 26 * 12 + 2048 <= 160 * 1024,
+static_assert(tile_base(4, 8) == 20, "upper triangle of 8 x 4 tiles");
+static_assert(1024 * n_tiles(6) + 8 * 64 * 36 + 8 * dense_waves(6) * 26 * 12 + 2048 <= 160 * 1024,
               "the largest instance fits LDS at k = 32");
 
-// LDS of a workgroup: [operand tiles 1 KB each][byte tiles 1 KB each][bit
-// rows][stacks: per wave, levels x (mask, rest)][items][branch counter].
+// The tile pairs of a pass over an item's masks: K = 1 and 2 hold all of
+// theirs in accumulators (3 and 10 of 16 registers) at once; larger
+// subgraphs go over the masks once per block of at most 10, what 256
+// registers hold beside the operands (blocks of up to 11 spill and cost 41
+// instead of 32 ms for three words and 53 instead of 19 for four).
+struct Block {
+    int x0, x1, y0, y1;
+};
+constexpr int n_passes(int K) { return K <= 2 ? 1 : (K == 3 ? 3 : (K == 4 ? 5 : (K == 5 ? 8 : 11))); }
+constexpr Block block_of(int K, int p)
+{
+    constexpr Block k3[] = {{0, 2, 0, 4}, {0, 2, 4, 6}, {2, 6, 2, 6}};
+    constexpr Block k4[] = {{0, 2, 0, 4}, {0, 2, 4, 8}, {2, 4, 2, 6}, {2, 4, 6, 8}, {4, 8, 4, 8}};
+    constexpr Block k5[] = {{0, 2, 0, 4}, {0, 2, 4, 7}, {0, 2, 7, 10}, {2, 4, 2, 6},
+                            {2, 4, 6, 10}, {4, 6, 4, 7}, {4, 6, 7, 10}, {6, 10, 6, 10}};
+    constexpr Block k6[] = {{0, 2, 0, 4}, {0, 2, 4, 8}, {0, 2, 8, 12}, {2, 4, 2, 6}, {2, 4, 6, 10}, {2, 4, 10, 12},
+                            {4, 6, 4, 8}, {4, 6, 8, 12}, {6, 8, 6, 9}, {6, 8, 9, 12}, {8, 12, 8, 12}};
+    return K <= 2 ? Block{0, 2 * K, 0, 2 * K} : (K == 3 ? k3[p] : (K == 4 ? k4[p] : (K == 5 ? k5[p] : k6[p])));
+}
+// masks a pass adds up before it sums: an accumulator stays below 2^20, so
+// that sixteen of them are exact in fp32
+constexpr int max_masks(int K) { return (1 << 20) / (64 * K); }
+
+// LDS of a workgroup: [operand tiles 1 KB each][bit rows][stacks: per wave,
+// levels x (mask, rest)][items][first item of the run, branch counters].
 __host__ __device__ constexpr int dense_stack_words(int K, int max_k)
 {
     return (max_k > 6 ? max_k - 6 : 0) * 2 * K;
 }
 __host__ __device__ constexpr int dense_lds_bytes(int K, int max_k)
 {
-    return 1024 * (n_tiles(K) + n_pairs(K)) + 8 * 64 * K * K +
-           8 * dense_waves(K, max_k) * dense_stack_words(K, max_k) + 4 * kItFields * kMaxClaim + 16;
+    return 1024 * n_tiles(K) + 8 * 64 * K * K +
+           8 * dense_waves(K) * dense_stack_words(K, max_k) + 4 * kItFields * kMaxClaim + 64;
 }
 
 __device__ __forceinline__ u64 uniform64(u64 v)
@@ -115,7 +131,6 @@ __device__ __forceinline__ int spread4(unsigned b)
 template <int K>
 struct Dense {
     const v4i* tiles;        // operand tiles
-    const v4i* bytes;        // byte tiles
     const u64* rows;         // bit rows, K words each
     int nt;                  // 32-row tiles in use, ceil(c / 32)
 
@@ -125,30 +140,45 @@ struct Dense {
         for (int w = 0; w < K; ++w) r[w] = uniform64(rows[x * K + w]);
     }
 
-    // T(M), this lane's share.  pat: M's 4-bit patterns (per bit tile, the
-    // lane's half).  kSplit: the row tiles x = first mod kSplit only.
-    template <int kSplit>
-    __device__ __forceinline__ unsigned triangles(const u64 (&M)[K], const v4i (&pat)[K], int first) const
+    // A[x tile][y tile] in the order of the accumulators: 4 q + j of this lane
+    // is row 8 q + 4 half + j of tile x, column l of tile y.
+    __device__ __forceinline__ unsigned bit(int x, int y, int i) const
     {
         const int lane = lane_of();
-        unsigned sum = 0, s[2 * K];      // per row tile y: its columns outside M are dropped at the end
+        const unsigned* rows32 = reinterpret_cast<const unsigned*>(rows) + 4 * (lane >> 5) * K * 2;
+        return (rows32[(32 * x + 8 * (i >> 2) + (i & 3)) * K * 2 + y] >> (lane & 31)) & 1u;
+    }
+    __device__ __forceinline__ v4i adjacency(int x, int y) const
+    {
+        v4i v;
 #pragma unroll
-        for (int y = 0; y < 2 * K; ++y) s[y] = 0;
+        for (int q = 0; q < 4; ++q)
+            v[q] = (int)(bit(x, y, 4 * q) | bit(x, y, 4 * q + 1) << 8 | bit(x, y, 4 * q + 2) << 16 |
+                         bit(x, y, 4 * q + 3) << 24);
+        return v;
+    }
+
+    // The whole subgraph's triangles, this lane's share: the row tiles x =
+    // first mod the waves only.  With one mask there is nothing to add up, so
+    // the products go to bytes (sixteen v_cvt_pk_u8_f32 and four
+    // v_dot4_u32_u8 per tile pair).
+    __device__ __forceinline__ unsigned triangles(int first) const
+    {
+        const int lane = lane_of();
+        unsigned sum = 0;
 #pragma unroll
         for (int x = 0; x < 2 * K; ++x) {
-            const unsigned mx = (unsigned)(M[x >> 1] >> (32 * (x & 1)));
-            if (mx == 0u || (kSplit > 1 && x % kSplit != first)) continue;
-            const int in = lanes32(mx) ? -1 : 0;
+            if (x >= nt || x % dense_waves(K) != first) continue;
             v4i a[K];
 #pragma unroll
             for (int z = 0; z < K; ++z) {
                 if (z < (x >> 1)) continue;
-                a[z] = tiles[(tile_base(K, x) + z - (x >> 1)) * kWave + lane] & pat[z] & in;
+                a[z] = tiles[(tile_base(K, x) + z - (x >> 1)) * kWave + lane];
             }
 #pragma unroll
             for (int y = 0; y < 2 * K; ++y) {
                 if (y < x || y >= nt) continue;
-                const v4i m = bytes[(pair_base(K, x) + y - x) * kWave + lane];
+                const v4i m = adjacency(x, y);
                 // chains of at most four bit tiles: with bit y itself never
                 // set, a product is then at most 255, what a byte holds
 #pragma unroll
@@ -170,134 +200,178 @@ struct Dense {
                         unsigned w = 0;
 #pragma unroll
                         for (int j = 0; j < 4; ++j) w = __builtin_amdgcn_cvt_pk_u8_f32(p[4 * q + j], j, w);
-                        s[y] = __builtin_amdgcn_udot4(w, (unsigned)m[q], s[y], false);
+                        sum = __builtin_amdgcn_udot4(w, (unsigned)m[q], sum, false);
                     }
                 }
             }
         }
-#pragma unroll
-        for (int y = 0; y < 2 * K; ++y) {
-            const unsigned my = (unsigned)(M[y >> 1] >> (32 * (y & 1)));
-            sum += lanes32(my) ? s[y] : 0u;
-        }
         return sum;
     }
 
-    // Sum of T(P & row x) over x in R (R within P).  all: P is the whole
-    // subgraph (its pattern is all ones).
-    __device__ __forceinline__ u64 last_levels(const u64 (&P)[K], u64 (&R)[K], bool all) const
+    // The pattern of all of P's bits (per bit tile, the lane's half).
+    __device__ __forceinline__ void spread(const u64 (&P)[K], v4i (&pp)[K]) const
     {
-        const int lane = lane_of();
-        const int half = lane >> 5;
-        v4i pp[K];
+        const int half = lane_of() >> 5;
 #pragma unroll
         for (int z = 0; z < K; ++z) {
             const unsigned b = half ? (unsigned)(P[z] >> 32) : (unsigned)P[z];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) pp[z][i] = all ? 0x22222222 : spread4(((b >> (8 * i)) & 0xffu) << 1);
+            for (int i = 0; i < 4; ++i) pp[z][i] = spread4(((b >> (8 * i)) & 0xffu) << 1);
         }
-        unsigned sum = 0;      // at most 384 masks of 78 tile pairs, 2 x 16 x 255 each: below 2^28
+    }
+};
+
+// The accumulators of one pass: tile pairs x <= y with x in [x0, x1), y in
+// [y0, y1).
+template <int K, int kPass>
+struct Pass {
+    static constexpr Block B = block_of(K, kPass);
+    static constexpr int index(int x, int y)
+    {
+        int n = 0;
+        for (int i = B.x0; i < x; ++i)
+            for (int j = B.y0; j < B.y1; ++j) n += j >= i;
+        for (int j = B.y0; j < y; ++j) n += j >= x;
+        return n;
+    }
+    static constexpr int kPairs = index(B.x1, B.y0);
+    static constexpr int kFirst = B.x0 >> 1;      // first bit tile of any operand
+    v16f acc[kPairs];
+
+    __device__ __forceinline__ void clear()
+    {
 #pragma unroll
-        for (int w = 0; w < K; ++w) {
-            u64 r = R[w];
-            while (r) {
-                const int x = w * 64 + __builtin_ctzll(r);
-                r &= r - 1;
-                u64 M[K];
-                row(x, M);
-                int c = 0;
-#pragma unroll
-                for (int i = 0; i < K; ++i) {
-                    M[i] &= P[i];
-                    c += __popcll(M[i]);
-                }
-                if (c < 3) continue;
-                v4i pat[K];
-#pragma unroll
-                for (int z = 0; z < K; ++z) {
-                    if (z < w) {
-                        pat[z] = v4i{0, 0, 0, 0};     // row x starts after bit x
-                        continue;
-                    }
-                    pat[z] = tiles[(tile_base(K, x >> 5) + z - w) * kWave + half * 32 + (x & 31)] & pp[z];
-                }
-                sum += triangles<1>(M, pat, 0);
-            }
-        }
-        return (u64)sum;
+        for (int i = 0; i < kPairs; ++i) acc[i] = v16f{};
     }
 
-    // Depth-first search below a node with mask M, r >= 4 vertices still to
-    // choose; this lane's share.  stack: (r - 4) levels of (mask, rest).
-    __device__ __forceinline__ u64 search(const u64 (&M0)[K], int r, u64* stack) const
+    static constexpr bool kHeld = K <= 2;      // the operand tiles, masked by the node's pattern, stay in registers
+    v4i held[kHeld ? n_tiles(K) : 1];
+
+    // Adds A_M A_M^T of this pass's tile pairs for the masks M = N & row x,
+    // x in R.  Tile by tile of x: rows of tile t have no bit before it, so
+    // the code for each first tile is straight, operand reads first.
+    template <int kTile = B.x0>
+    __device__ __forceinline__ void add(const Dense<K>& D, const u64 (&N)[K], const v4i (&pp)[K], const u64 (&R)[K])
+    {
+        if constexpr (kTile < B.x1) {
+            if constexpr (kHeld && kTile == B.x0)
+#pragma unroll
+                for (int x = 0; x < 2 * K; ++x)
+#pragma unroll
+                    for (int z = x >> 1; z < K; ++z) {
+                        const int f = tile_base(K, x) + z - (x >> 1);
+                        held[f] = D.tiles[f * kWave + lane_of()] & pp[z];
+                    }
+            for (int t = kTile == B.x0 ? 0 : kTile; t <= kTile; ++t) {
+                unsigned r = 0;
+#pragma unroll
+                for (int w = 0; w < K; ++w)
+                    if (w == (t >> 1)) r = (unsigned)(R[w] >> (32 * (t & 1)));
+                if (r) add_tile<kTile>(D, N, pp, t, r);
+            }
+            add<kTile + 1>(D, N, pp, R);
+        }
+    }
+
+    template <int kTile>
+    __device__ __forceinline__ void add_tile(const Dense<K>& D, const u64 (&N)[K], const v4i (&pp)[K], int t, unsigned r)
+    {
+        constexpr int X = B.x1 - B.x0;
+        constexpr int kY = kTile > B.y0 ? kTile : B.y0;
+        constexpr int kZ = kTile >> 1;             // first bit tile
+        const int lane = lane_of();
+        const u64* rows = D.rows + 32 * t * K;
+        const v4i* pats = D.tiles + (tile_base(K, t) - (t >> 1)) * kWave + (lane & 32);
+        u64 row[K];
+        v4i rpat[K];
+        int x = __builtin_ctz(r);
+        auto fetch = [&] {
+#pragma unroll
+            for (int z = kZ; z < K; ++z) {
+                row[z] = rows[x * K + z];
+                rpat[z] = pats[z * kWave + x];
+            }
+        };
+        fetch();
+        for (;;) {
+            u64 M[K];
+            v4i pat[K];
+#pragma unroll
+            for (int z = kZ; z < K; ++z) {
+                M[z] = uniform64(row[z]) & N[z];
+                pat[z] = kHeld ? rpat[z] : rpat[z] & pp[z];
+            }
+            // the next row's words and pattern are read beside the products
+            r &= r - 1;
+            if (r) x = __builtin_ctz(r);
+            fetch();
+            v4i ax[X][K];
+            auto operand = [&](int x, int z0, v4i (&a)[K]) {
+                const int in = lanes32((unsigned)(M[x >> 1] >> (32 * (x & 1)))) ? -1 : 0;
+#pragma unroll
+                for (int z = 0; z < K; ++z)
+                    if (z >= z0) {
+                        const int f = tile_base(K, x) + z - (x >> 1);
+                        a[z] = (kHeld ? held[kHeld ? f : 0] : D.tiles[f * kWave + lane]) & pat[z] & in;
+                    }
+            };
+            // x tiles that are none of the y tiles
+#pragma unroll
+            for (int x = kTile; x < B.x1; ++x)
+                if (x < kY) operand(x, kY >> 1, ax[x - B.x0]);
+#pragma unroll
+            for (int y = kY; y < B.y1; ++y) {
+                v4i own[K];
+                v4i (&ay)[K] = y < B.x1 ? ax[y < B.x1 ? y - B.x0 : 0] : own;
+                operand(y, y >> 1, ay);
+#pragma unroll
+                for (int z = 0; z < K; ++z) {
+                    if (z < (y >> 1)) continue;
+#pragma unroll
+                    for (int x = kTile; x < B.x1; ++x) {
+                        if (x > y) continue;
+                        v16f& p = acc[index(x, y)];
+                        const v4i a = ax[x - B.x0][z], b = ay[z];
+                        const v8i a8 = {a[0], a[1], a[2], a[3], 0, 0, 0, 0};
+                        const v8i b8 = {b[0], b[1], b[2], b[3], 0, 0, 0, 0};
+                        p = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, p, 4, 4, 0, 0, 0, 0);
+                    }
+                }
+            }
+            if (!r) break;
+        }
+    }
+
+    // The accumulators where A is 1, this lane's share.
+    __device__ __forceinline__ u64 sum(const Dense<K>& D) const
     {
         const int lane = lane_of();
-        u64 sum = 0;
-        u64 M[K], R[K];
+        unsigned s = 0;          // at most 10 pairs x 16 x 2^20
 #pragma unroll
-        for (int w = 0; w < K; ++w) M[w] = R[w] = M0[w];
-        if (r == 4) return last_levels(M, R, false);
-        int t = 0;             // levels on the stack; r - t vertices to choose at this node
-        for (;;) {
-            int x = -1;
+        for (int x = B.x0; x < B.x1; ++x) {
 #pragma unroll
-            for (int w = 0; w < K; ++w)
-                if (x < 0 && R[w]) {
-                    x = w * 64 + __builtin_ctzll(R[w]);
-                    R[w] &= R[w] - 1;
-                }
-            if (x < 0) {
-                if (t == 0) break;
-                --t;
+            for (int y = B.y0; y < B.y1; ++y) {
+                if (y < x || y >= D.nt) continue;
+                const v16f& p = acc[index(x, y)];
+                float f = 0.0f;
 #pragma unroll
-                for (int w = 0; w < K; ++w) {
-                    M[w] = uniform64(stack[t * 2 * K + w]);
-                    R[w] = uniform64(stack[t * 2 * K + K + w]);
-                }
-                continue;
+                for (int i = 0; i < 16; ++i) f = fmaf((float)D.bit(x, y, i), p[i], f);
+                s += (unsigned)f;
             }
-            u64 ch[K];
-            row(x, ch);
-            int c = 0;
-#pragma unroll
-            for (int w = 0; w < K; ++w) {
-                ch[w] &= M[w];
-                c += __popcll(ch[w]);
-            }
-            const int need = r - t - 1;
-            if (c < need) continue;
-            if (need == 4) {
-                u64 rest[K];
-#pragma unroll
-                for (int w = 0; w < K; ++w) rest[w] = ch[w];
-                sum += last_levels(ch, rest, false);
-                continue;
-            }
-#pragma unroll
-            for (int w = 0; w < K; ++w) {
-                if (lane == 0) {
-                    stack[t * 2 * K + w] = M[w];
-                    stack[t * 2 * K + K + w] = R[w];
-                }
-                M[w] = R[w] = ch[w];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            ++t;
         }
-        return sum;
+        return (u64)s;
     }
 };
 
 // Bit rows of the subgraph of mask M (lane q holds word q, W words) over the
 // sorted rows `src`, packed to K words each: the waves take 64 rows at a
 // time.  Rows c .. 64 K - 1 are zero.
-template <int K, int kWaves>
+template <int K>
 __device__ void pack_rows(const u64* __restrict__ src, int W, u64 M, int c, u64* __restrict__ dst)
 {
     const int lane = lane_of();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    for (int a0 = wid * kWave; a0 < 64 * K; a0 += kWaves * kWave) {
+    for (int a0 = wid * kWave; a0 < 64 * K; a0 += dense_waves(K) * kWave) {
         const int a = a0 + lane;
         const bool valid = a < c;
         const int xa = a0 < c ? wave_select(M, a, W) : 0;
@@ -322,9 +396,9 @@ __device__ void pack_rows(const u64* __restrict__ src, int W, u64 M, int c, u64*
     }
 }
 
-// Operand and byte tiles of the bit rows.
-template <int K, int kWaves>
-__device__ void build_tiles(const u64* __restrict__ rows, v4i* __restrict__ tiles, v4i* __restrict__ bytes, int nt)
+// Operand tiles of the bit rows.
+template <int K>
+__device__ void build_tiles(const u64* __restrict__ rows, v4i* __restrict__ tiles)
 {
     const int lane = lane_of();
     const int wid = threadIdx.x / kWave;
@@ -333,148 +407,250 @@ __device__ void build_tiles(const u64* __restrict__ rows, v4i* __restrict__ tile
     int f = 0;
     for (int x = 0; x < 2 * K; ++x)
         for (int z = x >> 1; z < K; ++z, ++f) {
-            if (f % kWaves != wid) continue;
+            if (f % dense_waves(K) != wid) continue;
             const unsigned b = rows32[((32 * x + l) * K + z) * 2 + half];
             v4i v;
 #pragma unroll
             for (int i = 0; i < 4; ++i) v[i] = spread4(((b >> (8 * i)) & 0xffu) << 1);
             tiles[f * kWave + lane] = v;
         }
-    for (int x = 0; x < nt; ++x)
-        for (int y = x; y < nt; ++y) {
-            const int p = pair_base(K, x) + y - x;
-            if (p % kWaves != wid) continue;
-            // accumulator 4 q + j of this lane: row 8 q + 4 half + j of tile x, column l of tile y
-            v4i v;
+}
+
+// Takes the lowest bit of R, or -1.
+template <int K>
+__device__ __forceinline__ int take(u64 (&R)[K])
+{
+    int x = -1;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                unsigned d = 0;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const unsigned b = rows32[(32 * x + 8 * q + 4 * half + j) * K * 2 + y];
-                    d |= ((b >> l) & 1u) << (8 * j);
-                }
-                v[q] = (int)d;
-            }
-            bytes[p * kWave + lane] = v;
+    for (int w = 0; w < K; ++w)
+        if (x < 0 && R[w]) {
+            x = w * 64 + __builtin_ctzll(R[w]);
+            R[w] &= R[w] - 1;
         }
+    return x;
+}
+
+// The nodes with four vertices to choose that one wave comes to, one after
+// the other.
+template <int K>
+struct Nodes {
+    u64 N[K], R[K];      // the node, and its rows to add
+    v4i pp[K];           // its pattern
+    int t;               // levels on the stack
+    bool started;
+
+    __device__ __forceinline__ void start(int c)
+    {
+        t = -1;
+        started = false;
+#pragma unroll
+        for (int w = 0; w < K; ++w) {
+            R[w] = 0;
+            const int rem = c - 64 * w;
+            N[w] = rem >= 64 ? ~0ull : (rem > 0 ? (1ull << rem) - 1ull : 0ull);
+            pp[w] = v4i{0x22222222, 0x22222222, 0x22222222, 0x22222222};
+        }
+    }
+
+    __device__ __forceinline__ bool next(const Dense<K>& D, int c, int need, int part, int P, int wid, u64* stack,
+                                         int* branch, bool per_arc)
+    {
+        const int lane = lane_of();
+        auto claim = [&] {
+            int j = 0;
+            if (lane == 0) j = atomicAdd(branch, 1);
+            return part + P * __builtin_amdgcn_readfirstlane(j);
+        };
+        if (need == 4) {
+            if (per_arc) {
+                const int x = claim();
+#pragma unroll
+                for (int w = 0; w < K; ++w) R[w] = (x >> 6) == w ? 1ull << (x & 63) : 0ull;
+                return x < c;
+            }
+            if (started) return false;
+            started = true;
+            const int stride = P * dense_waves(K);
+#pragma unroll
+            for (int w = 0; w < K; ++w) R[w] = __ballot((64 * w + lane) % stride == part + P * wid) & N[w];
+            return true;
+        }
+        for (;;) {
+            // stack[t]: (node, its branches left); r vertices to choose at
+            // the node that x is taken from
+            int r = need, x, n = 0;
+            u64* top = stack + t * 2 * K;
+            if (t < 0) {
+                x = claim();
+                if (x >= c) return false;
+                D.row(x, N);
+            } else {
+                u64 S[K];
+#pragma unroll
+                for (int w = 0; w < K; ++w) S[w] = uniform64(top[K + w]);
+                x = take<K>(S);
+                if (x < 0) {
+                    --t;
+                    continue;
+                }
+                r = need - 1 - t;
+                D.row(x, N);
+#pragma unroll
+                for (int w = 0; w < K; ++w) {
+                    N[w] &= uniform64(top[w]);
+                    if (lane == 0) top[K + w] = S[w];
+                }
+            }
+#pragma unroll
+            for (int w = 0; w < K; ++w) n += __popcll(N[w]);
+            const bool deeper = n >= r - 1 && r > 5;
+            if (deeper) {
+                ++t;
+#pragma unroll
+                for (int w = 0; w < K; ++w)
+                    if (lane == 0) stack[t * 2 * K + w] = stack[t * 2 * K + K + w] = N[w];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (n < r - 1 || deeper) continue;
+#pragma unroll
+            for (int w = 0; w < K; ++w) R[w] = N[w];
+            D.spread(N, pp);
+            return true;
+        }
+    }
+};
+
+// One wave's share of one pass, and of those after it.  need == 4: the masks
+// are the rows x = part mod P, dealt to the waves in turn (claimed one by one
+// where each row's own sum is wanted).  Deeper: first-level branches x = part
+// mod P are claimed, and a depth-first search below each comes to the nodes
+// whose rows are the masks; stack: need - 5 levels of (node, branches left).
+template <int K, int kPass>
+__device__ __forceinline__ void dense_passes(const Dense<K>& D, int c, int need, int part, int P, int wid, u64* stack,
+                                             int* branch, u64* per_arc, const uint16_t* inv, u64& sum)
+{
+    if constexpr (kPass < n_passes(K)) {
+        using Acc = Pass<K, kPass>;
+        if (Acc::B.x0 < D.nt && Acc::B.y0 < D.nt) {
+            const int lane = lane_of();
+            Nodes<K> node;
+            node.start(c);
+            bool more = true;
+            do {
+                Acc A;
+                A.clear();
+                int masks = 0, last = 0;
+                for (;;) {
+                    more = node.next(D, c, need, part, P, wid, stack, branch + kPass, per_arc != nullptr);
+                    if (!more) break;
+                    A.add(D, node.N, node.pp, node.R);
+#pragma unroll
+                    for (int w = 0; w < K; ++w) masks += __popcll(node.R[w]);
+                    if (per_arc) last = take<K>(node.R);
+                    if (per_arc || masks > max_masks(K) - 64 * K) break;
+                }
+                const u64 s = A.sum(D);
+                sum += s;
+                if (per_arc && more) {
+                    const u64 v = wave_sum_u64(s);
+                    if (lane == 0 && v) atomicAdd(per_arc + inv[last], v);
+                }
+            } while (more);
+        }
+        dense_passes<K, kPass + 1>(D, c, need, part, P, wid, stack, branch, per_arc, inv, sum);
+    }
 }
 
 // One item: an arc's subgraph (mask row r of its source's rows, packed) or a
 // whole vertex's (its rows as they are), laid out once; then its first level
 // is shared among the waves.  need: vertices to choose from the subgraph, 3
 // (one triangle count, k = 4) or more.  per_arc (vertices only): counts per
-// first vertex x go to per_arc[inv[x]].  Returns this lane's
-// share of the count.
-template <int K, int kWaves>
+// first vertex x go to per_arc[inv[x]].  Returns this lane's share.
+template <int K>
 __device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, int d, int r, int need, int part, int P,
                                           int max_k, unsigned char* smem, u64* stacks, int* branch, u64* per_arc,
                                           const uint16_t* inv)
 {
     v4i* tiles = reinterpret_cast<v4i*>(smem);
-    v4i* bytes = tiles + n_tiles(K) * kWave;
-    u64* rows = reinterpret_cast<u64*>(bytes + n_pairs(K) * kWave);
+    u64* rows = reinterpret_cast<u64*>(tiles + n_tiles(K) * kWave);
     const int lane = lane_of();
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     int c = d;
-    if (threadIdx.x == 0) *branch = 0;
+    if (threadIdx.x < n_passes(K)) branch[threadIdx.x] = 0;
     if (r < 0) {
         // W = K: the vertex's class is that of its out-degree
-        for (int i = threadIdx.x; i < 64 * K * K; i += kWaves * kWave) rows[i] = i < d * K ? src[i] : 0ull;
+        for (int i = threadIdx.x; i < 64 * K * K; i += dense_waves(K) * kWave) rows[i] = i < d * K ? src[i] : 0ull;
     } else {
         const u64 M = lane < W ? src[(int64_t)r * W + lane] : 0ull;
-        c = wave_sum_small(__popcll(M));
+        c = __builtin_amdgcn_readfirstlane(wave_sum_small(__popcll(M)));
         // rows past the last candidate, and words past a row's last, read as zero
-        for (int i = threadIdx.x; i < 64 * K * K; i += kWaves * kWave) rows[i] = 0ull;
+        for (int i = threadIdx.x; i < 64 * K * K; i += dense_waves(K) * kWave) rows[i] = 0ull;
         __syncthreads();
-        pack_rows<K, kWaves>(src, W, M, c, rows);
+        pack_rows<K>(src, W, M, c, rows);
     }
     const int nt = (c + 31) >> 5;
     __syncthreads();
-    build_tiles<K, kWaves>(rows, tiles, bytes, nt);
+    build_tiles<K>(rows, tiles);
     __syncthreads();
-    const Dense<K> D{tiles, bytes, rows, nt};
-    u64 all[K];
-#pragma unroll
-    for (int w = 0; w < K; ++w) {
-        const int rem = c - 64 * w;
-        all[w] = rem >= 64 ? ~0ull : (rem > 0 ? (1ull << rem) - 1ull : 0ull);
-    }
+    const Dense<K> D{tiles, rows, nt};
     u64 sum = 0;
     if (need == 3 && !per_arc) {
-        v4i pat[K];
-#pragma unroll
-        for (int z = 0; z < K; ++z) pat[z] = v4i{0x22222222, 0x22222222, 0x22222222, 0x22222222};
-        sum = D.template triangles<kWaves>(all, pat, wid);
+        sum = D.triangles(wid);
         __syncthreads();
         return sum;
     }
-    for (;;) {
-        int j = 0;
-        if (lane == 0) j = atomicAdd(branch, 1);
-        const int x = part + P * __builtin_amdgcn_readfirstlane(j);
-        if (x >= c) break;
-        u64 s = 0;
-        if (need == 3) {
-            // per-arc counts of k = 4 want row x's own sum: lanes over its y
-            u64 rx[K];
+    if (need == 3) {
+        // per-arc counts of k = 4 want row x's own sum: lanes over its y
+        for (int x = part + P * wid; x < c; x += P * dense_waves(K)) {
+            u64 rx[K], s = 0;
             D.row(x, rx);
             for (int y = lane; y < c; y += kWave)
                 if ((rows[x * K + (y >> 6)] >> (y & 63)) & 1)
 #pragma unroll
                     for (int w = 0; w < K; ++w) s += (u64)__popcll(rx[w] & rows[y * K + w]);
-        } else if (need == 4) {
-            u64 R[K];
-#pragma unroll
-            for (int w = 0; w < K; ++w) R[w] = (x >> 6) == w ? 1ull << (x & 63) : 0ull;
-            s = D.last_levels(all, R, true);
-        } else {
-            u64 ch[K];
-            D.row(x, ch);
-            int cc = 0;
-#pragma unroll
-            for (int w = 0; w < K; ++w) cc += __popcll(ch[w]);
-            if (cc >= need - 1) s = D.search(ch, need - 1, stacks + wid * dense_stack_words(K, max_k));
-        }
-        sum += s;
-        if (per_arc) {
+            sum += s;
             const u64 t = wave_sum_u64(s);
             if (lane == 0 && t) atomicAdd(per_arc + inv[x], t);
         }
+        __syncthreads();
+        return sum;
     }
+    u64* stack = stacks + wid * dense_stack_words(K, max_k);
+    dense_passes<K, 0>(D, c, need, part, P, wid, stack, branch, per_arc, inv, sum);
     __syncthreads();
     return sum;
 }
 
 }  // namespace
 
-template <int K, int kWaves>
-__global__ void __launch_bounds__(kWaves * kWave)
+template <int K>
+__global__ void __launch_bounds__(dense_waves(K) * kWave)
     __attribute__((amdgpu_waves_per_eu(dense_cu_waves(K) / 4))) dense_kernel(DenseParams P)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = lane_of();
-    u64* stacks = reinterpret_cast<u64*>(smem + 1024 * (n_tiles(K) + n_pairs(K)) + 8 * 64 * K * K);
-    int32_t* item = reinterpret_cast<int32_t*>(stacks + kWaves * dense_stack_words(K, P.max_k));
-    int* shared = item + kItFields * kMaxClaim;      // [0] branch counter, [1] first item of the run
+    u64* stacks = reinterpret_cast<u64*>(smem + 1024 * n_tiles(K) + 8 * 64 * K * K);
+    int32_t* item = reinterpret_cast<int32_t*>(stacks + dense_waves(K) * dense_stack_words(K, P.max_k));
+    int* shared = item + kItFields * kMaxClaim;      // first item of the run, then a branch counter per pass
     u64 acc = 0ull;
     int cur = -1;
     int shard = blockIdx.x % kClaimShards;
     bool fresh = true;
-    const int acc_slot = (int)((blockIdx.x * kWaves + threadIdx.x / kWave) & (kAccSlots - 1)) * kAccStride;
+    const int acc_slot = (int)((blockIdx.x * dense_waves(K) + threadIdx.x / kWave) & (kAccSlots - 1)) * kAccStride;
     for (;;) {
         if (threadIdx.x < kWave) {
             const int g = claim_run(P.items, blockIdx.x, gridDim.x, shard, fresh);
             const int n = g < 0 ? 0 : run_length(P.items, g);
             decode_run<kDenseClasses - K>(P.items, g, n, item);
             if (lane == 0) {
-                shared[1] = g;
+                shared[0] = g;
                 if (P.progress && g >= 0 && (((g + n - 1) ^ (g - 1)) & ~511))
                     __hip_atomic_store(P.progress, P.progress_base + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             }
         }
         __syncthreads();
-        const int g0 = __builtin_amdgcn_readfirstlane(shared[1]);
+        const int g0 = __builtin_amdgcn_readfirstlane(shared[0]);
         if (g0 < 0) break;
         const int n = run_length(P.items, g0);
         for (int j = 0; j < n; ++j) {
@@ -491,10 +667,10 @@ __global__ void __launch_bounds__(kWaves * kWave)
             const u64* src = q.rows.hrows + field(kItRowsOff);
             const bool vertex = field(kItKind) == kItemDenseVertex;
             const int a0 = field(kItArc0);
-            const u64 s = dense_item<K, kWaves>(src, W, field(kItDegree), r, vertex ? q.k - 1 : q.k - 2, pw & 0xffff, pw >> 16,
-                                        P.max_k, smem, stacks, shared, vertex && q.per_arc ? q.per_arc + a0 : nullptr,
+            const u64 s = dense_item<K>(src, W, field(kItDegree), r, vertex ? q.k - 1 : q.k - 2, pw & 0xffff, pw >> 16,
+                                        P.max_k, smem, stacks, shared + 1, vertex && q.per_arc ? q.per_arc + a0 : nullptr,
                                         q.rows.hinv + a0);
-            acc += s;            // a lane adds at most 2^28 per mask's children: 2^36 of them before it could wrap
+            acc += s;            // a lane adds below 2^28 per 2^9 masks or more
             if (q.per_arc && !vertex) {
                 const u64 t = wave_sum_u64(s);
                 if (lane == 0 && t) atomicAdd(q.per_arc + tag, t);
@@ -505,7 +681,7 @@ __global__ void __launch_bounds__(kWaves * kWave)
     if (cur >= 0) wave_flush(acc, 0, P.items.queries[cur].acc + acc_slot, P.items.queries[cur].overflow);
 }
 
-template <int K, int kWaves>
+template <int K>
 static hipError_t launch_class(const CountLaunch& cl, int cus, int32_t base, hipStream_t s)
 {
     const int space = kDenseClasses - K;
@@ -521,15 +697,15 @@ static hipError_t launch_class(const CountLaunch& cl, int cus, int32_t base, hip
     P.progress = cl.progress;
     P.progress_base = base;
     // as many workgroups as LDS and registers hold, no more than items
-    const int by_lds = 160 * 1024 / lds, by_regs = dense_cu_waves(K) / kWaves;
+    const int by_lds = 160 * 1024 / lds, by_regs = dense_cu_waves(K) / dense_waves(K);
     int64_t blocks = (int64_t)cus * (by_lds < by_regs ? by_lds : by_regs);
     if (blocks > n) blocks = n;
     set_runs(P.items, blocks, kDenseClaim);
     if (lds > 65536) {
-        hipError_t e = hipFuncSetAttribute((const void*)dense_kernel<K, kWaves>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        hipError_t e = hipFuncSetAttribute((const void*)dense_kernel<K>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
     }
-    dense_kernel<K, kWaves><<<(unsigned)blocks, kWaves * kWave, lds, s>>>(P);
+    dense_kernel<K><<<(unsigned)blocks, dense_waves(K) * kWave, lds, s>>>(P);
     return hipGetLastError();
 }
 
@@ -540,19 +716,17 @@ hipError_t launch_dense(const CountLaunch& cl, hipStream_t s)
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     int32_t base = 0;
-    if (e == hipSuccess) e = launch_class<6, dense_waves(6, 6)>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<6>(cl, cus, base, s);
     base += cl.space_items[0];
-    if (e == hipSuccess) e = launch_class<5, dense_waves(5, 6)>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<5>(cl, cus, base, s);
     base += cl.space_items[1];
-    if (e == hipSuccess) e = launch_class<4, dense_waves(4, 6)>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<4>(cl, cus, base, s);
     base += cl.space_items[2];
-    if (e == hipSuccess) e = launch_class<3, dense_waves(3, 6)>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<3>(cl, cus, base, s);
     base += cl.space_items[3];
-    if (e == hipSuccess) e = launch_class<2, dense_waves(2, 6)>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<2>(cl, cus, base, s);
     base += cl.space_items[4];
-    if (e == hipSuccess)
-        e = cl.max_k <= 6 ? launch_class<1, dense_waves(1, 6)>(cl, cus, base, s)
-                          : launch_class<1, dense_waves(1, 7)>(cl, cus, base, s);
+    if (e == hipSuccess) e = launch_class<1>(cl, cus, base, s);
     return e;
 }
 

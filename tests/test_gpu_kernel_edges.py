@@ -335,3 +335,25 @@ def test_dense_vertices_against_the_count_kernel(citron_gpu, n, p, k):
     assert citron_gpu.count_batch([h, h], [k, 6 - k + 3]) == [want, h.count_vertex_rooted(6 - k + 3)]
     assert h.work_stats(k)["word_ops"] > 0
     h.free()
+
+
+@pytest.mark.parametrize("n,k", [(67, 9), (131, 8), (195, 7), (259, 7), (323, 7), (388, 7)])
+def test_dense_items_of_more_masks_than_one_sum_holds(citron_gpu, n, k):
+    """Items whose masks are summed several times, for every number of row
+    words: a wave adds up at most 2^20 / (64 words) masks at once."""
+    from math import comb
+    g = gg.complete(n)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    assert h.count(k) == comb(n, k)
+    h.free()
+
+
+@pytest.mark.parametrize("n,p,k", [(150, 0.8, 8), (230, 0.6, 7), (300, 0.5, 7), (400, 0.4, 7)])
+def test_deep_dense_arcs_against_the_count_kernel(citron_gpu, n, p, k):
+    """Searches above the masks' nodes in subgraphs of several row words."""
+    g = gg.erdos_renyi(n, p * (n - 1), seed=n + k)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    want = h.count_vertex_rooted(k)
+    assert h.count(k) == want
+    assert h.count_per_arc(k)[0] == want
+    h.free()

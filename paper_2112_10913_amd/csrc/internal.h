@@ -227,10 +227,14 @@ __host__ __device__ inline int dense_parts(int c, int k, int pct)
 // planted 40-clique at k = 9 ran 24 of a launch's 28 ms while 88 % of the
 // wave time was idle (Chung-Lu 2^14; with 4 sub-parts and short runs 15.2 ms,
 // with 16 of them 12.3 ms, with complete nodes counted as binomials 6.4 ms).
+// At k = 6 the tail of small launches decides: 24 graphs of up to 2^13
+// vertices at k = 3..6 in one launch take 1.67 ms with d / 8 parts from
+// d = 32, 1.59 with d / 4, 1.17 with 3 parts for 24 to 31 as well, 1.27 with
+// d / 4 there too; a full chip (R-MAT 20) does not notice.
 __host__ __device__ inline int light_arcs(int d, int k, int pct)
 {
     if (k <= 5) return 1;
-    if (k == 6) return scale_parts(d >= 32 ? d / 8 : 1, pct);
+    if (k == 6) return scale_parts(d >= 32 ? d / 4 : (d >= 24 ? 3 : 1), pct);
     return scale_parts(d >= 12 ? d / 2 : 1, pct);
 }
 __host__ __device__ inline int light_subs(int d, int k)

@@ -394,7 +394,7 @@ citron_status ensure_scratch(citron_graph* g, int64_t bytes)
 }
 
 // Work items of a k-clique count (k >= 4): the dense kernel's vertices
-// (dense_vertex) in buckets of equal out-degree, or its arcs (dense_arc) in
+// (dense_vertex) in buckets of equal out-degree and its arcs (dense_arc) in
 // buckets of equal |C_uv|, largest first; then the other heavy
 // arcs with |C_uv| >= k-2 in buckets of equal |C_uv| and light vertices with
 // out-degree >= k-1 in buckets of equal out-degree, merged by cost key
@@ -436,6 +436,9 @@ citron_status ensure_buckets(citron_graph* g, int32_t k)
             if (dense_arc(c, k)) db.push_back({c, g->h_hscan[j], cnt, kItemDenseArc});
             else hb.push_back({c, g->h_hscan[j], cnt, kItemHeavyArc});
         }
+    // the dense spaces want their buckets largest first (k = 5: vertices and
+    // the arcs of larger ones)
+    std::stable_sort(db.begin(), db.end(), [](const B& a, const B& b) { return a.key > b.key; });
     // light-vertex buckets: out-degree d = 64 down to max(k-1, 2)
     for (int32_t d = kLightMaxDeg; d >= std::max(k - 1, 2); --d) {
         const int64_t cnt = v_at_least(d) - v_at_least(d + 1);

@@ -191,12 +191,17 @@ __host__ __device__ inline int arc_parts(int c, int k, int pct)
     return scale_parts(c < 16 ? 1 : (c / 8 < 32 ? c / 8 : 32), pct);
 }
 
-// Arcs of heavy vertices the dense kernel takes in a k-clique count: at least
-// two levels above the triangle level (k >= 6), so that an arc's subgraph,
-// once laid out, serves many triangle counts, and sizes whose tiles fit LDS.
+// Arcs of heavy vertices the dense kernel takes in a k-clique count: sizes
+// whose tiles fit LDS, at k >= 6, where an arc's subgraph, once laid out,
+// serves many triangle counts, and at k = 5 for the vertices above kDenseMax,
+// which dense_vertex leaves (R-MAT 20, k = 5: their arcs took 84 of 102 ms in
+// the count kernel; 28 ms in all here, build included, from 17 or 65
+// candidates on alike).  From 33, 17 and 9 candidates on: 100.9, 96 and 94.8
+// ms for R-MAT 20, k = 6; 23.2, 21.7 and 21.7 for R-MAT 16, k = 7; 4.29, 4.0
+// and 4.0 for a served mix of 48 counts.
 constexpr int kDenseMin = 17;
 constexpr int kDenseMax = 64 * kDenseClasses;
-__host__ __device__ inline bool dense_arc(int c, int k) { return k >= 6 && c >= kDenseMin && c <= kDenseMax; }
+__host__ __device__ inline bool dense_arc(int c, int k) { return k >= 5 && c >= kDenseMin && c <= kDenseMax; }
 
 // Heavy vertices the dense kernel takes whole in counts of k = 4 and 5, where
 // an arc's subgraph would serve one triangle count at most: the vertex's own

@@ -1,11 +1,12 @@
 // Dense kernel: k-clique counts of heavy arcs and vertices on the matrix cores.
 //
 // A work item is an arc u -> v with kDenseMin <= c = |C_uv| <= kDenseMax of a
-// count with k >= 6 (dense_arc), or a heavy vertex of up to kDenseMax
-// out-neighbours of a count with k = 4 or 5 (dense_vertex), whose subgraph
-// takes the place of the arc's below.  These subgraphs are dense (about 0.9 of all
-// pairs adjacent in the power-law families), and the search below an arc
-// ends, k - 5 levels down, in triangle counts of induced subgraphs
+// count with k >= 6, or k = 5 for u of more than kDenseMax out-neighbours
+// (dense_arc), or a heavy vertex of at most kDenseMax out-neighbours of a
+// count with k = 4 or 5 (dense_vertex), whose subgraph takes the place of the
+// arc's below.  These subgraphs are dense (about 0.9 of all pairs adjacent in
+// the power-law families), and the search below an arc ends, k - 5 levels
+// down, in triangle counts of induced subgraphs
 //     T(M) = sum over x, y in M, A[x][y] = 1, of |row x & row y & M|,
 // a matrix product: P = A_M A_M^T summed where A is 1, with A_M the rows of M
 // masked by M.  A is the same for every M of an item, so the products of all
@@ -565,7 +566,7 @@ __device__ __forceinline__ void dense_passes(const Dense<K>& D, int c, int need,
 // One item: an arc's subgraph (mask row r of its source's rows, packed) or a
 // whole vertex's (its rows as they are), laid out once; then its first level
 // is shared among the waves.  need: vertices to choose from the subgraph, 3
-// (one triangle count, k = 4) or more.  per_arc (vertices only): counts per
+// (one triangle count) or more.  per_arc (vertices only): counts per
 // first vertex x go to per_arc[inv[x]].  Returns this lane's share.
 template <int K>
 __device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, int d, int r, int need, int part, int P,

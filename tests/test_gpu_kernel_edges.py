@@ -357,3 +357,21 @@ def test_deep_dense_arcs_against_the_count_kernel(citron_gpu, n, p, k):
     assert h.count(k) == want
     assert h.count_per_arc(k)[0] == want
     h.free()
+
+
+@pytest.mark.parametrize("n,p", [(440, 0.97), (620, 0.75)])
+def test_arcs_of_vertices_too_large_for_a_dense_item_at_k_5(citron_gpu, n, p):
+    """k = 5 with out-degrees on both sides of 384: whole vertices below, arcs
+    above, in the same dense classes."""
+    g = gg.erdos_renyi(n, p * (n - 1), seed=n)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    assert h.info()["max_outdeg"] > 384
+    want = h.count_vertex_rooted(5)
+    assert h.count(5) == want
+    total, every = h.count_per_arc(5)
+    assert total == want
+    assert np.array_equal(every, h.count_arcs(5, np.arange(g.m)))
+    parts = [h.count_part(5, i, 4) for i in range(4)]
+    assert sum(c for c, _ in parts) == want
+    assert citron_gpu.count_batch([h, h], [5, 4]) == [want, h.count_vertex_rooted(4)]
+    h.free()

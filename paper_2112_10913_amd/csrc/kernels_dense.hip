@@ -26,13 +26,13 @@
 //  - Accumulators hold small integers, exact in fp32: they are summed before
 //    any could reach 2^20.
 //
-// What bounds it: latency and VALU issue about evenly with the matrix cores
-// (R-MAT 20, k = 6, two row words: 300 cycles per mask and SIMD, of which 175
-// are products of 32 cycles per 32 x 32 x 64, with two waves of 255 registers
-// per SIMD), and for small subgraphs their layout (a third of the time for
-// two words).  With every mask's products packed to bytes and summed on their
-// own, 20 VALU instructions per tile pair, R-MAT 20, k = 6 took 165 ms and
-// R-MAT 16, k = 7 32.7 ms; now 96 and 21.6 ms.
+// What bounds it: the matrix cores for about half of its time (R-MAT 20, k =
+// 6, two row words: 320 cycles per mask and SIMD, layout included, of which
+// the mask's tile pairs take 175 at 32 cycles per 32 x 32 x 64), with two
+// waves of 255 registers per SIMD to hide the latency of the rest, and for
+// small subgraphs their layout.  With every mask's products packed to bytes
+// and summed on their own, 20 VALU instructions per tile pair, R-MAT 20, k =
+// 6 took 165 ms and R-MAT 16, k = 7 32.7 ms; now 96 and 21.6 ms.
 #include "items.h"
 #include "wave.h"
 

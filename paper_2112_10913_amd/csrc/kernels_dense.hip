@@ -249,10 +249,10 @@ struct Pass {
     v4i held[kHeld ? n_tiles(K) : 1];
 
     // Adds A_M A_M^T of this pass's tile pairs for the masks M = N & row x,
-    // x in R.  Tile by tile of x: rows of tile t have no bit before it, so
+    // x in N, x = first mod stride.  Tile by tile of x: rows of tile t have no bit before it, so
     // the code for each first tile is straight, operand reads first.
     template <int kTile = B.x0>
-    __device__ __forceinline__ void add(const Dense<K>& D, const u64 (&N)[K], const v4i (&pp)[K], const u64 (&R)[K])
+    __device__ __forceinline__ void add(const Dense<K>& D, const u64 (&N)[K], const v4i (&pp)[K], int stride, int first)
     {
         if constexpr (kTile < B.x1) {
             if constexpr (kHeld && kTile == B.x0)
@@ -267,10 +267,11 @@ struct Pass {
                 unsigned r = 0;
 #pragma unroll
                 for (int w = 0; w < K; ++w)
-                    if (w == (t >> 1)) r = (unsigned)(R[w] >> (32 * (t & 1)));
+                    if (w == (t >> 1)) r = (unsigned)(N[w] >> (32 * (t & 1)));
+                if (stride > 1) r &= (unsigned)__ballot((32 * t + lane_of()) % stride == first);
                 if (r) add_tile<kTile>(D, N, pp, t, r);
             }
-            add<kTile + 1>(D, N, pp, R);
+            add<kTile + 1>(D, N, pp, stride, first);
         }
     }
 
@@ -435,7 +436,8 @@ __device__ __forceinline__ int take(u64 (&R)[K])
 // the other.
 template <int K>
 struct Nodes {
-    u64 N[K], R[K];      // the node, and its rows to add
+    u64 N[K];            // the node; its rows x = first mod stride are to add
+    int stride, first;
     v4i pp[K];           // its pattern
     int t;               // levels on the stack
     bool started;
@@ -444,9 +446,10 @@ struct Nodes {
     {
         t = -1;
         started = false;
+        stride = 1;
+        first = 0;
 #pragma unroll
         for (int w = 0; w < K; ++w) {
-            R[w] = 0;
             const int rem = c - 64 * w;
             N[w] = rem >= 64 ? ~0ull : (rem > 0 ? (1ull << rem) - 1ull : 0ull);
             pp[w] = v4i{0x22222222, 0x22222222, 0x22222222, 0x22222222};
@@ -464,16 +467,14 @@ struct Nodes {
         };
         if (need == 4) {
             if (per_arc) {
-                const int x = claim();
-#pragma unroll
-                for (int w = 0; w < K; ++w) R[w] = (x >> 6) == w ? 1ull << (x & 63) : 0ull;
-                return x < c;
+                first = claim();
+                stride = 1 << 20;
+                return first < c;
             }
             if (started) return false;
             started = true;
-            const int stride = P * dense_waves(K);
-#pragma unroll
-            for (int w = 0; w < K; ++w) R[w] = __ballot((64 * w + lane) % stride == part + P * wid) & N[w];
+            stride = P * dense_waves(K);
+            first = part + P * wid;
             return true;
         }
         for (;;) {
@@ -514,8 +515,6 @@ struct Nodes {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             if (n < r - 1 || deeper) continue;
-#pragma unroll
-            for (int w = 0; w < K; ++w) R[w] = N[w];
             D.spread(N, pp);
             return true;
         }
@@ -545,10 +544,10 @@ __device__ __forceinline__ void dense_passes(const Dense<K>& D, int c, int need,
                 for (;;) {
                     more = node.next(D, c, need, part, P, wid, stack, branch + kPass, per_arc != nullptr);
                     if (!more) break;
-                    A.add(D, node.N, node.pp, node.R);
+                    A.add(D, node.N, node.pp, node.stride, node.first);
 #pragma unroll
-                    for (int w = 0; w < K; ++w) masks += __popcll(node.R[w]);
-                    if (per_arc) last = take<K>(node.R);
+                    for (int w = 0; w < K; ++w) masks += __popcll(node.N[w]);
+                    last = node.first;
                     if (per_arc || masks > max_masks(K) - 64 * K) break;
                 }
                 const u64 s = A.sum(D);

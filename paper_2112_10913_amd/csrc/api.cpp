@@ -859,26 +859,27 @@ static citron_status peel_key(citron_graph* g)
     P.frontier[1] = lists + 2 * len;
     P.alive[0] = lists + 3 * len;
     P.alive[1] = lists + 4 * len;
-    P.ctl = &g->d_small->peel;
-    const PeelCtl& c = g->h_small->peel;
+    P.ctl = g->d_small->peel;
+    P.cnt = &g->d_small->peel_cnt;
     hipError_t e = launch_peel_init(g->n, P, s);
     // each launch is one phase; the host looks after every batch of them.  A
     // vertex leaves in one round, and a round is at most four phases.
-    int64_t left = 4ll * g->n + 4;
+    const int64_t most = 4ll * g->n + 4;
+    int64_t steps = 0;
     bool done = false;
-    while (e == hipSuccess && !done && left > 0) {
-        e = launch_peel_steps(P, kPeelBatch, s);
-        left -= kPeelBatch;
+    while (e == hipSuccess && !done && steps < most) {
+        e = launch_peel_steps(P, steps, kPeelBatch, s);
+        steps += kPeelBatch;
         if (e == hipSuccess)
-            e = hipMemcpyAsync(&g->h_small->peel, P.ctl, sizeof(PeelCtl), hipMemcpyDeviceToHost, s);
+            e = hipMemcpyAsync(g->h_small->peel, P.ctl, sizeof(g->h_small->peel), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
-        done = e == hipSuccess && c.phase == kPeelDone;
+        done = e == hipSuccess && g->h_small->peel[steps & 1].phase == kPeelDone;
     }
     if (e != hipSuccess) (void)hipStreamSynchronize(s);
     dfree(lists);
     if (e == hipSuccess && !done) e = hipErrorUnknown;   // cannot happen: every round removes a vertex
     if (e != hipSuccess) return hip_fail(e, "peeling kernels");
-    g->peel_rounds = c.r;
+    g->peel_rounds = g->h_small->peel[steps & 1].r;
     return CITRON_OK;
 }
 

@@ -16,7 +16,8 @@ struct SmallDev {
     int32_t err;
     int32_t max_outdeg;
     unsigned long long kept;     // sum of the out-degrees (validation)
-    PeelCtl peel;
+    PeelCtl peel[2];
+    PeelCounters peel_cnt;
     BuildSums build[kBuildSlots];
     int32_t list_cursors[kClaimInts];
 };
@@ -46,7 +47,7 @@ struct SmallHost {
     int32_t rows_total;
     int32_t hrows_total;
     int32_t hist[2 * kMaxDeg + 2];   // bucket bounds of a schedule order
-    PeelCtl peel;
+    PeelCtl peel[2];
     BuildSums build[kBuildSlots];
 };
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "internal.h"
+#include "peel.h"
 
 namespace citron {
 
@@ -21,30 +22,11 @@ hipError_t launch_orient(int32_t n, const int32_t* row_ptr, const int32_t* col, 
                          int32_t* scan_ws, hipStream_t s, const int32_t* key, bool count);
 
 // ---- core ordering by level-synchronous peeling (kernels_core.hip)
-enum PeelPhase { kPeelRelax, kPeelMark, kPeelMin, kPeelCollect, kPeelDone };
-struct PeelCtl {
-    int32_t phase;       // what the next launch does
-    int32_t t, r;        // threshold, round
-    int32_t remaining;   // vertices not yet relaxed
-    int32_t cur, n_cur;  // the round's frontier: list and size
-    int32_t side, n_alive;   // list of the vertices left at the last rise of t, and its size
-    int32_t n_frontier;  // appended to the next frontier
-    int32_t n_left;      // appended to the next list of vertices left
-    int32_t min_deg;     // smallest degree found (INT_MAX between searches)
-    int32_t done;        // workgroups of the launch that have finished
-};
-struct PeelParams {
-    const int32_t* row_ptr;
-    const int32_t* col;
-    int32_t* deg;        // n
-    int32_t* round;      // n: the round each vertex leaves in
-    int32_t* frontier[2];    // n each
-    int32_t* alive[2];       // n each
-    PeelCtl* ctl;
-};
 hipError_t launch_peel_init(int32_t n, const PeelParams& P, hipStream_t s);
-// `steps` launches; those after the last phase return at once
-hipError_t launch_peel_steps(const PeelParams& P, int32_t steps, hipStream_t s);
+// launches first .. first + steps - 1 (0 follows launch_peel_init); those after
+// the last phase return at once.  Copy (first + steps) & 1 of the control
+// block then names the next phase.
+hipError_t launch_peel_steps(const PeelParams& P, int64_t first, int32_t steps, hipStream_t s);
 
 // ---- deterministic schedule order (kernels_sched.hip)
 struct SortBuffers {

@@ -86,3 +86,39 @@ def test_core_ordering_full_size(citron_gpu, name, progress):
     assert h.info()["max_outdeg"] <= gold["max_outdeg"]
     for k, rec in gold["counts"].items():
         assert h.count(int(k)) == rec["count"], (name, k)
+
+
+def test_core_ordering_beside_a_long_count(citron_gpu):
+    """Orderings on one stream while counts on another keep the compute units
+    busy: workgroups of a launch then start at very different times."""
+    import threading
+    import torch
+    gs = [gg.rmat(10, 16, seed=31), gg.rmat(13, 12, seed=32), gg.erdos_renyi(4000, 18, seed=33)]
+    want = [(oracle.peel_rounds(g.n, g.row_ptr, g.col), *oracle.orient_peel(g)) for g in gs]
+    big = gg.rmat(15, 16, seed=34)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        load = citron_gpu.Graph.from_csr(big.row_ptr, big.col).order()
+    first = load.count(7)
+    stop, counts = threading.Event(), []
+
+    def busy():
+        while not stop.is_set():
+            counts.append(load.count(7))
+
+    t = threading.Thread(target=busy)
+    t.start()
+    try:
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for i in range(30):
+                g, (key, ptr, col) = gs[i % 3], want[i % 3]
+                h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order("core")
+                got, rounds = h.order_key()
+                assert np.array_equal(got, key) and rounds == int(key.max()) + 1, (g.name, i)
+                dptr, dcol = h.dag()
+                assert np.array_equal(dptr, ptr) and np.array_equal(dcol, col), (g.name, i)
+                h.free()
+    finally:
+        stop.set()
+        t.join()
+    assert counts and all(c == first for c in counts)
+    load.free()

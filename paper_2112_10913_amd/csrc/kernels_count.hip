@@ -27,12 +27,13 @@
 // engine; a node with two levels left and more than 64 candidates is
 // finished lane-per-child from the LDS copy (need3_lanes).
 //
-// Exact arithmetic: per-lane uint64 accumulators (a lane adds at most 64 per
-// step and cannot run 2^58 steps; the binomials of complete nodes, which can
-// be large, are carry-checked; 32-bit partial sums are bounded where they are
+// Exact arithmetic: per-lane uint64 accumulators (lane_sum.h: small additions
+// as they are, the binomials of complete nodes through a carry check that
+// leaves room for them; 32-bit partial sums are bounded where they are
 // used); wave sums and the global accumulator are carry-checked, and a carry
 // sets the query's overflow flag.
 #include "items.h"
+#include "lane_sum.h"
 #include "wave.h"
 
 namespace citron {
@@ -125,7 +126,7 @@ __host__ __device__ inline int wave_lds_bytes(int max_k, int arc_max, bool per_a
 // A lane that finishes a unit takes the next one at once.
 
 struct Acc {
-    u64 acc;
+    u64 acc;             // with ovf, the lane's sum (lane_sum.h)
     int ovf;
     u64 st[kNumStats];   // per-lane work counters (instrumented launches only)
 };
@@ -449,8 +450,7 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
                 probe = false;
                 if (2 * edges == (unsigned)(c * (c - 1))) {
                     const u64 b = binomials.c[c][need];
-                    A.acc += b;
-                    if (A.acc < b) A.ovf = 1;
+                    add_big(A.acc, A.ovf, b);
                     if (kPerArc) uacc += b;
                 } else {
                     R = M;
@@ -936,7 +936,8 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
             if (qi != cur) {
                 if (cur >= 0) {
                     const QueryDesc& oq = P.items.queries[cur];
-                    wave_flush(A.acc, A.ovf, oq.acc + acc_slot, oq.overflow);
+                    const u64 total = lane_total(A.acc, A.ovf);
+                    wave_flush(total, A.ovf, oq.acc + acc_slot, oq.overflow);
                     if (kStats) wave_flush_stats(A.st, oq.stats);
                     A.acc = 0ull;
                     A.ovf = 0;

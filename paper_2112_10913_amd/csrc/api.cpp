@@ -162,6 +162,8 @@ static void free_graph_memory(citron_graph* g)
         dfree(g->d_vbuckets[k]);
         g->vbucket_bytes[k] = 0;
     }
+    dfree(g->d_buckets[kPerArcSlot]);
+    g->bucket_bytes[kPerArcSlot] = 0;
     g->rows_valid = false;
     free_plan(g);
     pool_host_free(g->h_small, sizeof(SmallHost));
@@ -401,15 +403,15 @@ citron_status ensure_scratch(citron_graph* g, int64_t bytes)
 // (|C_uv|, or out-degree - 1 for a light vertex), largest first, so that the
 // costliest work starts first.  Arcs and vertices are split into parts
 // (dense_parts, arc_parts, light_parts).
-citron_status ensure_buckets(citron_graph* g, int32_t k)
+citron_status ensure_buckets(citron_graph* g, int32_t k, int32_t slot)
 {
     const int32_t pct = g->tuning.split_pct;
-    if (g->d_buckets[k] && g->bucket_split[k] == pct) return CITRON_OK;
-    if (g->d_buckets[k]) {
+    if (g->d_buckets[slot] && g->bucket_split[slot] == pct) return CITRON_OK;
+    if (g->d_buckets[slot]) {
         // another split: the old table stays valid for readers that hold it
         // (a captured batch, an admitted request) until the graph is freed
-        g->retired_buckets.push_back(g->d_buckets[k]);
-        g->d_buckets[k] = nullptr;
+        g->retired_buckets.push_back(g->d_buckets[slot]);
+        g->d_buckets[slot] = nullptr;
     }
     const int32_t D = std::max(g->max_outdeg, 2);
     auto v_at_least = [&](int32_t x) -> int64_t {   // vertices with out-degree >= x
@@ -418,18 +420,19 @@ citron_status ensure_buckets(citron_graph* g, int32_t k)
         return g->h_vscan[(size_t)(D - x + 1)];
     };
     const int64_t n_heavy = v_at_least(kLightMaxDeg + 1);
+    auto whole = [&](int32_t d) { return slot == k && dense_vertex(d, k); };
     struct B { int32_t key, first, cnt, kind; };
     std::vector<B> db, hb, lb;
     // vertices the dense kernel takes whole (k = 4, 5), by out-degree
     for (int32_t d = kDenseMax; d > kLightMaxDeg; --d) {
         const int64_t cnt = v_at_least(d) - v_at_least(d + 1);
-        if (cnt > 0 && dense_vertex(d, k)) db.push_back({d, (int32_t)v_at_least(d + 1), (int32_t)cnt, kItemDenseVertex});
+        if (cnt > 0 && whole(d)) db.push_back({d, (int32_t)v_at_least(d + 1), (int32_t)cnt, kItemDenseVertex});
     }
     // heavy-arc buckets by |C_uv|, of vertices above kDenseMax (group 0) and
     // of the others, whose arcs are not scheduled where the vertices are
     for (int32_t c = D - 1; c >= k - 2; --c)
         for (int32_t grp = 0; grp < 2; ++grp) {
-            if (grp == 1 && dense_vertex(kDenseMax, k)) continue;
+            if (grp == 1 && whole(kDenseMax)) continue;
             const size_t j = (size_t)(grp * D + D - 1 - c);
             const int32_t cnt = g->h_hscan[j + 1] - g->h_hscan[j];
             if (cnt <= 0) continue;
@@ -476,15 +479,15 @@ citron_status ensure_buckets(citron_graph* g, int32_t k)
     tab.push_back(0);
     tab.push_back(0);
     tab.push_back(0);
-    citron_status st = dalloc(&g->d_buckets[k], tab.size(), &g->device_bytes, "item buckets");
+    citron_status st = dalloc(&g->d_buckets[slot], tab.size(), &g->device_bytes, "item buckets");
     if (st) return st;
-    g->bucket_bytes[k] += (int64_t)(sizeof(int32_t) * tab.size());   // retired tables stay counted
-    hipError_t e = hipMemcpy(g->d_buckets[k], tab.data(), sizeof(int32_t) * tab.size(), hipMemcpyHostToDevice);
+    g->bucket_bytes[slot] += (int64_t)(sizeof(int32_t) * tab.size());   // retired tables stay counted
+    hipError_t e = hipMemcpy(g->d_buckets[slot], tab.data(), sizeof(int32_t) * tab.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "item buckets");
-    g->n_buckets[k] = nb;
-    g->n_work[k] = (int32_t)items;
-    memcpy(g->sched_end[k], ends, sizeof(ends));
-    g->bucket_split[k] = pct;
+    g->n_buckets[slot] = nb;
+    g->n_work[slot] = (int32_t)items;
+    memcpy(g->sched_end[slot], ends, sizeof(ends));
+    g->bucket_split[slot] = pct;
     return CITRON_OK;
 }
 
@@ -529,7 +532,7 @@ citron_status ensure_vbuckets(citron_graph* g, int32_t k)
     return CITRON_OK;
 }
 
-QueryDesc make_query(const citron_graph* g, int32_t k, unsigned long long* acc, int32_t* ovf,
+QueryDesc make_query(const citron_graph* g, int32_t k, int32_t slot, unsigned long long* acc, int32_t* ovf,
                      unsigned long long* per_arc, unsigned long long* stats)
 {
     QueryDesc q;
@@ -550,14 +553,14 @@ QueryDesc make_query(const citron_graph* g, int32_t k, unsigned long long* acc, 
     q.per_arc = per_arc;
     q.stats = stats;
     q.k = k;
-    q.buckets = g->d_buckets[k];
-    q.n_buckets = g->n_buckets[k];
+    q.buckets = g->d_buckets[slot];
+    q.n_buckets = g->n_buckets[slot];
     q.light_first = g->plan.n_heavy;
-    q.n_work = g->n_work[k];
-    memcpy(q.sched_end, g->sched_end[k], sizeof(q.sched_end));
+    q.n_work = g->n_work[slot];
+    memcpy(q.sched_end, g->sched_end[slot], sizeof(q.sched_end));
     q.n_items = q.n_work;
     q.item_stride = 1;
-    q.split_pct = g->bucket_split[k];
+    q.split_pct = g->bucket_split[slot];
     return q;
 }
 
@@ -630,6 +633,7 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
     const uint64_t seed = g->seed_pending ? g->seed_base : 0;
     g->seed_pending = false;
     hipStream_t s = g->stream;
+    const int32_t slot = schedule_slot(k, per_arc && !arc_list);
     if (stats) memset(g->h_small->stats, 0, sizeof(g->h_small->stats));
     if (vertex_rooted) {
         // the vertex-rooted unit runs the kernel for every k >= 3 (no
@@ -660,7 +664,7 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
         return CITRON_OK;
     }
     if (!vertex_rooted) {
-        st = ensure_buckets(g, k);
+        st = ensure_buckets(g, k, slot);
         if (st) return st;
     }
     const citron_tuning& t = g->tuning;
@@ -689,7 +693,7 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
         return hip_fail(e, "fill");
     if (per_arc && (e = launch_fill_u64(per_arc, 0, arc_list ? n_list : g->m, s)) != hipSuccess)
         return hip_fail(e, "fill");
-    ctl.query = make_query(g, k, g->d_ctl->acc, &g->d_ctl->overflow, per_arc, stats ? g->d_stats : nullptr);
+    ctl.query = make_query(g, k, slot, g->d_ctl->acc, &g->d_ctl->overflow, per_arc, stats ? g->d_stats : nullptr);
     if (vertex_rooted) {
         QueryDesc& q = ctl.query;
         q.buckets = g->d_vbuckets[k];

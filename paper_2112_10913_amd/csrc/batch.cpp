@@ -143,7 +143,8 @@ citron_status batch_build(const BatchKey& key, const citron_tuning& t, BatchExec
         return fail(CITRON_ENOMEM, "hipHostMalloc failed for batch");
     be->h_ovf = reinterpret_cast<int32_t*>(be->h_acc + (size_t)nq * kAccWords);
     for (int32_t i = 0; i < nq; ++i) {
-        be->h_q[i] = make_query(key.graphs[i], key.ks[i], be->d_acc + (size_t)i * kAccWords, be->d_ovf + i, nullptr, nullptr);
+        be->h_q[i] = make_query(key.graphs[i], key.ks[i], key.ks[i], be->d_acc + (size_t)i * kAccWords, be->d_ovf + i,
+                                nullptr, nullptr);
         place_query(be->h_q[i], true, cl.space_items);
     }
     be->nq = nq;
@@ -236,7 +237,7 @@ extern "C" citron_status citron_count_batch(citron_graph* const* gs, const int32
             citron_graph* g = const_cast<citron_graph*>(key.graphs[j]);
             if (key.ks[j] < 4) continue;
             std::lock_guard<std::mutex> gl(g->mu);
-            st = ensure_buckets(g, key.ks[j]);
+            st = ensure_buckets(g, key.ks[j], key.ks[j]);
             if (st) return st;
         }
         // k = 3 is the build's triangle count; the rest go to the kernel

@@ -457,7 +457,7 @@ struct Nodes {
     }
 
     __device__ __forceinline__ bool next(const Dense<K>& D, int c, int need, int part, int P, int wid, u64* stack,
-                                         int* branch, bool per_arc)
+                                         int* branch)
     {
         const int lane = lane_of();
         auto claim = [&] {
@@ -466,11 +466,6 @@ struct Nodes {
             return part + P * __builtin_amdgcn_readfirstlane(j);
         };
         if (need == 4) {
-            if (per_arc) {
-                first = claim();
-                stride = 1 << 20;
-                return first < c;
-            }
             if (started) return false;
             started = true;
             stride = P * dense_waves(K);
@@ -522,51 +517,43 @@ struct Nodes {
 };
 
 // One wave's share of one pass, and of those after it.  need == 4: the masks
-// are the rows x = part mod P, dealt to the waves in turn (claimed one by one
-// where each row's own sum is wanted).  Deeper: first-level branches x = part
-// mod P are claimed, and a depth-first search below each comes to the nodes
+// are the rows x = part mod P, dealt to the waves in turn.  Deeper:
+// first-level branches x = part mod P are claimed, and a depth-first search below each comes to the nodes
 // whose rows are the masks; stack: need - 5 levels of (node, branches left).
 template <int K, int kPass>
 __device__ __forceinline__ void dense_passes(const Dense<K>& D, int c, int need, int part, int P, int wid, u64* stack,
-                                             int* branch, u64* per_arc, const uint16_t* inv, u64& sum)
+                                             int* branch, u64& sum)
 {
     if constexpr (kPass < n_passes(K)) {
         using Acc = Pass<K, kPass>;
         if (Acc::B.x0 < D.nt && Acc::B.y0 < D.nt) {
-            const int lane = lane_of();
             Nodes<K> node;
             node.start(c);
             bool more = true;
             do {
                 Acc A;
                 A.clear();
-                int masks = 0, last = 0;
+                int masks = 0;
                 for (;;) {
-                    more = node.next(D, c, need, part, P, wid, stack, branch + kPass, per_arc != nullptr);
+                    more = node.next(D, c, need, part, P, wid, stack, branch + kPass);
                     if (!more) break;
                     A.add(D, node.N, node.pp, node.stride, node.first);
 #pragma unroll
                     for (int w = 0; w < K; ++w) masks += __popcll(node.N[w]);
-                    last = node.first;
-                    if (per_arc || masks > max_masks(K) - 64 * K) break;
+                    if (masks > max_masks(K) - 64 * K) break;
                 }
-                const u64 s = A.sum(D);
-                sum += s;
-                if (per_arc && more) {
-                    const u64 v = wave_sum_u64(s);
-                    if (lane == 0 && v) atomicAdd(per_arc + inv[last], v);
-                }
+                sum += A.sum(D);
             } while (more);
         }
-        dense_passes<K, kPass + 1>(D, c, need, part, P, wid, stack, branch, per_arc, inv, sum);
+        dense_passes<K, kPass + 1>(D, c, need, part, P, wid, stack, branch, sum);
     }
 }
 
 // One item: an arc's subgraph (mask row r of its source's rows, packed) or a
 // whole vertex's (its rows as they are), laid out once; then its first level
 // is shared among the waves.  need: vertices to choose from the subgraph, 3
-// (one triangle count) or more.  per_arc (vertices only): counts per
-// first vertex x go to per_arc[inv[x]].  Returns this lane's share.
+// (one triangle count) or more.  per_arc (vertices at k = 4 only): counts
+// per first vertex x go to per_arc[inv[x]].  Returns this lane's share.
 template <int K>
 __device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, int d, int r, int need, int part, int P,
                                           int max_k, unsigned char* smem, u64* stacks, int* branch, u64* per_arc,
@@ -617,7 +604,7 @@ __device__ __forceinline__ u64 dense_item(const u64* __restrict__ src, int W, in
         return sum;
     }
     u64* stack = stacks + wid * dense_stack_words(K, max_k);
-    dense_passes<K, 0>(D, c, need, part, P, wid, stack, branch, per_arc, inv, sum);
+    dense_passes<K, 0>(D, c, need, part, P, wid, stack, branch, sum);
     __syncthreads();
     return sum;
 }

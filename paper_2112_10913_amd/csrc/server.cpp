@@ -299,7 +299,7 @@ void worker_main(citron_server* s)
                 if (s->free_slots.empty() || s->used + r.footprint > s->budget) break;
                 {
                     std::lock_guard<std::mutex> gl(g->mu);
-                    st = ensure_buckets(g, r.k);
+                    st = ensure_buckets(g, r.k, r.k);
                 }
                 if (st) {
                     r.t_admit = now_ns();
@@ -312,7 +312,7 @@ void worker_main(citron_server* s)
                 s->used += r.footprint;
                 r.t_admit = now_ns();
                 r.id = s->next_id++;
-                r.q = make_query(g, r.k, s->d_acc + (size_t)r.slot * kAccWords, s->d_ovf + r.slot, nullptr, nullptr);
+                r.q = make_query(g, r.k, r.k, s->d_acc + (size_t)r.slot * kAccWords, s->d_ovf + r.slot, nullptr, nullptr);
                 r.n_items = r.q.n_items;
                 r.fast = r.n_items <= kFastItems;
                 r.issued = 0;

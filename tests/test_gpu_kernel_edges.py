@@ -375,3 +375,28 @@ def test_arcs_of_vertices_too_large_for_a_dense_item_at_k_5(citron_gpu, n, p):
     assert sum(c for c, _ in parts) == want
     assert citron_gpu.count_batch([h, h], [5, 4]) == [want, h.count_vertex_rooted(4)]
     h.free()
+
+
+@pytest.mark.parametrize("n,p", [(90, 0.7), (300, 0.5), (440, 0.9)])
+def test_per_arc_counts_of_k_5_keep_a_schedule_of_their_own(citron_gpu, n, p):
+    """Per-arc counts of k = 5 take arcs where whole counts take vertices: both
+    from one handle in turn, also after a change of split."""
+    import oracle
+    g = gg.erdos_renyi(n, p * (n - 1), seed=n)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    want = h.count_vertex_rooted(5)
+    every = h.count_arcs(5, np.arange(g.m))
+    assert int(every.sum()) == want
+    if n < 400:
+        ptr, col = h.dag()
+        src = np.repeat(np.arange(g.n), np.diff(ptr)).astype(np.int32)
+        assert np.array_equal(every, oracle.count_arcs(g.n, ptr, col, 5, src, col)[0])
+    for split in (100, 50, 100):
+        h.set_tuning(split_pct=split)
+        for _ in range(2):
+            assert h.count(5) == want
+            total, per = h.count_per_arc(5)
+            assert total == want and np.array_equal(per, every)
+    assert h.count_per_arc(4)[0] == h.count(4)
+    assert citron_gpu.count_batch([h], [5]) == [want]
+    h.free()

@@ -45,15 +45,23 @@ constexpr int kArcMaxC = kArcLdsMax;    // LDS subgraph copies hold at most this
 constexpr int kDonateMinIdle = 8;       // idle lanes that trigger work donation
 // A unit with at least this many vertices to choose is dealt branch by branch:
 // a wave's queue holds few units of a deep count (two arcs per part of a split
-// vertex), which kept lanes idle or trading work.
+// vertex), which kept lanes idle or trading work.  Units of less than
+// kBranchMin candidates are dealt whole where the stacks are deep enough
+// (below heavy nodes): such units come many at a time.
 constexpr int kBranchNeed = 4;
+constexpr int kBranchMin = 24;
 // A node with at least this many vertices to choose has its edges counted
 // before it is searched: when every pair is adjacent its count is a binomial.
 // The probe costs one word operation per candidate, against a subtree of
 // about c^3 / 24 in a dense subgraph; in graphs with planted cliques most
 // such nodes are complete (Chung-Lu 2^14, k = 9: 12.0 -> 6.4 ms; R-MAT 16,
-// k = 7, where they hardly ever are: no change).
+// k = 7, where they hardly ever are: no change).  A wave goes on probing
+// while one node in kProbeRate is complete, after kProbeTrial tries; later it
+// tries kProbeAgain more per queue.
 constexpr int kProbeNeed = 4;
+constexpr int kProbeTrial = 256;
+constexpr int kProbeRate = 16;
+constexpr int kProbeAgain = 8;
 constexpr int kDeepClaim = 2;           // items a wave claims at once, at most, for k >= 8
 constexpr int kBurstIters = 32;         // last-level steps of one leaf burst at most
 constexpr int kBurstMinLanes = 32;      // lanes at a last-level node to keep a burst going
@@ -145,6 +153,8 @@ struct WaveBuf {
     int n;           // rows in use (wave-uniform)
     int nu;          // units in use (wave-uniform)
     int arc_max;     // nodes with 64 < c <= arc_max are copied to LDS
+    int whole_need;  // the light stacks hold units of up to this many vertices to choose whole
+    int tried, hits; // probed nodes, and complete ones among them (wave-uniform)
 };
 
 // Per-lane light stack: slot s holds the (M, R) pair of level s + 1.  In
@@ -242,7 +252,7 @@ __device__ __forceinline__ unsigned leaf_step(const u64* __restrict__ rows, int 
 }
 
 template <bool kStats, bool kPerArc, int kRegL>
-__device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __restrict__ per_arc)
+__device__ __forceinline__ void light_engine(WaveBuf& wb, Acc& A, u64* __restrict__ per_arc)
 {
     const int lane = lane_of();
     const u64 lt_mask = lane == 0 ? 0ull : (~0ull >> (kWave - lane));
@@ -253,59 +263,62 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
     int next = 0;                      // wave-uniform unit counter
     u64 branches = 0ull;               // first-level branches left of the unit before it (wave-uniform)
     int urow = 0, uneed = 0, ubase = 0;
+    int tried = 0, hits = 0;           // probes and complete nodes among them (wave-uniform)
+    if (kProbe) {
+        tried = wb.tried > kProbeTrial ? wb.tried - kProbeAgain : wb.tried;
+        hits = wb.hits;
+    }
     bool active = false;
-    bool probe = false;                // counting the node's edges before searching it
-    unsigned edges = 0;
+    bool scan = false;                 // at a last-level node, or counting a node's edges before searching it
+    unsigned sum = 0;                  // of the node scanned: cliques, or edges (below 2^12)
     u64 M = 0, R = 0, uacc = 0;
     int t = 0, need = 0, base = 0, tag = 0;
+    auto probes = [&](int n) { return kProbe && n >= kProbeNeed && tried <= kProbeTrial + kProbeRate * hits; };
     for (;;) {
         u64 want = __ballot(!active);
         while (want && (branches || next < nunits)) {
             if (branches == 0ull) {
-                // the next units: with at least kBranchNeed vertices to choose
-                // one unit is dealt branch by branch, smaller ones whole, a
-                // lane each
-                const int uw = __builtin_amdgcn_readfirstlane(wb.units[next]);
-                const int row = uw & 0xff;
-                const int mt = __builtin_amdgcn_readfirstlane(wb.meta[row]);
-                if ((mt & 255) >= kBranchNeed) {
-                    const u64 m1 = readlane64(rows[row], 0);
-                    urow = row;
-                    uneed = mt & 255;
-                    ubase = mt >> 8;
-                    // a sub-part takes the branches at positions q mod 2^s
-                    const int s = uw >> 16;
-                    branches = m1 & ((s == 4 ? 0x0001000100010001ull : s == 2 ? 0x1111111111111111ull : ~0ull)
-                                     << ((uw >> 8) & 0xff));
-                    if (__popcll(m1) < uneed) branches = 0ull;
-                    ++next;
-                    continue;
-                }
+                // the next units, a wanting lane each, up to the first that is
+                // dealt branch by branch; units too small for the rest of the
+                // clique are passed over
                 const int u = next + __popcll(want & lt_mask);
-                const int row_u = u < nunits ? wb.units[u] & 0xff : row;
-                const int mt_u = wb.meta[row_u];
-                // units of one kind lead the list; the rest waits for its turn
-                const u64 small = __ballot(u < nunits && (mt_u & 255) < kBranchNeed) & want;
-                const u64 stop = want & ~small;
-                const u64 take = stop ? small & ((1ull << __builtin_ctzll(stop)) - 1ull) : small;
-                next += __popcll(take);
-                if ((take >> lane) & 1) {
-                    const u64 m1 = rows[row_u];
-                    base = mt_u >> 8;
-                    need = mt_u & 255;
-                    const int c = __popcll(m1);
+                const bool mine = !active && u < nunits;
+                const int uw = wb.units[min(u, nunits - 1)];
+                const int row = uw & 0xff;
+                const int mt = wb.meta[row];
+                const u64 m1 = rows[row];
+                const int n = mt & 255, c = __popcll(m1);
+                const bool viable = mine && c >= n;
+                const u64 deal = __ballot(viable && n >= kBranchNeed &&
+                                           (c >= kBranchMin || n > wb.whole_need || uw >> 16));
+                const u64 take = deal ? want & ((1ull << __builtin_ctzll(deal)) - 1ull) : want;
+                next += deal ? __popcll(take) + 1 : __popcll(take);
+                if (viable && ((take >> lane) & 1)) {
+                    base = mt >> 8;
+                    need = n;
                     if (kStats) A.st[kStatLightUnits] += 1;
-                    if (kPerArc) tag = wb.tags[row_u];
-                    if (need == 1) {
+                    if (kPerArc) tag = wb.tags[row];
+                    if (n == 1) {
                         A.acc += (u64)c;
                         if (kPerArc && c) atomicAdd(per_arc + tag, (u64)c);
-                    } else if (c >= need) {
+                    } else {
                         M = m1;
                         R = m1;
                         t = 1;
+                        scan = n == 2 || probes(n);
                         uacc = 0;
                         active = true;
                     }
+                }
+                if (deal) {
+                    const int l = __builtin_ctzll(deal);
+                    const int uwl = __builtin_amdgcn_readlane(uw, l), mtl = __builtin_amdgcn_readlane(mt, l);
+                    urow = uwl & 0xff;
+                    uneed = mtl & 255;
+                    ubase = mtl >> 8;
+                    // a sub-part takes the branches at positions q mod 2^s
+                    const int s = uwl >> 16;
+                    branches = readlane64(m1, l) & ((s == 4 ? 0x0001000100010001ull : ~0ull) << ((uwl >> 8) & 0xff));
                 }
             } else {
                 const int r = __popcll(want & lt_mask);
@@ -320,8 +333,7 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
                         t = 1;
                         need = uneed - 1;
                         base = ubase;
-                        probe = kProbe && need >= kProbeNeed;
-                        edges = 0;
+                        scan = probes(need);
                         if (kPerArc) tag = wb.tags[urow];
                         uacc = 0;
                         active = true;
@@ -349,7 +361,8 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
             int lvl = 0;
             u64 Ml = 0ull, Rl = 0ull;
             if (active) {
-                for (int l = 1; l <= t - (probe ? 1 : 0); ++l) {
+                // (what a probe has left is no part of the search)
+                for (int l = 1; l <= t - (scan && need != 2 ? 1 : 0); ++l) {
                     const u64 r = (l == t) ? R : stk.get_r(l - 1);
                     const int pc = __popcll(r);
                     if (pc >= 2 && (need + (t - l) >= 3 || pc >= 8)) {
@@ -391,7 +404,7 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
                     t = 1;
                     uacc = 0;
                     active = true;
-                    probe = false;
+                    scan = need == 2;
                     if (kStats) A.st[kStatDonations] += 1;
                 }
                 __builtin_amdgcn_wave_barrier();
@@ -401,15 +414,13 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
             A.st[kStatLightIters] += 1;
             A.st[kStatLightActive] += (u64)__popcll(act);
         }
+        bool probed = false, complete = false;
         if (active) {
             if (R != 0ull) {
-                if (need == 2 || probe) {
-                    // degrees-only last level (or the probe's edge count), two
+                if (scan) {
+                    // degrees-only last level (or a probe's edge count), two
                     // candidates per step
-                    const unsigned c = leaf_step(rows, base, M, R);
-                    if (probe) edges += c;
-                    else A.acc += (u64)c;
-                    if (kPerArc && !probe) uacc += (u64)c;
+                    sum += leaf_step(rows, base, M, R);
                     if (kStats) A.st[kStatWordOps] += 2;
                 } else {
                     const int x = __builtin_ctzll(R);
@@ -421,40 +432,43 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
                         R = nm;
                         ++t;
                         --need;
-                        probe = kProbe && need >= kProbeNeed;
-                        edges = 0;
+                        scan = need == 2 || probes(need);
                         if (kStats) A.st[kStatPushes] += 1;
                     }
                 }
             }
-            if ((need == 2 || probe) && R != 0ull) {
-                // leaf burst: while most lanes sit at a last-level node, run
-                // only last-level steps, two candidates at a time
-                unsigned bacc = 0;             // <= 2 * 64 * kBurstIters
+            if (scan && R != 0ull) {
+                // leaf burst: while most lanes scan a node, run only such
+                // steps, two candidates at a time
                 for (int it = 0; it < kBurstIters; ++it) {
                     const bool leaf = R != 0ull;
                     if (__popcll(__ballot(leaf)) < kBurstMinLanes) break;
                     if (leaf) {
-                        bacc += leaf_step(rows, base, M, R);
+                        sum += leaf_step(rows, base, M, R);
                         if (kStats) A.st[kStatWordOps] += 2;
                     }
                 }
-                if (probe) edges += bacc;
-                else A.acc += (u64)bacc;
-                if (kPerArc && !probe) uacc += (u64)bacc;
             }
-            if (kProbe && probe && R == 0ull) {
-                // every pair adjacent: the node's cliques are its subsets of
-                // `need`; otherwise it is searched
-                const int c = __popcll(M);
-                probe = false;
-                if (2 * edges == (unsigned)(c * (c - 1))) {
-                    const u64 b = binomials.c[c][need];
-                    add_big(A.acc, A.ovf, b);
-                    if (kPerArc) uacc += b;
+            if (R == 0ull) {
+                if (kProbe && scan && need != 2) {
+                    // every pair adjacent: the node's cliques are its subsets
+                    // of `need`; otherwise it is searched
+                    const int c = __popcll(M);
+                    probed = true;
+                    complete = 2 * sum == (unsigned)(c * (c - 1));
+                    if (complete) {
+                        const u64 b = binomials.c[c][need];
+                        add_big(A.acc, A.ovf, b);
+                        if (kPerArc) uacc += b;
+                    } else {
+                        R = M;
+                    }
                 } else {
-                    R = M;
+                    A.acc += (u64)sum;         // 0 unless the node was scanned
+                    if (kPerArc) uacc += (u64)sum;
                 }
+                scan = false;
+                sum = 0;
             }
             if (R == 0ull) {
                 if (t == 1) {
@@ -469,6 +483,21 @@ __device__ __forceinline__ void light_engine(const WaveBuf& wb, Acc& A, u64* __r
                 }
             }
         }
+        if (kProbe) {
+            const u64 p = __ballot(probed);
+            if (p) {
+                tried += __popcll(p);
+                hits += __popcll(__ballot(complete));
+                if (tried > 16 * kProbeTrial) {
+                    tried >>= 1;
+                    hits >>= 1;
+                }
+            }
+        }
+    }
+    if (kProbe) {
+        wb.tried = tried;
+        wb.hits = hits;
     }
 }
 
@@ -887,6 +916,9 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
     wb.n = 0;
     wb.nu = 0;
     wb.arc_max = P.arc_lds_max;
+    wb.whole_need = light_levels(P.max_k) + 2;
+    wb.tried = 0;
+    wb.hits = 0;
 
     Acc A;
     A.acc = 0ull;
@@ -999,7 +1031,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
             const u64 um = __ballot(unit);
             if (unit)
                 wb.units[wb.nu + __popcll(um & (lane == 0 ? 0ull : (~0ull >> (kWave - lane))))] =
-                    (wb.n + lane) | (sub << 8) | (subs == 16 ? 4 << 16 : subs == 4 ? 2 << 16 : 0);
+                    (wb.n + lane) | (sub << 8) | (subs == 16 ? 4 << 16 : 0);
             wb.nu += __popcll(um) + (from_root ? 1 : 0);
             wb.n += d + (from_root ? 1 : 0);
         }

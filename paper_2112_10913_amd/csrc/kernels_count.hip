@@ -42,7 +42,7 @@ constexpr int kMaxBlock = 512;          // threads per count workgroup (8 waves)
 constexpr int kWaveBufRows = 128;       // one-word rows queued per wave
 constexpr int kLdsStackLevels = 7;      // deeper stacks (k > 12) live in device memory
 constexpr int kArcMaxC = kArcLdsMax;    // LDS subgraph copies hold at most this many rows
-constexpr int kDonateMinIdle = 8;       // idle lanes that trigger work donation
+constexpr int kDonateMinIdle = 16;      // idle lanes that trigger work donation
 // A unit with at least this many vertices to choose is dealt branch by branch:
 // a wave's queue holds few units of a deep count (two arcs per part of a split
 // vertex), which kept lanes idle or trading work.  Units of less than
@@ -83,7 +83,7 @@ __host__ __device__ inline int light_levels(int max_k) { return max_k > 6 ? max_
 // (k <= 12) or device memory.  The heavy stacks are always in
 // device memory: they are touched only when a heavy node is pushed or popped,
 // and keeping them out of LDS lets more waves share a CU.
-constexpr int kRegLevels = 4;
+constexpr int kRegLevels = 2;
 enum StackMode { kStackOne, kStackReg, kStackLds, kStackGlobal };
 __host__ __device__ inline int stack_mode(int max_k)
 {
@@ -164,31 +164,24 @@ template <int L>
 struct LightStack;
 
 template <>
-struct LightStack<4> {
-    u64 m0 = 0, m1 = 0, m2 = 0, m3 = 0, r0 = 0, r1 = 0, r2 = 0, r3 = 0;
+struct LightStack<2> {
+    u64 m0 = 0, m1 = 0, r0 = 0, r1 = 0;
     __device__ __forceinline__ LightStack(const WaveBuf&) {}
     __device__ __forceinline__ void put(int s, u64 M, u64 R)
     {
         m0 = s == 0 ? M : m0;
-        m1 = s == 1 ? M : m1;
-        m2 = s == 2 ? M : m2;
-        m3 = s == 3 ? M : m3;
-        r0 = s == 0 ? R : r0;
-        r1 = s == 1 ? R : r1;
-        r2 = s == 2 ? R : r2;
-        r3 = s == 3 ? R : r3;
+        m1 = s == 0 ? m1 : M;
+        set_r(s, R);
     }
     __device__ __forceinline__ void set_r(int s, u64 R)
     {
         r0 = s == 0 ? R : r0;
-        r1 = s == 1 ? R : r1;
-        r2 = s == 2 ? R : r2;
-        r3 = s == 3 ? R : r3;
+        r1 = s == 0 ? r1 : R;
     }
-    __device__ __forceinline__ u64 get_m(int s) const { return s == 0 ? m0 : s == 1 ? m1 : s == 2 ? m2 : m3; }
-    __device__ __forceinline__ u64 get_r(int s) const { return s == 0 ? r0 : s == 1 ? r1 : s == 2 ? r2 : r3; }
+    __device__ __forceinline__ u64 get_m(int s) const { return s == 0 ? m0 : m1; }
+    __device__ __forceinline__ u64 get_r(int s) const { return s == 0 ? r0 : r1; }
 };
-static_assert(kRegLevels == 4, "LightStack<4> holds the register levels");
+static_assert(kRegLevels == 2, "LightStack<2> holds the register levels");
 
 template <>
 struct LightStack<1> {
@@ -269,7 +262,7 @@ __device__ __forceinline__ void light_engine(WaveBuf& wb, Acc& A, u64* __restric
         hits = wb.hits;
     }
     bool active = false;
-    bool scan = false;                 // at a last-level node, or counting a node's edges before searching it
+    int scan = 0;                      // 1 at a last-level node, or counting a node's edges before searching it
     unsigned sum = 0;                  // of the node scanned: cliques, or edges (below 2^12)
     u64 M = 0, R = 0, uacc = 0;
     int t = 0, need = 0, base = 0, tag = 0;
@@ -362,7 +355,7 @@ __device__ __forceinline__ void light_engine(WaveBuf& wb, Acc& A, u64* __restric
             u64 Ml = 0ull, Rl = 0ull;
             if (active) {
                 // (what a probe has left is no part of the search)
-                for (int l = 1; l <= t - (scan && need != 2 ? 1 : 0); ++l) {
+                for (int l = 1; l <= t - (scan != 0 && need != 2 ? 1 : 0); ++l) {
                     const u64 r = (l == t) ? R : stk.get_r(l - 1);
                     const int pc = __popcll(r);
                     if (pc >= 2 && (need + (t - l) >= 3 || pc >= 8)) {

@@ -154,6 +154,7 @@ static void free_graph_memory(citron_graph* g)
     dfree(g->d_hinv);
     dfree(g->d_harcs);
     dfree(g->d_hscan);
+    dfree(g->d_deep_order);
     for (int32_t* p : g->retired_buckets) dfree(p);
     g->retired_buckets.clear();
     for (int k = 0; k <= CITRON_KMAX; ++k) {
@@ -382,6 +383,59 @@ citron_status ensure_rows(citron_graph* g)
     return CITRON_OK;
 }
 
+// Plan order of counts of k >= kDeepK: the light vertices that such a count may
+// split further (out-degree kDeepDeg and more) with those of a deep subgraph
+// first, the rest as in the plan; built at the first such count.
+static citron_status ensure_deep_order(citron_graph* g)
+{
+    if (!g->h_deep.empty()) return CITRON_OK;
+    const int32_t D = std::max(g->max_outdeg, 2);
+    const int32_t heavy = g->plan.n_heavy;
+    const int32_t n = D >= kDeepDeg ? g->h_vscan[(size_t)(D - kDeepDeg + 1)] - heavy : 0;
+    std::vector<int32_t> bounds(2 * kDeepBuckets + 1, 0);
+    if (n > 0) {
+        hipStream_t s = g->stream;
+        citron_status st;
+        if (!g->d_deep_order && (st = dalloc(&g->d_deep_order, (size_t)g->n + 1, &g->device_bytes, "deep order")))
+            return st;
+        const size_t tb = sched_sort_temp_bytes(n, 2 * kDeepBuckets);
+        if (tb == 0) return fail(CITRON_EDEVICE, "sort workspace query failed");
+        SortBuffers sb = {};
+        unsigned char* tmp = nullptr;
+        int32_t* d_bounds = nullptr;
+        if ((st = dalloc(&sb.keys_a, (size_t)n, nullptr, "deep order")) ||
+            (st = dalloc(&sb.keys_b, (size_t)n, nullptr, "deep order")) ||
+            (st = dalloc(&tmp, tb, nullptr, "deep order")) ||
+            (st = dalloc(&d_bounds, bounds.size(), nullptr, "deep order"))) {
+            dfree(sb.keys_a);
+            dfree(sb.keys_b);
+            dfree(tmp);
+            return st;
+        }
+        sb.temp = tmp;
+        sb.temp_bytes = tb;
+        hipError_t e = hipMemcpyAsync(g->d_deep_order, g->pb.order, sizeof(int32_t) * (size_t)g->n,
+                                      hipMemcpyDeviceToDevice, s);
+        if (e == hipSuccess)
+            e = sched_deep_order(n, g->pb.order + heavy, g->d_dag_ptr, g->d_rows_off, g->d_rows, d_bounds,
+                                 g->d_deep_order + heavy, sb, s);
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(g->h_small->hist, d_bounds, sizeof(int32_t) * bounds.size(), hipMemcpyDeviceToHost, s);
+        {
+            const hipError_t w = hipStreamSynchronize(s);
+            if (e == hipSuccess) e = w;
+        }
+        dfree(sb.keys_a);
+        dfree(sb.keys_b);
+        dfree(tmp);
+        dfree(d_bounds);
+        if (e != hipSuccess) return hip_fail(e, "deep order");
+        memcpy(bounds.data(), g->h_small->hist, sizeof(int32_t) * bounds.size());
+    }
+    g->h_deep = std::move(bounds);
+    return CITRON_OK;
+}
+
 // Device scratch for the count kernel of this graph (grows on demand).
 citron_status ensure_scratch(citron_graph* g, int64_t bytes)
 {
@@ -402,11 +456,15 @@ citron_status ensure_scratch(citron_graph* g, int64_t bytes)
 // out-degree >= k-1 in buckets of equal out-degree, merged by cost key
 // (|C_uv|, or out-degree - 1 for a light vertex), largest first, so that the
 // costliest work starts first.  Arcs and vertices are split into parts
-// (dense_parts, arc_parts, light_parts).
+// (dense_parts, arc_parts, light_arcs, kLightSubs).
 citron_status ensure_buckets(citron_graph* g, int32_t k, int32_t slot)
 {
     const int32_t pct = g->tuning.split_pct;
     if (g->d_buckets[slot] && g->bucket_split[slot] == pct) return CITRON_OK;
+    if (k >= kDeepK) {
+        const citron_status st = ensure_deep_order(g);
+        if (st) return st;
+    }
     if (g->d_buckets[slot]) {
         // another split: the old table stays valid for readers that hold it
         // (a captured batch, an admitted request) until the graph is freed
@@ -444,13 +502,21 @@ citron_status ensure_buckets(citron_graph* g, int32_t k, int32_t slot)
     std::stable_sort(db.begin(), db.end(), [](const B& a, const B& b) { return a.key > b.key; });
     // light-vertex buckets: out-degree d = 64 down to max(k-1, 2)
     for (int32_t d = kLightMaxDeg; d >= std::max(k - 1, 2); --d) {
+        if (k >= kDeepK && d >= kDeepDeg) {
+            for (int32_t grp = 0; grp < 2; ++grp) {
+                const int32_t* b = &g->h_deep[(size_t)(grp * kDeepBuckets + kLightMaxDeg - d)];
+                if (b[1] > b[0]) lb.push_back({d - 1, b[0], b[1] - b[0], grp == 0 ? kItemDeepVertex : kItemLightVertex});
+            }
+            continue;
+        }
         const int64_t cnt = v_at_least(d) - v_at_least(d + 1);
         if (cnt > 0) lb.push_back({d - 1, (int32_t)(v_at_least(d + 1) - n_heavy), (int32_t)cnt, kItemLightVertex});
     }
     std::vector<int32_t> tab;
     int64_t items = 0;
     auto add = [&](const B& b) {
-        const int32_t parts = b.kind == kItemLightVertex ? light_parts(b.key + 1, k, pct)
+        const int32_t parts = b.kind == kItemLightVertex ? light_arcs(b.key + 1, k, pct)
+                              : b.kind == kItemDeepVertex ? light_arcs(b.key + 1, k, pct) * kLightSubs
                               : b.kind == kItemDenseArc  ? dense_parts(b.key, k, pct)
                               : b.kind == kItemDenseVertex ? 1
                                                          : arc_parts(b.key, k, pct);
@@ -539,7 +605,7 @@ QueryDesc make_query(const citron_graph* g, int32_t k, int32_t slot, unsigned lo
     memset(&q, 0, sizeof(q));
     q.dag_ptr = g->d_dag_ptr;
     q.dag_src = g->d_dag_src;
-    q.order = g->pb.order;
+    q.order = k >= kDeepK && g->d_deep_order ? g->d_deep_order : g->pb.order;
     q.rows.rows_off = g->d_rows_off;
     q.rows.rows = g->d_rows;
     q.rows.arc_c = g->d_arc_c;
@@ -696,6 +762,7 @@ static citron_status run_single(citron_graph* g, int32_t k, unsigned long long* 
     ctl.query = make_query(g, k, slot, g->d_ctl->acc, &g->d_ctl->overflow, per_arc, stats ? g->d_stats : nullptr);
     if (vertex_rooted) {
         QueryDesc& q = ctl.query;
+        q.order = g->pb.order;
         q.buckets = g->d_vbuckets[k];
         q.n_buckets = g->n_vbuckets[k];
         q.n_work = g->n_vwork[k];

@@ -105,6 +105,8 @@ struct citron_graph {
     int32_t* d_hscan = nullptr;             // 2 D + 1
     std::vector<int32_t> h_hscan;           // heavy arcs by group and |C_uv|, scanned
     std::vector<int32_t> h_vscan;           // vertices by out-degree, scanned
+    int32_t* d_deep_order = nullptr;        // n: plan order of deep counts (sched_deep_order)
+    std::vector<int32_t> h_deep;            // its bucket bounds (empty: not built)
     uint64_t tri = 0;
     bool tri_ovf = false;
     // per k, and one more (schedule_slot): the merged bucket table of the

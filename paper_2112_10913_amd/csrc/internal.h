@@ -123,7 +123,7 @@ __host__ __device__ inline int dense_space(int c) { return kDenseClasses - (c + 
 struct QueryDesc {
     const int32_t* dag_ptr;
     const int32_t* dag_src;      // source vertex of every arc
-    const int32_t* order;        // vertices by out-degree descending
+    const int32_t* order;        // vertices by out-degree descending (k >= kDeepK: light ones of a deep subgraph first)
     RowsDev rows;
     unsigned long long* acc;     // kAccSlots partial sums, kAccStride words apart
     int32_t* overflow;           // set to 1 when an addition carried
@@ -134,8 +134,8 @@ struct QueryDesc {
     // merged.  Bucket b: buckets[4b] = first item, [4b+1] = first arc (index
     // into harcs) or first light vertex (index into the light part of order),
     // [4b+2] = arcs or vertices in the bucket, [4b+3] = key << 3 | kind
-    // (BucketKind).  An arc or vertex is split into parts (arc_parts /
-    // light_parts); items of a bucket are part-major.  buckets[4 n_buckets]
+    // (BucketKind).  An arc or vertex is split into parts (arc_parts,
+    // light_arcs); items of a bucket are part-major.  buckets[4 n_buckets]
     // = item count.  The vertex-rooted schedule has only the two vertex
     // kinds, each item one whole vertex (heavy ones indexed in order itself).
     const int32_t* buckets;
@@ -154,7 +154,7 @@ struct QueryDesc {
     int32_t sched_end[kDenseClasses];
     int32_t space_begin[kSpaces];
     int32_t space_off[kSpaces];
-    int32_t split_pct;           // split scale the buckets were built with (arc_parts, light_parts)
+    int32_t split_pct;           // split scale the buckets were built with (arc_parts, light_arcs)
     // list mode (arc_list != nullptr): item j is (slot, part) = (arc_items[2j],
     // arc_items[2j+1] & 0xffff) of arc arc_list[slot], split into
     // arc_items[2j+1] >> 16 parts; its counts go to per-arc slot `slot`
@@ -170,7 +170,8 @@ enum BucketKind {
     kItemHeavyVertex = 2,  // a whole heavy vertex, searched from its own root (vertex-rooted)
     kItemLightRoot = 3,    // a whole light vertex, one unit rooted at the vertex (vertex-rooted)
     kItemDenseArc = 4,     // one part of a heavy vertex's arc for the dense kernel (edge-rooted)
-    kItemDenseVertex = 5   // one part of a heavy vertex for the dense kernel: its arcs in turn
+    kItemDenseVertex = 5,  // one part of a heavy vertex for the dense kernel: its arcs in turn
+    kItemDeepVertex = 6    // (a part of) a light vertex with its arcs' branches dealt to kLightSubs sub-parts (edge-rooted)
 };
 
 // Parts a heavy arc with |C_uv| = c is split into for a k-clique count; each
@@ -226,7 +227,7 @@ __host__ __device__ inline int dense_parts(int c, int k, int pct)
 
 // Parts a light vertex (out-degree d <= 64, its subgraph one word per row)
 // is split into: light_arcs of them take every light_arcs-th arc of the
-// vertex, and for deep counts each of these is split again into light_subs
+// vertex, and for deep counts each of these is split again into kLightSubs
 // (a power of two) that take the first-level branches of the same arcs at
 // positions of one residue (speed only).  One wave searching two arcs of a
 // planted 40-clique at k = 9 ran 24 of a launch's 28 ms while 88 % of the
@@ -242,11 +243,15 @@ __host__ __device__ inline int light_arcs(int d, int k, int pct)
     if (k == 6) return scale_parts(d >= 32 ? d / 4 : (d >= 24 ? 3 : 1), pct);
     return scale_parts(d >= 12 ? d / 2 : 1, pct);
 }
-__host__ __device__ inline int light_subs(int d, int k)
-{
-    return k >= 9 && d >= 24 ? 16 : 1;
-}
-__host__ __device__ inline int light_parts(int d, int k, int pct) { return light_arcs(d, k, pct) * light_subs(d, k); }
+// Only vertices of a deep subgraph are split that far: one that closes at
+// least as many triangles as a complete graph of kDeepDeg vertices.  Where
+// every vertex of out-degree 24 and more was, a power-law graph without
+// planted cliques (Chung-Lu 2^17, k = 9) took 4.1 ms for its millions of empty
+// items; 0.95 ms now.
+constexpr int kDeepK = 9;
+constexpr int kDeepDeg = 24;
+constexpr int kDeepTriangles = kDeepDeg * (kDeepDeg - 1) * (kDeepDeg - 2) / 6;
+constexpr int kLightSubs = 16;
 
 // Place a query's launch items (n_items, item_lo, item_stride set) in the
 // item spaces, after those placed before.  Without `dense` the count kernel

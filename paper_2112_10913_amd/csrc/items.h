@@ -137,7 +137,8 @@ __device__ __forceinline__ void decode_run(const ItemSpace& P, int g0, int n, in
             tag = -1;
         } else {
             u = q.order[q.light_first + which];
-            nparts = kind == kItemLightVertex ? light_parts(key + 1, q.k, q.split_pct) : 1;
+            nparts = kind == kItemLightRoot ? 1 : light_arcs(key + 1, q.k, q.split_pct);
+            if (kind == kItemDeepVertex) nparts *= kLightSubs;
             tag = -1;
         }
     }

@@ -46,6 +46,13 @@ hipError_t sched_plan_order(int32_t n, const int32_t* dag_ptr, int32_t D, int32_
 // bounds[b] (b <= 2D) = arcs in the buckets before b
 hipError_t sched_heavy_arcs(int64_t m, const int32_t* dag_ptr, const int32_t* dag_src, const int32_t* arc_c,
                             int32_t D, int32_t* bounds, int32_t* harcs, const SortBuffers& sb, hipStream_t s);
+// out[0 .. n) = the light vertices order[0 .. n) (out-degrees 64 .. kDeepDeg),
+// those of a deep subgraph first, each group by out-degree descending, ties by
+// place in `order`; bucket (g, d) is g kDeepBuckets + 64 - d
+constexpr int kDeepBuckets = kLightMaxDeg - kDeepDeg + 1;
+hipError_t sched_deep_order(int32_t n, const int32_t* order, const int32_t* dag_ptr, const int32_t* rows_off,
+                            const unsigned long long* rows, int32_t* bounds, int32_t* out, const SortBuffers& sb,
+                            hipStream_t s);
 
 // ---- vertex schedule (kernels_sched.hip)
 struct PlanBuffers {

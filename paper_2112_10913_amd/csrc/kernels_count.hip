@@ -62,7 +62,7 @@ constexpr int kProbeNeed = 4;
 constexpr int kProbeTrial = 256;
 constexpr int kProbeRate = 16;
 constexpr int kProbeAgain = 8;
-constexpr int kDeepClaim = 2;           // items a wave claims at once, at most, for k >= 8
+constexpr int kDeepClaim = 8;           // items a wave claims at once, at most, for k >= 7
 constexpr int kBurstIters = 32;         // last-level steps of one leaf burst at most
 constexpr int kBurstMinLanes = 32;      // lanes at a last-level node to keep a burst going
 constexpr int kN3Burst = 8;             // two-level steps between refills of idle lanes
@@ -149,7 +149,7 @@ struct WaveBuf {
     u64* sR;
     u64* hM;         // heavy stacks
     u64* hR;
-    int32_t* units;  // search roots: row | sub-part << 8 | log2 of the sub-parts << 16
+    int32_t* units;  // search roots: row | sub-part << 8 | (one of kLightSubs sub-parts) << 16
     int n;           // rows in use (wave-uniform)
     int nu;          // units in use (wave-uniform)
     int arc_max;     // nodes with 64 < c <= arc_max are copied to LDS
@@ -309,9 +309,9 @@ __device__ __forceinline__ void light_engine(WaveBuf& wb, Acc& A, u64* __restric
                     urow = uwl & 0xff;
                     uneed = mtl & 255;
                     ubase = mtl >> 8;
-                    // a sub-part takes the branches at positions q mod 2^s
-                    const int s = uwl >> 16;
-                    branches = readlane64(m1, l) & ((s == 4 ? 0x0001000100010001ull : ~0ull) << ((uwl >> 8) & 0xff));
+                    // a sub-part takes the branches at positions q mod kLightSubs
+                    static_assert(kLightSubs == 16, "mask of every 16th position");
+                    branches = readlane64(m1, l) & ((uwl >> 16 ? 0x0001000100010001ull : ~0ull) << ((uwl >> 8) & 0xff));
                 }
             } else {
                 const int r = __popcll(want & lt_mask);
@@ -953,7 +953,7 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
         const int qi = end ? -1 : field(kItQuery);
         const int kind = end ? kItemHeavyArc : field(kItKind);
         const int d = end ? 0 : field(kItDegree);
-        const bool heavy = kind != kItemLightVertex && kind != kItemLightRoot;
+        const bool heavy = kind != kItemLightVertex && kind != kItemDeepVertex && kind != kItemLightRoot;
         // run the queue before an item whose rows it cannot take, once it is
         // full enough, and before the query changes
         if (wb.n + (heavy ? 0 : d + 1) > kWaveBufRows || wb.n >= P.flush_rows || qi != cur) {
@@ -1018,13 +1018,13 @@ __global__ void __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(
                 wb.units[wb.nu] = wb.n + d;
             }
             // part = arc residue + light_arcs * sub-part
-            const int subs = nparts > 1 ? light_subs(d, k) : 1;
+            const int subs = kind == kItemDeepVertex ? kLightSubs : 1;
             const int every = nparts / subs, sub = part / every;
             const bool unit = !from_root && lane < d && (r >= 0 ? lane == r : lane % every == part - sub * every);
             const u64 um = __ballot(unit);
             if (unit)
                 wb.units[wb.nu + __popcll(um & (lane == 0 ? 0ull : (~0ull >> (kWave - lane))))] =
-                    (wb.n + lane) | (sub << 8) | (subs == 16 ? 4 << 16 : 0);
+                    (wb.n + lane) | (sub << 8) | (subs > 1 ? 1 << 16 : 0);
             wb.nu += __popcll(um) + (from_root ? 1 : 0);
             wb.n += d + (from_root ? 1 : 0);
         }
@@ -1130,9 +1130,9 @@ hipError_t launch_count(const CountLaunch& cl, hipStream_t s)
     const int64_t need = ((int64_t)rest + cl.wg_waves - 1) / cl.wg_waves;
     if (need < c2.blocks) c2.blocks = (int32_t)need;
     // deep counts: an item's cost is far from what its key says, so runs stay
-    // short (16 light items of a planted clique's vertices in one run took as
-    // long as the rest of a k = 9 launch)
-    set_runs(P.items, (int64_t)c2.blocks * cl.wg_waves, cl.max_k <= 6 ? kMaxClaim : (cl.max_k == 7 ? 8 : kDeepClaim));
+    // shorter (Chung-Lu 2^17, k = 8, runs of 2, 4 and 8: 1.21, 1.04 and 0.92
+    // ms, for their decoding; with planted cliques, 2^14, k = 9, 4.6 to 4.8 ms)
+    set_runs(P.items, (int64_t)c2.blocks * cl.wg_waves, cl.max_k <= 6 ? kMaxClaim : kDeepClaim);
     switch (stack_mode(cl.max_k)) {
     case kStackOne: return launch_mode<kStackOne>(P, c2, s);
     case kStackReg: return launch_mode<kStackReg>(P, c2, s);

@@ -5,6 +5,8 @@
 // into batches of about light_rows rows, and a header with the item counts.
 // The heavy arcs: arcs of heavy vertices, those above kDenseMax first, each
 // group by |C_uv| (descending).
+// Deep counts take the light vertices in an order of their own, those of a
+// deep subgraph first.
 //
 // Both orders break ties by id, so they are fixed by the graph alone: the
 // strided shares of a count (citron_count_part) cover the same items in
@@ -123,6 +125,43 @@ hipError_t sched_heavy_arcs(int64_t m, const int32_t* dag_ptr, const int32_t* da
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return sort_and_split(m, 2 * D, bounds, harcs, sb, s);
+}
+
+// deep light vertices: one wave per vertex u = order[j] counts the triangles of
+// its subgraph (rows of one word, a lane each); key = (deep ? 0 : kDeepBuckets)
+// + 64 - d(u), over u
+__global__ void __launch_bounds__(256) deep_keys_kernel(int32_t n, const int32_t* __restrict__ order,
+                                                        const int32_t* __restrict__ dag_ptr,
+                                                        const int32_t* __restrict__ rows_off,
+                                                        const u64* __restrict__ rows, u64* __restrict__ keys)
+{
+    __shared__ u64 row[256];
+    const int wid = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const int j = blockIdx.x * (256 / kWave) + wid;
+    if (j >= n) return;                  // whole waves; each keeps to its own rows
+    const int u = order[j];
+    const int d = dag_ptr[u + 1] - dag_ptr[u];
+    u64* const mine = row + wid * kWave;
+    const u64 m = lane < d ? rows[(int64_t)rows_off[u] + lane] : 0ull;
+    mine[lane] = m;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    int t = 0;
+    for (u64 r = m; r; r &= r - 1) t += __popcll(m & mine[__builtin_ctzll(r)]);
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, kWave);
+    if (lane == 0)
+        keys[j] = ((u64)(unsigned)((t >= kDeepTriangles ? 0 : kDeepBuckets) + kLightMaxDeg - d) << 32) | (u64)(unsigned)u;
+}
+
+hipError_t sched_deep_order(int32_t n, const int32_t* order, const int32_t* dag_ptr, const int32_t* rows_off,
+                            const u64* rows, int32_t* bounds, int32_t* out, const SortBuffers& sb, hipStream_t s)
+{
+    if (n <= 0) return launch_fill_i32(bounds, 0, 2 * kDeepBuckets + 1, s);
+    deep_keys_kernel<<<(n + 256 / kWave - 1) / (256 / kWave), 256, 0, s>>>(n, order, dag_ptr, rows_off, rows, sb.keys_a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return sort_and_split(n, 2 * kDeepBuckets, bounds, out, sb, s);
 }
 
 // ---------------------------------------------------------------- plan

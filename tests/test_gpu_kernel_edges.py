@@ -400,3 +400,28 @@ def test_per_arc_counts_of_k_5_keep_a_schedule_of_their_own(citron_gpu, n, p):
     assert h.count_per_arc(4)[0] == h.count(4)
     assert citron_gpu.count_batch([h], [5]) == [want]
     h.free()
+
+
+@pytest.mark.parametrize("k", [8, 9, 11])
+def test_light_vertices_of_deep_and_shallow_subgraphs(citron_gpu, k):
+    """k >= 9 splits light vertices further from the triangles of K_24 on: out-
+    degrees around 24 and 64, complete subgraphs beside sparse ones of the same
+    out-degree, in whole counts, shares, batches and per arc."""
+    from math import comb
+    sizes = [23, 24, 25, 26, 40, 64, 65, 66]
+    cl = gg.disjoint_cliques(sizes)
+    er = gg.erdos_renyi(400, 90, seed=k)
+    ptr = np.concatenate([cl.row_ptr, cl.row_ptr[-1] + er.row_ptr[1:]]).astype(np.int32)
+    g = gg.CSR(cl.n + er.n, ptr, np.concatenate([cl.col, er.col + cl.n]).astype(np.int32), "mixed")
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    sparse = citron_gpu.Graph.from_csr(er.row_ptr, er.col).order()
+    want = sum(comb(s, k) for s in sizes) + sparse.count_vertex_rooted(k)
+    assert h.count(k) == want
+    assert h.count_vertex_rooted(k) == want
+    assert sum(h.count_part(k, i, 5)[0] for i in range(5)) == want
+    total, per = h.count_per_arc(k)
+    assert total == want and int(per.sum()) == want
+    assert citron_gpu.count_batch([h, sparse, h], [k, k, 9]) == [want, sparse.count(k), h.count(9)]
+    assert sparse.count(k) == sparse.count_vertex_rooted(k)
+    for x in (h, sparse):
+        x.free()

@@ -152,8 +152,10 @@ static void free_graph_memory(citron_graph* g)
     dfree(g->d_hrows);
     dfree(g->d_hpos);
     dfree(g->d_hinv);
-    dfree(g->d_harcs);
-    dfree(g->d_hscan);
+    for (auto& ha : g->harcs) {
+        dfree(ha.d_arcs);
+        ha.h_scan.clear();
+    }
     dfree(g->d_deep_order);
     for (int32_t* p : g->retired_buckets) dfree(p);
     g->retired_buckets.clear();
@@ -234,8 +236,26 @@ citron_status ensure_plan(citron_graph* g, const citron_tuning& t)
     return CITRON_OK;
 }
 
-// Subgraph rows of every vertex (Algorithm 5), per-arc |C_uv|, the triangle
-// count and the schedule of heavy arcs; built once per graph.
+static SortedRowsParams sorted_rows_params(const citron_graph* g)
+{
+    SortedRowsParams sp;
+    sp.n_heavy = g->plan.n_heavy;
+    sp.order = g->pb.order;
+    sp.dag_ptr = g->d_dag_ptr;
+    sp.dag_col = g->d_dag_col;
+    sp.row_ptr = g->d_row_ptr;
+    sp.key = g->order_kind == 1 ? g->d_key : nullptr;
+    sp.rows_off = g->d_rows_off;
+    sp.rows = g->d_rows;
+    sp.hoff = g->d_hoff;
+    sp.hrows = g->d_hrows;
+    sp.hpos = g->d_hpos;
+    sp.hinv = g->d_hinv;
+    return sp;
+}
+
+// Subgraph rows of every vertex (Algorithm 5), per-arc |C_uv| and the triangle
+// count; built once per graph.
 citron_status ensure_rows(citron_graph* g)
 {
     if (g->rows_valid) return CITRON_OK;
@@ -245,14 +265,11 @@ citron_status ensure_rows(citron_graph* g)
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     if (g->max_outdeg > kMaxDeg)
         return fail(CITRON_EINVAL, "out-degree above 4096 in the degree-ordered DAG is not supported");
-    const int32_t D = std::max(g->max_outdeg, 2);
-    const bool heavy = g->plan.n_heavy > 0;     // without heavy vertices there is no arc schedule
+    const bool heavy = g->plan.n_heavy > 0;
     hipStream_t s = g->stream;
     int64_t* acct = &g->device_bytes;
     if ((!g->d_rows_off && (st = dalloc(&g->d_rows_off, (size_t)g->n + 1, acct, "row offsets"))) ||
-        (!g->d_arc_c && (st = dalloc(&g->d_arc_c, (size_t)g->m, acct, "arc sizes"))) ||
-        (heavy && !g->d_harcs && (st = dalloc(&g->d_harcs, (size_t)g->m, acct, "heavy arcs"))) ||
-        (heavy && !g->d_hscan && (st = dalloc(&g->d_hscan, 2 * (size_t)D + 1, acct, "arc histogram"))))
+        (!g->d_arc_c && (st = dalloc(&g->d_arc_c, (size_t)g->m, acct, "arc sizes"))))
         return st;
     // Row offsets are int32, so the rows of all vertices, sum over u of
     // d(u) * ceil(d(u)/64) words, must stay below 2^31.  That sum is at most
@@ -318,56 +335,16 @@ citron_status ensure_rows(citron_graph* g)
     e = launch_build_rows(P, device_cus(g->device) * g->tuning.build_blocks_per_cu, s);
     if (e != hipSuccess) return hip_fail(e, "subgraph build");
     if (heavy) {
-        SortedRowsParams sp;
-        sp.n_heavy = g->plan.n_heavy;
-        sp.order = g->pb.order;
-        sp.dag_ptr = g->d_dag_ptr;
-        sp.dag_col = g->d_dag_col;
-        sp.row_ptr = g->d_row_ptr;
-        sp.key = g->order_kind == 1 ? g->d_key : nullptr;
-        sp.rows_off = g->d_rows_off;
-        sp.rows = g->d_rows;
-        sp.hoff = g->d_hoff;
-        sp.hrows = g->d_hrows;
-        sp.hpos = g->d_hpos;
-        sp.hinv = g->d_hinv;
-        e = launch_sorted_rows(sp, s);
+        e = launch_sorted_rows(sorted_rows_params(g), s);
         if (e != hipSuccess) return hip_fail(e, "sorted rows");
     }
-    SortBuffers sb = {};
-    if (heavy) {
-        const size_t tb = sched_sort_temp_bytes(g->m, 2 * D);
-        if (tb == 0) return fail(CITRON_EDEVICE, "sort workspace query failed");
-        unsigned char* tmp = nullptr;
-        if ((st = dalloc(&sb.keys_a, (size_t)g->m + 1, nullptr, "arc schedule")) ||
-            (st = dalloc(&sb.keys_b, (size_t)g->m + 1, nullptr, "arc schedule")) ||
-            (st = dalloc(&tmp, tb, nullptr, "arc schedule"))) {
-            dfree(sb.keys_a);
-            dfree(sb.keys_b);
-            return st;
-        }
-        sb.temp = tmp;
-        sb.temp_bytes = tb;
-    }
-    if (heavy) e = sched_heavy_arcs(g->m, g->d_dag_ptr, g->d_dag_src, g->d_arc_c, D, g->d_hscan, g->d_harcs, sb, s);
-    g->h_hscan.assign(2 * (size_t)D + 1, 0);
-    if (e == hipSuccess && heavy)
-        e = hipMemcpyAsync(g->h_small->hist, g->d_hscan, sizeof(int32_t) * (2 * (size_t)D + 1),
-                           hipMemcpyDeviceToHost, s);
     if (e == hipSuccess)
         e = hipMemcpyAsync(g->h_small->build, sd->build, sizeof(sd->build), hipMemcpyDeviceToHost, s);
     {
         const hipError_t w = hipStreamSynchronize(s);
         if (e == hipSuccess) e = w;
     }
-    dfree(sb.keys_a);
-    dfree(sb.keys_b);
-    {
-        unsigned char* tmp = static_cast<unsigned char*>(sb.temp);
-        dfree(tmp);
-    }
     if (e != hipSuccess) return hip_fail(e, "subgraph build");
-    if (heavy) memcpy(g->h_hscan.data(), g->h_small->hist, sizeof(int32_t) * (2 * (size_t)D + 1));
     g->tri = 0;
     g->tri_ovf = false;
     memset(g->build_stats, 0, sizeof(g->build_stats));
@@ -380,6 +357,59 @@ citron_status ensure_rows(citron_graph* g)
         g->build_stats[kStatBytes] += b.bytes;
     }
     g->rows_valid = true;
+    return CITRON_OK;
+}
+
+// Heavy arcs of counts of k < kDensityK, or (deep) of the others, by group and
+// |C_uv|; built at the first such count, none without heavy vertices.
+citron_status ensure_heavy_arcs(citron_graph* g, bool deep)
+{
+    citron_graph::HeavyArcs& ha = g->harcs[deep];
+    if (!ha.h_scan.empty() || g->plan.n_heavy == 0) return CITRON_OK;
+    const int32_t D = std::max(g->max_outdeg, 2);
+    const int32_t nb = kHeavyGroups * D;
+    hipStream_t s = g->stream;
+    citron_status st;
+    if (!ha.d_arcs && (st = dalloc(&ha.d_arcs, (size_t)g->m, &g->device_bytes, "heavy arcs"))) return st;
+    const size_t tb = sched_sort_temp_bytes(g->m, nb);
+    if (tb == 0) return fail(CITRON_EDEVICE, "sort workspace query failed");
+    SortBuffers sb = {};
+    unsigned char* tmp = nullptr;
+    int32_t* d_scan = nullptr;
+    uint8_t* density = nullptr;
+    if ((st = dalloc(&sb.keys_a, (size_t)g->m, nullptr, "arc schedule")) ||
+        (st = dalloc(&sb.keys_b, (size_t)g->m, nullptr, "arc schedule")) ||
+        (st = dalloc(&tmp, tb, nullptr, "arc schedule")) ||
+        (st = dalloc(&d_scan, (size_t)nb + 1, nullptr, "arc schedule")) ||
+        (deep && (st = dalloc(&density, (size_t)g->n, nullptr, "arc schedule")))) {
+        dfree(sb.keys_a);
+        dfree(sb.keys_b);
+        dfree(tmp);
+        dfree(d_scan);
+        return st;
+    }
+    sb.temp = tmp;
+    sb.temp_bytes = tb;
+    hipError_t e = deep ? launch_density(sorted_rows_params(g), g->d_arc_c, density, s) : hipSuccess;
+    if (e == hipSuccess)
+        e = sched_heavy_arcs(g->m, g->d_dag_ptr, g->d_dag_src, g->d_arc_c, density, D, d_scan, ha.d_arcs, sb, s);
+    std::vector<int32_t> scan((size_t)nb + 1);
+    // (through pinned memory up to out-degrees of about 1,000)
+    const size_t bytes = sizeof(int32_t) * scan.size();
+    int32_t* hist = bytes <= sizeof(g->h_small->hist) ? g->h_small->hist : scan.data();
+    if (e == hipSuccess) e = hipMemcpyAsync(hist, d_scan, bytes, hipMemcpyDeviceToHost, s);
+    {
+        const hipError_t w = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = w;
+    }
+    dfree(sb.keys_a);
+    dfree(sb.keys_b);
+    dfree(tmp);
+    dfree(d_scan);
+    dfree(density);
+    if (e != hipSuccess) return hip_fail(e, "arc schedule");
+    if (hist != scan.data()) memcpy(scan.data(), hist, bytes);
+    ha.h_scan = std::move(scan);
     return CITRON_OK;
 }
 
@@ -461,8 +491,9 @@ citron_status ensure_buckets(citron_graph* g, int32_t k, int32_t slot)
 {
     const int32_t pct = g->tuning.split_pct;
     if (g->d_buckets[slot] && g->bucket_split[slot] == pct) return CITRON_OK;
-    if (k >= kDeepK) {
-        const citron_status st = ensure_deep_order(g);
+    {
+        citron_status st = ensure_heavy_arcs(g, k >= kDensityK);
+        if (!st && k >= kDeepK) st = ensure_deep_order(g);
         if (st) return st;
     }
     if (g->d_buckets[slot]) {
@@ -486,16 +517,18 @@ citron_status ensure_buckets(citron_graph* g, int32_t k, int32_t slot)
         const int64_t cnt = v_at_least(d) - v_at_least(d + 1);
         if (cnt > 0 && whole(d)) db.push_back({d, (int32_t)v_at_least(d + 1), (int32_t)cnt, kItemDenseVertex});
     }
-    // heavy-arc buckets by |C_uv|, of vertices above kDenseMax (group 0) and
-    // of the others, whose arcs are not scheduled where the vertices are
-    for (int32_t c = D - 1; c >= k - 2; --c)
-        for (int32_t grp = 0; grp < 2; ++grp) {
-            if (grp == 1 && whole(kDenseMax)) continue;
-            const size_t j = (size_t)(grp * D + D - 1 - c);
-            const int32_t cnt = g->h_hscan[j + 1] - g->h_hscan[j];
+    // heavy-arc buckets by |C_uv|, of vertices above kDenseMax (the first
+    // kDensities groups) and of the others, whose arcs are not scheduled where
+    // the vertices are
+    const std::vector<int32_t>& hscan = g->harcs[k >= kDensityK].h_scan;
+    for (int32_t c = D - 1; c >= k - 2 && n_heavy > 0; --c)
+        for (int32_t grp = 0; grp < kHeavyGroups; ++grp) {
+            if (grp >= kDensities && whole(kDenseMax)) continue;
+            const size_t j = (size_t)grp * D + (size_t)(D - 1 - c);
+            const int32_t cnt = hscan[j + 1] - hscan[j];
             if (cnt <= 0) continue;
-            if (dense_arc(c, k)) db.push_back({c, g->h_hscan[j], cnt, kItemDenseArc});
-            else hb.push_back({c, g->h_hscan[j], cnt, kItemHeavyArc});
+            if (dense_arc(c, k, grp % kDensities)) db.push_back({c, hscan[j], cnt, kItemDenseArc});
+            else hb.push_back({c, hscan[j], cnt, kItemHeavyArc});
         }
     // the dense spaces want their buckets largest first (k = 5: vertices and
     // the arcs of larger ones)
@@ -609,7 +642,7 @@ QueryDesc make_query(const citron_graph* g, int32_t k, int32_t slot, unsigned lo
     q.rows.rows_off = g->d_rows_off;
     q.rows.rows = g->d_rows;
     q.rows.arc_c = g->d_arc_c;
-    q.rows.harcs = g->d_harcs;
+    q.rows.harcs = g->harcs[k >= kDensityK].d_arcs;
     q.rows.hoff = g->d_hoff;
     q.rows.hrows = g->d_hrows;
     q.rows.hpos = g->d_hpos;

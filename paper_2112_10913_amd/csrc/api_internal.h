@@ -101,9 +101,12 @@ struct citron_graph {
     unsigned long long* d_hrows = nullptr;
     uint16_t* d_hpos = nullptr;             // m
     uint16_t* d_hinv = nullptr;             // m
-    int32_t* d_harcs = nullptr;             // m
-    int32_t* d_hscan = nullptr;             // 2 D + 1
-    std::vector<int32_t> h_hscan;           // heavy arcs by group and |C_uv|, scanned
+    // heavy arcs by group and |C_uv|: of counts of k < kDensityK, which take all
+    // vertices for one class, and of deeper ones
+    struct HeavyArcs {
+        int32_t* d_arcs = nullptr;          // m
+        std::vector<int32_t> h_scan;        // bucket bounds (empty: not built)
+    } harcs[2];
     std::vector<int32_t> h_vscan;           // vertices by out-degree, scanned
     int32_t* d_deep_order = nullptr;        // n: plan order of deep counts (sched_deep_order)
     std::vector<int32_t> h_deep;            // its bucket bounds (empty: not built)
@@ -146,6 +149,7 @@ int32_t arc_max_for(const citron_tuning& t, int32_t max_k);
 int device_cus(int dev);
 citron_status ensure_plan(citron_graph* g, const citron_tuning& t);
 citron_status ensure_rows(citron_graph* g);
+citron_status ensure_heavy_arcs(citron_graph* g, bool deep);
 // The schedule of a k-clique count: that of k, except that per-arc counts of
 // k = 5 keep to arcs.  The dense kernel adds a vertex's products up over all
 // its arcs, and separating them again, an accumulator pass per arc, cost more

@@ -97,7 +97,7 @@ struct RowsDev {
     const int32_t* rows_off;        // n + 1: first word of u's rows (< 2^31 words)
     const unsigned long long* rows; // all rows
     const int32_t* arc_c;           // m: popcount of arc e's row = |C_uv|
-    const int32_t* harcs;           // arcs of heavy vertices: of those above kDenseMax, then of the others, each by |C_uv| descending
+    const int32_t* harcs;           // arcs of heavy vertices by group (heavy_group), then |C_uv| descending
     // Rows of the heavy vertices again, in the order of the DAG: positions
     // sorted by the ordering (key, id), so that a vertex's neighbours come
     // after it and every matrix of rows is strictly upper triangular.  The
@@ -200,9 +200,37 @@ __host__ __device__ inline int arc_parts(int c, int k, int pct)
 // candidates on alike).  From 33, 17 and 9 candidates on: 100.9, 96 and 94.8
 // ms for R-MAT 20, k = 6; 23.2, 21.7 and 21.7 for R-MAT 16, k = 7; 4.29, 4.0
 // and 4.0 for a served mix of 48 counts.
+//
+// A mask costs the dense kernel the same however few candidates it has left,
+// while the count kernel packs them, so the deeper the count the denser a
+// subgraph has to be.  Random graphs of edge probability p, dense kernel and
+// count kernel: k = 6, p = 0.2 0.30 and 0.27 ms, 0.4 0.31 and 0.41; k = 7,
+// 0.3 0.79 and 0.64, 0.4 1.0 and 1.0, 0.5 1.6 and 2.2; k = 8, 0.5 8.1 and 3.3,
+// 0.7 12.8 and 12.3, 0.8 13.7 and 16.5; k = 9, 0.7 71 and 36, 0.8 72 and 65,
+// 0.9 144 and 202; k = 10, 0.8 449 and 252.  The subgraphs of power-law graphs
+// lie between 0.75 and 0.95 (R-MAT 12, k = 10: 76 and 101 ms).
 constexpr int kDenseMin = 17;
 constexpr int kDenseMax = 64 * kDenseClasses;
-__host__ __device__ inline bool dense_arc(int c, int k) { return k >= 5 && c >= kDenseMin && c <= kDenseMax; }
+__host__ __device__ inline bool dense_size(int c) { return c >= kDenseMin && c <= kDenseMax; }
+// class of subgraphs with `edges` of `pairs` pairs adjacent (pairs < 2^20)
+constexpr int kDensities = 4;
+constexpr int kDensityK = 7;         // counts that look at it
+__host__ __device__ inline int density_class(unsigned edges, unsigned pairs)
+{
+    const unsigned e = 100 * edges;
+    return (e >= 40 * pairs) + (e >= 75 * pairs) + (e >= 88 * pairs);
+}
+__host__ __device__ inline bool dense_arc(int c, int k, int density)
+{
+    return k >= 5 && dense_size(c) && density >= (k < kDensityK ? 0 : k == 7 ? 1 : k <= 9 ? 2 : 3);
+}
+// Group of a heavy vertex's arc in harcs: arcs of vertices above kDenseMax
+// first, and, where the dense kernel may take them, by their vertex's class.
+constexpr int kHeavyGroups = 2 * kDensities;
+__host__ __device__ inline int heavy_group(int d, int c, int density)
+{
+    return (d > kDenseMax ? 0 : kDensities) + (dense_size(c) ? density : 0);
+}
 
 // Heavy vertices the dense kernel takes whole in counts of k = 4 and 5, where
 // an arc's subgraph would serve one triangle count at most: the vertex's own

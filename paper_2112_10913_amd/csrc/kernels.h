@@ -40,12 +40,13 @@ size_t sched_sort_temp_bytes(int64_t n, int32_t nb);   // n keys of nb buckets
 // descending, ties by id; bounds[i] (i < D) = vertices of out-degree > D - i
 hipError_t sched_plan_order(int32_t n, const int32_t* dag_ptr, int32_t D, int32_t* bounds, int32_t* order,
                             const SortBuffers& sb, hipStream_t s);
-// harcs[0 .. bounds[2D]) = arcs of vertices with out-degree > 64: first those
-// of vertices above kDenseMax, then the others, each by |C_uv| descending,
-// ties by arc index; bucket (g, c) of group g = 0, 1 is g D + D - 1 - c, and
-// bounds[b] (b <= 2D) = arcs in the buckets before b
+// harcs[0 .. bounds[kHeavyGroups D]) = arcs of vertices with out-degree > 64 by
+// group, each by |C_uv| descending, ties by arc index; bucket (g, c) is
+// g D + D - 1 - c, and bounds[b] = arcs in the buckets before b.  density[u]
+// is the class of a heavy vertex u (launch_density); null: all of class 0.
 hipError_t sched_heavy_arcs(int64_t m, const int32_t* dag_ptr, const int32_t* dag_src, const int32_t* arc_c,
-                            int32_t D, int32_t* bounds, int32_t* harcs, const SortBuffers& sb, hipStream_t s);
+                            const uint8_t* density, int32_t D, int32_t* bounds, int32_t* harcs, const SortBuffers& sb,
+                            hipStream_t s);
 // out[0 .. n) = the light vertices order[0 .. n) (out-degrees 64 .. kDeepDeg),
 // those of a deep subgraph first, each group by out-degree descending, ties by
 // place in `order`; bucket (g, d) is g kDeepBuckets + 64 - d
@@ -109,6 +110,8 @@ struct SortedRowsParams {
     uint16_t* hinv;
 };
 hipError_t launch_sorted_rows(const SortedRowsParams& P, hipStream_t s);
+// density[u] = class (density_class) of every heavy vertex u; the sorted rows are built
+hipError_t launch_density(const SortedRowsParams& P, const int32_t* arc_c, uint8_t* density, hipStream_t s);
 hipError_t launch_build_rows(const BuildParams& P, int32_t blocks, hipStream_t s);
 hipError_t launch_arc_c_to_u64(int64_t m, const int32_t* arc_c, unsigned long long* out, hipStream_t s);
 

@@ -3,8 +3,8 @@
 // The plan: vertices of out-degree >= 2 by out-degree (descending), the
 // heavy ones (out-degree > 64) as items of their own, the light ones packed
 // into batches of about light_rows rows, and a header with the item counts.
-// The heavy arcs: arcs of heavy vertices, those above kDenseMax first, each
-// group by |C_uv| (descending).
+// The heavy arcs: arcs of heavy vertices by group (heavy_group), each group by
+// |C_uv| (descending).
 // Deep counts take the light vertices in an order of their own, those of a
 // deep subgraph first.
 //
@@ -35,15 +35,20 @@ __global__ void plan_keys_kernel(int32_t n, const int32_t* __restrict__ dag_ptr,
 }
 
 // heavy arcs: key of arc e = (group D + D - 1 - |C_uv|) << 32 | e when the
-// source has out-degree > 64, group 0 above kDenseMax, else 1
+// source has out-degree > 64
 __global__ void harc_keys_kernel(int64_t m, const int32_t* __restrict__ dag_ptr, const int32_t* __restrict__ dag_src,
-                                 const int32_t* __restrict__ arc_c, int32_t D, u64* __restrict__ keys)
+                                 const int32_t* __restrict__ arc_c, const uint8_t* __restrict__ density, int32_t D,
+                                 u64* __restrict__ keys)
 {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= m) return;
     const int u = dag_src[e];
     const int d = dag_ptr[u + 1] - dag_ptr[u];
-    const int bucket = d <= kLightMaxDeg ? 2 * D : (d > kDenseMax ? 0 : D) + D - 1 - arc_c[e];
+    int bucket = kHeavyGroups * D;
+    if (d > kLightMaxDeg) {
+        const int c = arc_c[e];
+        bucket = heavy_group(d, c, density ? density[u] : 0) * D + D - 1 - c;
+    }
     keys[e] = ((u64)(unsigned)bucket << 32) | (u64)e;
 }
 
@@ -118,13 +123,14 @@ hipError_t sched_plan_order(int32_t n, const int32_t* dag_ptr, int32_t D, int32_
 }
 
 hipError_t sched_heavy_arcs(int64_t m, const int32_t* dag_ptr, const int32_t* dag_src, const int32_t* arc_c,
-                            int32_t D, int32_t* bounds, int32_t* harcs, const SortBuffers& sb, hipStream_t s)
+                            const uint8_t* density, int32_t D, int32_t* bounds, int32_t* harcs, const SortBuffers& sb,
+                            hipStream_t s)
 {
-    if (m <= 0) return launch_fill_i32(bounds, 0, 2 * D + 1, s);
-    harc_keys_kernel<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(m, dag_ptr, dag_src, arc_c, D, sb.keys_a);
+    if (m <= 0) return launch_fill_i32(bounds, 0, kHeavyGroups * D + 1, s);
+    harc_keys_kernel<<<(unsigned)((m + 255) / 256), 256, 0, s>>>(m, dag_ptr, dag_src, arc_c, density, D, sb.keys_a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return sort_and_split(m, 2 * D, bounds, harcs, sb, s);
+    return sort_and_split(m, kHeavyGroups * D, bounds, harcs, sb, s);
 }
 
 // deep light vertices: one wave per vertex u = order[j] counts the triangles of

@@ -479,6 +479,7 @@ citron_status citron_server_add_graph(citron_server* s, citron_graph* g, int32_t
         // out-neighbours roots a possible triangle
         if (g->max_outdeg >= 2) {
             citron_status st = ensure_rows(g);
+            if (!st) st = ensure_heavy_arcs(g, false);
             if (st) return st;
         }
     }

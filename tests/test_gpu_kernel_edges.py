@@ -425,3 +425,32 @@ def test_light_vertices_of_deep_and_shallow_subgraphs(citron_gpu, k):
     assert sparse.count(k) == sparse.count_vertex_rooted(k)
     for x in (h, sparse):
         x.free()
+
+
+@pytest.mark.parametrize("k", [6, 7, 8, 9, 10])
+def test_heavy_arcs_of_every_density_class(citron_gpu, k):
+    """One graph of heavy vertices of four densities: from k = 7 on the dense
+    kernel takes the arcs of the denser ones only, the count kernel the rest."""
+    sizes = ((620, 0.2), (260, 0.55), (180, 0.8)) if k < 9 else ((620, 0.2), (220, 0.5), (110, 0.8))
+    parts = [gg.erdos_renyi(n, p * (n - 1), seed=n) for n, p in sizes] + [gg.complete(84 if k < 9 else 70)]
+    n = 0
+    ptr, col = [np.zeros(1, np.int64)], []
+    for g in parts:
+        ptr.append(g.row_ptr[1:] + ptr[-1][-1])
+        col.append(g.col + n)
+        n += g.n
+    g = gg.CSR(n, np.concatenate(ptr).astype(np.int32), np.concatenate(col).astype(np.int32), "classes")
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    want = 0
+    for p in parts:
+        one = citron_gpu.Graph.from_csr(p.row_ptr, p.col).order()
+        want += one.count_vertex_rooted(k)
+        one.free()
+    assert h.count(k) == want
+    assert sum(h.count_part(k, i, 3)[0] for i in range(3)) == want
+    total, per = h.count_per_arc(k)
+    assert total == want and int(per.sum()) == want
+    some = np.random.default_rng(k).choice(g.m, 300, replace=False)
+    assert np.array_equal(h.count_arcs(k, some), per[some])
+    assert citron_gpu.count_batch([h, h], [k, 5]) == [want, h.count(5)]
+    h.free()

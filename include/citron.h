@@ -294,6 +294,12 @@ citron_status citron_work_stats(citron_graph* g, int32_t k, uint64_t* stats);
 
 void citron_free(citron_graph* g);       /* NULL is a no-op */
 
+/* Device and pinned host memory of freed graphs is kept for later ones, up to
+ * 1 GiB per device, and given back when an allocation of the library's fails.
+ * This call gives all of it back at once, for a program that wants the memory
+ * for something else; graphs, batches and servers in use are not touched. */
+void citron_release_memory(void);
+
 /* Reason for the last failure on this thread; valid until the next call. */
 const char* citron_last_error(void);
 

@@ -134,6 +134,8 @@ def load_library():
     lib.citron_work_stats.restype = ctypes.c_int32
     lib.citron_free.argtypes = [vp]
     lib.citron_free.restype = None
+    lib.citron_release_memory.argtypes = []
+    lib.citron_release_memory.restype = None
     lib.citron_last_error.argtypes = []
     lib.citron_last_error.restype = ctypes.c_char_p
     lib.citron_device_info.argtypes = [_i32p, _i32p, ctypes.c_char_p]
@@ -437,6 +439,12 @@ def order_noalloc(row_ptr, col, dag_ptr, dag_col, stream=None) -> int:
     if st:
         raise _err(st)
     return mx.value
+
+
+def release_memory() -> None:
+    """Give back the device and pinned memory that freed graphs left for later
+    ones (the library does so by itself when it runs out)."""
+    load_library().citron_release_memory()
 
 
 def batch_progress() -> tuple[int, int]:

@@ -1342,6 +1342,8 @@ void citron_free(citron_graph* g)
     delete g;
 }
 
+void citron_release_memory(void) { pool_release(); }
+
 const char* citron_last_error(void) { return g_last_error.c_str(); }
 
 citron_status citron_device_info(int32_t* cus, int32_t* lds_bytes, char* name64)

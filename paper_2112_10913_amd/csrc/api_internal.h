@@ -137,6 +137,10 @@ namespace citron {
 // graphs (pool.cpp).  A block goes back only after the work that used it.
 hipError_t pool_malloc(void** p, size_t bytes);
 void pool_free(void* p);
+// Gives all idle blocks back.
+void pool_release();
+// hipMalloc, with the pool's idle blocks given back first if it fails.
+hipError_t device_malloc(void** p, size_t bytes);
 hipError_t pool_host_malloc(void** p, size_t bytes);
 void pool_host_free(void* p, size_t bytes);
 

@@ -125,7 +125,7 @@ citron_status batch_build(const BatchKey& key, const citron_tuning& t, BatchExec
     const int64_t swords = count_scratch_words(0, max_k, wg);
 #define BALLOC(p, bytes)                                                              \
     do {                                                                              \
-        e = hipMalloc((void**)&(p), (bytes) > 0 ? (bytes) : 8);                       \
+        e = device_malloc((void**)&(p), (bytes));                                     \
         if (e != hipSuccess) return fail(CITRON_ENOMEM, "hipMalloc failed for batch"); \
     } while (0)
     // one block: partial sums, flags, and from a line of their own the cursors

@@ -6,7 +6,9 @@
 // of a 2^20-vertex graph and more than half of the 0.44 ms of a 2^8-vertex
 // one.  Freed blocks are kept, at most kPoolBytes per device and
 // kPoolHostBlocks pinned ones, the oldest given back first, all of them when
-// an allocation fails.  A block is only handed to pool_free once the work that
+// an allocation fails, here or through device_malloc, which the library's
+// other device memory comes from, or when the program asks (pool_release).  A
+// block is only handed to pool_free once the work that
 // used it has completed, so its next owner may use it on any stream.
 #include "api_internal.h"
 
@@ -63,7 +65,43 @@ void drop_oldest(Pool& P, int dev)
         }
 }
 
+// hipMalloc on the current device dev; if that fails, once more without the
+// device's idle blocks.
+hipError_t malloc_or_drop(Pool& P, int dev, void** p, size_t bytes)
+{
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess && P.idle_bytes[dev] > 0) {
+        (void)hipGetLastError();
+        while (P.idle_bytes[dev] > 0) drop_oldest(P, dev);
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) *p = nullptr;
+    return e;
+}
+
 }  // namespace
+
+hipError_t device_malloc(void** p, size_t bytes)
+{
+    *p = nullptr;
+    int dev = 0;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    return malloc_or_drop(P, dev, p, bytes ? bytes : 1);
+}
+
+void pool_release()
+{
+    Pool& P = pool();
+    std::lock_guard<std::mutex> lock(P.mu);
+    for (const Block& b : P.idle) (void)hipFree(b.p);
+    P.idle.clear();
+    P.idle_bytes.clear();
+    for (const auto& h : P.host) (void)hipHostFree(h.first);
+    P.host.clear();
+}
 
 hipError_t pool_malloc(void** p, size_t bytes)
 {
@@ -82,16 +120,8 @@ hipError_t pool_malloc(void** p, size_t bytes)
             P.idle.erase(std::next(it).base());
             return hipSuccess;
         }
-    e = hipMalloc(p, size);
-    if (e != hipSuccess && P.idle_bytes[dev] > 0) {
-        (void)hipGetLastError();
-        while (P.idle_bytes[dev] > 0) drop_oldest(P, dev);
-        e = hipMalloc(p, size);
-    }
-    if (e != hipSuccess) {
-        *p = nullptr;
-        return e;
-    }
+    e = malloc_or_drop(P, dev, p, size);
+    if (e != hipSuccess) return e;
     P.live[*p] = Block{*p, dev, size};
     return hipSuccess;
 }

@@ -442,8 +442,8 @@ citron_server* citron_server_create(int64_t hbm_budget_bytes, int32_t max_slots,
     // deepest supported k sizes the stack scratch of each step
     const int32_t blocks = device_cus(s->device) * s->tuning.blocks_per_cu;
     s->scratch_words = count_scratch_words(0, CITRON_KMAX, s->tuning.wg_waves);
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_acc, sizeof(unsigned long long) * kAccWords * (size_t)max_slots);
-    if (e == hipSuccess) e = hipMalloc((void**)&s->d_ovf, sizeof(int32_t) * (size_t)max_slots);
+    if (e == hipSuccess) e = device_malloc((void**)&s->d_acc, sizeof(unsigned long long) * kAccWords * (size_t)max_slots);
+    if (e == hipSuccess) e = device_malloc((void**)&s->d_ovf, sizeof(int32_t) * (size_t)max_slots);
     if (e == hipSuccess)
         e = hipHostMalloc((void**)&s->h_acc, sizeof(unsigned long long) * kAccWords * (size_t)max_slots, hipHostMallocDefault);
     if (e == hipSuccess) e = hipHostMalloc((void**)&s->h_ovf, sizeof(int32_t) * (size_t)max_slots, hipHostMallocDefault);
@@ -451,11 +451,11 @@ citron_server* citron_server_create(int64_t hbm_budget_bytes, int32_t max_slots,
         if (e == hipSuccess) e = hipStreamCreateWithFlags(&st.stream, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreate(&st.start);
         if (e == hipSuccess) e = hipEventCreate(&st.done);
-        if (e == hipSuccess) e = hipMalloc((void**)&st.d_q, sizeof(QueryDesc) * (size_t)max_slots);
+        if (e == hipSuccess) e = device_malloc((void**)&st.d_q, sizeof(QueryDesc) * (size_t)max_slots);
         if (e == hipSuccess)
             e = hipHostMalloc((void**)&st.h_q, sizeof(QueryDesc) * (size_t)max_slots, hipHostMallocDefault);
-        if (e == hipSuccess) e = hipMalloc((void**)&st.d_item_ctr, sizeof(int32_t) * kLaunchInts);
-        if (e == hipSuccess) e = hipMalloc((void**)&st.d_scratch, (size_t)(s->scratch_words * 8 * blocks));
+        if (e == hipSuccess) e = device_malloc((void**)&st.d_item_ctr, sizeof(int32_t) * kLaunchInts);
+        if (e == hipSuccess) e = device_malloc((void**)&st.d_scratch, (size_t)(s->scratch_words * 8 * blocks));
     }
     if (e != hipSuccess) {
         hip_fail(e, "server set-up");

@@ -454,3 +454,23 @@ def test_heavy_arcs_of_every_density_class(citron_gpu, k):
     assert np.array_equal(h.count_arcs(k, some), per[some])
     assert citron_gpu.count_batch([h, h], [k, 5]) == [want, h.count(5)]
     h.free()
+
+
+def test_released_memory_returns_to_the_device(citron_gpu):
+    """What freed graphs leave in the pool is the program's again on request,
+    and graphs in use stay as they are."""
+    import torch
+    keep = citron_gpu.Graph.from_csr(*(lambda g: (g.row_ptr, g.col))(gg.rmat(9, 16, seed=5))).order()
+    want = keep.count(5)
+    citron_gpu.release_memory()
+    before = torch.cuda.mem_get_info()[0]
+    g = gg.rmat(16, 16, seed=6)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    h.count(4)
+    h.free()
+    held = before - torch.cuda.mem_get_info()[0]
+    citron_gpu.release_memory()
+    left = before - torch.cuda.mem_get_info()[0]
+    assert held > 16 << 20 and left < held // 4
+    assert keep.count(5) == want and keep.count(6) == keep.count_vertex_rooted(6)
+    keep.free()

@@ -46,9 +46,11 @@ Pool& pool()
 }
 
 // Sizes in eighths of a power of two, so that graphs of about one size share
-// blocks at the price of at most an eighth.
+// blocks at the price of at most an eighth.  A block that is not kept has
+// nothing to share and is as large as asked.
 size_t size_class(size_t bytes)
 {
+    if (bytes > kPoolMaxBlock) return bytes;
     size_t step = 64;
     while (step * 16 < bytes) step *= 2;
     return (bytes + step - 1) / step * step;

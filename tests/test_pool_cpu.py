@@ -69,3 +69,15 @@ def test_all_device_memory_comes_through_the_pools_file():
     for name in os.listdir(CSRC):
         text = re.sub(r"//.*", "", open(os.path.join(CSRC, name)).read())
         assert name == "pool.cpp" or not re.search(r"\bhipMalloc\w*\s*\(", text), name
+
+
+def test_blocks_too_large_to_keep_are_as_large_as_asked(pool):
+    pool.replay_capacity(1024 * MIB)
+    for mib in (257, 300, 577, 1000, 1024):
+        b = pool.replay_pool_malloc(mib * MIB)
+        assert b and pool.replay_used() == mib * MIB
+        pool.replay_pool_free(b)
+        assert pool.replay_used() == 0                      # nothing idle
+    b = pool.replay_pool_malloc(256 * MIB)                  # the largest that is kept
+    pool.replay_pool_free(b)
+    assert pool.replay_used() == 256 * MIB

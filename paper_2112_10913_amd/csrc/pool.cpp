@@ -7,12 +7,15 @@
 // one.  Freed blocks are kept, at most kPoolBytes per device and
 // kPoolHostBlocks pinned ones, the oldest given back first, all of them when
 // an allocation fails, here or through device_malloc, which the library's
-// other device memory comes from, or when the program asks (pool_release).  A
-// block is only handed to pool_free once the work that
+// other device memory comes from, or when the program asks (pool_release).
+// A block is only handed to pool_free once the work that
 // used it has completed, so its next owner may use it on any stream.
 #include "api_internal.h"
 
+#include <deque>
 #include <list>
+#include <map>
+#include <new>
 #include <unordered_map>
 
 namespace citron {
@@ -22,18 +25,27 @@ namespace {
 constexpr size_t kPoolBytes = (size_t)1 << 30;        // cached per device
 constexpr size_t kPoolMaxBlock = (size_t)1 << 28;     // larger blocks are not cached
 constexpr size_t kPoolHostBlocks = 64;
+constexpr size_t kPage = 4096;                        // what a block takes at least
 
 struct Block {
     void* p;
     int dev;
     size_t size;
 };
+typedef std::list<Block> Blocks;
+
+// Idle blocks of one device: by age, and of each size by age again, so that
+// neither a search nor giving the oldest back looks at the others.
+struct Idle {
+    Blocks all;                                       // oldest first
+    std::map<size_t, std::deque<Blocks::iterator>> by_size;
+    size_t bytes = 0;
+};
 
 struct Pool {
     std::mutex mu;
-    std::list<Block> idle;                            // oldest first
     std::unordered_map<void*, Block> live;
-    std::unordered_map<int, size_t> idle_bytes;
+    std::unordered_map<int, Idle> idle;
     std::list<std::pair<void*, size_t>> host;
 };
 
@@ -46,25 +58,27 @@ Pool& pool()
 }
 
 // Sizes in eighths of a power of two, so that graphs of about one size share
-// blocks at the price of at most an eighth.  A block that is not kept has
-// nothing to share and is as large as asked.
+// blocks at the price of at most an eighth; a page at least, which the device
+// gives a smaller block too.  A block that is not kept has nothing to share
+// and is as large as asked.
 size_t size_class(size_t bytes)
 {
     if (bytes > kPoolMaxBlock) return bytes;
-    size_t step = 64;
+    if (bytes <= kPage) return kPage;
+    size_t step = kPage / 16;
     while (step * 16 < bytes) step *= 2;
     return (bytes + step - 1) / step * step;
 }
 
-void drop_oldest(Pool& P, int dev)
+void drop_oldest(Idle& I)
 {
-    for (auto it = P.idle.begin(); it != P.idle.end(); ++it)
-        if (it->dev == dev) {
-            (void)hipFree(it->p);
-            P.idle_bytes[dev] -= it->size;
-            P.idle.erase(it);
-            return;
-        }
+    const Block b = I.all.front();
+    const auto it = I.by_size.find(b.size);           // its oldest is the oldest of all
+    it->second.pop_front();
+    if (it->second.empty()) I.by_size.erase(it);
+    I.all.pop_front();
+    I.bytes -= b.size;
+    (void)hipFree(b.p);
 }
 
 // hipMalloc on the current device dev; if that fails, once more without the
@@ -72,9 +86,10 @@ void drop_oldest(Pool& P, int dev)
 hipError_t malloc_or_drop(Pool& P, int dev, void** p, size_t bytes)
 {
     hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess && P.idle_bytes[dev] > 0) {
+    const auto it = P.idle.find(dev);
+    if (e != hipSuccess && it != P.idle.end() && !it->second.all.empty()) {
         (void)hipGetLastError();
-        while (P.idle_bytes[dev] > 0) drop_oldest(P, dev);
+        while (!it->second.all.empty()) drop_oldest(it->second);
         e = hipMalloc(p, bytes);
     }
     if (e != hipSuccess) *p = nullptr;
@@ -98,34 +113,44 @@ void pool_release()
 {
     Pool& P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
-    for (const Block& b : P.idle) (void)hipFree(b.p);
-    P.idle.clear();
-    P.idle_bytes.clear();
+    for (auto& dev : P.idle)
+        while (!dev.second.all.empty()) drop_oldest(dev.second);
     for (const auto& h : P.host) (void)hipHostFree(h.first);
     P.host.clear();
 }
 
+// (no exception leaves these functions: without host memory for the books, a
+// block is not handed out, or not kept)
 hipError_t pool_malloc(void** p, size_t bytes)
 {
     *p = nullptr;
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    const size_t size = size_class(bytes ? bytes : 1);
+    const size_t size = size_class(bytes);
     Pool& P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
-    for (auto it = P.idle.rbegin(); it != P.idle.rend(); ++it)
-        if (it->dev == dev && it->size == size) {
-            *p = it->p;
-            P.live[*p] = *it;
-            P.idle_bytes[dev] -= size;
-            P.idle.erase(std::next(it).base());
+    try {
+        Idle& I = P.idle[dev];
+        const auto it = I.by_size.find(size);
+        if (it != I.by_size.end()) {
+            const Blocks::iterator newest = it->second.back();
+            P.live[newest->p] = *newest;
+            *p = newest->p;
+            it->second.pop_back();
+            if (it->second.empty()) I.by_size.erase(it);
+            I.all.erase(newest);
+            I.bytes -= size;
             return hipSuccess;
         }
-    e = malloc_or_drop(P, dev, p, size);
-    if (e != hipSuccess) return e;
-    P.live[*p] = Block{*p, dev, size};
-    return hipSuccess;
+        e = malloc_or_drop(P, dev, p, size);
+        if (e == hipSuccess) P.live[*p] = Block{*p, dev, size};
+        return e;
+    } catch (const std::bad_alloc&) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
+        return hipErrorOutOfMemory;
+    }
 }
 
 void pool_free(void* p)
@@ -141,9 +166,23 @@ void pool_free(void* p)
         (void)hipFree(p);
         return;
     }
-    P.idle.push_back(b);
-    P.idle_bytes[b.dev] += b.size;
-    while (P.idle_bytes[b.dev] > kPoolBytes) drop_oldest(P, b.dev);
+    bool listed = false;
+    try {
+        Idle& I = P.idle[b.dev];
+        I.all.push_back(b);
+        listed = true;
+        I.by_size[b.size].push_back(std::prev(I.all.end()));
+        I.bytes += b.size;
+        while (I.bytes > kPoolBytes) drop_oldest(I);
+    } catch (const std::bad_alloc&) {
+        if (listed) {
+            Idle& I = P.idle[b.dev];
+            I.all.pop_back();
+            const auto c = I.by_size.find(b.size);
+            if (c != I.by_size.end() && c->second.empty()) I.by_size.erase(c);
+        }
+        (void)hipFree(p);
+    }
 }
 
 hipError_t pool_host_malloc(void** p, size_t bytes)
@@ -164,11 +203,14 @@ void pool_host_free(void* p, size_t bytes)
     if (!p) return;
     Pool& P = pool();
     std::lock_guard<std::mutex> lock(P.mu);
-    if (P.host.size() >= kPoolHostBlocks) {
-        (void)hipHostFree(p);
-        return;
+    try {
+        if (P.host.size() < kPoolHostBlocks) {
+            P.host.emplace_back(p, bytes);
+            return;
+        }
+    } catch (const std::bad_alloc&) {
     }
-    P.host.emplace_back(p, bytes);
+    (void)hipHostFree(p);
 }
 
 }  // namespace citron

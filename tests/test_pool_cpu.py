@@ -81,3 +81,44 @@ def test_blocks_too_large_to_keep_are_as_large_as_asked(pool):
     b = pool.replay_pool_malloc(256 * MIB)                  # the largest that is kept
     pool.replay_pool_free(b)
     assert pool.replay_used() == 256 * MIB
+
+
+def test_small_blocks_count_the_page_they_take(pool):
+    """The bound of 1 GiB holds for what the device has given, also for many
+    blocks of a few bytes."""
+    pool.replay_capacity(4096 * MIB)
+    blocks = [pool.replay_pool_malloc(64 + i % 512) for i in range(400_000)]
+    for b in blocks:
+        pool.replay_pool_free(b)
+    assert pool.replay_used() <= 1024 * MIB
+
+
+def test_a_search_does_not_look_at_every_idle_block(pool):
+    """A program that drops many graphs goes on at the speed of one that has
+    none: 100,000 idle blocks, then blocks of sizes that are not among them."""
+    import time
+    pool.replay_capacity(4096 * MIB)
+    blocks = [pool.replay_pool_malloc(4096) for i in range(100_000)]
+    for b in blocks:
+        pool.replay_pool_free(b)
+    t = time.perf_counter()
+    held = [pool.replay_pool_malloc(10_000) for _ in range(20_000)]
+    assert all(held) and time.perf_counter() - t < 2.0      # 2,000,000,000 steps when each search walks the list
+
+
+def test_the_newest_of_a_size_is_reused_and_the_oldest_goes_first(pool):
+    pool.replay_capacity(4096 * MIB)
+    a, b = pool.replay_pool_malloc(9000), pool.replay_pool_malloc(9000)
+    pool.replay_pool_free(a)
+    pool.replay_pool_free(b)
+    assert pool.replay_pool_malloc(8900) == b               # one size class
+    pool.replay_pool_free(b)
+    calls = pool.replay_calls()
+    assert {pool.replay_pool_malloc(9000), pool.replay_pool_malloc(9000)} == {a, b}
+    assert pool.replay_calls() == calls
+    big = [pool.replay_pool_malloc(200 * MIB) for _ in range(6)]
+    pool.replay_pool_free(a)                                # the oldest idle block
+    for x in big:
+        pool.replay_pool_free(x)
+    assert pool.replay_used() <= 1024 * MIB + 8192
+    assert pool.replay_pool_malloc(9000) is not None and pool.replay_calls() == calls + 7

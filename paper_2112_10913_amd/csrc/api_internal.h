@@ -45,7 +45,6 @@ struct SmallHost {
     PlanHeader plan;
     uint64_t stats[kNumStats];
     int32_t rows_total;
-    int32_t hrows_total;
     int32_t hist[2 * kMaxDeg + 2];   // bucket bounds of a schedule order
     PeelCtl peel[2];
     BuildSums build[kBuildSlots];
@@ -97,6 +96,7 @@ struct citron_graph {
     int32_t* d_rows_off = nullptr;          // n + 1
     unsigned long long* d_rows = nullptr;
     int32_t* d_arc_c = nullptr;             // m
+    bool hrows_valid = false;
     int32_t* d_hoff = nullptr;              // n + 1: the heavy vertices' rows in sorted positions
     unsigned long long* d_hrows = nullptr;
     uint16_t* d_hpos = nullptr;             // m

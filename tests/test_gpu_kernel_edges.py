@@ -474,3 +474,27 @@ def test_released_memory_returns_to_the_device(citron_gpu):
     assert held > 16 << 20 and left < held // 4
     assert keep.count(5) == want and keep.count(6) == keep.count_vertex_rooted(6)
     keep.free()
+
+
+def test_memory_that_only_scheduled_counts_need_is_theirs(citron_gpu):
+    """Triangle counts, vertex-rooted counts and listing hold the subgraph rows
+    once; a scheduled count brings the heavy vertices' sorted rows, once."""
+    g = gg.rmat(13, 24, seed=13)
+    h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+    tri = h.count(3)
+    built = h.info()["device_bytes"]
+    assert int(h.count_per_arc(3)[1].sum()) == tri and h.count_vertex_rooted(3) == tri
+    some = np.arange(0, g.m, 97)
+    assert h.list_arcs(3, some)[0].shape[0] == int(h.count_arcs(3, some).sum())
+    assert h.info()["device_bytes"] - built < 16 << 20          # stacks and tables
+    four = h.count_vertex_rooted(4)
+    every = h.count_arcs(4, np.arange(g.m))
+    assert int(every.sum()) == four
+    before = h.info()["device_bytes"]
+    assert h.count(4) == four
+    sorted_rows = h.info()["device_bytes"] - before
+    assert sorted_rows > 8 * g.m                                  # rows, positions, arcs by size
+    assert h.count(5) == h.count_vertex_rooted(5) and h.count(4) == four
+    assert h.info()["device_bytes"] - before - sorted_rows < 16 << 20
+    assert np.array_equal(h.count_per_arc(4)[1], every)
+    h.free()

@@ -230,11 +230,13 @@ citron_status citron_count_batch(citron_graph* const* gs, const int32_t* ks, int
                                  const citron_tuning* t);
 
 /* Progress of the citron_count_batch launch running now (for a thread
- * other than the one that called citron_count_batch): *items_taken = work
- * items claimed so far by the launch's waves (in steps of 512),
- * *items_total = its items; both 0 when no batch launch is running.  The
- * kernel stores its progress into a host-mapped word, so this call makes
- * no HIP call and never waits for the device. */
+ * other than the one that called citron_count_batch): *items_taken = how far
+ * the launch's waves have come in its schedule of work items (one item in 512
+ * is reported, and all items before it have been claimed up to a few runs of
+ * 16; it never goes back within a launch), *items_total = its items; both 0
+ * when no batch launch is running.  The kernels store their progress into a
+ * host-mapped word, so this call makes no HIP call and never waits for the
+ * device. */
 citron_status citron_batch_progress(int32_t* items_taken, int32_t* items_total);
 
 /* Copy the DAG to host memory: dag_ptr int32[n+1], dag_col int32[m], in

@@ -63,13 +63,14 @@ std::mutex g_batch_mu;
 std::map<BatchKey, std::unique_ptr<BatchExec>> g_cache;
 
 // Progress of the batch launch in flight, for queries from other threads:
-// the kernel stores the items claimed (every 512th) into a host-mapped
-// pinned word, which the host reads without any HIP call (a copy from the
+// the kernels store the first item of a claimed run (one in 512 items) into a
+// host-mapped pinned word, which the host reads without any HIP call (a copy from the
 // device could wait for compute units the launch holds).  Its device
 // address is baked into captured launches, so the word lives until the
 // process ends.  g_progress_mu guards the published total.
 std::mutex g_progress_mu;
 int32_t g_run_total = 0;
+int32_t g_run_taken = 0;               // the furthest progress reported of this run
 volatile int32_t* g_progress_word = nullptr;
 int32_t* g_progress_dev = nullptr;
 
@@ -272,6 +273,7 @@ extern "C" citron_status citron_count_batch(citron_graph* const* gs, const int32
                 std::lock_guard<std::mutex> pl(g_progress_mu);
                 if (g_progress_word) *g_progress_word = 0;
                 g_run_total = be->total_items;
+                g_run_taken = 0;
             }
             e = hipGraphLaunch(be->exec, s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -302,7 +304,10 @@ extern "C" citron_status citron_batch_progress(int32_t* items_taken, int32_t* it
     if (!items_taken || !items_total) return fail(CITRON_EINVAL, "NULL argument");
     std::lock_guard<std::mutex> pl(g_progress_mu);
     *items_total = g_run_total;
+    // runs are claimed from several cursors, so a later store may be of an
+    // earlier run: what has been reported stays
     const int32_t v = (g_run_total && g_progress_word) ? *g_progress_word : 0;
-    *items_taken = v < g_run_total ? v : g_run_total;
+    g_run_taken = std::max(g_run_taken, std::min(v, g_run_total));
+    *items_taken = g_run_total ? g_run_taken : 0;
     return CITRON_OK;
 }

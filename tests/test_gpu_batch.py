@@ -121,3 +121,32 @@ def test_progress_of_a_running_batch(citron_gpu):
     assert out["c"][0] == want
     assert seen and seen[-1] >= seen[0]
     assert citron_gpu.batch_progress() == (0, 0)
+
+
+def test_progress_never_goes_back(citron_gpu):
+    """Work items are claimed from several cursors at once; the progress that
+    another thread reads only rises within a launch."""
+    import threading
+    hs = [citron_gpu.Graph.from_csr(*(lambda g: (g.row_ptr, g.col))(gg.rmat(15, 16, seed=s))).order() for s in (1, 2)]
+    ks = [5, 6, 7]
+    queries = [(h, k) for h in hs for k in ks]
+    want = [h.count(k) for h, k in queries]
+    rises = 0
+    for _ in range(6):
+        out = []
+        t = threading.Thread(target=lambda: out.append(
+            citron_gpu.count_batch([h for h, _ in queries], [k for _, k in queries])))
+        last = 0
+        t.start()
+        while t.is_alive():
+            taken, total = citron_gpu.batch_progress()
+            if total == 0:
+                continue
+            assert last <= taken <= total
+            rises += taken > last
+            last = taken
+        t.join()
+        assert out == [want]
+    assert rises > 3
+    for h in hs:
+        h.free()

@@ -232,12 +232,22 @@ class Graph:
         if n < 0:
             raise ValueError("row_ptr must have n+1 >= 1 entries")
         s = ctypes.c_void_p(stream.cuda_stream) if stream is not None else _current_stream()
+        if flags and s.value != _current_stream().value:
+            _torch().cuda.current_stream().synchronize()     # rp and cl may be conversions queued there
         out = ctypes.c_void_p()
         st = lib.citron_load_csr(n, nnz, prp, pcl, flags, s, ctypes.byref(out))
         del keep
         if st:
             raise _err(st)
         return cls(out.value, n, nnz // 2, s)
+
+    def _meet(self) -> None:
+        """The library works on the graph's stream: where torch's current one
+        is another, what it still does with the memory of tensors made here
+        comes first."""
+        current = _torch().cuda.current_stream()
+        if current.cuda_stream != (self._stream.value or 0):
+            current.synchronize()
 
     def _handle(self):
         if self._h is None or not self._h.value:
@@ -300,12 +310,14 @@ class Graph:
         offsets = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
         total = ctypes.c_int64(0)
         pa = arcs.data_ptr() if n else None
+        self._meet()
         st = lib.citron_list_arcs(self._handle(), int(k), pa, n, offsets.data_ptr(), None, 0,
                                   ctypes.byref(total))
         if st not in (OK, ENOMEM):
             raise _err(st)
         out = torch.empty((max(total.value, 1), k), dtype=torch.int32, device="cuda")
         if total.value > 0:
+            self._meet()
             st = lib.citron_list_arcs(self._handle(), int(k), pa, n, offsets.data_ptr(), out.data_ptr(),
                                       total.value, ctypes.byref(total))
             if st:
@@ -327,6 +339,7 @@ class Graph:
         """(total, per-arc counts as a uint64 numpy array in DAG arc order)."""
         torch = _torch()
         buf = torch.empty(max(self.m, 1), dtype=torch.int64, device="cuda")
+        self._meet()
         st = ctypes.c_int32(0)
         v = load_library().citron_count_per_arc(self._handle(), int(k), buf.data_ptr(), ctypes.byref(st))
         if st.value not in (OK, EOVERFLOW):
@@ -348,9 +361,7 @@ class Graph:
         a = torch.as_tensor(np.ascontiguousarray(arcs, dtype=np.int32)).cuda()
         n = int(a.numel())
         out = torch.empty(max(n, 1), dtype=torch.int64, device="cuda")   # every entry is written
-        # the arc list is copied on torch's current stream; the library works
-        # on the graph's stream, which need not be the same one
-        torch.cuda.current_stream().synchronize()
+        self._meet()
         st = ctypes.c_int32(0)
         load_library().citron_count_arcs(self._handle(), int(k), a.data_ptr(), n, out.data_ptr(),
                                          ctypes.byref(st))

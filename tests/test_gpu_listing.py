@@ -88,3 +88,38 @@ def test_listing_refuses_a_small_buffer(citron_gpu):
     st = lib.citron_list_arcs(h._handle(), 3, bad.data_ptr(), 2, offs.data_ptr(), out.data_ptr(), 5,
                               ctypes.byref(total))
     assert st == 1                                             # arc index out of range
+
+
+def test_calls_from_a_stream_that_is_not_the_graphs(citron_gpu):
+    """Arc lists, outputs and converted inputs made on a busy stream, for a
+    graph of another one: the library does not read them before they exist."""
+    import torch
+    g = gg.rmat(10, 12, seed=3)
+    own, busy = torch.cuda.Stream(), torch.cuda.Stream()
+    with torch.cuda.stream(own):
+        h = citron_gpu.Graph.from_csr(g.row_ptr, g.col).order()
+        cliques, offsets = h.list_arcs(4)
+        total, per = h.count_per_arc(5)
+        some = h.count_arcs(5, np.arange(0, g.m, 3))
+    want = cliques.cpu(), offsets.cpu()
+    row_ptr, col = torch.from_numpy(g.row_ptr).cuda(), torch.from_numpy(g.col).cuda()
+    a = torch.rand(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with torch.cuda.stream(busy):
+            def work():
+                for _ in range(20):
+                    torch.mm(a, a)
+            work()
+            got = h.list_arcs(4)
+            assert torch.equal(got[0].cpu(), want[0]) and torch.equal(got[1].cpu(), want[1])
+            work()
+            t, p = h.count_per_arc(5)
+            assert t == total and np.array_equal(p, per)
+            work()
+            assert np.array_equal(h.count_arcs(5, np.arange(0, g.m, 3)), some)
+            work()
+            h2 = citron_gpu.Graph.from_csr(row_ptr.long(), col.long(), stream=own).order()
+            assert h2.count(5) == total
+            h2.free()
+    h.free()

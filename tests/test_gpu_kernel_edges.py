@@ -498,3 +498,35 @@ def test_memory_that_only_scheduled_counts_need_is_theirs(citron_gpu):
     assert h.info()["device_bytes"] - before - sorted_rows < 16 << 20
     assert np.array_equal(h.count_per_arc(4)[1], every)
     h.free()
+
+
+def test_threads_and_streams_all_finish_with_the_oracles_results(citron_gpu):
+    """As test_blocks_reused_across_threads_and_streams, with every thread's
+    errors reported, its passes counted, and order keys and DAGs compared: a
+    block handed on too early shows as any of these."""
+    from concurrent.futures import ThreadPoolExecutor
+    from math import comb
+    import oracle
+    import torch
+    gs = [gg.rmat(9, 20, seed=80), gg.rmat(10, 14, seed=81), gg.erdos_renyi(700, 26, seed=82), gg.complete(80), gg.empty(500)]
+    want = {(i, k): comb(80, k) if i == 3 else oracle.count(g, k)[0] for i, g in enumerate(gs) for k in (3, 4, 6)}
+    dags = {(i, o): (oracle.orient(g.n, g.row_ptr, g.col) if o == "degree" else oracle.orient_peel(g))
+            for i, g in enumerate(gs) for o in ("degree", "core")}
+
+    def work(seed):
+        rng = np.random.default_rng(seed)
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for done in range(25):
+                i, k = int(rng.integers(len(gs))), int(rng.choice([3, 4, 6]))
+                ordering = "core" if rng.random() < 0.3 else "degree"
+                h = citron_gpu.Graph.from_csr(gs[i].row_ptr, gs[i].col).order(ordering)
+                ptr, col = h.dag()
+                assert np.array_equal(ptr, dags[(i, ordering)][0]) and np.array_equal(col, dags[(i, ordering)][1])
+                assert h.count(k) == want[(i, k)], (i, k, ordering)
+                if rng.random() < 0.3:
+                    assert citron_gpu.count_batch([h, h], [4, k]) == [want[(i, 4)], want[(i, k)]]
+                h.free()
+        return done + 1
+
+    with ThreadPoolExecutor(4) as pool:
+        assert list(pool.map(work, range(4))) == [25] * 4

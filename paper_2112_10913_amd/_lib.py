@@ -241,13 +241,15 @@ class Graph:
             raise _err(st)
         return cls(out.value, n, nnz // 2, s)
 
-    def _meet(self) -> None:
+    def _meet(self) -> bool:
         """The library works on the graph's stream: where torch's current one
-        is another, what it still does with the memory of tensors made here
-        comes first."""
+        is another (True), what it still does with the memory of tensors made
+        here comes first."""
         current = _torch().cuda.current_stream()
-        if current.cuda_stream != (self._stream.value or 0):
-            current.synchronize()
+        if current.cuda_stream == (self._stream.value or 0):
+            return False
+        current.synchronize()
+        return True
 
     def _handle(self):
         if self._h is None or not self._h.value:
@@ -310,14 +312,15 @@ class Graph:
         offsets = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
         total = ctypes.c_int64(0)
         pa = arcs.data_ptr() if n else None
-        self._meet()
+        other = self._meet()
         st = lib.citron_list_arcs(self._handle(), int(k), pa, n, offsets.data_ptr(), None, 0,
                                   ctypes.byref(total))
         if st not in (OK, ENOMEM):
             raise _err(st)
         out = torch.empty((max(total.value, 1), k), dtype=torch.int32, device="cuda")
         if total.value > 0:
-            self._meet()
+            if other:
+                self._meet()
             st = lib.citron_list_arcs(self._handle(), int(k), pa, n, offsets.data_ptr(), out.data_ptr(),
                                       total.value, ctypes.byref(total))
             if st:

@@ -232,7 +232,7 @@ class Graph:
         if n < 0:
             raise ValueError("row_ptr must have n+1 >= 1 entries")
         s = ctypes.c_void_p(stream.cuda_stream) if stream is not None else _current_stream()
-        if flags and s.value != _current_stream().value:
+        if flags and stream is not None and s.value != _current_stream().value:
             _torch().cuda.current_stream().synchronize()     # rp and cl may be conversions queued there
         out = ctypes.c_void_p()
         st = lib.citron_load_csr(n, nnz, prp, pcl, flags, s, ctypes.byref(out))

@@ -19,9 +19,11 @@ run asked for many steps of a workload whose steps take tens of seconds
 still ends within a ten-minute limit); at least one step is always timed.
 The line reports the steps actually run and the ones asked for.
 
-Roofline of the dominant kernel (the count kernel): algorithmic int32 VALU
-lane-ops per launch (4 per 64-bit AND+popcount, one per j-clique for
-j = 3..k-1) over the mean launch time, against 256 CUs x 64 lanes x 2.4 GHz.
+Roofline of the counts (nearly all of it the dense kernel, which does the last
+three levels on the matrix cores; the rest is the count kernel): algorithmic
+int32 VALU lane-ops per count (4 per 64-bit AND+popcount, one per j-clique for
+j = 3..k-1) over the mean count time, against 256 CUs x 64 lanes x 2.4 GHz,
+what a count on the vector units alone could reach.
 Per k, the line also gives the HBM figure of the paper's merge-based
 subgraph construction: the algorithmic bytes of every arc that survives
 pruning over the count time, against 8 TB/s.
@@ -693,7 +695,7 @@ def main():
     achieved = tot_ops / (tot_ms / 1e3) / 1e12
     roofline = {"bound": "alu", "achieved": achieved, "peak": PEAK_VALU_TOPS, "unit": "Top/s",
                 "frac": achieved / PEAK_VALU_TOPS, "traffic": traffic_per_launch(args.ks),
-                "kernel": "count_kernel",
+                "kernel": "dense_kernel",
                 "algorithmic_unit": "int32 VALU lane-ops: 4 per 64-bit AND+popcount, one per j-clique, "
                                     "j = 3..k-1",
                 "launch_ms_mean": tot_ms / len(args.ks),

@@ -261,12 +261,17 @@ citron_status citron_set_tuning(citron_graph* g, const citron_tuning* t);
 citron_status citron_get_tuning(const citron_graph* g, citron_tuning* t);
 
 /* Work counters of one k, measured by an instrumented launch of the count
- * kernel (not a timed path).  stats receives CITRON_NSTATS uint64:
+ * kernel (not a timed path).  That launch takes every item to the count
+ * kernel, also those that citron_count gives to the dense kernel, which counts
+ * no work of its own: the numbers describe the count kernel's way to the same
+ * count.  stats receives CITRON_NSTATS uint64:
  *   [0] subgraphs built (vertices)       [1] rows built (arcs)
- *   [2] out-list entries read by the build (sum over arcs u->v of d->(v))
+ *   [2] out-list entries of the build by Algorithm 5 (sum over arcs u->v of
+ *       d->(v); where that is more than 4 d->(u), the build searches u's
+ *       entries in v's list instead and reads fewer)
  *   [3] last-level AND+popcount row-word operations
  *   [4] recursion nodes pushed
- *   [5] bytes of the DAG read by the build: 4 (d->(u) + 2) per built
+ *   [5] bytes of the DAG that go with [2]: 4 (d->(u) + 2) per built
  *       vertex + 4 (d->(v) + 2) per built arc
  *   [6] search steps on multi-word masks (a whole wave per step)
  *   [7] nodes compacted to one word per row   [8] rows they produced

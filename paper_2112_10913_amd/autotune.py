@@ -34,7 +34,7 @@ DEFAULT_SPACE = {
     "arc_lds_max": [128, 192, 256],
     "split_pct": [50, 100, 200],
 }
-# waves per CU worth trying: registers allow 16 count waves (k <= 9: 128
+# waves per CU worth trying: registers allow 16 count waves (k <= 12: 128
 # VGPRs, 4 per SIMD), LDS 16 with LDS copies up to 192 candidates
 MAX_WAVES_PER_CU = 16
 

@@ -14,8 +14,9 @@ SOURCES = ["kernels_order.hip", "kernels_rows.hip", "kernels_count.hip", "kernel
 ARCH = os.environ.get("CITRON_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-# Packed fp32 instructions are kept out of every device object; this code
-# has no floating point, the flag only guards against the compiler's own use.
+# Packed fp32 instructions are kept out of every device object: the dense
+# kernel sums its matrix products in fp32 (exact integers), and the compiler
+# would pair such additions by itself.
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 

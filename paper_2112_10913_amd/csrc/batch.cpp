@@ -1,7 +1,8 @@
 // Batched counts: many (graph, k) queries in one persistent launch of the
-// count kernel.  Items of all queries form one global item space; each
-// workgroup pulls items from one cursor, so short and long queries share
-// the device without a launch (or a host round trip) per query.  The whole
+// dense kernel's instances and the count kernel.  The items of all queries
+// form one space per kernel, which its waves or workgroups claim from, so short
+// and long queries share the device without a launch (or a host round trip)
+// per query.  The whole
 // sequence -- counter resets, descriptor upload, kernel, result download --
 // is captured once into a HIP graph per distinct query set and replayed on
 // later calls with the same set.

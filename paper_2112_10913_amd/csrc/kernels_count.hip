@@ -19,7 +19,7 @@
 // word per row -- is searched by the light engine: one depth-first search
 // per lane (a whole arc, or one branch below an arc in deep counts), rows in
 // the wave's LDS
-// buffer, stacks in registers (k <= 9), LDS (k <= 12) or device memory.
+// buffer, stacks in registers (k <= 7), LDS (k <= 12) or device memory.
 // A heavy arc is walked by the whole wave in step (lane q holding word q of
 // each mask).  A node with at most 256 candidates is copied to the wave's
 // LDS, compacted to ceil(c/64) words per row; a node with at most 64
@@ -79,8 +79,10 @@ __host__ __device__ inline int heavy_levels(int max_k) { return max_k > 4 ? max_
 __host__ __device__ inline int light_levels(int max_k) { return max_k > 6 ? max_k - 5 : 1; }
 
 // Where the light stacks live, by the largest k of a launch: registers (one
-// level for k <= 6, four for k <= 9: each access selects among them), LDS
-// (k <= 12) or device memory.  The heavy stacks are always in
+// level for k <= 6, two for k = 7), LDS (k <= 12) or device memory.  Each
+// access to registers selects among the levels, since the lanes sit at
+// different depths: with four, 16 selects a push, k = 8 of G(70, 0.8) took 1.88
+// ms, with LDS 1.44 (R-MAT 12: 11.1 and 9.4 ms).  The heavy stacks are always in
 // device memory: they are touched only when a heavy node is pushed or popped,
 // and keeping them out of LDS lets more waves share a CU.
 constexpr int kRegLevels = 2;
@@ -158,8 +160,7 @@ struct WaveBuf {
 };
 
 // Per-lane light stack: slot s holds the (M, R) pair of level s + 1.  In
-// registers (L > 0 levels, each access a select over the levels, since the
-// lanes sit at different depths) or in memory, one word per lane per level.
+// registers (L > 0 levels) or in memory, one word per lane per level.
 template <int L>
 struct LightStack;
 
@@ -1087,9 +1088,7 @@ extern template hipError_t launch_mode<kStackGlobal>(const KParams&, const Count
 
 int64_t count_scratch_words(int32_t, int32_t max_k, int32_t wg_waves)
 {
-    const int64_t w = wave_global_stack_words(max_k);
-    if (w == 0) return 0;
-    return ((int64_t)wg_waves * w + 31) & ~31ll;
+    return ((int64_t)wg_waves * wave_global_stack_words(max_k) + 31) & ~31ll;
 }
 
 int64_t count_deep_scratch_words(int32_t max_k, int32_t wg_waves)

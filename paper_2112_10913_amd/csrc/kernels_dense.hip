@@ -1,12 +1,12 @@
 // Dense kernel: k-clique counts of heavy arcs and vertices on the matrix cores.
 //
 // A work item is an arc u -> v with kDenseMin <= c = |C_uv| <= kDenseMax of a
-// count with k >= 6, or k = 5 for u of more than kDenseMax out-neighbours
-// (dense_arc), or a heavy vertex of at most kDenseMax out-neighbours of a
-// count with k = 4 or 5 (dense_vertex), whose subgraph takes the place of the
-// arc's below.  These subgraphs are dense (about 0.9 of all pairs adjacent in
-// the power-law families), and the search below an arc ends, k - 5 levels
-// down, in triangle counts of induced subgraphs
+// count with k >= 6 (dense_arc: from k = 7 on of a dense enough subgraph), or k
+// = 5 for u of more than kDenseMax out-neighbours and in per-arc counts, or a
+// heavy vertex of at most kDenseMax out-neighbours of a count with k = 4 or 5
+// (dense_vertex), whose subgraph takes the place of the arc's below.  The
+// search below an arc ends, k - 5 levels down, in triangle counts of induced
+// subgraphs
 //     T(M) = sum over x, y in M, A[x][y] = 1, of |row x & row y & M|,
 // a matrix product: P = A_M A_M^T summed where A is 1, with A_M the rows of M
 // masked by M.  A is the same for every M of an item, so the products of all
@@ -26,13 +26,14 @@
 //  - Accumulators hold small integers, exact in fp32: they are summed before
 //    any could reach 2^20.
 //
-// What bounds it: the matrix cores for about half of its time (R-MAT 20, k =
-// 6, two row words: 320 cycles per mask and SIMD, layout included, of which
-// the mask's tile pairs take 175 at 32 cycles per 32 x 32 x 64), with two
-// waves of 255 registers per SIMD to hide the latency of the rest, and for
-// small subgraphs their layout.  With every mask's products packed to bytes
-// and summed on their own, 20 VALU instructions per tile pair, R-MAT 20, k =
-// 6 took 165 ms and R-MAT 16, k = 7 32.7 ms; now 96 and 21.6 ms.
+// What bounds it (R-MAT 20, k = 6, counters): the matrix cores are busy 0.63 to
+// 0.72 of the time for two to six row words, with vector instructions issued in
+// 0.47 to 0.56 of the cycles beside them and two waves of 255 registers per
+// SIMD to hide the latency of the rest; for one row word 0.49, beside 0.71 for
+// layout and search.  LDS is read in 0.15 to 0.23 of the cycles, with hardly a
+// bank conflict.  With every mask's products packed to bytes and summed on
+// their own, 20 VALU instructions per tile pair, R-MAT 20, k = 6 took 165 ms
+// and R-MAT 16, k = 7 32.7 ms; now 94 and 20.8 ms.
 #include "items.h"
 #include "wave.h"
 

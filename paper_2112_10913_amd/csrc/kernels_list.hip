@@ -6,8 +6,7 @@
 // arc the cliques come in the order of a depth-first search that takes the
 // candidates of every level in ascending position (= ascending id) order.
 //
-// One wave per arc at a time (a persistent grid pulls arcs from one
-// cursor).  The search state is wave-uniform, lane q holding word q of each
+// One wave per arc at a time (a persistent grid).  The search state is wave-uniform, lane q holding word q of each
 // candidate mask over the positions of N->(u), as in the heavy count engine;
 // the masks of the open levels live in the wave's LDS, k - 2 levels of one
 // word per lane (3 KB per wave at k = 5, 14 KB at k = 16).  The last two
@@ -23,6 +22,7 @@
 // every write is checked against the arc's slot and a mismatch raises a
 // flag instead of writing outside it.
 #include "items.h"
+#include "wave.h"
 
 #include <numeric>
 
@@ -30,56 +30,8 @@ namespace citron {
 
 namespace {
 
-typedef unsigned long long u64;
-
 constexpr int kListBlock = 256;                 // 4 waves
 constexpr int kListWaves = kListBlock / kWave;
-
-__device__ __forceinline__ int lane_of() { return threadIdx.x & (kWave - 1); }
-
-__device__ __forceinline__ u64 readlane64(u64 v, int lane)
-{
-    unsigned lo = __builtin_amdgcn_readlane((unsigned)v, lane);
-    unsigned hi = __builtin_amdgcn_readlane((unsigned)(v >> 32), lane);
-    return ((u64)hi << 32) | lo;
-}
-
-// Position of the r-th (0-based) set bit of v.
-__device__ __forceinline__ int select64(u64 v, int r)
-{
-    int pos = 0;
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) {
-        const u64 low = v & ((1ull << s) - 1);
-        const int c = __popcll(low);
-        if (r >= c) {
-            r -= c;
-            v >>= s;
-            pos += s;
-        } else {
-            v = low;
-        }
-    }
-    return pos;
-}
-
-// Position of the r-th (0-based) candidate of a W-word mask held one word per
-// lane; the whole wave calls it.
-__device__ __forceinline__ int wave_select(u64 m, int r, int W)
-{
-    int before = 0, my_w = 0, my_r = 0;
-    u64 my_word = 0;
-    for (int w = 0; w < W; ++w) {
-        const u64 mw = readlane64(m, w);
-        const int pc = __popcll(mw);
-        const bool here = r >= before && r < before + pc;
-        my_w = here ? w : my_w;
-        my_r = here ? r - before : my_r;
-        my_word = here ? mw : my_word;
-        before += pc;
-    }
-    return my_w * 64 + select64(my_word, my_r);
-}
 
 // Levels whose masks are kept for the way back: a node at level t is
 // pushed only while k - 2 - t >= 3 vertices remain to choose, so levels

@@ -53,15 +53,8 @@ __device__ __forceinline__ int lower_bound_i32(const int32_t* a, int n, int32_t 
     return lo;
 }
 
-struct BuildCtrl {
-    int32_t item;
-    int32_t first;
-    int32_t nb;
-    int32_t R;
-    int32_t wsum[16];
-};
-
 constexpr int kLightBlock = 256;
+constexpr int kLightWaves = kLightBlock / kWave;
 constexpr int kProbeRatio = 4;
 constexpr int kHeavyBlock = 512;
 constexpr int kHeavyWaves = kHeavyBlock / kWave;
@@ -106,7 +99,7 @@ static int32_t light_lds_bytes(int32_t light_rows)
 {
     const int Dc = build_rows_cap(light_rows);
     const int Vc = Dc / 2 + 2;
-    int b = (int)sizeof(BuildCtrl) + 5 * 4 * (Dc + 4) + 4 * 4 * Vc;
+    int b = 4 * kLightWaves + 5 * 4 * (Dc + 4) + 4 * 4 * Vc;
     b = (b + 15) & ~15;
     return b + 8 * Dc;
 }
@@ -124,11 +117,11 @@ __global__ void __launch_bounds__(kLightBlock) build_light_kernel(BuildParams P)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int T = kLightBlock, tid = threadIdx.x, lane = lane_of(), wid = tid / kWave_;
-    const int nwaves = T / kWave_;
+    const int nwaves = kLightWaves;
     const int Dc = build_rows_cap(P.plan.light_rows);
     const int Vc = Dc / 2 + 2;
-    BuildCtrl* ctrl = reinterpret_cast<BuildCtrl*>(smem);
-    int32_t* row_v = reinterpret_cast<int32_t*>(smem + sizeof(BuildCtrl));
+    int32_t* wsum = reinterpret_cast<int32_t*>(smem);       // a word per wave
+    int32_t* row_v = wsum + kLightWaves;
     int32_t* row_owner = row_v + (Dc + 4);
     int32_t* row_begin = row_owner + (Dc + 4);
     int32_t* row_n = row_begin + (Dc + 4);       // length of N->(v) for a row that probes it, else 0
@@ -178,11 +171,11 @@ __global__ void __launch_bounds__(kLightBlock) build_light_kernel(BuildParams P)
                 const int r = base + tid;
                 const int v = r < R ? pre[r] : 0;
                 const int inc = wave_incl_scan(v);
-                if (lane == kWave_ - 1) ctrl->wsum[wid] = inc;
+                if (lane == kWave_ - 1) wsum[wid] = inc;
                 __syncthreads();
                 int o = 0, tot = 0;
                 for (int w = 0; w < nwaves; ++w) {
-                    const int x = ctrl->wsum[w];
+                    const int x = wsum[w];
                     if (w < wid) o += x;
                     tot += x;
                 }

@@ -204,25 +204,31 @@ __host__ __device__ inline int arc_parts(int c, int k, int pct)
 // A mask costs the dense kernel the same however few candidates it has left,
 // while the count kernel packs them, so the deeper the count the denser a
 // subgraph has to be.  Random graphs of edge probability p, dense kernel and
-// count kernel: k = 6, p = 0.2 0.30 and 0.27 ms, 0.4 0.31 and 0.41; k = 7,
-// 0.3 0.79 and 0.64, 0.4 1.0 and 1.0, 0.5 1.6 and 2.2; k = 8, 0.5 8.1 and 3.3,
-// 0.7 12.8 and 12.3, 0.8 13.7 and 16.5; k = 9, 0.7 71 and 36, 0.8 72 and 65,
-// 0.9 144 and 202; k = 10, 0.8 449 and 252.  The subgraphs of power-law graphs
-// lie between 0.75 and 0.95 (R-MAT 12, k = 10: 76 and 101 ms).
+// count kernel, about 50 candidates an arc: k = 6, p = 0.2 0.30 and 0.27 ms,
+// 0.4 0.31 and 0.41; k = 7, 0.3 0.79 and 0.64, 0.4 1.0 and 1.0, 0.5 1.6 and
+// 2.2; k = 8, 0.5 8.1 and 3.3, 0.7 12.8 and 12.3, 0.8 13.7 and 16.5; k = 9, 0.7
+// 71 and 36, 0.8 72 and 65, 0.9 144 and 202; k = 10, 0.8 449 and 252.  About
+// 200 candidates: k = 8, 0.6 546 and 546, 0.7 557 and 1255; k = 9 (an eighth),
+// 0.7 1089 and 961, 0.8 1165 and 2971.  In power-law graphs the subgraphs get
+// denser with every level, so what counts is the density one level down, of
+// the neighbours of a candidate: 0.86 to 0.99 on R-MAT, where an arc's own
+// is 0.6 to 0.95 and the dense kernel wins at every one of them (R-MAT 20, k = 8:
+// 240 and 2606 ms for a share).
 constexpr int kDenseMin = 17;
 constexpr int kDenseMax = 64 * kDenseClasses;
 __host__ __device__ inline bool dense_size(int c) { return c >= kDenseMin && c <= kDenseMax; }
-// class of subgraphs with `edges` of `pairs` pairs adjacent (pairs < 2^20)
-constexpr int kDensities = 4;
+// class of subgraphs where `edges` of `pairs` pairs of a candidate's neighbours
+// are adjacent (pairs < 2^25)
+constexpr int kDensities = 5;
 constexpr int kDensityK = 7;         // counts that look at it
 __host__ __device__ inline int density_class(unsigned edges, unsigned pairs)
 {
     const unsigned e = 100 * edges;
-    return (e >= 40 * pairs) + (e >= 75 * pairs) + (e >= 88 * pairs);
+    return (e >= 40 * pairs) + (e >= 66 * pairs) + (e >= 80 * pairs) + (e >= 88 * pairs);
 }
 __host__ __device__ inline bool dense_arc(int c, int k, int density)
 {
-    return k >= 5 && dense_size(c) && density >= (k < kDensityK ? 0 : k == 7 ? 1 : k <= 9 ? 2 : 3);
+    return k >= 5 && dense_size(c) && density >= (k < kDensityK ? 0 : k <= 10 ? k - kDensityK + 1 : kDensities - 1);
 }
 // Group of a heavy vertex's arc in harcs: arcs of vertices above kDenseMax
 // first, and, where the dense kernel may take them, by their vertex's class.

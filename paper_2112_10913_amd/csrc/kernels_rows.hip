@@ -401,13 +401,14 @@ __global__ void __launch_bounds__(256) sorted_rows_kernel(SortedRowsParams P)
 }
 
 // Class of every heavy vertex (density_class): of each four of its sorted rows
-// one wave takes one, and counts the edges below the largest arc among them
-// that the dense kernel could take.  Four arcs give the mean over all of a
-// vertex's arcs to 0.12 on R-MAT, Chung-Lu and random graphs.
+// one wave takes one, and there the largest arc that the dense kernel could
+// take; of its candidates kSampled at even distances, and of each the pairs of
+// its neighbours among the candidates that are adjacent.
+constexpr int kSampled = 8;
 __global__ void __launch_bounds__(256) density_kernel(SortedRowsParams P, const int32_t* __restrict__ arc_c,
                                                       uint8_t* __restrict__ density)
 {
-    __shared__ unsigned found[4][2];      // edges and pairs below the waves' arcs
+    __shared__ unsigned found[4][2];      // adjacent pairs and pairs, per wave
     const int tid = threadIdx.x, lane = lane_of(), wid = __builtin_amdgcn_readfirstlane(tid / kWave_);
     for (int b = blockIdx.x; b < P.n_heavy; b += gridDim.x) {
         const int u = P.order[b];
@@ -424,19 +425,27 @@ __global__ void __launch_bounds__(256) density_kernel(SortedRowsParams P, const 
         const int c = __builtin_amdgcn_readfirstlane(best >> 16), row = __builtin_amdgcn_readfirstlane(best & 0xffff);
         const u64* __restrict__ rows = P.hrows + P.hoff[u];
         const u64 m = lane < W && c ? rows[(int64_t)row * W + lane] : 0ull;
-        unsigned edges = 0;
-        for (int j0 = 0; j0 < c; j0 += kWave_) {
-            const int x = wave_select(m, j0 + lane, W);      // any position past the last
-            const bool in = j0 + lane < c;
-            const u64* __restrict__ rx = rows + (int64_t)(in ? x : 0) * W;
-            for (int w0 = row >> 6; w0 < W; w0 += 4) {       // four words in flight
-                u64 r[4];
+        // the sampled candidates, a lane each
+        const int xs = wave_select(m, (2 * (lane & (kSampled - 1)) + 1) * c / (2 * kSampled), W);
+        unsigned edges = 0, pairs = 0;
+        for (int i = 0; c && i < kSampled; ++i) {
+            const int x = __builtin_amdgcn_readlane(xs, i);
+            const u64 near = lane < W ? m & rows[(int64_t)x * W + lane] : 0ull;
+            const int r = wave_sum_small(__popcll(near));
+            pairs += (unsigned)(r * (r - 1) / 2);
+            for (int j0 = 0; j0 < r; j0 += kWave_) {
+                const int y = wave_select(near, j0 + lane, W);   // any position past the last
+                const bool in = j0 + lane < r;
+                const u64* __restrict__ ry = rows + (int64_t)(in ? y : 0) * W;
+                for (int w0 = x >> 6; w0 < W; w0 += 4) {         // four words in flight
+                    u64 q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) r[i] = rx[min(w0 + i, W - 1)];
+                    for (int t = 0; t < 4; ++t) q[t] = ry[min(w0 + t, W - 1)];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const u64 mw = w0 + i < W ? readlane64(m, w0 + i) : 0ull;
-                    edges += in ? __popcll(mw & r[i]) : 0;
+                    for (int t = 0; t < 4; ++t) {
+                        const u64 nw = w0 + t < W ? readlane64(near, w0 + t) : 0ull;
+                        edges += in ? __popcll(nw & q[t]) : 0;
+                    }
                 }
             }
         }
@@ -444,12 +453,12 @@ __global__ void __launch_bounds__(256) density_kernel(SortedRowsParams P, const 
         for (int o = kWave_ / 2; o > 0; o >>= 1) edges += __shfl_xor(edges, o, kWave_);
         if (lane == 0) {
             found[wid][0] = edges;
-            found[wid][1] = (unsigned)(c * (c - 1) / 2);
+            found[wid][1] = pairs;
         }
         __syncthreads();
         if (tid == 0) {
-            const unsigned pairs = found[0][1] + found[1][1] + found[2][1] + found[3][1];
-            density[u] = (uint8_t)(pairs ? density_class(found[0][0] + found[1][0] + found[2][0] + found[3][0], pairs) : 0);
+            const unsigned all = found[0][1] + found[1][1] + found[2][1] + found[3][1];
+            density[u] = (uint8_t)(all ? density_class(found[0][0] + found[1][0] + found[2][0] + found[3][0], all) : 0);
         }
         __syncthreads();
     }

@@ -249,7 +249,8 @@ __host__ __device__ inline bool dense_vertex(int d, int k)
 
 // Parts of a dense arc (every P-th first-level branch).  One to four waves
 // share an arc, so counts of k >= 8 are cut finely for the launch's tail
-// (Chung-Lu 2^14, k = 9: c / 8 parts 7.3 ms, c / 4 6.5 ms); at k = 7 the
+// (R-MAT 14, k = 8: c / 64 parts 52.1 ms, c / 24 43.6, c / 12 41.7, c / 4 40.6;
+// Chung-Lu 2^14, k = 9: c / 8 7.3 ms, c / 4 6.5 ms); at k = 7 the
 // parts' repeated layout costs more than it saves (R-MAT 16: c / 64 21.6 ms,
 // c / 24 22.2 ms).
 __host__ __device__ inline int dense_parts(int c, int k, int pct)

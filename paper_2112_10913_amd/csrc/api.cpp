@@ -382,6 +382,8 @@ citron_status ensure_heavy_arcs(citron_graph* g, bool deep)
     const int32_t D = std::max(g->max_outdeg, 2);
     const int32_t nb = kHeavyGroups * D;
     hipStream_t s = g->stream;
+    hipError_t e = hipSetDevice(g->device);
+    if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     citron_status st = queue_sorted_rows(g);
     if (st) return st;
     if (!ha.d_arcs && (st = dalloc(&ha.d_arcs, (size_t)g->m, &g->device_bytes, "heavy arcs"))) return st;
@@ -404,7 +406,7 @@ citron_status ensure_heavy_arcs(citron_graph* g, bool deep)
     }
     sb.temp = tmp;
     sb.temp_bytes = tb;
-    hipError_t e = deep ? launch_density(sorted_rows_params(g), g->d_arc_c, density, s) : hipSuccess;
+    if (deep) e = launch_density(sorted_rows_params(g), g->d_arc_c, density, s);
     if (e == hipSuccess)
         e = sched_heavy_arcs(g->m, g->d_dag_ptr, g->d_dag_src, g->d_arc_c, density, D, d_scan, ha.d_arcs, sb, s);
     std::vector<int32_t> scan((size_t)nb + 1);
@@ -439,6 +441,8 @@ static citron_status ensure_deep_order(citron_graph* g)
     std::vector<int32_t> bounds(2 * kDeepBuckets + 1, 0);
     if (n > 0) {
         hipStream_t s = g->stream;
+        hipError_t e = hipSetDevice(g->device);
+        if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
         citron_status st;
         if (!g->d_deep_order && (st = dalloc(&g->d_deep_order, (size_t)g->n + 1, &g->device_bytes, "deep order")))
             return st;
@@ -458,8 +462,7 @@ static citron_status ensure_deep_order(citron_graph* g)
         }
         sb.temp = tmp;
         sb.temp_bytes = tb;
-        hipError_t e = hipMemcpyAsync(g->d_deep_order, g->pb.order, sizeof(int32_t) * (size_t)g->n,
-                                      hipMemcpyDeviceToDevice, s);
+        e = hipMemcpyAsync(g->d_deep_order, g->pb.order, sizeof(int32_t) * (size_t)g->n, hipMemcpyDeviceToDevice, s);
         if (e == hipSuccess)
             e = sched_deep_order(n, g->pb.order + heavy, g->d_dag_ptr, g->d_rows_off, g->d_rows, d_bounds,
                                  g->d_deep_order + heavy, sb, s);

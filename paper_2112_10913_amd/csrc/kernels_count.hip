@@ -1129,8 +1129,9 @@ hipError_t launch_count(const CountLaunch& cl, hipStream_t s)
     const int64_t need = ((int64_t)rest + cl.wg_waves - 1) / cl.wg_waves;
     if (need < c2.blocks) c2.blocks = (int32_t)need;
     // deep counts: an item's cost is far from what its key says, so runs stay
-    // shorter (Chung-Lu 2^17, k = 8, runs of 2, 4 and 8: 1.21, 1.04 and 0.92
-    // ms, for their decoding; with planted cliques, 2^14, k = 9, 4.6 to 4.8 ms)
+    // shorter (Chung-Lu 2^17, k = 8, runs of 2, 4 and 8: 1.10, 0.87 and 0.74
+    // ms, for their decoding; with planted cliques, k = 10, 1.23, 0.98 and 0.85;
+    // R-MAT 12, k = 10, whose light vertices are deep, 73.3, 75.3 and 76.6)
     set_runs(P.items, (int64_t)c2.blocks * cl.wg_waves, cl.max_k <= 6 ? kMaxClaim : kDeepClaim);
     switch (stack_mode(cl.max_k)) {
     case kStackOne: return launch_mode<kStackOne>(P, c2, s);
